@@ -249,7 +249,7 @@ mm_status mm_noise_method_used(const mm_noise *nz, mm_noise_method *method);
  * *n_fft is 16,384 (lambda <= 6,144; two blocks share a compute unit) or
  * 32,768 (one block per compute unit), picked at build by a measured time
  * model (blocks run in waves over the compute units; a wave of the large
- * blocks takes 1.1 times as long), so it depends on the interval lengths,
+ * blocks takes 1.05 times as long), so it depends on the interval lengths,
  * lambda and the device's compute-unit count; mm_noise_set_fft_block and
  * mm_autotune can change it. */
 mm_status mm_noise_fft_block(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid);

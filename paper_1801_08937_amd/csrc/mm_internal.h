@@ -193,8 +193,8 @@ struct mm_noise {
     // FFT: per-filter packed spectrum and block table
     int32_t fft_n = 0;       // real block length
     int32_t fft_valid = 0;   // valid outputs per block
-    mm::DBuf fft_spec;       // per filter: A_k, B_k (2 * fft_n/2 doubles)
-    mm::DBuf fft_tw;         // twiddles exp(-2 pi i m / (fft_n/2)), m < fft_n/2
+    mm::DBuf fft_spec;       // per filter: A_k, then W^k B_k / 2, in the kernel's order
+    mm::DBuf fft_tw;         // twiddles of the transform's first two passes
     mm::DBuf fft_blocks;     // int64 pairs (first output sample, interval index)
     int64_t n_fft_blocks = 0;
     // polynomial template filter (method MM_NOISE_POLY): subscan table, the

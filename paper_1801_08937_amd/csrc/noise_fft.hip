@@ -55,27 +55,14 @@ __global__ void __launch_bounds__(256)
     H[(int64_t)f * (NC + 1) + k] = c[0] + 2.0 * s;
 }
 
-template <typename T>
-__global__ void k_fft_ab(const double *__restrict__ H, int n_filters, int NC,
-                         typename Vec2T<T>::type *__restrict__ ab) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= (int64_t)n_filters * NC) return;
-    const int64_t f = e / NC;
-    const int k = (int)(e % NC);
-    const double hk = H[f * (NC + 1) + k];
-    const double hc = H[f * (NC + 1) + (NC - k)];  // H_{k+NC} = H_{NC-k}
-    typename Vec2T<T>::type v;
-    v.x = (T)((hk + hc) / (2.0 * NC));
-    v.y = (T)((hk - hc) / (2.0 * NC));
-    ab[e] = v;
-}
-
 }  // namespace
 
 bool noise_fft_big_supported(int half_bw);
 bool noise_fft_mid_supported(int half_bw);
 int noise_fft_big_nc();
 int noise_fft_mid_nc();
+void noise_fft_tables_dev(mm_ctx *ctx, mm_noise *nz, int nc, const double *H,
+                          const double *qtab);
 void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
 
 bool noise_fft_supported(int half_bw, int64_t min_len) {
@@ -84,11 +71,12 @@ bool noise_fft_supported(int half_bw, int64_t min_len) {
 }
 
 // Measured time model of one overlap-save apply with N-sample blocks.  Blocks
-// run in waves of n_cu x (blocks per CU): two 16,384-sample blocks share a CU,
-// a 32,768-sample block fills one.  A wave takes 40 (16,384) or 44 (32,768)
-// time units; the count of waves is rounded up.  Fitted to FP64 and FP32
-// applies of 2^23 and 2^27 samples in 2^16-sample intervals, lambda 512 to
-// 4,096: the pick is the faster kernel, or within 5 % of it, in every case.
+// run in waves of n_cu x (blocks per CU): in FP64 two 16,384-sample blocks
+// share a CU and a 32,768-sample block fills one; in FP32 twice as many.  A
+// wave takes 40 (16,384) or 42 (32,768) time units (29.3 and 30.6 us at 2^27
+// samples, FP64 and FP32 alike, lambda 1,024 and 4,096); the count of waves is
+// rounded up.  On less than one wave the smaller block is the faster one
+// (18.7 against 26.4 us at 2^20 samples, lambda 1,024).
 static double fft_time_model(const mm_noise *nz, int N, int n_cu) {
     const int64_t lam = nz->half_bw, V = N - 2 * lam;
     if (V <= 0) return 1e300;
@@ -96,9 +84,9 @@ static double fft_time_model(const mm_noise *nz, int N, int n_cu) {
     for (int i = 0; i < nz->n_int; ++i)
         nb += (nz->h_istart[i + 1] - nz->h_istart[i] + V - 1) / V;
     const bool mid = N == 2 * noise_fft_mid_nc();
-    const int64_t per_wave = (int64_t)n_cu * (mid ? 2 : 1);
+    const int64_t per_wave = (int64_t)n_cu * (mid ? 2 : 1) * (nz->prec == MM_F32 ? 2 : 1);
     const int64_t waves = (nb + per_wave - 1) / per_wave;
-    return (double)waves * (mid ? 40.0 : 44.0);
+    return (double)waves * (mid ? 40.0 : 42.0);
 }
 
 // Tables for blocks of n_fft real samples (0 = pick by the model above).
@@ -120,36 +108,10 @@ void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
     const int N = 2 * NC;
     nz->fft_n = N;
     nz->fft_valid = N - 2 * lam;
-    const bool f32 = nz->prec == MM_F32;
-    const size_t e2 = f32 ? sizeof(float2) : sizeof(double2);
-    // twiddle tables (long double on the host, rounded once)
+    // quarter period of cos(2 pi m / N) (long double on the host, rounded once)
     std::vector<double> qtab(N / 4 + 1);
-    std::vector<double> tw(2 * NC), twN(2 * NC);
     const long double pi2 = 6.283185307179586476925286766559L;
     for (int m = 0; m <= N / 4; ++m) qtab[m] = (double)cosl(pi2 * m / N);
-    for (int m = 0; m < NC; ++m) {
-        tw[2 * m] = (double)cosl(pi2 * m / NC);
-        tw[2 * m + 1] = (double)-sinl(pi2 * m / NC);
-        twN[2 * m] = (double)cosl(pi2 * m / N);
-        twN[2 * m + 1] = (double)-sinl(pi2 * m / N);
-    }
-    nz->fft_tw.alloc(2 * e2 * NC);  // tw then twN
-    if (f32) {
-        std::vector<float> a(4 * (size_t)NC);
-        for (int i = 0; i < 2 * NC; ++i) {
-            a[i] = (float)tw[i];
-            a[2 * NC + i] = (float)twN[i];
-        }
-        MM_HIP(hipMemcpyAsync(nz->fft_tw.ptr, a.data(), sizeof(float) * a.size(),
-                              hipMemcpyHostToDevice, s));
-        MM_HIP(hipStreamSynchronize(s));
-    } else {
-        MM_HIP(hipMemcpyAsync(nz->fft_tw.ptr, tw.data(), sizeof(double) * tw.size(),
-                              hipMemcpyHostToDevice, s));
-        MM_HIP(hipMemcpyAsync(nz->fft_tw.as<double>() + 2 * NC, twN.data(),
-                              sizeof(double) * twN.size(), hipMemcpyHostToDevice, s));
-        MM_HIP(hipStreamSynchronize(s));
-    }
     // spectra
     DBuf dq, H;
     dq.alloc(sizeof(double) * qtab.size());
@@ -159,15 +121,8 @@ void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
     dim3 g((NC + 1 + 255) / 256, nz->n_filters);
     k_fft_spectrum<<<g, 256, 0, s>>>(nz->band64.as<double>(), lam, N, dq.as<double>(),
                                      H.as<double>());
-    nz->fft_spec.alloc(e2 * (size_t)nz->n_filters * NC);
-    const int64_t tot = (int64_t)nz->n_filters * NC;
-    if (f32)
-        k_fft_ab<float><<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(
-            H.as<double>(), nz->n_filters, NC, nz->fft_spec.as<float2>());
-    else
-        k_fft_ab<double><<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(
-            H.as<double>(), nz->n_filters, NC, nz->fft_spec.as<double2>());
     MM_HIP(hipGetLastError());
+    noise_fft_tables_dev(ctx, nz, NC, H.as<double>(), dq.as<double>());
     // block table
     std::vector<int64_t> blocks;
     for (int i = 0; i < nz->n_int; ++i)

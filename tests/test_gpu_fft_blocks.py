@@ -1,0 +1,46 @@
+"""N^-1 by FFT at the edges of its overlap-save blocks: intervals shorter than
+a block, of exactly one or two blocks' valid outputs and one sample more or
+less, odd bandwidths, both block sizes, one and several columns.  The band is
+random, so every frequency of the spectrum (0 and Nyquist among them) counts.
+
+FP64 tolerance: a transform pair of 2^15 points loses about 30 rounding steps
+(3e-15 of the largest output, as the band's symbol and the inputs are of order
+one per frequency); 1e-12 leaves two orders.  FP32: the same with 6e-8 steps,
+2e-6, times ten."""
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_util import dev, host, maxrel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1801_08937_amd import mapmaker as mm
+    return mm.Context(0)
+
+
+@pytest.mark.parametrize("n_fft", [16384, 32768])
+@pytest.mark.parametrize("lam", [31, 32, 1000, 4095])
+@pytest.mark.parametrize("prec,R", [(0, 1), (0, 2), (1, 1), (1, 4)])
+def test_fft_block_edges(ctx, n_fft, lam, prec, R):
+    import torch
+    rng = np.random.default_rng(1000 * lam + n_fft + 10 * prec + R)
+    V = n_fft - 2 * lam
+    lens = [2 * lam + 1, V - 1, V, V + 1, 2 * V, 2 * lam + 2]
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    fid = np.array([0, 1, 0, 1, 1, 0], dtype=np.int32)
+    band = rng.standard_normal((2, lam + 1)) / np.sqrt(2 * lam + 1)
+    nz = ctx.noise(istart, fid, band, lam, method=2, prec=prec)
+    nz.set_fft_block(n_fft)
+    assert nz.fft_n == n_fft
+    y = rng.standard_normal((istart[-1], R)) + 1.0
+    t = dev(y, torch.float32 if prec else torch.float64)
+    z = host(ctx.noise_apply(nz, t.reshape(-1), nrhs=R)).reshape(-1, R)
+    on = O.noise_build(istart, fid, band, lam)
+    tol = 2e-5 if prec else 1e-12
+    for r in range(R):
+        ref = O.noise_apply_fft(on, host(t)[:, r].astype(np.float64))
+        assert maxrel(z[:, r], ref) <= tol, (r, maxrel(z[:, r], ref))
