@@ -152,7 +152,7 @@ mm_status mm_pair_sum_diff(mm_ctx *ctx, int64_t n, mm_precision prec, const void
  * then visits the pixels in 32 x 32 tiles of that grid, so the pixels reduced
  * together are hit by the same stretches of the scan and share cache lines.
  * The
- * single-column IQU P (FP64 and FP32) gathers from up to 4 copies of the
+ * single-column P (FP64 and FP32) gathers from up to 4 copies of the
  * map, one per scan direction found in the samples (chunks of 4,096 samples
  * vote by their displacement over 8 samples), each ordered by the first
  * sample of its chunks that hits each pixel, so the lanes of a wave, which
@@ -168,8 +168,8 @@ mm_status mm_pair_sum_diff(mm_ctx *ctx, int64_t n, mm_precision prec, const void
  * restores ascending order and one map copy.
  * Errors: MM_E_INVALID (negative width). */
 mm_status mm_pointing_set_grid(mm_ctx *ctx, mm_pointing *p, int32_t width);
-/* Map copies the single-column IQU P gathers from: 0 without a grid (one
- * copy in compact id order), else 1 to 4.  [host] output. */
+/* Map copies the single-column P gathers from: 0 without a grid (one copy
+ * in compact id order), else 1 to 4.  [host] output. */
 mm_status mm_pointing_p_layout(const mm_pointing *p, int32_t *copies);
 /* n_obs (observed pixels) and n_valid (unflagged samples).  [host] outputs. */
 mm_status mm_pointing_counts(const mm_pointing *p, int32_t *n_obs, int64_t *n_valid);

@@ -306,7 +306,8 @@ __device__ __forceinline__ double sl_value<double>(const double *__restrict__ ps
 __device__ __forceinline__ void sl_zero(float2 &v) { v = make_float2(0.f, 0.f); }
 __device__ __forceinline__ void sl_zero(double &v) { v = 0.0; }
 
-template <typename V>
+// W = false: no weight records (I).
+template <typename V, bool W = true>
 __global__ void k_sl_fill(const int64_t *__restrict__ base, const int32_t *__restrict__ cnt,
                           const int32_t *__restrict__ start, const int32_t *__restrict__ perm,
                           const V *__restrict__ src, int64_t n_waves,
@@ -315,20 +316,22 @@ __global__ void k_sl_fill(const int64_t *__restrict__ base, const int32_t *__res
     const int64_t nw = ((int64_t)gridDim.x * BS) >> 6;
     for (int64_t w = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6; w < n_waves; w += nw) {
         const int64_t b0 = base[w];
-        const int64_t W = (base[w + 1] - b0) >> 6;
+        const int64_t len = (base[w + 1] - b0) >> 6;
         const int32_t c = cnt[w * 64 + lane];
         const int32_t st = start[w * 64 + lane];
-        for (int64_t k = 0; k < W; ++k) {
+        for (int64_t k = 0; k < len; ++k) {
             const int64_t idx = b0 + 64 * k + lane;
             if (k < c) {
                 const int32_t t = perm[st + k];
                 sl_perm[idx] = t;
-                sl_w[idx] = sl_value<V>(src, st + k, t);
+                if (W) sl_w[idx] = sl_value<V>(src, st + k, t);
             } else {
-                V zero;
-                sl_zero(zero);
                 sl_perm[idx] = -1;
-                sl_w[idx] = zero;
+                if (W) {
+                    V zero;
+                    sl_zero(zero);
+                    sl_w[idx] = zero;
+                }
             }
         }
     }
@@ -342,7 +345,7 @@ int grid_for(int64_t n, int max_blocks = 8192) {
 
 }  // namespace
 
-// Map copies of the single-column IQU P (width > 0), or none.  The lanes of
+// Map copies of the single-column P (width > 0), or none.  The lanes of
 // a wave gather the map at consecutive samples, i.e. along the scan, so the
 // gather touches few cache lines when pixels met one after the other along
 // the scan sit next to each other in memory.  One order cannot do that for
@@ -359,7 +362,7 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     p->p_chunk_grp.release();
     p->p_copies = 0;
     const int32_t n_obs = p->n_obs;
-    if (width <= 0 || n_obs == 0 || p->nc != 3) return;
+    if (width <= 0 || n_obs == 0) return;
     const int64_t n = p->n_samp;
     const int64_t n_chunks = (n + DIR_CHUNK - 1) / DIR_CHUNK;
     DBuf dbin;
@@ -398,6 +401,14 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     }
     int G = kept.empty() ? 1 : (int)kept.size();
     if ((int64_t)G * n_obs >= (int64_t)1 << 31) G = 1;
+    // I and QU: the packed copies fit in a TOD vector, where the A apply that
+    // allocates nothing puts them (they would not only for a few hits per pixel)
+    if (p->nc != 3) {
+        const size_t te = p->prec == MM_F32 ? sizeof(float) : sizeof(double);
+        const size_t tod = te * (size_t)n;
+        if (sizeof(double) * (size_t)(p->n() * G) > tod) G = 1;
+        if (sizeof(double) * (size_t)p->n() > tod) return;
+    }
     // each chunk to the copy of the nearest kept direction (angles mod 180),
     // undirected chunks to the most common one
     std::vector<int32_t> grp(n_chunks, 0);
@@ -500,8 +511,7 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     p->sl_perm.release();
     p->sl_w.release();
     const int32_t n_obs = p->n_obs;
-    // IQU only: the I and QU pointings reduce with the one-wave-per-pixel form
-    if (n_obs == 0 || p->n_valid == 0 || p->nc != 3) return;
+    if (n_obs == 0 || p->n_valid == 0) return;
     const int32_t G0 = (n_obs + 63) / 64;
     // below ~2,048 waves the one-wave-per-pixel kernel is the faster one
     if ((int64_t)G0 * slice_segments(p->n_samp, p->n_valid, n_obs, G0, 1) < 2048) return;
@@ -512,6 +522,10 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     const int32_t G = G0 * D;
     const int64_t nv = p->n_valid;
     const bool f32 = p->prec == MM_F32;
+    // I and QU: the partial maps too fit in a TOD vector (see the map copies)
+    if (p->nc != 3 && sizeof(double) * (size_t)(p->n() * S * D) >
+                          (f32 ? sizeof(float) : sizeof(double)) * (size_t)p->n_samp)
+        return;
     // the pixel-sorted samples and their CSR offsets, over virtual pixels
     // d n_obs + c when cut by direction
     const int32_t *perm_u = p->perm.as<int32_t>();
@@ -535,7 +549,7 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
                                          vals.as<int32_t>(), idx.as<int32_t>(), (size_t)nv, 0u,
                                          8u, s));
         perm2.alloc(sizeof(int32_t) * nv);
-        if (f32) {
+        if (f32 && p->nc > 1) {
             ws2.alloc(sizeof(float2) * nv);
             k_perm_gather<float2><<<grid_for(nv), BS, 0, s>>>(
                 idx.as<int32_t>(), perm_u, p->ws.as<float2>(), nv, perm2.as<int32_t>(),
@@ -563,7 +577,7 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
         MM_HIP(hipStreamSynchronize(s));
         perm_u = perm2.as<int32_t>();
         off_u = off2.as<int32_t>();
-        if (f32) ws_u = ws2.ptr;
+        if (f32 && p->nc > 1) ws_u = ws2.ptr;
     }
 
     p->sl_pix.alloc(sizeof(int32_t) * (size_t)G * 64);
@@ -622,9 +636,13 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
                           hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
     p->sl_perm.alloc(sizeof(int32_t) * (size_t)total);
-    p->sl_w.alloc((f32 ? sizeof(float2) : sizeof(double)) * (size_t)total);
+    if (p->nc > 1) p->sl_w.alloc(sizeof(double) * (size_t)total);  // psi, or two FP32 weights
     const unsigned fb = (unsigned)std::min<int64_t>((n_waves * 64 + BS - 1) / BS, 16384);
-    if (f32)
+    if (p->nc == 1)
+        k_sl_fill<double, false><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt.as<int32_t>(),
+                                                   start.as<int32_t>(), perm_u, nullptr, n_waves,
+                                                   p->sl_perm.as<int32_t>(), nullptr);
+    else if (f32)
         k_sl_fill<float2><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt.as<int32_t>(),
                                             start.as<int32_t>(), perm_u,
                                             static_cast<const float2 *>(ws_u), n_waves,
@@ -736,6 +754,7 @@ void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, cons
         int32_t mx1 = 0;
         for (int32_t c = 0; c < n_obs; ++c) mx1 = std::max(mx1, hoff1[c + 1] - hoff1[c]);
         p->max_seg = mx1;
+        pointing_slices_device(ctx, p, 0);
         return;
     }
     if (!f32) {

@@ -298,7 +298,7 @@ template <> struct SlRec<float> {
     }
 };
 
-template <typename T>
+template <typename T, int NC>
 __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ base,
                                                     const int32_t *__restrict__ sl_perm,
                                                     const typename SlRec<T>::type *__restrict__ sl_w,
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
     const int64_t b0 = base[w];
     const int64_t W = (base[w + 1] - b0) >> 6;
     const int32_t *pp = sl_perm + b0 + lane;
-    const auto *wp = sl_w + b0 + lane;
+    const auto *wp = NC > 1 ? sl_w + b0 + lane : nullptr;
     T s0 = 0, s1 = 0, s2 = 0;
     int64_t k = 0;
     // eight entries in flight per lane, accumulated in entry order
@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
         for (int q = 0; q < 8; ++q) tt[q] = __builtin_nontemporal_load(pp + 64 * (k + q));
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            ww[q] = nt_load_w(wp + 64 * (k + q));
+            if constexpr (NC > 1) ww[q] = nt_load_w(wp + 64 * (k + q));
             // a padding entry (-1) reads sample 0 and adds 0: no branch
             // between the eight gathers
             const T zq = z[tt[q] < 0 ? 0 : tt[q]];
@@ -336,28 +336,34 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            T c, sn;
-            SlRec<T>::weights(ww[q], c, sn);
-            s0 += zz[q];
-            s1 += c * zz[q];
-            s2 += sn * zz[q];
+            if constexpr (NC != 2) s0 += zz[q];
+            if constexpr (NC > 1) {
+                T c, sn;
+                SlRec<T>::weights(ww[q], c, sn);
+                s1 += c * zz[q];
+                s2 += sn * zz[q];
+            }
         }
     }
     for (; k < W; ++k) {
         const int32_t tq = pp[64 * k];
-        T c, sn;
-        SlRec<T>::weights(wp[64 * k], c, sn);
         const T zq = tq >= 0 ? z[tq] : (T)0;
-        s0 += zq;
-        s1 += c * zq;
-        s2 += sn * zq;
+        if constexpr (NC != 2) s0 += zq;
+        if constexpr (NC > 1) {
+            T c, sn;
+            SlRec<T>::weights(wp[64 * k], c, sn);
+            s1 += c * zq;
+            s2 += sn * zq;
+        }
     }
     const int32_t c = sl_pix[(int64_t)g * 64 + lane];
     if (c < 0) return;
-    double *o = out + ((int64_t)sg * n_obs + c) * 3;
-    o[0] = (double)s0;
-    o[1] = (double)s1;
-    o[2] = (double)s2;
+    double *o = out + ((int64_t)sg * n_obs + c) * NC;
+    if constexpr (NC != 2) *o++ = (double)s0;
+    if constexpr (NC > 1) {
+        o[0] = (double)s1;
+        o[1] = (double)s2;
+    }
 }
 
 // x[e] = part[0][e] + part[1][e] + ... in segment order; the partials' loads
@@ -407,6 +413,80 @@ __global__ void __launch_bounds__(BS) k_apply_P_nc(const int32_t *__restrict__ j
         typename Vec2<T>::type ww{};
         if constexpr (NC == 2) ww = w[t];
         y[t * R + r] = p_gather_nc<T, R, NC>(jpix[t], ww, x, r);
+    }
+}
+
+// One column of an I or QU pointing: as k_apply_P1 / k_apply_P1_psi, eight
+// samples in flight per thread and no branch between their gathers.  The map
+// xm holds NC values per slot: the copies packed by k_pack_map_nc (with a
+// grid), or x itself.  2^25 samples of a cross-linked QU scan, FP64: the A apply
+// with offsets and slopes removed went from 613 to 453 us (P took 248 and P^T
+// 303 us when P walked one sample per round trip without copies and P^T one
+// wave per pixel).  Bound as the IQU P is: the gather's cache lines, then HBM.
+template <typename T> struct P1W {  // weight record of a sample in time order
+    using type = typename SlRec<T>::type;
+};
+template <typename T, int NC>
+__global__ void __launch_bounds__(BS) k_apply_P1_nc(const int32_t *__restrict__ jpix,
+                                                    const typename P1W<T>::type *__restrict__ w,
+                                                    int64_t n, const double *__restrict__ xm,
+                                                    T *__restrict__ y) {
+    const int64_t step = (int64_t)gridDim.x * BS;
+    int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
+    auto value = [&](int32_t j, typename P1W<T>::type ww, double x0, double x1) {
+        T v;
+        if constexpr (NC == 1) {
+            v = (T)x0;
+        } else {
+            T c, s;
+            SlRec<T>::weights(ww, c, s);
+            v = c * (T)x0 + s * (T)x1;
+        }
+        return j < 0 ? (T)0 : v;
+    };
+    for (; t + 7 * step < n; t += 8 * step) {
+        int32_t j[8];
+        typename P1W<T>::type ww[8]{};
+        double x0[8], x1[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            j[q] = __builtin_nontemporal_load(jpix + t + q * step);
+            if constexpr (NC == 2) ww[q] = nt_load_w(w + t + q * step);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t jj = (int64_t)NC * (j[q] < 0 ? 0 : j[q]);
+            x0[q] = xm[jj];
+            x1[q] = NC == 2 ? xm[jj + NC - 1] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            __builtin_nontemporal_store(value(j[q], ww[q], x0[q], x1[q]), y + t + q * step);
+    }
+    for (; t < n; t += step) {
+        const int32_t j = jpix[t];
+        const int64_t jj = (int64_t)NC * (j < 0 ? 0 : j);
+        typename P1W<T>::type ww{};
+        if constexpr (NC == 2) ww = w[t];
+        y[t] = value(j, ww, xm[jj], NC == 2 ? xm[jj + NC - 1] : 0.0);
+    }
+}
+
+template <int NC>
+__global__ void __launch_bounds__(BS) k_pack_map_nc(const double *__restrict__ x, int32_t n_obs,
+                                                    int n_copies,
+                                                    const int32_t *__restrict__ slot,
+                                                    double *__restrict__ xm) {
+    for (int64_t c = (int64_t)blockIdx.x * BS + threadIdx.x; c < n_obs;
+         c += (int64_t)gridDim.x * BS) {
+        double v[NC];
+#pragma unroll
+        for (int a = 0; a < NC; ++a) v[a] = x[NC * c + a];
+        for (int g = 0; g < n_copies; ++g) {
+            const int64_t s = slot[(int64_t)g * n_obs + c];
+#pragma unroll
+            for (int a = 0; a < NC; ++a) xm[NC * s + a] = v[a];
+        }
     }
 }
 
@@ -619,6 +699,17 @@ template <typename F> void dispatch_r(int nrhs, F &&f) {
     }
 }
 
+// f(time-domain type, component count 1 or 2) of an I or QU pointing.
+template <typename F> void dispatch_t_nc(const mm_pointing *p, F &&f) {
+    if (p->prec == MM_F32) {
+        if (p->nc == 1) f(0.f, std::integral_constant<int, 1>());
+        else f(0.f, std::integral_constant<int, 2>());
+    } else {
+        if (p->nc == 1) f(0.0, std::integral_constant<int, 1>());
+        else f(0.0, std::integral_constant<int, 2>());
+    }
+}
+
 }  // namespace
 
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
@@ -636,6 +727,33 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
         }
         return;
     }
+    if (p->nc != 3 && nrhs == 1) {
+        const bool slots = p->p_j.ptr != nullptr;
+        const int tuned = p->p_blocks[0];
+        const int grid = tuned > 0 ? tuned : grid_for(n, 32 * ctx->n_cu * 4);
+        if (slots && !scratch) {
+            ws_alloc(ctx, ctx->xpack, apply_P_scratch_bytes(p, nrhs));
+            scratch = static_cast<char *>(ctx->xpack.ptr);
+        }
+        auto go = [&](auto TT, auto NN) {
+            using T = decltype(TT);
+            constexpr int NC = decltype(NN)::value;
+            const double *xm = x;
+            if (slots) {
+                double *pk = reinterpret_cast<double *>(scratch);
+                k_pack_map_nc<NC><<<grid_for(p->n_obs, 1024), BS, 0, ctx->stream>>>(
+                    x, p->n_obs, p->p_copies, p->p_slot.as<int32_t>(), pk);
+                xm = pk;
+            }
+            const void *w = NC == 1 ? nullptr : (p->prec == MM_F32 ? p->w.ptr : p->psi.ptr);
+            k_apply_P1_nc<T, NC><<<grid, BS, 0, ctx->stream>>>(
+                slots ? p->p_j.as<int32_t>() : p->j.as<int32_t>(),
+                static_cast<const typename P1W<T>::type *>(w), n, xm, static_cast<T *>(y));
+        };
+        dispatch_t_nc(p, go);
+        MM_HIP(hipGetLastError());
+        return;
+    }
     if (p->nc != 3) {
         dispatch_r(nrhs, [&](auto RR) {
             constexpr int R = decltype(RR)::value;
@@ -648,13 +766,7 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
                     NC == 2 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, n,
                     x, static_cast<T *>(y));
             };
-            if (p->prec == MM_F32) {
-                if (p->nc == 1) go(0.f, std::integral_constant<int, 1>());
-                else go(0.f, std::integral_constant<int, 2>());
-            } else {
-                if (p->nc == 1) go(0.0, std::integral_constant<int, 1>());
-                else go(0.0, std::integral_constant<int, 2>());
-            }
+            dispatch_t_nc(p, go);
         });
         MM_HIP(hipGetLastError());
         return;
@@ -707,21 +819,57 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
 }
 
 size_t apply_P_scratch_bytes(const mm_pointing *p, int nrhs) {
-    if (p->nc != 3 || nrhs != 1) return 0;
+    if (nrhs != 1) return 0;
+    // I and QU gather from x itself without a grid, else from NC-value copies
+    if (p->nc != 3)
+        return p->p_j.ptr ? sizeof(double) * (size_t)(p->nc * (int64_t)p->n_obs * p->p_copies) : 0;
     const int copies = p->p_j.ptr != nullptr ? p->p_copies : 1;
     return sizeof(double2) * 2 * (size_t)(p->n_obs > 0 ? p->n_obs : 1) * copies;
 }
 
 size_t apply_PT_scratch_bytes(const mm_pointing *p, int nrhs) {
-    if (p->nc != 3 || nrhs != 1 || p->sl_G <= 0 || p->n_obs == 0) return 0;
+    if (nrhs != 1 || p->sl_G <= 0 || p->n_obs == 0) return 0;
     const int64_t parts = (int64_t)p->sl_S * p->sl_D;
-    return parts > 1 ? sizeof(double) * (size_t)(3 * (int64_t)p->n_obs * parts) : 0;
+    return parts > 1 ? sizeof(double) * (size_t)(p->n() * parts) : 0;
 }
 
 void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, double *x,
                   char *scratch) {
     Scope sc(ctx->prof, ctx->stream, "PT");
     if (p->n_obs == 0) return;
+    if (nrhs == 1 && p->sl_G > 0) {
+        // lane pixels are virtual ids d n_obs + c (sl_D scan directions), so
+        // wave (s, g) writes partial map s D + d; the partials are then
+        // added in that fixed order
+        const int32_t G = p->sl_G, S = p->sl_S, D = p->sl_D;
+        const int64_t n3 = p->n();
+        const int32_t parts = S * D;
+        double *out = x;
+        if (parts > 1) {
+            if (!scratch) {
+                ws_alloc(ctx, ctx->pt_part, apply_PT_scratch_bytes(p, nrhs));
+                scratch = static_cast<char *>(ctx->pt_part.ptr);
+            }
+            out = reinterpret_cast<double *>(scratch);
+        }
+        const int32_t nv = D * p->n_obs;
+        int64_t nb = ((int64_t)G * S + 3) / 4;
+        if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
+        auto go = [&](auto TT, auto NN) {
+            using T = decltype(TT);
+            k_apply_PT_sl<T, decltype(NN)::value><<<(unsigned)nb, BS, 0, ctx->stream>>>(
+                p->sl_base.as<int64_t>(), p->sl_perm.as<int32_t>(),
+                p->sl_w.as<typename SlRec<T>::type>(), p->sl_pix.as<int32_t>(), G, S, nv,
+                static_cast<const T *>(z), out);
+        };
+        if (p->nc != 3) dispatch_t_nc(p, go);
+        else if (p->prec == MM_F32) go(0.f, std::integral_constant<int, 3>());
+        else go(0.0, std::integral_constant<int, 3>());
+        if (parts > 1)
+            k_pt_sum_parts<<<grid_for(n3, 2048), BS, 0, ctx->stream>>>(out, parts, n3, x);
+        MM_HIP(hipGetLastError());
+        return;
+    }
     if (p->nc != 3) {
         int64_t nb = (p->n_obs + 3) / 4;
         if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
@@ -736,45 +884,8 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
                     NC == 2 ? static_cast<const typename Vec2<T>::type *>(p->ws.ptr) : nullptr,
                     p->n_obs, order, static_cast<const T *>(z), x);
             };
-            if (p->prec == MM_F32) {
-                if (p->nc == 1) go(0.f, std::integral_constant<int, 1>());
-                else go(0.f, std::integral_constant<int, 2>());
-            } else {
-                if (p->nc == 1) go(0.0, std::integral_constant<int, 1>());
-                else go(0.0, std::integral_constant<int, 2>());
-            }
+            dispatch_t_nc(p, go);
         });
-        MM_HIP(hipGetLastError());
-        return;
-    }
-    if (nrhs == 1 && p->sl_G > 0) {
-        // lane pixels are virtual ids d n_obs + c (sl_D scan directions), so
-        // wave (s, g) writes partial map s D + d; the partials are then
-        // added in that fixed order
-        const int32_t G = p->sl_G, S = p->sl_S, D = p->sl_D;
-        const int64_t n3 = 3 * (int64_t)p->n_obs;
-        const int32_t parts = S * D;
-        double *out = x;
-        if (parts > 1) {
-            if (!scratch) {
-                ws_alloc(ctx, ctx->pt_part, apply_PT_scratch_bytes(p, nrhs));
-                scratch = static_cast<char *>(ctx->pt_part.ptr);
-            }
-            out = reinterpret_cast<double *>(scratch);
-        }
-        const int32_t nv = D * p->n_obs;
-        int64_t nb = ((int64_t)G * S + 3) / 4;
-        if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
-        if (p->prec == MM_F32)
-            k_apply_PT_sl<float><<<(unsigned)nb, BS, 0, ctx->stream>>>(
-                p->sl_base.as<int64_t>(), p->sl_perm.as<int32_t>(), p->sl_w.as<float2>(),
-                p->sl_pix.as<int32_t>(), G, S, nv, static_cast<const float *>(z), out);
-        else
-            k_apply_PT_sl<double><<<(unsigned)nb, BS, 0, ctx->stream>>>(
-                p->sl_base.as<int64_t>(), p->sl_perm.as<int32_t>(), p->sl_w.as<double>(),
-                p->sl_pix.as<int32_t>(), G, S, nv, static_cast<const double *>(z), out);
-        if (parts > 1)
-            k_pt_sum_parts<<<grid_for(n3, 2048), BS, 0, ctx->stream>>>(out, parts, n3, x);
         MM_HIP(hipGetLastError());
         return;
     }
