@@ -735,15 +735,18 @@ extern "C" mm_status mm_rhs(mm_ctx *ctx, const mm_pointing *p, const mm_noise *n
     MM_CHECK(tod && b, MM_E_INVALID, "rhs: null argument");
     check_nrhs(nrhs);
     ensure_tod(ctx, p, nrhs);
-    DBuf flag;
-    flag.alloc(sizeof(int));
-    MM_HIP(hipMemsetAsync(flag.ptr, 0, sizeof(int), ctx->stream));
-    mask_tod_dev(ctx, p, nrhs, tod, ctx->tod_a.ptr, flag.as<int>());
-    int hf = 0;
-    MM_HIP(hipMemcpyAsync(&hf, flag.ptr, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    ctx->flag.alloc(sizeof(int));
+    int *flag = ctx->flag.as<int>();
+    MM_HIP(hipMemsetAsync(flag, 0, sizeof(int), ctx->stream));
+    // the FFT masks the data as it reads it; the other methods read a masked copy
+    const bool fft = nz->method == MM_NOISE_FFT;
+    if (fft) noise_fft_masked_dev(ctx, p, nz, nrhs, tod, ctx->tod_b.ptr, flag);
+    else mask_tod_dev(ctx, p, nrhs, tod, ctx->tod_a.ptr, flag);
+    int *hf = reinterpret_cast<int *>(pinned(ctx, sizeof(int)));
+    MM_HIP(hipMemcpyAsync(hf, flag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     MM_HIP(hipStreamSynchronize(ctx->stream));
-    MM_CHECK(!hf, MM_E_NONFINITE, "rhs: non-finite TOD sample on an observed pixel");
-    noise_apply_dev(ctx, nz, nrhs, ctx->tod_a.ptr, ctx->tod_b.ptr);
+    MM_CHECK(!*hf, MM_E_NONFINITE, "rhs: non-finite TOD sample on an observed pixel");
+    if (!fft) noise_apply_dev(ctx, nz, nrhs, ctx->tod_a.ptr, ctx->tod_b.ptr);
     apply_PT_dev(ctx, p, nrhs, ctx->tod_b.ptr, b);
     API_END
     return MM_OK;

@@ -107,6 +107,7 @@ struct mm_ctx {
     mm::DBuf gram_part, coef_g;    // MFMA Gram partials, coarse right-hand sides
     mm::DBuf xpack;                // map repacked for P: (I, Q, U, 0) records, or I and (Q, U) split
     mm::DBuf pt_part;              // per-segment partial maps of the sliced P^T
+    mm::DBuf flag;                 // device error flag of a call
     mm::DBuf tod_c;                // template filter: filtered TOD, ground sums and amplitudes
     // Bumped whenever one of the workspaces above is reallocated: captured
     // graphs hold their addresses and are re-captured when it changes.
@@ -263,6 +264,10 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
 int band_tile_len(int nrhs, bool small);
 void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod_rm, void *y,
                   int *nonfinite_flag);
+// z = N^-1 (mask . tod) by the FFT method, tod [nrhs][n_samp] masked as it is
+// read; *bad = 1 if a kept sample is not finite.
+void noise_fft_masked_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
+                          const void *tod, void *z, int *bad);
 void pair_sum_diff_dev(mm_ctx *ctx, int64_t n, mm_precision prec, const void *a, const void *b,
                        void *plus, void *minus);
 // FFT tables (spectra, twiddles, block table) for overlap-save blocks of

@@ -44,3 +44,45 @@ def test_fft_block_edges(ctx, n_fft, lam, prec, R):
     for r in range(R):
         ref = O.noise_apply_fft(on, host(t)[:, r].astype(np.float64))
         assert maxrel(z[:, r], ref) <= tol, (r, maxrel(z[:, r], ref))
+
+
+@pytest.mark.parametrize("n_fft", [16384, 32768])
+@pytest.mark.parametrize("lam", [33, 1000])
+@pytest.mark.parametrize("prec,R", [(0, 1), (0, 4), (1, 1), (1, 2)])
+def test_fft_masked_rhs(ctx, n_fft, lam, prec, R):
+    """b = P^T N^-1 (mask . d) with the mask applied as the FFT reads d:
+    non-finite values on flagged samples (and on pixels below the hit
+    threshold) are ignored, one on a kept sample is an error that leaves b
+    untouched."""
+    import torch
+    from paper_1801_08937_amd import mapmaker as mm
+    rng = np.random.default_rng(lam + n_fft + R)
+    V = n_fft - 2 * lam
+    istart = np.concatenate([[0], np.cumsum([2 * lam + 1, V + 1, 2 * lam + 7, V])]).astype(np.int64)
+    n = int(istart[-1])
+    pix = rng.integers(-1, 30, n).astype(np.int32)
+    pix[17] = 31  # a single hit: dropped
+    psi = rng.uniform(0, np.pi, n)
+    band = rng.standard_normal((2, lam + 1)) / np.sqrt(2 * lam + 1)
+    fid = np.array([0, 1, 1, 0], dtype=np.int32)
+    lp = ctx.pointing(dev(pix), dev(psi), 32, 3, prec)
+    nz = ctx.noise(istart, fid, band, lam, method=2, prec=prec)
+    nz.set_fft_block(n_fft)
+    op, on = O.pointing_build(pix, psi, 32, 3), O.noise_build(istart, fid, band, lam)
+    d = rng.standard_normal((R, n)).astype(np.float32 if prec else np.float64)
+    off = op.j < 0
+    dn = d.copy()
+    dn[:, off] = np.nan
+    dn[0, 17] = np.inf
+    b = host(ctx.rhs(lp, nz, dev(dn).reshape(-1), nrhs=R)).reshape(-1, R)
+    tol = 2e-5 if prec else 1e-12
+    for r in range(R):
+        ref = O.rhs(op, on, np.where(off, 0.0, d[r].astype(np.float64)), "fft")
+        assert maxrel(b[:, r], ref) <= tol, (r, maxrel(b[:, r], ref))
+    for t in (int(np.flatnonzero(~off)[0]), int(np.flatnonzero(~off)[-1])):
+        dn2 = d.copy()
+        dn2[R - 1, t] = np.nan
+        out = torch.full((op.n * R,), 7.0, dtype=torch.float64, device="cuda")
+        with pytest.raises(mm.MapmakerError, match="NONFINITE"):
+            ctx.rhs(lp, nz, dev(dn2).reshape(-1), out, nrhs=R)
+        assert bool((out == 7.0).all())
