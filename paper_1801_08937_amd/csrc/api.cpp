@@ -546,7 +546,9 @@ extern "C" mm_status mm_noise_build(mm_ctx *ctx, int32_t n_intervals,
         MM_HIP(hipMemcpyAsync(nz->fid.ptr, filter_id, sizeof(int32_t) * n_intervals,
                               hipMemcpyHostToDevice, s));
         MM_HIP(hipMemcpyAsync(nz->band64.ptr, band, sizeof(double) * nb, hipMemcpyHostToDevice, s));
-        if (prec == MM_F32) {
+        if (nz->method == MM_NOISE_FFT) {
+            // the transform's tables come from band64
+        } else if (prec == MM_F32) {
             std::vector<float> bf(band, band + nb);
             nz->band.alloc(sizeof(float) * nb);
             MM_HIP(hipMemcpyAsync(nz->band.ptr, bf.data(), sizeof(float) * nb,
@@ -561,8 +563,8 @@ extern "C" mm_status mm_noise_build(mm_ctx *ctx, int32_t n_intervals,
         // applies never modify the handle; one column on a short stream is
         // cut into small tiles so that it still fills the CUs
         nz->band_small = nz->n_samp <= (int64_t(1) << 20);
-        build_band_tiles(ctx, nz);
         if (nz->method == MM_NOISE_FFT) noise_fft_prepare(ctx, nz, 0);
+        else build_band_tiles(ctx, nz);
     } catch (...) {
         delete nz;
         throw;

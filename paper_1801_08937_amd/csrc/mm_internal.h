@@ -184,6 +184,7 @@ struct mm_noise {
     std::vector<int32_t> h_fid;
     std::vector<double> h_band;
     mm::DBuf istart, fid, band, band64;
+    mm::DBuf band_full;  // direct band: the symmetric filters [n_filters][2 half_bw + 1]
     // direct band: per column count R = 2^li (li = 0..6), the number of
     // tiles in the intervals before each interval, int64[7][n_int + 1]
     // (device copy and host copy); built with the handle, read-only after
@@ -261,7 +262,7 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
                   char *scratch = nullptr);
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
                      char *scratch = nullptr);
-int band_tile_len(int nrhs, bool small);
+int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp);
 void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod_rm, void *y,
                   int *nonfinite_flag);
 // z = N^-1 (mask . tod) by the FFT method, tod [nrhs][n_samp] masked as it is

@@ -659,6 +659,121 @@ __global__ void __launch_bounds__(NT) k_band_tiled(const int64_t *__restrict__ p
     }
 }
 
+// Direct band for several columns (8 and more), without LDS: thread (g, r) of
+// a wave keeps BC_OPT consecutive outputs of column r in registers and walks
+// the BC_OPT + 2 lambda input rows they need once, in ascending order, eight
+// loads in flight.  Every lane of the wave uses the same tap at the same time,
+// so the taps (the full symmetric filter, 2 lambda + 1 per filter) come through
+// scalar loads and each row feeds BC_OPT FMAs from registers: 1 + 2 lambda /
+// BC_OPT row loads per output, from the L1 and L2, against the tiled kernel's
+// 23 LDS reads per 64 FMAs.  Rows whose taps do not cover all BC_OPT outputs
+// (the first and last BC_OPT - 1) are unrolled on their own, so only true taps
+// are used.  Every output sums its taps in ascending offset, as in
+// k_band_tiled: the same bits.  Bound by FP64 FMA issue and the traffic of the
+// rows, which add up: 64 columns of 131,072 samples, lambda 32, 65.5 -> 44.2 us
+// (FMAs 14, reading and writing the columns once 27), lambda 100 175 -> 78 us; 8
+// columns of 2^20 samples, lambda 100, 110 -> 80 us.  8 outputs per thread took
+// 48.5 us, 24 and 32 the same as 16 but longer with fewer columns; holding the
+// kernel to 8 waves per SIMD spills (62 us).
+constexpr int BC_OPT = 16;
+constexpr int BC_MIN_R = 8;       // fewer columns: a wave's row loads fall in 16 or more lines
+constexpr int BC_MIN_LAMBDA = 8;  // 2 lambda + 1 >= BC_OPT
+
+template <typename T, int R, bool EDGE>
+__device__ __forceinline__ void band_rows(const T *__restrict__ f, int lam, int64_t t0,
+                                          int64_t a, int64_t b, int r, const T *__restrict__ y,
+                                          T *__restrict__ z) {
+    constexpr int O = BC_OPT;
+    const T *yr = y + r;
+    auto row = [&](int u) {  // input row t0 - lam + u, 0 outside the interval
+        const int64_t t = t0 - lam + u;
+        if (!EDGE) return yr[t * R];
+        const bool in = t >= a && t < b;
+        const T v = yr[(in ? t : a) * R];
+        return in ? v : (T)0;
+    };
+    T acc[O];
+#pragma unroll
+    for (int m = 0; m < O; ++m) acc[m] = 0;
+    T w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = row(q);
+    // rows 0 .. O - 1: outputs m <= u
+#pragma unroll
+    for (int ub = 0; ub < O; ub += 8) {
+        if (ub > 0) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) w[q] = row(ub + q);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int m = 0; m < O; ++m)
+                if (m <= ub + q) acc[m] += f[ub + q - m] * w[q];
+    }
+    // rows O .. 2 lam: all outputs (w holds rows u .. u + 7)
+    const int last = 2 * lam;
+    int u = O;
+    for (; u + 7 <= last; u += 8) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[q] = row(u + q);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int m = 0; m < O; ++m) acc[m] += f[u + q - m] * w[q];
+    }
+    for (; u <= last; ++u) {
+        const T v = row(u);
+#pragma unroll
+        for (int m = 0; m < O; ++m) acc[m] += f[u - m] * v;
+    }
+    // rows 2 lam + 1 .. 2 lam + O - 1: outputs m >= u - 2 lam
+    const T *fe = f + last;
+#pragma unroll
+    for (int db = 1; db < O; db += 8) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (db + q < O) w[q] = row(last + db + q);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int m = 0; m < O; ++m)
+                if (m >= db + q) acc[m] += fe[db + q - m] * w[q];
+    }
+#pragma unroll
+    for (int m = 0; m < O; ++m)
+        if (!EDGE || t0 + m < b) z[(t0 + m) * R + r] = acc[m];
+}
+
+template <typename T, int R>
+__global__ void __launch_bounds__(BS) k_band_cols(const int64_t *__restrict__ pref, int n_int,
+                                                  const int64_t *__restrict__ istart,
+                                                  const int32_t *__restrict__ fid,
+                                                  const T *__restrict__ full, int lam,
+                                                  int64_t n_tiles, const T *__restrict__ y,
+                                                  T *__restrict__ z) {
+    constexpr int GW = 64 / R, TL = (BS / R) * BC_OPT;
+    // neighbouring tiles share 2 lambda rows: contiguous runs per XCD
+    const int64_t bt = xcd_block(blockIdx.x, gridDim.x);
+    if (bt >= n_tiles) return;
+    int lo = 0, hi = n_int;  // pref[lo] <= bt < pref[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pref[mid] <= bt) lo = mid; else hi = mid;
+    }
+    const int64_t a = istart[lo], b = istart[lo + 1];
+    const T *f = full + (int64_t)fid[lo] * (2 * lam + 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t tw = a + (bt - pref[lo]) * TL + wave * GW * BC_OPT;  // the wave's first output
+    if (tw >= b) return;
+    const int64_t t0 = tw + lane / R * BC_OPT;
+    // rows read ahead past the last needed one by at most 8
+    if (tw - lam >= a && tw + GW * BC_OPT + lam + 8 <= b)
+        band_rows<T, R, false>(f, lam, t0, a, b, lane % R, y, z);
+    else
+        band_rows<T, R, true>(f, lam, t0, a, b, lane % R, y, z);
+}
+
 // y[t R + r] = mask_t * tod[r * n + t]; flags non-finite data on kept samples.
 template <typename T, int R>
 __global__ void __launch_bounds__(BS) k_mask(const int32_t *__restrict__ jpix, int64_t n,
@@ -909,16 +1024,28 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
 
 void noise_fft_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
 
+// Whether R columns take the register kernel without LDS: from 8 columns on,
+// where a row load of a wave falls in at most 8 runs of cache lines, and from
+// 2^21 values on, 8 waves per CU: with fewer its longer threads (16 outputs
+// each, against 8) leave the chip idle (us, register / tiled kernel, 8 columns,
+// lambda 64: 2^19 values 12.8 / 10.1, 2^20 14.0 / 15.7, 2^21 19.9 / 26.4; 16
+// columns: 12.4 / 8.8, 13.6 / 11.4, 20.8 / 20.4, 2^22 32.5 / 34.7; 64 columns:
+// 14.1 / 11.6, 15.3 / 18.7, 19.6 / 33.9).
+static bool band_by_rows(int nrhs, int lam, int64_t n_samp) {
+    return nrhs >= BC_MIN_R && lam >= BC_MIN_LAMBDA && n_samp * nrhs >= ((int64_t)1 << 21);
+}
+
 // Tile length of the direct band for R columns.
-int band_tile_len(int nrhs, bool small) {
+int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp) {
+    if (band_by_rows(nrhs, lam, n_samp)) return (BS / nrhs) * BC_OPT;
     return nrhs == 1 && small ? BAND_SMALL_NT * BT_OPT : (BS / nrhs) * BT_OPT;
 }
 
 // Taps per LDS chunk of the direct band: taps + window rows of R values fit
 // in BT_LDS bytes; a multiple of BT_OPT, at most the padded filter length.
-static int band_chunk(int lam, int R, mm_precision prec, bool small) {
+static int band_chunk(int lam, int R, mm_precision prec, bool small, int64_t n_samp) {
     const size_t te = prec == MM_F32 ? sizeof(float) : sizeof(double);
-    const int tl = band_tile_len(R, small);
+    const int tl = band_tile_len(R, small, lam, n_samp);
     const int nf_pad = (2 * lam + 1 + BT_OPT - 1) / BT_OPT * BT_OPT;
     int cl = (int)(((int64_t)(BT_LDS / te) - (int64_t)(tl - 1) * R) / (R + 1));
     cl = cl / BT_OPT * BT_OPT;
@@ -941,14 +1068,14 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
     }
     Scope sc(ctx->prof, ctx->stream, "Ninv_band");
     const int lam = nz->half_bw;
-    const int tl = band_tile_len(nrhs, nz->band_small);
+    const int tl = band_tile_len(nrhs, nz->band_small, lam, nz->n_samp);
     // tile counts for every column count are built with the noise handle, so
     // an apply never modifies it (handles may be shared across contexts)
     const int li = log2i(nrhs);
     const int64_t *pref = nz->tile_pref.as<int64_t>() + (int64_t)li * (nz->n_int + 1);
     const unsigned n_tiles = (unsigned)nz->h_tile_pref[(size_t)li * (nz->n_int + 1) + nz->n_int];
     const int cl =
-        nz->band_cl[li] > 0 ? nz->band_cl[li] : band_chunk(lam, nrhs, nz->prec, nz->band_small);
+        nz->band_cl[li] > 0 ? nz->band_cl[li] : band_chunk(lam, nrhs, nz->prec, nz->band_small, nz->n_samp);
     const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
     const size_t sm = te * ((size_t)cl + (size_t)(tl + cl - 1) * nrhs);
     if (nrhs == 1 && nz->band_small) {  // short single streams: 64-thread blocks
@@ -962,6 +1089,25 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
                 pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(),
                 nz->band.as<double>(), lam, cl, static_cast<const double *>(y),
                 static_cast<double *>(z));
+        MM_HIP(hipGetLastError());
+        return;
+    }
+    if (band_by_rows(nrhs, lam, nz->n_samp)) {
+        dispatch_r(nrhs, [&](auto RR) {
+            constexpr int R = decltype(RR)::value;
+            if constexpr (R >= BC_MIN_R) {
+                const unsigned grid = (n_tiles + 7) / 8 * 8;
+                auto go = [&](auto TT) {
+                    using T = decltype(TT);
+                    k_band_cols<T, R><<<grid, BS, 0, ctx->stream>>>(
+                        pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(),
+                        nz->band_full.as<T>(), lam, n_tiles, static_cast<const T *>(y),
+                        static_cast<T *>(z));
+                };
+                if (nz->prec == MM_F32) go(0.f);
+                else go(0.0);
+            }
+        });
         MM_HIP(hipGetLastError());
         return;
     }
@@ -1016,12 +1162,29 @@ void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod, 
 namespace mm {
 
 // Tile counts of the direct band for every column count R = 2^li (tile
-// length band_tile_len(R)): pref[li][i] = tiles in the intervals before i.
+// length band_tile_len(R)): pref[li][i] = tiles in the intervals before i; and
+// the full symmetric filters f[d] = c_|d - lambda| of the register kernel.
 void build_band_tiles(mm_ctx *ctx, mm_noise *nz) {
+    if (nz->half_bw >= BC_MIN_LAMBDA) {
+        const size_t lam = (size_t)nz->half_bw, nf = 2 * lam + 1;
+        auto fill = [&](auto TT) {
+            using T = decltype(TT);
+            std::vector<T> full(nf * nz->n_filters);
+            for (size_t f = 0; f < (size_t)nz->n_filters; ++f)
+                for (size_t d = 0; d < nf; ++d)
+                    full[f * nf + d] = (T)nz->h_band[f * (lam + 1) + (d < lam ? lam - d : d - lam)];
+            nz->band_full.alloc(sizeof(T) * full.size());
+            MM_HIP(hipMemcpyAsync(nz->band_full.ptr, full.data(), sizeof(T) * full.size(),
+                                  hipMemcpyHostToDevice, ctx->stream));
+            MM_HIP(hipStreamSynchronize(ctx->stream));
+        };
+        if (nz->prec == MM_F32) fill(0.f);
+        else fill(0.0);
+    }
     const size_t np = (size_t)nz->n_int + 1;
     nz->h_tile_pref.assign(7 * np, 0);
     for (int li = 0; li < 7; ++li) {
-        const int64_t tl = band_tile_len(1 << li, nz->band_small);
+        const int64_t tl = band_tile_len(1 << li, nz->band_small, nz->half_bw, nz->n_samp);
         int64_t *pr = nz->h_tile_pref.data() + li * np;
         for (int i = 0; i < nz->n_int; ++i)
             pr[i + 1] = pr[i] + (nz->h_istart[i + 1] - nz->h_istart[i] + tl - 1) / tl;
@@ -1094,7 +1257,7 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
         }
         // stage 1: taps per LDS chunk of the direct band
         if (nz->method == MM_NOISE_DIRECT) {
-            const int def = band_chunk(nz->half_bw, nrhs, nz->prec, nz->band_small);
+            const int def = band_chunk(nz->half_bw, nrhs, nz->prec, nz->band_small, nz->n_samp);
             double best = 1e30;
             int best_c = 0;
             for (int div : {1, 2, 4, 8}) {

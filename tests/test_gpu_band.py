@@ -97,3 +97,41 @@ def test_band_columns_do_not_mix(ctx):
     Z = host(ctx.noise_apply(nz, dev(Y.reshape(-1)), nrhs=R)).reshape(n, R)
     Z2 = host(ctx.noise_apply(nz, dev(Y2.reshape(-1)), nrhs=R)).reshape(n, R)
     np.testing.assert_array_equal(Z[:, 5], Z2[:, 5])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("R", [8, 64])
+@pytest.mark.parametrize("lam", [7, 8, 9, 31, 100])
+def test_band_columns_by_rows(ctx, lam, R, prec):
+    """8 columns and more from bandwidth 8 and 2^21 values on: intervals of the
+    shortest length, of one tile and one sample more or less, and a long one.  The same
+    bits as the tiled kernel (2 columns), and a non-finite input reaches the
+    outputs within lambda samples of it in its own column only."""
+    import torch
+    tile = 256 // R * 16
+    lens = [2 * lam + 1] + [max(2 * lam + 1, n) for n in (tile - 1, tile, tile + 1, (1 << 21) // R)]
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    fid = np.array([0, 1, 0, 1, 1], dtype=np.int32)
+    rng = np.random.default_rng(10 * lam + R)
+    band = rng.standard_normal((2, lam + 1))
+    nz = ctx.noise(istart, fid, band, lam, method=1, prec=prec)
+    n = int(istart[-1])
+    dt = torch.float32 if prec else torch.float64
+    y = dev(rng.standard_normal((n, R)), dt)
+    z = ctx.noise_apply(nz, y.reshape(-1), nrhs=R).reshape(n, R)
+    for c in (0, R - 2):
+        two = y[:, c:c + 2].contiguous()
+        z2 = ctx.noise_apply(nz, two.reshape(-1), nrhs=2).reshape(n, 2)
+        assert torch.equal(z[:, c:c + 2], z2)
+    on = O.noise_build(istart, fid, band, lam)
+    ref = O.noise_apply_direct(on, host(y)[:, 1].astype(np.float64))
+    assert maxrel(host(z)[:, 1], ref) <= (2e-5 if prec else TOL_OP)
+    if lam < 8:  # the tiled kernel: its zero-padded taps reach a little further
+        return
+    t = int(istart[4]) + 2 * tile
+    y[t, 3] = float("inf")
+    bad = ~torch.isfinite(ctx.noise_apply(nz, y.reshape(-1), nrhs=R).reshape(n, R))
+    assert int(bad[:, :3].sum()) == 0 and int(bad[:, 4:].sum()) == 0
+    hit = torch.nonzero(bad[:, 3]).reshape(-1)
+    assert int(hit.min()) == max(t - lam, int(istart[4]))
+    assert int(hit.max()) == min(t + lam, n - 1)
