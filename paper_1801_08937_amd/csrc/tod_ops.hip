@@ -12,15 +12,10 @@
 #include <type_traits>
 
 #include "mm_internal.h"
-#include "pol_weights.h"
+#include "pointing_gather.h"
 #include "xcd.h"
 
 namespace mm {
-
-template <typename T> struct Vec2;
-template <> struct Vec2<float> { using type = float2; };
-template <> struct Vec2<double> { using type = double2; };
-
 
 namespace {
 
@@ -92,57 +87,6 @@ __global__ void __launch_bounds__(BS) k_pack_map(const double *__restrict__ x, i
     }
 }
 
-template <typename T>
-__device__ __forceinline__ T p_gather4(int32_t j, typename Vec2<T>::type ww,
-                                       const double2 *__restrict__ x4) {
-    const int64_t jj = j < 0 ? 0 : j;  // branch-free, as p_gather
-    const double2 iq = x4[2 * jj];
-    const double u = x4[2 * jj + 1].x;
-    const T v = (T)iq.x + ww.x * (T)iq.y + ww.y * (T)u;
-    return j < 0 ? (T)0 : v;
-}
-
-// A once-read stream element loaded with the non-temporal cache policy: a
-// double, or a float2 moved as one 64-bit word.
-__device__ __forceinline__ double nt_load_w(const double *p) {
-    return __builtin_nontemporal_load(p);
-}
-__device__ __forceinline__ float2 nt_load_w(const float2 *p) {
-    return __builtin_bit_cast(
-        float2, __builtin_nontemporal_load(reinterpret_cast<const unsigned long long *>(p)));
-}
-__device__ __forceinline__ double2 nt_load_w(const double2 *p) { return *p; }
-
-template <typename T>
-__global__ void __launch_bounds__(BS) k_apply_P1(const int32_t *__restrict__ jpix,
-                                                 const typename Vec2<T>::type *__restrict__ w,
-                                                 int64_t n, const double2 *__restrict__ x4,
-                                                 T *__restrict__ y) {
-    const int64_t step = (int64_t)gridDim.x * BS;
-    int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    for (; t + 7 * step < n; t += 8 * step) {
-        int32_t j[8];
-        typename Vec2<T>::type ww[8];
-        // slots and weights are read once, and y written once: non-temporal,
-        // so that they do not push the gathered map lines out of the L2
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            j[q] = __builtin_nontemporal_load(jpix + t + q * step);
-            ww[q] = nt_load_w(w + t + q * step);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            __builtin_nontemporal_store(p_gather4<T>(j[q], ww[q], x4), y + t + q * step);
-    }
-    for (; t < n; t += step) y[t] = p_gather4<T>(jpix[t], w[t], x4);
-}
-
-// Single column, FP64: the weights are formed from the stored angles, so a
-// sample costs its map slot and angle (12 bytes) instead of index and two
-// weights (20 bytes).  The map is split into I (8 bytes) and (Q, U) (16
-// bytes) per slot; with a grid the slots follow Morton order, so the pixels
-// of 64 consecutive samples fall in few cache lines whatever the scan
-// direction.  Same arithmetic and order as k_apply_P (bitwise the same y).
 // Split map for P: I in xi, (Q, U) in xqu, at each of the n_copies slots of
 // every pixel (slot = NULL: one copy at the compact id).
 __global__ void __launch_bounds__(BS) k_pack_map_split(const double *__restrict__ x,
@@ -162,55 +106,32 @@ __global__ void __launch_bounds__(BS) k_pack_map_split(const double *__restrict_
     }
 }
 
-__device__ __forceinline__ double p_gather_psi(int32_t j, double psi,
-                                               const double *__restrict__ xi,
-                                               const double2 *__restrict__ xqu) {
-    const int32_t jj = j < 0 ? 0 : j;  // branch-free, as p_gather
-    const double i0 = xi[jj];
-    const double2 qu = xqu[jj];
-    double c, s;
-    pol_weights(psi, c, s);
-    const double v = i0 + c * qu.x + s * qu.y;
-    return j < 0 ? 0.0 : v;
-}
-
-__global__ void __launch_bounds__(BS) k_apply_P1_psi(const int32_t *__restrict__ jpix,
-                                                     const double *__restrict__ psi, int64_t n,
-                                                     const double *__restrict__ xi,
-                                                     const double2 *__restrict__ xqu,
-                                                     double *__restrict__ y) {
-    const int64_t step = (int64_t)gridDim.x * BS;
-    int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    // eight samples in flight per thread (measured: 0.70 ms against 0.73 with
-    // four at 1.34e8 samples; sixteen gave no more): their slots and angles,
-    // then their eight map gathers (from slot 0 where the sample is
-    // unobserved, so that no gather waits behind a branch), then the weights
-    for (; t + 7 * step < n; t += 8 * step) {
-        int32_t j[8];
-        double a[8], i8[8];
-        double2 qu8[8];
-        // slots and angles are read once, and y written once: non-temporal,
-        // so that they do not push the gathered map lines out of the L2
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            j[q] = __builtin_nontemporal_load(jpix + t + q * step);
-            a[q] = __builtin_nontemporal_load(psi + t + q * step);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int32_t jj = j[q] < 0 ? 0 : j[q];
-            i8[q] = xi[jj];
-            qu8[q] = xqu[jj];
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            double c, s;
-            pol_weights(a[q], c, s);
-            const double v = i8[q] + c * qu8[q].x + s * qu8[q].y;
-            __builtin_nontemporal_store(j[q] < 0 ? 0.0 : v, y + t + q * step);
-        }
+// y = P x, one column: a thread forms two neighbouring samples, read and
+// written in one access per stream, and blocks take consecutive samples, so the
+// blocks resident together gather from neighbouring pixels.  FP64 forms the
+// weights from the stored angles (12 bytes per sample with the slot, against 20
+// with stored weights).  Bound by HBM: 2^27 samples with three map copies (IQU
+// FP64) 595 -> 537 us, 5.0 TB/s of its 20 bytes per sample, the rate of a copy; 2^25
+// 240 -> 142 us, 2^23 54 -> 39 us.  Eight samples per thread a grid's stride apart
+// (150 VGPRs, three waves per SIMD, and only one sample per thread below 2^26)
+// was the earlier form; four neighbours per thread take 595 us, one 684 us, and
+// contiguous runs of blocks per XCD 603 us.
+template <typename T, typename S>
+__global__ void __launch_bounds__(BS) k_apply_P1(S src, int64_t n, T *__restrict__ y) {
+    const int64_t t = 2 * ((int64_t)blockIdx.x * BS + threadIdx.x);
+    if (t + 1 < n) {
+        typedef T t2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+        T v[2];
+        src.get_pair(t, v);
+        const t2 o = {v[0], v[1]};
+        // written once, read by the next kernel from beyond the L2
+        __builtin_nontemporal_store(o, reinterpret_cast<t2 *>(y + t));
+    } else if (t < n) {
+        const int64_t t1[1] = {t};
+        T v[1];
+        src.get(t1, v);
+        y[t] = v[0];
     }
-    for (; t < n; t += step) y[t] = p_gather_psi(jpix[t], psi[t], xi, xqu);
 }
 
 // Pixels are visited in the order `order` (NULL = ascending), e.g. square
@@ -283,21 +204,6 @@ __global__ void __launch_bounds__(BS) k_apply_PT(const int32_t *__restrict__ off
 // similar pace and the lines of z it gathers are shared in L2 and the
 // Infinity Cache instead of re-read from HBM.  Partial maps per segment go to
 // part[s][3 c + a] (or straight to x when S = 1).
-// Weight record of an entry: FP64 stores the angle and forms the weights
-// here; FP32 stores the two weights.
-template <typename T> struct SlRec;
-template <> struct SlRec<double> {
-    using type = double;
-    __device__ static void weights(double psi, double &c, double &s) { pol_weights(psi, c, s); }
-};
-template <> struct SlRec<float> {
-    using type = float2;
-    __device__ static void weights(float2 w, float &c, float &s) {
-        c = w.x;
-        s = w.y;
-    }
-};
-
 template <typename T, int NC>
 __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ base,
                                                     const int32_t *__restrict__ sl_perm,
@@ -416,62 +322,7 @@ __global__ void __launch_bounds__(BS) k_apply_P_nc(const int32_t *__restrict__ j
     }
 }
 
-// One column of an I or QU pointing: as k_apply_P1 / k_apply_P1_psi, eight
-// samples in flight per thread and no branch between their gathers.  The map
-// xm holds NC values per slot: the copies packed by k_pack_map_nc (with a
-// grid), or x itself.  2^25 samples of a cross-linked QU scan, FP64: the A apply
-// with offsets and slopes removed went from 613 to 453 us (P took 248 and P^T
-// 303 us when P walked one sample per round trip without copies and P^T one
-// wave per pixel).  Bound as the IQU P is: the gather's cache lines, then HBM.
-template <typename T> struct P1W {  // weight record of a sample in time order
-    using type = typename SlRec<T>::type;
-};
-template <typename T, int NC>
-__global__ void __launch_bounds__(BS) k_apply_P1_nc(const int32_t *__restrict__ jpix,
-                                                    const typename P1W<T>::type *__restrict__ w,
-                                                    int64_t n, const double *__restrict__ xm,
-                                                    T *__restrict__ y) {
-    const int64_t step = (int64_t)gridDim.x * BS;
-    int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    auto value = [&](int32_t j, typename P1W<T>::type ww, double x0, double x1) {
-        T v;
-        if constexpr (NC == 1) {
-            v = (T)x0;
-        } else {
-            T c, s;
-            SlRec<T>::weights(ww, c, s);
-            v = c * (T)x0 + s * (T)x1;
-        }
-        return j < 0 ? (T)0 : v;
-    };
-    for (; t + 7 * step < n; t += 8 * step) {
-        int32_t j[8];
-        typename P1W<T>::type ww[8]{};
-        double x0[8], x1[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            j[q] = __builtin_nontemporal_load(jpix + t + q * step);
-            if constexpr (NC == 2) ww[q] = nt_load_w(w + t + q * step);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t jj = (int64_t)NC * (j[q] < 0 ? 0 : j[q]);
-            x0[q] = xm[jj];
-            x1[q] = NC == 2 ? xm[jj + NC - 1] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            __builtin_nontemporal_store(value(j[q], ww[q], x0[q], x1[q]), y + t + q * step);
-    }
-    for (; t < n; t += step) {
-        const int32_t j = jpix[t];
-        const int64_t jj = (int64_t)NC * (j < 0 ? 0 : j);
-        typename P1W<T>::type ww{};
-        if constexpr (NC == 2) ww = w[t];
-        y[t] = value(j, ww, xm[jj], NC == 2 ? xm[jj + NC - 1] : 0.0);
-    }
-}
-
+// The copies of an I or QU map, NC values per slot.
 template <int NC>
 __global__ void __launch_bounds__(BS) k_pack_map_nc(const double *__restrict__ x, int32_t n_obs,
                                                     int n_copies,
@@ -827,6 +678,55 @@ template <typename F> void dispatch_t_nc(const mm_pointing *p, F &&f) {
 
 }  // namespace
 
+PMap p_map_dev(mm_ctx *ctx, const mm_pointing *p, const double *x, char *scratch) {
+    const bool f32 = p->prec == MM_F32;
+    PMap m{};
+    m.w = p->nc == 1 ? nullptr : (f32 ? p->w.ptr : p->psi.ptr);
+    // Gathering from copies saves cache lines per sample, packing them costs a
+    // launch and a pass over copies x n_obs: it pays from 2^22 samples and 256
+    // per pixel on (us, copies / x itself, IQU FP64, three directions: 64 x 64
+    // pixels, 2^20 samples 8.3 / 6.2; 128 x 128, 2^21 14.0 / 12.4, 2^23 38.8 / 43.6;
+    // 256 x 256, 2^23 44.7 / 42.5, 2^25 138 / 160, 2^27 520 / 632).
+    if (p->p_j.ptr == nullptr || p->n_samp < ((int64_t)1 << 22) ||
+        p->n_samp < 256 * (int64_t)p->n_obs) {
+        m.kind = p->nc;
+        m.slot = p->j.as<int32_t>();
+        m.xm = x;
+        return m;
+    }
+    if (!scratch) {
+        ws_alloc(ctx, ctx->xpack, apply_P_scratch_bytes(p, 1));
+        scratch = static_cast<char *>(ctx->xpack.ptr);
+    }
+    const int copies = p->p_copies, grid = grid_for(p->n_obs, 1024);
+    const int32_t *slot = p->p_slot.as<int32_t>();
+    m.slot = p->p_j.as<int32_t>();
+    double *pk = reinterpret_cast<double *>(scratch);
+    if (p->nc != 3) {
+        m.kind = p->nc;
+        m.xm = pk;
+        if (p->nc == 1)
+            k_pack_map_nc<1><<<grid, BS, 0, ctx->stream>>>(x, p->n_obs, copies, slot, pk);
+        else
+            k_pack_map_nc<2><<<grid, BS, 0, ctx->stream>>>(x, p->n_obs, copies, slot, pk);
+    } else if (f32) {
+        m.kind = PK_PACKED;
+        m.xq = reinterpret_cast<double2 *>(scratch);
+        k_pack_map<<<grid, BS, 0, ctx->stream>>>(x, p->n_obs, copies, slot,
+                                                 reinterpret_cast<double2 *>(scratch));
+    } else {
+        // I of all slots, then (Q, U) of all slots, 16-byte aligned
+        m.kind = PK_PACKED;
+        const size_t no = (size_t)p->n_obs * copies;
+        m.xm = pk;
+        double2 *xqu = reinterpret_cast<double2 *>(pk + 2 * ((no + 1) / 2));
+        m.xq = xqu;
+        k_pack_map_split<<<grid, BS, 0, ctx->stream>>>(x, p->n_obs, copies, slot, pk, xqu);
+    }
+    MM_HIP(hipGetLastError());
+    return m;
+}
+
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
                  char *scratch) {
     Scope sc(ctx->prof, ctx->stream, "P");
@@ -842,30 +742,17 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
         }
         return;
     }
-    if (p->nc != 3 && nrhs == 1) {
-        const bool slots = p->p_j.ptr != nullptr;
-        const int tuned = p->p_blocks[0];
-        const int grid = tuned > 0 ? tuned : grid_for(n, 32 * ctx->n_cu * 4);
-        if (slots && !scratch) {
-            ws_alloc(ctx, ctx->xpack, apply_P_scratch_bytes(p, nrhs));
-            scratch = static_cast<char *>(ctx->xpack.ptr);
-        }
-        auto go = [&](auto TT, auto NN) {
+    if (nrhs == 1) {
+        const PMap m = p_map_dev(ctx, p, x, scratch);
+        const unsigned grid = (unsigned)((n + 2 * BS - 1) / (2 * BS));
+        auto go = [&](auto TT) {
             using T = decltype(TT);
-            constexpr int NC = decltype(NN)::value;
-            const double *xm = x;
-            if (slots) {
-                double *pk = reinterpret_cast<double *>(scratch);
-                k_pack_map_nc<NC><<<grid_for(p->n_obs, 1024), BS, 0, ctx->stream>>>(
-                    x, p->n_obs, p->p_copies, p->p_slot.as<int32_t>(), pk);
-                xm = pk;
-            }
-            const void *w = NC == 1 ? nullptr : (p->prec == MM_F32 ? p->w.ptr : p->psi.ptr);
-            k_apply_P1_nc<T, NC><<<grid, BS, 0, ctx->stream>>>(
-                slots ? p->p_j.as<int32_t>() : p->j.as<int32_t>(),
-                static_cast<const typename P1W<T>::type *>(w), n, xm, static_cast<T *>(y));
+            dispatch_src<T>(m, [&](auto src) {
+                k_apply_P1<T><<<grid, BS, 0, ctx->stream>>>(src, n, static_cast<T *>(y));
+            });
         };
-        dispatch_t_nc(p, go);
+        if (p->prec == MM_F32) go(0.f);
+        else go(0.0);
         MM_HIP(hipGetLastError());
         return;
     }
@@ -883,37 +770,6 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
             };
             dispatch_t_nc(p, go);
         });
-        MM_HIP(hipGetLastError());
-        return;
-    }
-    if (nrhs == 1) {
-        const bool slots = p->p_j.ptr != nullptr;
-        const int copies = slots ? p->p_copies : 1;
-        const size_t no = (size_t)(p->n_obs > 0 ? p->n_obs : 1) * copies;
-        if (!scratch) {
-            ws_alloc(ctx, ctx->xpack, apply_P_scratch_bytes(p, nrhs));
-            scratch = static_cast<char *>(ctx->xpack.ptr);
-        }
-        double2 *xpack = reinterpret_cast<double2 *>(scratch);
-        const int tuned = p->p_blocks[0];
-        if (p->prec == MM_F32) {
-            k_pack_map<<<grid_for(p->n_obs, 1024), BS, 0, ctx->stream>>>(
-                x, p->n_obs, copies, slots ? p->p_slot.as<int32_t>() : nullptr, xpack);
-            const int grid = tuned > 0 ? tuned : grid_for(n, 8 * ctx->n_cu * 4);
-            k_apply_P1<float><<<grid, BS, 0, ctx->stream>>>(
-                slots ? p->p_j.as<int32_t>() : p->j.as<int32_t>(), p->w.as<float2>(), n, xpack,
-                static_cast<float *>(y));
-        } else {
-            // xpack holds I (no doubles) then (Q, U) (no double2), no = n_obs x copies
-            double *xi = reinterpret_cast<double *>(scratch);
-            double2 *xqu = reinterpret_cast<double2 *>(xi + 2 * ((no + 1) / 2));
-            k_pack_map_split<<<grid_for(p->n_obs, 1024), BS, 0, ctx->stream>>>(
-                x, p->n_obs, copies, slots ? p->p_slot.as<int32_t>() : nullptr, xi, xqu);
-            const int grid = tuned > 0 ? tuned : grid_for(n, 32 * ctx->n_cu * 4);
-            k_apply_P1_psi<<<grid, BS, 0, ctx->stream>>>(
-                slots ? p->p_j.as<int32_t>() : p->j.as<int32_t>(), p->psi.as<double>(), n, xi, xqu,
-                static_cast<double *>(y));
-        }
         MM_HIP(hipGetLastError());
         return;
     }
