@@ -154,7 +154,7 @@ struct mm_pointing {
     // pixel's own sum is independent of it; it only shapes cache locality.
     mm::DBuf seg_order;
     int32_t grid_width = 0;
-    int32_t p_blocks[7] = {0, 0, 0, 0, 0, 0, 0};  // tuned P grid per log2(nrhs); 0 = default
+    int32_t p_blocks[7] = {0, 0, 0, 0, 0, 0, 0};  // tuned P grid of several columns per log2(nrhs); 0 = default
     // tuned: visit pixels in seg_order (1) or ascending (0) in the
     // one-wave-per-pixel P^T, per log2(nrhs); -1 = default (seg_order if set)
     int32_t pt_order[7] = {-1, -1, -1, -1, -1, -1, -1};
@@ -207,12 +207,12 @@ struct mm_noise {
     int64_t pf_max_len = 0;  // longest subscan (picks the apply's register cache)
     mm::DBuf pf_sub, pf_omega, pf_ginv, pf_mask;
     // ground templates (pf_nb bins, 0 = none): each sample's bin, 1 / sum of
-    // w per bin, and the bin-sorted samples and weights interleaved per wave
+    // w per bin, and the bin-sorted samples interleaved per wave
     // (wave w = a chunk of a group of 64 bins: entries [gbase[w], gbase[w+1]),
     // lane = bin; gfirst[g] = first wave of group g)
     int32_t pf_nb = 0;
     int32_t pf_n_gwave = 0;
-    mm::DBuf pf_gbin, pf_gwinv, pf_gbase, pf_gfirst, pf_gsp, pf_gsw;
+    mm::DBuf pf_gbin, pf_gwinv, pf_gbase, pf_gfirst, pf_gsp;
 };
 
 struct mm_precond {

@@ -23,11 +23,12 @@
 // both template sets the filter is the symmetric combination
 //     F = F_B W^+ F_G W^+ F_B = W (I - Pi_B)(I - Pi_G)(I - Pi_B),
 // Pi_X = X (X^T W X)^+ X^T W, W^+ the pseudo-inverse (zero on flagged
-// samples).  Apply: y1 = (I - Pi_B) y on weighted samples (0 elsewhere); per
-// bin the weighted sums of y1 over fixed chunks of the bin's time-sorted
-// samples, then g = (chunk sums in chunk order) / (sum of w); z = W (I - Pi_B)
-// (y1 - G g), the subtraction done as the last pass reads y1.  No atomics:
-// every sum has a fixed order.
+// samples).  Apply: u = F_B y = W (I - Pi_B) y; per bin the sums of u over fixed
+// chunks of the bin's time-sorted samples, then g = (chunk sums in chunk order)
+// / (sum of w); z = W (I - Pi_B) W^+ (u - W G g), the subtraction done as the
+// last pass reads u.  Keeping u rather than W^+ u leaves the bin sums without
+// weights to read (8 of 20 bytes per entry).  No atomics: every sum has a fixed
+// order.
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -41,7 +42,15 @@ namespace {
 
 constexpr int BS = 256;
 constexpr int PF_MAX_ORDER = 7;
-constexpr int64_t GB_CHUNK = 512;  // entries per lane and wave of the ground sums
+// Entries per lane and wave of the ground sums, for n binned samples: enough
+// waves to fill the card (8,192 = 32 per CU on 256 CUs), at least four rounds of
+// eight loads and at most 512 entries.  A function of the problem alone.  With 512
+// throughout, 33.5M samples in 4,864 bins made 1,064 waves and took 213 us, and
+// 1M samples in 704 bins 33 waves.
+int64_t gb_chunk(int64_t n) {
+    const int64_t c = (n / (64 * 8192) + 7) / 8 * 8;
+    return c < 32 ? 32 : (c > 512 ? 512 : c);
+}
 
 // P_0..P_NP-1 at u by the three-term recurrence.
 template <typename T, int NP>
@@ -50,12 +59,17 @@ __device__ __forceinline__ void legendre(T u, T (&P)[NP]) {
     if constexpr (NP > 1) P[1] = u;
 #pragma unroll
     for (int k = 1; k + 1 < NP; ++k)
-        P[k + 1] = ((T)(2 * k + 1) * u * P[k] - (T)k * P[k - 1]) / (T)(k + 1);
+        P[k + 1] = ((T)(2 * k + 1) * u * P[k] - (T)k * P[k - 1]) * (T)(1.0 / (k + 1));
 }
 
-template <typename T>
-__device__ __forceinline__ T subscan_u(int64_t t, int64_t a, int64_t L) {
-    return L > 1 ? (T)(-1.0 + 2.0 * (double)(t - a) / (double)(L - 1)) : (T)0;
+// Position in [-1, 1] of sample a + i of a subscan of L samples, h =
+// subscan_step(L) formed once per subscan (a division per sample and pass was a
+// third of the apply's arithmetic).
+__device__ __forceinline__ double subscan_step(int64_t L) {
+    return L > 1 ? 2.0 / (double)(L - 1) : 0.0;
+}
+template <typename T> __device__ __forceinline__ T subscan_u(int64_t i, double h) {
+    return h > 0 ? (T)(-1.0 + (double)i * h) : (T)0;
 }
 
 __device__ __forceinline__ bool unflagged(const uint32_t *__restrict__ mask, int64_t t) {
@@ -85,7 +99,7 @@ __global__ void __launch_bounds__(BS) k_pf_gram(const int64_t *__restrict__ sub,
     const int64_t s = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
     if (s >= n_sub) return;
     const int64_t a = sub[s], b = sub[s + 1], L = b - a;
-    const double om = omega[s];
+    const double om = omega[s], h = subscan_step(L);
     double g[NP * NP];
 #pragma unroll
     for (int e = 0; e < NP * NP; ++e) g[e] = 0;
@@ -93,7 +107,7 @@ __global__ void __launch_bounds__(BS) k_pf_gram(const int64_t *__restrict__ sub,
     for (int64_t t = a + lane; t < b; t += 64) {
         if (!unflagged(mask, t) || !(om > 0)) continue;
         double P[NP];
-        legendre<double, NP>(subscan_u<double>(t, a, L), P);
+        legendre<double, NP>(subscan_u<double>(t - a, h), P);
         ++cnt;
 #pragma unroll
         for (int k = 0; k < NP; ++k)
@@ -151,17 +165,15 @@ __global__ void __launch_bounds__(BS) k_pf_gram(const int64_t *__restrict__ sub,
         }
 }
 
-// Input value of sample t: y, minus its bin's ground amplitude when ghat is
-// given.
+// w times the input value of sample t: w y, or with ghat (y already weighted)
+// y - w times the sample's ground amplitude.
 template <typename T>
-__device__ __forceinline__ T pf_value(const T *__restrict__ y, const int32_t *__restrict__ gbin,
-                                      const T *__restrict__ ghat, int64_t t, int R, int r) {
-    T v = y[t * R + r];
-    if (ghat) {
-        const int32_t g = gbin[t];
-        if (g >= 0) v -= ghat[(int64_t)g * R + r];
-    }
-    return v;
+__device__ __forceinline__ T pf_weighted(const T *__restrict__ y, const int32_t *__restrict__ gbin,
+                                         const T *__restrict__ ghat, int64_t t, int R, int r, T w) {
+    const T v = y[t * R + r];
+    if (!ghat) return w * v;
+    const int32_t g = gbin[t];
+    return g >= 0 ? v - w * ghat[(int64_t)g * R + r] : v;
 }
 
 // The apply for a subscan of at most 64 NV samples (the usual case): a
@@ -169,21 +181,20 @@ __device__ __forceinline__ T pf_value(const T *__restrict__ y, const int32_t *__
 // branch per sample), kept in registers for the second pass, and summed in
 // the same order as the streaming loop of k_pf_apply, so the result is the
 // same bits in one round trip instead of two per 64 samples.  NV is the
-// smallest of 4 and 8 that holds the longest subscan: loads beyond it would
-// be wasted issue slots and registers (measured: 0.51 against 0.67 ms for 4
-// and 8 at 256-sample subscans).
+// smallest of 1, 2, 4, 6, 8 and 16 that holds the longest subscan: loads beyond it
+// would be wasted issue slots and registers (measured: 0.51 against 0.67 ms for
+// 4 and 8 at 256-sample subscans).
 template <typename T, int NP, int NV>
-__device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, int64_t L, int lane,
+__device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, double h, int lane,
                                                 const double *__restrict__ gi, T om,
                                                 const uint32_t *__restrict__ mask, int R, int r,
                                                 const T *__restrict__ y,
                                                 const int32_t *__restrict__ gbin,
-                                                const T *__restrict__ ghat, bool weighted,
-                                                T *__restrict__ z) {
+                                                const T *__restrict__ ghat, T *__restrict__ z) {
     T mom[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k) mom[k] = 0;
-    T val[NV];
+    T val[NV];  // w times the input value
     bool in[NV], on[NV];
     int64_t tc[NV];
     uint32_t mw[NV];
@@ -195,6 +206,8 @@ __device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, int64_t L,
         val[q] = y[tc[q] * R + r];
         mw[q] = mask[tc[q] >> 5];
     }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) on[q] = in[q] && ((mw[q] >> (tc[q] & 31)) & 1u);
     if (ghat) {  // bins, then their amplitudes, each batch in flight together
         int32_t g[NV];
         T gv[NV];
@@ -203,16 +216,14 @@ __device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, int64_t L,
 #pragma unroll
         for (int q = 0; q < NV; ++q) gv[q] = ghat[(int64_t)(g[q] < 0 ? 0 : g[q]) * R + r];
 #pragma unroll
-        for (int q = 0; q < NV; ++q) val[q] = g[q] >= 0 ? val[q] - gv[q] : val[q];
+        for (int q = 0; q < NV; ++q)
+            val[q] = g[q] >= 0 ? val[q] - (on[q] ? om : (T)0) * gv[q] : val[q];
     }
 #pragma unroll
-    for (int q = 0; q < NV; ++q) on[q] = in[q] && ((mw[q] >> (tc[q] & 31)) & 1u);
-#pragma unroll
     for (int q = 0; q < NV; ++q) {
-        const int64_t t = a + lane + 64 * q;
-        const T wy = (on[q] ? om : (T)0) * val[q];
+        const T wy = ghat ? val[q] : (on[q] ? om : (T)0) * val[q];
         T P[NP];
-        legendre<T, NP>(subscan_u<T>(t, a, L), P);
+        legendre<T, NP>(subscan_u<T>(lane + 64 * q, h), P);
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
             const T nm = mom[k] + P[k] * wy;
@@ -237,18 +248,16 @@ __device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, int64_t L,
         const int64_t t = a + lane + 64 * q;
         const T w = on[q] ? om : (T)0;
         T P[NP];
-        legendre<T, NP>(subscan_u<T>(t, a, L), P);
+        legendre<T, NP>(subscan_u<T>(lane + 64 * q, h), P);
         T fit = 0;
 #pragma unroll
         for (int k = 0; k < NP; ++k) fit += P[k] * c[k];
-        const T res = val[q] - fit;
-        z[t * R + r] = weighted ? w * res : (on[q] && om > (T)0 ? res : (T)0);
+        z[t * R + r] = ghat ? val[q] - w * fit : w * (val[q] - fit);
     }
 }
 
-// One (subscan, column) per wave: weighted ? z = W (v - B c) : z = v - B c on
-// weighted samples and 0 elsewhere, with v the input value above and c the
-// subscan's weighted fit to v.
+// One (subscan, column) per wave: z = W (v - B c), c the subscan's weighted fit
+// to v.  v = y, or with ghat W v = y - W G ghat (y already weighted).
 template <typename T, int NP, int NV>
 __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub,
                                                  const double *__restrict__ omega, int64_t n_sub,
@@ -256,13 +265,13 @@ __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub
                                                  const double *__restrict__ ginv, int R,
                                                  const T *__restrict__ y,
                                                  const int32_t *__restrict__ gbin,
-                                                 const T *__restrict__ ghat, bool weighted,
-                                                 T *__restrict__ z) {
+                                                 const T *__restrict__ ghat, T *__restrict__ z) {
     const int lane = threadIdx.x & 63;
     const int64_t s = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
     if (s >= n_sub) return;
     const int r = blockIdx.y;
     const int64_t a = sub[s], b = sub[s + 1], L = b - a;
+    const double h = subscan_step(L);
     const double *gi = ginv + s * NP * NP;
     const T om = (T)omega[s];
     bool live = false;
@@ -278,16 +287,15 @@ __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub
     if (L <= 0) return;  // no sample (the cached path clamps to the first one)
     if constexpr (NV > 0) {
         if (L <= 64 * NV) {
-            pf_apply_cached<T, NP, NV>(a, b, L, lane, gi, om, mask, R, r, y, gbin, ghat, weighted,
-                                       z);
+            pf_apply_cached<T, NP, NV>(a, b, h, lane, gi, om, mask, R, r, y, gbin, ghat, z);
             return;
         }
     }
     for (int64_t t = a + lane; t < b; t += 64) {
         const T w = unflagged(mask, t) ? om : (T)0;
-        const T wy = w * pf_value(y, gbin, ghat, t, R, r);
+        const T wy = pf_weighted(y, gbin, ghat, t, R, r, w);
         T P[NP];
-        legendre<T, NP>(subscan_u<T>(t, a, L), P);
+        legendre<T, NP>(subscan_u<T>(t - a, h), P);
 #pragma unroll
         for (int k = 0; k < NP; ++k) mom[k] += P[k] * wy;
     }
@@ -304,15 +312,14 @@ __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub
         c[k] = v;
     }
     for (int64_t t = a + lane; t < b; t += 64) {
-        const bool on = unflagged(mask, t);
-        const T w = on ? om : (T)0;
+        const T w = unflagged(mask, t) ? om : (T)0;
         T P[NP];
-        legendre<T, NP>(subscan_u<T>(t, a, L), P);
+        legendre<T, NP>(subscan_u<T>(t - a, h), P);
         T fit = 0;
 #pragma unroll
         for (int k = 0; k < NP; ++k) fit += P[k] * c[k];
-        const T res = pf_value(y, gbin, ghat, t, R, r) - fit;
-        z[t * R + r] = weighted ? w * res : (on && om > (T)0 ? res : (T)0);
+        z[t * R + r] = ghat ? pf_weighted(y, gbin, ghat, t, R, r, w) - w * fit
+                            : w * (y[t * R + r] - fit);
     }
 }
 
@@ -364,17 +371,17 @@ __global__ void k_gb_weights(const int32_t *__restrict__ gperm, int64_t nv,
 }
 
 // Interleaved bin layout.  Bins are taken 64 at a time (group g: bins 64 g
-// + lane), and each group's entries are cut into chunks of at most GB_CHUNK
+// + lane), and each group's entries are cut into chunks of at most gb_chunk(n)
 // per lane; wave w = one (group, chunk).  Entry i of lane l of wave w sits at
 // base[w] + 64 i + l (padded with t = -1), so the 64 lanes read their bins'
 // i-th samples together: for neighbouring azimuth bins those are neighbouring
-// samples of one sweep, and the gather of y1 is coalesced.  Each lane sums
+// samples of one sweep, and the gather of u is coalesced.  Each lane sums
 // its entries in order; the partial sums of a bin are added in chunk order.
 template <typename T>
 __global__ void __launch_bounds__(BS) k_gb_part(const int64_t *__restrict__ base,
                                                 int32_t n_wave, const int32_t *__restrict__ sp,
-                                                const double *__restrict__ sw, int R,
-                                                const T *__restrict__ y1, T *__restrict__ part) {
+                                                int R, const T *__restrict__ u,
+                                                T *__restrict__ part) {
     const int lane = threadIdx.x & 63;
     const int64_t w = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
     if (w >= n_wave) return;
@@ -382,57 +389,71 @@ __global__ void __launch_bounds__(BS) k_gb_part(const int64_t *__restrict__ base
     const int64_t b0 = base[w];
     const int64_t W = (base[w + 1] - b0) >> 6;
     const int32_t *pp = sp + b0 + lane;
-    const double *wp = sw + b0 + lane;
     T acc = 0;
     int64_t i = 0;
-    // eight entries in flight: their samples and weights together, then the
-    // eight gathers (a padding entry, -1, reads sample 0 and adds 0, so no
-    // gather waits behind a branch), summed in entry order
+    // eight entries in flight: their samples, then the eight gathers (a padding
+    // entry, -1, reads sample 0 and adds 0, so no gather waits behind a
+    // branch), summed in entry order
     for (; i + 7 < W; i += 8) {
         int32_t t[8];
-        double wv[8];
         T v[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            t[q] = pp[64 * (i + q)];
-            wv[q] = wp[64 * (i + q)];
-        }
+        for (int q = 0; q < 8; ++q) t[q] = __builtin_nontemporal_load(pp + 64 * (i + q));
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const T g = y1[(int64_t)(t[q] < 0 ? 0 : t[q]) * R + r];
+            const T g = u[(int64_t)(t[q] < 0 ? 0 : t[q]) * R + r];
             v[q] = t[q] >= 0 ? g : (T)0;
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc += (T)wv[q] * v[q];
+        for (int q = 0; q < 8; ++q) acc += v[q];
     }
     for (; i < W; ++i) {
         const int32_t t = pp[64 * i];
-        if (t >= 0) acc += (T)wp[64 * i] * y1[(int64_t)t * R + r];
+        if (t >= 0) acc += u[(int64_t)t * R + r];
     }
     part[(w * R + r) * 64 + lane] = acc;
 }
 
-// ghat[b R + r] = (bin b's partial sums in chunk order) / (sum of w).
+// ghat[b R + r] = (sum of bin b's partial sums) / (sum of w): a block per group
+// of 64 bins (lane = bin) and column; each of its waves adds a quarter of the
+// group's chunks in order, eight loads in flight, and the quarters are added in
+// order.
 template <typename T>
-__global__ void k_gb_final(const int32_t *__restrict__ first, int32_t nb,
-                           const double *__restrict__ gwinv, int R, const T *__restrict__ part,
-                           T *__restrict__ ghat) {
-    const int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (e >= (int64_t)nb * R) return;
-    const int64_t b = e / R;
-    const int r = (int)(e % R);
-    const int64_t g = b >> 6, l = b & 63;
+__global__ void __launch_bounds__(BS) k_gb_final(const int32_t *__restrict__ first, int32_t nb,
+                                                 const double *__restrict__ gwinv, int R,
+                                                 const T *__restrict__ part,
+                                                 T *__restrict__ ghat) {
+    __shared__ T sm[BS];
+    const int64_t g = blockIdx.x;
+    const int r = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int32_t w0 = first[g], nw = first[g + 1] - w0;
+    const int32_t i0 = (int32_t)((int64_t)nw * wv / 4), i1 = (int32_t)((int64_t)nw * (wv + 1) / 4);
+    const T *pp = part + ((int64_t)w0 * R + r) * 64 + lane;
+    const int64_t st = (int64_t)64 * R;
     T acc = 0;
-    for (int64_t w = first[g]; w < first[g + 1]; ++w) acc += part[(w * R + r) * 64 + l];
-    ghat[e] = acc * (T)gwinv[b];
+    int32_t i = i0;
+    for (; i + 7 < i1; i += 8) {
+        T v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = pp[(i + q) * st];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += v[q];
+    }
+    for (; i < i1; ++i) acc += pp[i * st];
+    sm[threadIdx.x] = acc;
+    __syncthreads();
+    const int64_t b = g * 64 + lane;
+    if (wv == 0 && b < nb)
+        ghat[b * R + r] = (((sm[lane] + sm[64 + lane]) + sm[128 + lane]) + sm[192 + lane]) *
+                          (T)gwinv[b];
 }
 
 // Fill the interleaved layout from the bin-sorted entries.
 __global__ void k_gb_fill(const int64_t *__restrict__ base, int32_t n_wave,
                           const int32_t *__restrict__ wgroup, const int32_t *__restrict__ first,
                           const int64_t *__restrict__ goff, int32_t nb,
-                          const int32_t *__restrict__ gperm, const double *__restrict__ gw,
-                          int32_t *__restrict__ sp, double *__restrict__ sw) {
+                          const int32_t *__restrict__ gperm, int64_t chunk,
+                          int32_t *__restrict__ sp) {
     const int lane = threadIdx.x & 63;
     const int64_t nwv = ((int64_t)gridDim.x * BS) >> 6;
     for (int64_t w = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6; w < n_wave; w += nwv) {
@@ -441,8 +462,8 @@ __global__ void k_gb_fill(const int64_t *__restrict__ base, int32_t n_wave,
         const int64_t b = (int64_t)g * 64 + lane;
         int64_t lo = 0, hi = 0;
         if (b < nb) {
-            lo = goff[b] + k * GB_CHUNK;
-            hi = goff[b + 1] < lo + GB_CHUNK ? goff[b + 1] : lo + GB_CHUNK;
+            lo = goff[b] + k * chunk;
+            hi = goff[b + 1] < lo + chunk ? goff[b + 1] : lo + chunk;
         }
         const int64_t b0 = base[w];
         const int64_t W = (base[w + 1] - b0) >> 6;
@@ -451,7 +472,6 @@ __global__ void k_gb_fill(const int64_t *__restrict__ base, int32_t n_wave,
             const int64_t dst = b0 + 64 * i + lane;
             const bool ok = src < hi;
             sp[dst] = ok ? gperm[src] : -1;
-            sw[dst] = ok ? gw[src] : 0.0;
         }
     }
 }
@@ -493,7 +513,7 @@ int grid_for(int64_t n, int max_blocks = 8192) {
 }
 
 // Bin table of the ground templates: samples sorted by (bin, time), each
-// entry's weight, per-bin 1 / sum w, and chunks of at most GB_CHUNK entries
+// entry's weight, per-bin 1 / sum w, and chunks of at most gb_chunk entries
 // that never cross a bin.
 void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) {
     hipStream_t s = ctx->stream;
@@ -539,7 +559,8 @@ void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) 
     std::vector<int64_t> goff(nb + 1, 0);
     for (int32_t b = 0; b < nb; ++b) goff[b + 1] = goff[b] + hc[b];
     const int64_t nv = goff[nb];
-    // waves: per group of 64 bins, ceil(largest bin / GB_CHUNK) chunks; the
+    const int64_t chunk = gb_chunk(nv);
+    // waves: per group of 64 bins, ceil(largest bin / chunk) chunks; the
     // width of a wave is its largest lane count
     const int32_t ng = (nb + 63) / 64;
     std::vector<int32_t> first(ng + 1, 0), wgroup;
@@ -548,10 +569,10 @@ void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) 
         first[g] = (int32_t)wgroup.size();
         int64_t mx = 0;
         for (int32_t b = g * 64; b < std::min(nb, g * 64 + 64); ++b) mx = std::max<int64_t>(mx, hc[b]);
-        for (int64_t k = 0; k * GB_CHUNK < mx; ++k) {
+        for (int64_t k = 0; k * chunk < mx; ++k) {
             int64_t wd = 0;
             for (int32_t b = g * 64; b < std::min(nb, g * 64 + 64); ++b)
-                wd = std::max<int64_t>(wd, std::min<int64_t>(GB_CHUNK, hc[b] - k * GB_CHUNK));
+                wd = std::max<int64_t>(wd, std::min<int64_t>(chunk, hc[b] - k * chunk));
             wgroup.push_back(g);
             base.push_back(base.back() + 64 * wd);
         }
@@ -567,7 +588,6 @@ void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) 
     nz->pf_gbase.alloc(sizeof(int64_t) * base.size());
     nz->pf_gfirst.alloc(sizeof(int32_t) * (ng + 1));
     nz->pf_gsp.alloc(sizeof(int32_t) * (base.back() > 0 ? base.back() : 1));
-    nz->pf_gsw.alloc(sizeof(double) * (base.back() > 0 ? base.back() : 1));
     nz->pf_gwinv.alloc(sizeof(double) * nb);
     MM_HIP(hipMemcpyAsync(goff_d.ptr, goff.data(), sizeof(int64_t) * (nb + 1),
                           hipMemcpyHostToDevice, s));
@@ -589,8 +609,7 @@ void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) 
         k_gb_fill<<<(unsigned)std::min<int64_t>(((int64_t)n_wave * 64 + BS - 1) / BS, 16384), BS,
                     0, s>>>(nz->pf_gbase.as<int64_t>(), n_wave, wgroup_d.as<int32_t>(),
                             nz->pf_gfirst.as<int32_t>(), goff_d.as<int64_t>(), nb,
-                            gperm.as<int32_t>(), gw_d.as<double>(), nz->pf_gsp.as<int32_t>(),
-                            nz->pf_gsw.as<double>());
+                            gperm.as<int32_t>(), chunk, nz->pf_gsp.as<int32_t>());
     MM_HIP(hipGetLastError());
     MM_HIP(hipStreamSynchronize(s));
 }
@@ -636,7 +655,7 @@ void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void 
     dim3 grid((unsigned)((nz->pf_n_sub * 64 + BS - 1) / BS), nrhs);
     const bool f32 = nz->prec == MM_F32;
     const size_t te = f32 ? sizeof(float) : sizeof(double);
-    auto run = [&](auto TT, const void *in, const void *gh, bool weighted, void *out) {
+    auto run = [&](auto TT, const void *in, const void *gh, void *out) {
         using T = decltype(TT);
         dispatch_np(NP, [&](auto NN) {
             constexpr int N = decltype(NN)::value;
@@ -647,50 +666,54 @@ void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void 
                     nz->pf_sub.as<int64_t>(), nz->pf_omega.as<double>(), nz->pf_n_sub,
                     nz->pf_mask.as<uint32_t>(), nz->pf_ginv.as<double>(), nrhs,
                     static_cast<const T *>(in), gh ? nz->pf_gbin.as<int32_t>() : nullptr,
-                    static_cast<const T *>(gh), weighted, static_cast<T *>(out));
+                    static_cast<const T *>(gh), static_cast<T *>(out));
             };
-            if (nz->pf_max_len <= 256) go(std::integral_constant<int, 4>());
-            else if (nz->pf_max_len <= 512) go(std::integral_constant<int, 8>());
+            const int64_t m = nz->pf_max_len;
+            if (m <= 64) go(std::integral_constant<int, 1>());
+            else if (m <= 128) go(std::integral_constant<int, 2>());
+            else if (m <= 256) go(std::integral_constant<int, 4>());
+            else if (m <= 384) go(std::integral_constant<int, 6>());
+            else if (m <= 512) go(std::integral_constant<int, 8>());
+            else if (m <= 1024 && N <= 4) go(std::integral_constant<int, N <= 4 ? 16 : 0>());
             else go(std::integral_constant<int, 0>());
         });
     };
-    auto ground = [&](auto TT, const void *y1, void *part, void *ghat) {
+    auto ground = [&](auto TT, const void *u, void *part, void *ghat) {
         using T = decltype(TT);
         if (nz->pf_n_gwave > 0)
             k_gb_part<T><<<dim3((unsigned)(((int64_t)nz->pf_n_gwave * 64 + BS - 1) / BS), nrhs),
                            BS, 0, s>>>(nz->pf_gbase.as<int64_t>(), nz->pf_n_gwave,
-                                       nz->pf_gsp.as<int32_t>(), nz->pf_gsw.as<double>(), nrhs,
-                                       static_cast<const T *>(y1), static_cast<T *>(part));
-        const int64_t ne = (int64_t)nz->pf_nb * nrhs;
-        k_gb_final<T><<<(unsigned)((ne + BS - 1) / BS), BS, 0, s>>>(
+                                       nz->pf_gsp.as<int32_t>(), nrhs,
+                                       static_cast<const T *>(u), static_cast<T *>(part));
+        k_gb_final<T><<<dim3((unsigned)((nz->pf_nb + 63) / 64), nrhs), BS, 0, s>>>(
             nz->pf_gfirst.as<int32_t>(), nz->pf_nb, nz->pf_gwinv.as<double>(), nrhs,
             static_cast<const T *>(part), static_cast<T *>(ghat));
     };
     if (nz->pf_nb == 0) {
-        if (f32) run(0.f, y, nullptr, true, z);
-        else run(0.0, y, nullptr, true, z);
+        if (f32) run(0.f, y, nullptr, z);
+        else run(0.0, y, nullptr, z);
         MM_HIP(hipGetLastError());
         return;
     }
-    // scratch: the filtered TOD y1, then the ground chunk sums and amplitudes
+    // scratch: the filtered TOD u, then the ground chunk sums and amplitudes
     const size_t n_part = (size_t)(nz->pf_n_gwave > 0 ? nz->pf_n_gwave : 1) * nrhs * 64;
     const size_t n_ghat = (size_t)nz->pf_nb * nrhs;
-    const size_t y1_bytes = (te * (size_t)nz->n_samp * nrhs + 255) / 256 * 256;
+    const size_t u_bytes = (te * (size_t)nz->n_samp * nrhs + 255) / 256 * 256;
     if (!scratch) {
         ws_alloc(ctx, ctx->tod_c, polyfilter_scratch_bytes(nz, nrhs));
         scratch = static_cast<char *>(ctx->tod_c.ptr);
     }
-    void *y1 = scratch;
-    char *part = scratch + y1_bytes;
+    void *u = scratch;
+    char *part = scratch + u_bytes;
     char *ghat = part + te * n_part;
     if (f32) {
-        run(0.f, y, nullptr, false, y1);
-        ground(0.f, y1, part, ghat);
-        run(0.f, y1, ghat, true, z);
+        run(0.f, y, nullptr, u);
+        ground(0.f, u, part, ghat);
+        run(0.f, u, ghat, z);
     } else {
-        run(0.0, y, nullptr, false, y1);
-        ground(0.0, y1, part, ghat);
-        run(0.0, y1, ghat, true, z);
+        run(0.0, y, nullptr, u);
+        ground(0.0, u, part, ghat);
+        run(0.0, u, ghat, z);
     }
     MM_HIP(hipGetLastError());
 }
