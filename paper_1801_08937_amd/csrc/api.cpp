@@ -92,9 +92,7 @@ void ensure_tod(mm_ctx *ctx, const mm_pointing *p, int nrhs) {
 void apply_A_impl(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
                   const double *x, double *y) {
     ensure_tod(ctx, p, nrhs);
-    apply_P_dev(ctx, p, nrhs, x, ctx->tod_a.ptr);
-    noise_apply_dev(ctx, nz, nrhs, ctx->tod_a.ptr, ctx->tod_b.ptr);
-    apply_PT_dev(ctx, p, nrhs, ctx->tod_b.ptr, y);
+    apply_A_dev(ctx, p, nz, nrhs, x, y, ctx->tod_a.ptr, ctx->tod_b.ptr, nullptr);
 }
 
 double *pinned(mm_ctx *ctx, size_t bytes) {

@@ -212,6 +212,7 @@ struct mm_noise {
     // lane = bin; gfirst[g] = first wave of group g)
     int32_t pf_nb = 0;
     int32_t pf_n_gwave = 0;
+    int32_t pf_n_gwave512 = 0;  // waves that chunks of 512 entries would make (scratch count)
     mm::DBuf pf_gbin, pf_gwinv, pf_gbase, pf_gfirst, pf_gsp;
 };
 
@@ -250,9 +251,9 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width);
 void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width);
 
 // tod_ops.hip
-// The P, P^T and N^-1 launchers take an optional device scratch region of at
-// least *_scratch_bytes(...) bytes (256-byte aligned); with nullptr they use
-// (and grow) the context's workspaces instead.
+// The P and P^T launchers take an optional device scratch region of at least
+// *_scratch_bytes(...) bytes (256-byte aligned); with nullptr they use (and grow)
+// the context's workspaces instead.
 size_t apply_P_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t apply_PT_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t noise_scratch_bytes(const mm_noise *nz, int nrhs);
@@ -260,8 +261,7 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
                  char *scratch = nullptr);
 void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, double *x,
                   char *scratch = nullptr);
-void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                     char *scratch = nullptr);
+void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
 int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp);
 void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod_rm, void *y,
                   int *nonfinite_flag);
@@ -279,8 +279,18 @@ int polyfilter_max_order();
 void polyfilter_prepare(mm_ctx *ctx, const mm_pointing *p, mm_noise *nz,
                         const int32_t *ground_bin, int32_t n_ground_bins);
 size_t polyfilter_scratch_bytes(const mm_noise *nz, int nrhs);
-void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                          char *scratch = nullptr);
+void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
+// F P x into one of the two TOD vectors (returned); the other one is free after.
+// scratch (ground sums) and map_scratch (apply_P_scratch_bytes; may be ta): NULL =
+// the context's workspaces.
+const void *polyfilter_apply_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz,
+                                   int nrhs, const double *x, void *ta, void *tb, char *scratch,
+                                   char *map_scratch);
+// y = P^T N^-1 P x with the TOD vectors ta and tb.  scratch: at least
+// apply_A_scratch_bytes, or NULL to use the context's workspaces.
+size_t apply_A_scratch_bytes(const mm_pointing *p, const mm_noise *nz, int nrhs);
+void apply_A_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
+                 const double *x, double *y, void *ta, void *tb, char *scratch);
 bool noise_fft_supported(int half_bw, int64_t min_len);
 
 // map_ops.hip

@@ -64,17 +64,7 @@ extern "C" mm_status mm_apply_A_noalloc(mm_ctx *ctx, const mm_pointing *p, const
     MM_CHECK(base, MM_E_DEVICE, "apply_A_noalloc: scratch not set up for this device");
     const size_t te = p->prec == MM_F32 ? sizeof(float) : sizeof(double);
     const size_t tod = round256(te * (size_t)p->n_samp * nrhs);
-    // I and QU: P's map copies go where N^-1 will write, and P^T's partial maps
-    // where N^-1 has read; both fit there (checked when they are laid out)
-    const bool in_tod = p->nc != 3;
-    size_t stage = noise_scratch_bytes(nz, nrhs);
-    if (!in_tod) {
-        stage = std::max(stage, apply_P_scratch_bytes(p, nrhs));
-        stage = std::max(stage, apply_PT_scratch_bytes(p, nrhs));
-    }
-    MM_CHECK(!in_tod || std::max(apply_P_scratch_bytes(p, nrhs),
-                                 apply_PT_scratch_bytes(p, nrhs)) <= tod,
-             MM_E_DEVICE, "apply_A_noalloc: stage scratch above a TOD vector");
+    const size_t stage = apply_A_scratch_bytes(p, nz, nrhs);
     const size_t need = 2 * tod + round256(stage);
     if (scratch_used) *scratch_used = need;
     MM_CHECK(need <= NOALLOC_SCRATCH_BYTES, MM_E_INVALID,
@@ -84,11 +74,7 @@ extern "C" mm_status mm_apply_A_noalloc(mm_ctx *ctx, const mm_pointing *p, const
     const bool prof = ctx->prof.on;
     ctx->prof.on = false;
     try {
-        void *ta = base, *tb = base + tod;
-        char *st = base + 2 * tod;
-        apply_P_dev(ctx, p, nrhs, x, ta, in_tod ? static_cast<char *>(tb) : st);
-        noise_apply_dev(ctx, nz, nrhs, ta, tb, st);
-        apply_PT_dev(ctx, p, nrhs, tb, y, in_tod ? static_cast<char *>(ta) : st);
+        apply_A_dev(ctx, p, nz, nrhs, x, y, base, base + tod, base + 2 * tod);
     } catch (...) {
         ctx->prof.on = prof;
         throw;

@@ -36,13 +36,14 @@
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "mm_internal.h"
+#include "pointing_gather.h"
 
 namespace mm {
 namespace {
 
 constexpr int BS = 256;
 constexpr int PF_MAX_ORDER = 7;
-// Entries per lane and wave of the ground sums, for n binned samples: enough
+// Entries per lane and wave of the ground sums, for n entries with padding: enough
 // waves to fill the card (8,192 = 32 per CU on 256 CUs), at least four rounds of
 // eight loads and at most 512 entries.  A function of the problem alone.  With 512
 // throughout, 33.5M samples in 4,864 bins made 1,064 waves and took 213 us, and
@@ -184,13 +185,17 @@ __device__ __forceinline__ T pf_weighted(const T *__restrict__ y, const int32_t 
 // smallest of 1, 2, 4, 6, 8 and 16 that holds the longest subscan: loads beyond it
 // would be wasted issue slots and registers (measured: 0.51 against 0.67 ms for
 // 4 and 8 at 256-sample subscans).
-template <typename T, int NP, int NV>
+// With a gather source S (one column) the input y = P x is formed here instead of
+// read.
+struct NoSrc {};
+template <typename T, int NP, int NV, typename S>
 __device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, double h, int lane,
                                                 const double *__restrict__ gi, T om,
                                                 const uint32_t *__restrict__ mask, int R, int r,
-                                                const T *__restrict__ y,
+                                                const S &src, const T *__restrict__ y,
                                                 const int32_t *__restrict__ gbin,
                                                 const T *__restrict__ ghat, T *__restrict__ z) {
+    constexpr bool FROM_MAP = !std::is_same<S, NoSrc>::value;
     T mom[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k) mom[k] = 0;
@@ -203,9 +208,10 @@ __device__ __forceinline__ void pf_apply_cached(int64_t a, int64_t b, double h, 
         const int64_t t = a + lane + 64 * q;
         in[q] = t < b;
         tc[q] = in[q] ? t : a;
-        val[q] = y[tc[q] * R + r];
+        if constexpr (!FROM_MAP) val[q] = y[tc[q] * R + r];
         mw[q] = mask[tc[q] >> 5];
     }
+    if constexpr (FROM_MAP) src.get(tc, val);
 #pragma unroll
     for (int q = 0; q < NV; ++q) on[q] = in[q] && ((mw[q] >> (tc[q] & 31)) & 1u);
     if (ghat) {  // bins, then their amplitudes, each batch in flight together
@@ -287,7 +293,8 @@ __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub
     if (L <= 0) return;  // no sample (the cached path clamps to the first one)
     if constexpr (NV > 0) {
         if (L <= 64 * NV) {
-            pf_apply_cached<T, NP, NV>(a, b, h, lane, gi, om, mask, R, r, y, gbin, ghat, z);
+            pf_apply_cached<T, NP, NV>(a, b, h, lane, gi, om, mask, R, r, NoSrc(), y, gbin, ghat,
+                                       z);
             return;
         }
     }
@@ -321,6 +328,35 @@ __global__ void __launch_bounds__(BS) k_pf_apply(const int64_t *__restrict__ sub
         z[t * R + r] = ghat ? pf_weighted(y, gbin, ghat, t, R, r, w) - w * fit
                             : w * (y[t * R + r] - fit);
     }
+}
+
+// z = F_B P x, one column, for subscans of at most 64 NV samples: the map is
+// gathered where the filter would read y, so the time stream is written once
+// instead of written, read and written.  Bound by HBM (slot, angle and output, 20
+// bytes per sample in FP64) and the gather.  A apply, 2^25 samples, IQU, quadratics
+// per 256 samples 436 -> 345 us, with ground templates 681 -> 618; 2^24, QU, cubics per
+// 512 223 -> 172, I, quadratics per 777 190 -> 137.
+template <typename T, int NP, int NV, typename S>
+__global__ void __launch_bounds__(BS) k_pf_apply_P(const int64_t *__restrict__ sub,
+                                                   const double *__restrict__ omega,
+                                                   int64_t n_sub,
+                                                   const uint32_t *__restrict__ mask,
+                                                   const double *__restrict__ ginv, S src,
+                                                   T *__restrict__ z) {
+    const int lane = threadIdx.x & 63;
+    const int64_t s = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
+    if (s >= n_sub) return;
+    const int64_t a = sub[s], b = sub[s + 1], L = b - a;
+    const double *gi = ginv + s * NP * NP;
+    bool live = false;
+#pragma unroll
+    for (int e = 0; e < NP; ++e) live |= gi[e * NP + e] != 0.0;
+    if (!live) {
+        for (int64_t t = a + lane; t < b; t += 64) z[t] = (T)0;
+        return;
+    }
+    pf_apply_cached<T, NP, NV>(a, b, subscan_step(L), lane, gi, (T)omega[s], mask, 1, 0, src,
+                               (const T *)nullptr, nullptr, (const T *)nullptr, z);
 }
 
 // --- ground templates -------------------------------------------------------
@@ -559,10 +595,28 @@ void ground_prepare(mm_ctx *ctx, mm_noise *nz, const int32_t *gbin, int32_t nb) 
     std::vector<int64_t> goff(nb + 1, 0);
     for (int32_t b = 0; b < nb; ++b) goff[b + 1] = goff[b] + hc[b];
     const int64_t nv = goff[nb];
-    const int64_t chunk = gb_chunk(nv);
     // waves: per group of 64 bins, ceil(largest bin / chunk) chunks; the
     // width of a wave is its largest lane count
     const int32_t ng = (nb + 63) / 64;
+    // chunks small enough to fill the card, but (a few large bins among empty ones)
+    // no more chunk sums than a TOD vector holds beside those of 512-entry chunks
+    int64_t padded = 0;
+    auto n_waves = [&](int64_t c) {
+        int64_t w = 0;
+        padded = 0;
+        for (int32_t g = 0; g < ng; ++g) {
+            int64_t mx = 0;
+            for (int32_t b = g * 64; b < std::min(nb, g * 64 + 64); ++b)
+                mx = std::max<int64_t>(mx, hc[b]);
+            w += (mx + c - 1) / c;
+            padded += 64 * mx;
+        }
+        return w;
+    };
+    const int64_t w512 = n_waves(512);
+    int64_t chunk = gb_chunk(padded);
+    while (chunk < 512 && (n_waves(chunk) - w512) * 64 > n) chunk = std::min<int64_t>(512, 2 * chunk);
+    nz->pf_n_gwave512 = (int32_t)w512;
     std::vector<int32_t> first(ng + 1, 0), wgroup;
     std::vector<int64_t> base(1, 0);
     for (int32_t g = 0; g < ng; ++g) {
@@ -639,83 +693,141 @@ void polyfilter_prepare(mm_ctx *ctx, const mm_pointing *p, mm_noise *nz,
     if (ground_bin) ground_prepare(ctx, nz, ground_bin, n_ground_bins);
 }
 
+// Bytes of the ground sums: the chunk sums, then the amplitudes.
+static size_t ground_sum_bytes(const mm_noise *nz, int nrhs) {
+    const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
+    return te * nrhs *
+           ((size_t)(nz->pf_n_gwave > 0 ? nz->pf_n_gwave : 1) * 64 + (size_t)nz->pf_nb);
+}
+
+static size_t filtered_tod_bytes(const mm_noise *nz, int nrhs) {
+    const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
+    return (te * (size_t)nz->n_samp * nrhs + 255) / 256 * 256;
+}
+
+// Scratch counted for an A apply: a TOD vector and the ground sums with chunks of
+// 512 entries.  The sums of the chunks taken fit in that (ground_prepare); the
+// filtered TOD lies in one of the A apply's own TOD vectors.
 size_t polyfilter_scratch_bytes(const mm_noise *nz, int nrhs) {
     if (nz->pf_nb == 0) return 0;
     const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
-    const size_t n_part = (size_t)(nz->pf_n_gwave > 0 ? nz->pf_n_gwave : 1) * nrhs * 64;
-    const size_t n_ghat = (size_t)nz->pf_nb * nrhs;
-    return (te * (size_t)nz->n_samp * nrhs + 255) / 256 * 256 + te * (n_part + n_ghat);
+    return filtered_tod_bytes(nz, nrhs) +
+           te * nrhs * ((size_t)(nz->pf_n_gwave512 > 0 ? nz->pf_n_gwave512 : 1) * 64 +
+                        (size_t)nz->pf_nb);
 }
 
-void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                          char *scratch) {
-    Scope sc(ctx->prof, ctx->stream, "Ninv_poly");
-    const int NP = nz->pf_order + 1;
-    hipStream_t s = ctx->stream;
-    dim3 grid((unsigned)((nz->pf_n_sub * 64 + BS - 1) / BS), nrhs);
-    const bool f32 = nz->prec == MM_F32;
-    const size_t te = f32 ? sizeof(float) : sizeof(double);
-    auto run = [&](auto TT, const void *in, const void *gh, void *out) {
-        using T = decltype(TT);
-        dispatch_np(NP, [&](auto NN) {
+// f(T, integral constants NP and NV): the register cache that holds the longest
+// subscan (one kernel per size: a kernel's registers are those of its largest
+// path), 0 = streaming.
+template <typename F> static void dispatch_pf(const mm_noise *nz, F &&f) {
+    auto go = [&](auto TT) {
+        dispatch_np(nz->pf_order + 1, [&](auto NN) {
             constexpr int N = decltype(NN)::value;
-            // the register cache that holds the longest subscan (one kernel
-            // per size: a kernel's registers are those of its largest path)
-            auto go = [&](auto VV) {
-                k_pf_apply<T, N, decltype(VV)::value><<<grid, BS, 0, s>>>(
-                    nz->pf_sub.as<int64_t>(), nz->pf_omega.as<double>(), nz->pf_n_sub,
-                    nz->pf_mask.as<uint32_t>(), nz->pf_ginv.as<double>(), nrhs,
-                    static_cast<const T *>(in), gh ? nz->pf_gbin.as<int32_t>() : nullptr,
-                    static_cast<const T *>(gh), static_cast<T *>(out));
-            };
             const int64_t m = nz->pf_max_len;
-            if (m <= 64) go(std::integral_constant<int, 1>());
-            else if (m <= 128) go(std::integral_constant<int, 2>());
-            else if (m <= 256) go(std::integral_constant<int, 4>());
-            else if (m <= 384) go(std::integral_constant<int, 6>());
-            else if (m <= 512) go(std::integral_constant<int, 8>());
-            else if (m <= 1024 && N <= 4) go(std::integral_constant<int, N <= 4 ? 16 : 0>());
-            else go(std::integral_constant<int, 0>());
+            if (m <= 64) f(TT, NN, std::integral_constant<int, 1>());
+            else if (m <= 128) f(TT, NN, std::integral_constant<int, 2>());
+            else if (m <= 256) f(TT, NN, std::integral_constant<int, 4>());
+            else if (m <= 384) f(TT, NN, std::integral_constant<int, 6>());
+            else if (m <= 512) f(TT, NN, std::integral_constant<int, 8>());
+            else if (m <= 1024 && N <= 4) f(TT, NN, std::integral_constant<int, N <= 4 ? 16 : 0>());
+            else f(TT, NN, std::integral_constant<int, 0>());
         });
     };
-    auto ground = [&](auto TT, const void *u, void *part, void *ghat) {
+    if (nz->prec == MM_F32) go(0.f);
+    else go(0.0);
+}
+
+// out = F_B in, or with amplitudes gh (in = F_B y) W (I - Pi_B) W^+ (in - W G gh).
+static void pf_pass(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *in, const void *gh,
+                    void *out) {
+    const dim3 grid((unsigned)((nz->pf_n_sub * 64 + BS - 1) / BS), nrhs);
+    dispatch_pf(nz, [&](auto TT, auto NN, auto VV) {
         using T = decltype(TT);
+        k_pf_apply<T, decltype(NN)::value, decltype(VV)::value><<<grid, BS, 0, ctx->stream>>>(
+            nz->pf_sub.as<int64_t>(), nz->pf_omega.as<double>(), nz->pf_n_sub,
+            nz->pf_mask.as<uint32_t>(), nz->pf_ginv.as<double>(), nrhs,
+            static_cast<const T *>(in), gh ? nz->pf_gbin.as<int32_t>() : nullptr,
+            static_cast<const T *>(gh), static_cast<T *>(out));
+    });
+    MM_HIP(hipGetLastError());
+}
+
+// z = F y from u = F_B y (y not needed any more): ground amplitudes, last pass.
+static void pf_ground(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *u, void *z,
+                      char *sums) {
+    hipStream_t s = ctx->stream;
+    const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
+    char *ghat = sums + te * (size_t)(nz->pf_n_gwave > 0 ? nz->pf_n_gwave : 1) * nrhs * 64;
+    auto go = [&](auto TT) {
+        using T = decltype(TT);
+        T *part = reinterpret_cast<T *>(sums);
         if (nz->pf_n_gwave > 0)
             k_gb_part<T><<<dim3((unsigned)(((int64_t)nz->pf_n_gwave * 64 + BS - 1) / BS), nrhs),
                            BS, 0, s>>>(nz->pf_gbase.as<int64_t>(), nz->pf_n_gwave,
                                        nz->pf_gsp.as<int32_t>(), nrhs,
-                                       static_cast<const T *>(u), static_cast<T *>(part));
+                                       static_cast<const T *>(u), part);
         k_gb_final<T><<<dim3((unsigned)((nz->pf_nb + 63) / 64), nrhs), BS, 0, s>>>(
-            nz->pf_gfirst.as<int32_t>(), nz->pf_nb, nz->pf_gwinv.as<double>(), nrhs,
-            static_cast<const T *>(part), static_cast<T *>(ghat));
+            nz->pf_gfirst.as<int32_t>(), nz->pf_nb, nz->pf_gwinv.as<double>(), nrhs, part,
+            reinterpret_cast<T *>(ghat));
     };
+    if (nz->prec == MM_F32) go(0.f);
+    else go(0.0);
+    MM_HIP(hipGetLastError());
+    pf_pass(ctx, nz, nrhs, u, ghat, z);
+}
+
+void polyfilter_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {
+    Scope sc(ctx->prof, ctx->stream, "Ninv_poly");
     if (nz->pf_nb == 0) {
-        if (f32) run(0.f, y, nullptr, z);
-        else run(0.0, y, nullptr, z);
-        MM_HIP(hipGetLastError());
+        pf_pass(ctx, nz, nrhs, y, nullptr, z);
         return;
     }
-    // scratch: the filtered TOD u, then the ground chunk sums and amplitudes
-    const size_t n_part = (size_t)(nz->pf_n_gwave > 0 ? nz->pf_n_gwave : 1) * nrhs * 64;
-    const size_t n_ghat = (size_t)nz->pf_nb * nrhs;
-    const size_t u_bytes = (te * (size_t)nz->n_samp * nrhs + 255) / 256 * 256;
+    const size_t ub = filtered_tod_bytes(nz, nrhs);
+    ws_alloc(ctx, ctx->tod_c, ub + ground_sum_bytes(nz, nrhs));
+    char *u = static_cast<char *>(ctx->tod_c.ptr);
+    pf_pass(ctx, nz, nrhs, y, nullptr, u);
+    pf_ground(ctx, nz, nrhs, u, z, u + ub);
+}
+
+// Whether the filter gathers the map itself: one column, and subscans and orders
+// that the register-cached apply holds without spilling the gather.
+static bool pf_gathers(const mm_pointing *p, const mm_noise *nz, int nrhs) {
+    return nrhs == 1 && p->n_obs > 0 && nz->pf_max_len <= 1024 && nz->pf_order <= 3;
+}
+
+const void *polyfilter_apply_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz,
+                                   int nrhs, const double *x, void *ta, void *tb, char *scratch,
+                                   char *map_scratch) {
+    if (!pf_gathers(p, nz, nrhs)) {
+        apply_P_dev(ctx, p, nrhs, x, ta,
+                    map_scratch == ta ? static_cast<char *>(tb) : map_scratch);
+        Scope sc(ctx->prof, ctx->stream, "Ninv_poly");
+        pf_pass(ctx, nz, nrhs, ta, nullptr, tb);
+    } else {
+        Scope sc(ctx->prof, ctx->stream, "P_Ninv_poly");
+        const PMap m = p_map_dev(ctx, p, x, map_scratch);
+        const unsigned grid = (unsigned)((nz->pf_n_sub * 64 + BS - 1) / BS);
+        dispatch_pf(nz, [&](auto TT, auto NN, auto VV) {
+            using T = decltype(TT);
+            constexpr int N = decltype(NN)::value, V = decltype(VV)::value;
+            if constexpr (N <= 4 && V > 0)
+                dispatch_src<T>(m, [&](auto src) {
+                    k_pf_apply_P<T, N, V><<<grid, BS, 0, ctx->stream>>>(
+                        nz->pf_sub.as<int64_t>(), nz->pf_omega.as<double>(), nz->pf_n_sub,
+                        nz->pf_mask.as<uint32_t>(), nz->pf_ginv.as<double>(), src,
+                        static_cast<T *>(tb));
+                });
+        });
+        MM_HIP(hipGetLastError());
+    }
+    if (nz->pf_nb == 0) return tb;
+    Scope sc(ctx->prof, ctx->stream, "Ninv_poly");
     if (!scratch) {
-        ws_alloc(ctx, ctx->tod_c, polyfilter_scratch_bytes(nz, nrhs));
+        ws_alloc(ctx, ctx->tod_c, ground_sum_bytes(nz, nrhs));
         scratch = static_cast<char *>(ctx->tod_c.ptr);
     }
-    void *u = scratch;
-    char *part = scratch + u_bytes;
-    char *ghat = part + te * n_part;
-    if (f32) {
-        run(0.f, y, nullptr, u);
-        ground(0.f, u, part, ghat);
-        run(0.f, u, ghat, z);
-    } else {
-        run(0.0, y, nullptr, u);
-        ground(0.0, u, part, ghat);
-        run(0.0, u, ghat, z);
-    }
-    MM_HIP(hipGetLastError());
+    pf_ground(ctx, nz, nrhs, tb, ta, scratch);
+    return ta;
 }
 
 }  // namespace mm

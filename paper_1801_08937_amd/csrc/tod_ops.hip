@@ -8,6 +8,7 @@
 // so one wave step touches G consecutive samples x R columns: contiguous TOD
 // rows.  Each column is computed with the same arithmetic and order whatever
 // the other columns hold.
+#include <algorithm>
 #include <functional>
 #include <type_traits>
 
@@ -912,14 +913,13 @@ size_t noise_scratch_bytes(const mm_noise *nz, int nrhs) {
     return nz->method == MM_NOISE_POLY ? polyfilter_scratch_bytes(nz, nrhs) : 0;
 }
 
-void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                     char *scratch) {
+void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {
     if (nz->method == MM_NOISE_FFT) {
         noise_fft_apply_dev(ctx, nz, nrhs, y, z);
         return;
     }
     if (nz->method == MM_NOISE_POLY) {
-        polyfilter_apply_dev(ctx, nz, nrhs, y, z, scratch);
+        polyfilter_apply_dev(ctx, nz, nrhs, y, z);
         return;
     }
     Scope sc(ctx->prof, ctx->stream, "Ninv_band");
@@ -979,6 +979,31 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
                 lam, cl, static_cast<const double *>(y), static_cast<double *>(z));
     });
     MM_HIP(hipGetLastError());
+}
+
+// I and QU: P's map copies and P^T's partial maps lie in whichever TOD vector is
+// not in use then; both fit there (checked when they are laid out).
+size_t apply_A_scratch_bytes(const mm_pointing *p, const mm_noise *nz, int nrhs) {
+    size_t b = noise_scratch_bytes(nz, nrhs);
+    if (p->nc == 3)
+        b = std::max(b, std::max(apply_P_scratch_bytes(p, nrhs), apply_PT_scratch_bytes(p, nrhs)));
+    return b;
+}
+
+void apply_A_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
+                 const double *x, double *y, void *ta, void *tb, char *scratch) {
+    const bool in_tod = scratch && p->nc != 3;
+    const void *z = tb;
+    if (nz->method == MM_NOISE_POLY) {
+        // the filter's first pass reads the copies while it writes tb
+        z = polyfilter_apply_P_dev(ctx, p, nz, nrhs, x, ta, tb, scratch,
+                                   in_tod ? static_cast<char *>(ta) : scratch);
+    } else {
+        apply_P_dev(ctx, p, nrhs, x, ta, in_tod ? static_cast<char *>(tb) : scratch);
+        noise_apply_dev(ctx, nz, nrhs, ta, tb);
+    }
+    apply_PT_dev(ctx, p, nrhs, z, y,
+                 in_tod ? static_cast<char *>(z == tb ? ta : tb) : scratch);
 }
 
 void pair_sum_diff_dev(mm_ctx *ctx, int64_t n, mm_precision prec, const void *a, const void *b,
