@@ -6,11 +6,104 @@
 #include <limits>
 #include <cstring>
 #include <functional>
+#include <map>
+#include <mutex>
 #include <numeric>
 
 #include "mm_internal.h"
 
 namespace mm {
+
+// ------------------------------------------------------- device memory
+
+namespace {
+struct Pool {
+    std::mutex mu;
+    std::map<int, std::multimap<size_t, void *>> free;  // per device, by size
+    std::map<int, size_t> kept;
+    std::map<int, int> contexts;
+};
+Pool &pool() {
+    static Pool *p = new Pool();  // never destroyed: the runtime may go first at exit
+    return *p;
+}
+std::vector<void *> take_all(Pool &P, int dev) {
+    std::vector<void *> v;
+    for (auto &e : P.free[dev]) v.push_back(e.second);
+    P.free[dev].clear();
+    P.kept[dev] = 0;
+    return v;
+}
+}  // namespace
+
+void *dev_alloc(size_t bytes, size_t *got) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    bytes = (bytes + 255) / 256 * 256;
+    Pool &P = pool();
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        auto &f = P.free[dev];
+        auto it = f.lower_bound(bytes);
+        if (it != f.end() && it->first <= bytes + bytes / 8 + 4096) {
+            void *p = it->second;
+            *got = it->first;
+            P.kept[dev] -= it->first;
+            f.erase(it);
+            return p;
+        }
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        std::vector<void *> v;
+        {
+            std::lock_guard<std::mutex> lk(P.mu);
+            v = take_all(P, dev);
+        }
+        for (void *q : v) (void)hipFree(q);
+        p = nullptr;
+        if (v.empty() || hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+    }
+    *got = bytes;
+    return p;
+}
+
+void dev_free(void *ptr, size_t bytes) {
+    int cur = 0, dev = 0;
+    (void)hipGetDevice(&cur);
+    hipPointerAttribute_t at;
+    const bool known = hipPointerGetAttributes(&at, ptr) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    dev = known ? at.device : cur;
+    Pool &P = pool();
+    // no kernel may still use the block when it is handed out again
+    if (dev != cur) (void)hipSetDevice(dev);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (dev != cur) (void)hipSetDevice(cur);
+    if (known && idle) {
+        std::lock_guard<std::mutex> lk(P.mu);
+        if (P.contexts[dev] > 0 && P.kept[dev] + bytes <= POOL_MAX_BYTES) {
+            P.free[dev].emplace(bytes, ptr);
+            P.kept[dev] += bytes;
+            return;
+        }
+    }
+    (void)hipFree(ptr);
+}
+
+void dev_pool_ctx(int device, int delta) {
+    Pool &P = pool();
+    std::vector<void *> v;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        if ((P.contexts[device] += delta) <= 0) v = take_all(P, device);
+    }
+    for (void *q : v) (void)hipFree(q);
+}
 
 // ------------------------------------------------------------ profiler
 
@@ -121,21 +214,21 @@ void precond_apply_impl(mm_ctx *ctx, const mm_precond *M, int nrhs, const double
 // literally), into host out[R]; with M NULL, ||r|| / ||b||.  tmp: n R doubles.
 void precond_rel_res(mm_ctx *ctx, const mm_precond *M, int64_t n, int R, const double *r,
                      const double *b, double *tmp, std::vector<double> &out) {
-    DBuf d;
-    d.alloc(sizeof(double) * 2 * R);
+    Scratch sc(ctx);
+    double *d = sc.get<double>(2 * R);
     const double *vr = r, *vb = b;
     if (M) {
         precond_apply_impl(ctx, M, R, r, tmp, nullptr, 0);
         vr = tmp;
     }
-    dot_cols(ctx, n, R, vr, vr, d.as<double>());
+    dot_cols(ctx, n, R, vr, vr, d);
     if (M) {
         precond_apply_impl(ctx, M, R, b, tmp, nullptr, 0);
         vb = tmp;
     }
-    dot_cols(ctx, n, R, vb, vb, d.as<double>() + R);
+    dot_cols(ctx, n, R, vb, vb, d + R);
     std::vector<double> h(2 * R);
-    MM_HIP(hipMemcpyAsync(h.data(), d.ptr, sizeof(double) * 2 * R, hipMemcpyDeviceToHost,
+    MM_HIP(hipMemcpyAsync(h.data(), d, sizeof(double) * 2 * R, hipMemcpyDeviceToHost,
                           ctx->stream));
     MM_HIP(hipStreamSynchronize(ctx->stream));
     out.resize(R);
@@ -179,21 +272,31 @@ struct PcgWork {
     int R = 1;
     int64_t n = 0;
     int n_part = 1;
-    DBuf r, z, pv, q, part, part2, sc;  // part2: the ||r||^2 partials of an iteration
+    // a device array of its own (a session's), or from a call's scratch
+    struct Vec {
+        DBuf own;
+        void *ptr = nullptr;
+        void alloc(size_t b, Scratch *tmp) {
+            if (!tmp) own.alloc(b);
+            ptr = tmp ? tmp->get<char>((int64_t)b) : own.ptr;
+        }
+        template <typename T> T *as() const { return static_cast<T *>(ptr); }
+    };
+    Vec r, z, pv, q, part, part2, sc;  // part2: the ||r||^2 partials of an iteration
     PcgDev sd{};
     bool flexible = false;  // Polak-Ribiere beta (sd.rzo holds r'.z_old)
-    void alloc(int64_t n_, int R_) {
+    void alloc(int64_t n_, int R_, Scratch *tmp = nullptr) {
         n = n_;
         R = R_;
         n_part = reduction_parts(n, R_);
         const size_t vb = sizeof(double) * n * R;
-        r.alloc(vb);
-        z.alloc(vb);
-        pv.alloc(vb);
-        q.alloc(vb);
-        part.alloc(sizeof(double) * n_part * R);
-        part2.alloc(sizeof(double) * n_part * R);
-        sc.alloc(sizeof(double) * 8 * 64 + sizeof(int) * 3 * 64);
+        r.alloc(vb, tmp);
+        z.alloc(vb, tmp);
+        pv.alloc(vb, tmp);
+        q.alloc(vb, tmp);
+        part.alloc(sizeof(double) * n_part * R, tmp);
+        part2.alloc(sizeof(double) * n_part * R, tmp);
+        sc.alloc(sizeof(double) * 8 * 64 + sizeof(int) * 3 * 64, tmp);
         double *sb = sc.as<double>();
         sd.rho = sb; sd.pq = sb + 64; sd.alpha = sb + 128; sd.beta = sb + 192;
         sd.rn2 = sb + 256; sd.bn2 = sb + 320; sd.tol2 = sb + 384;
@@ -316,6 +419,7 @@ extern "C" mm_status mm_ctx_create(int device, void *hip_stream, mm_ctx **out) {
         MM_HIP(hipGetDeviceProperties(&prop, device));
         ctx->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
         noalloc_init(device);
+        dev_pool_ctx(device, 1);
         *out = ctx;
         return MM_OK;
     } catch (const mm::Error &e) {
@@ -334,7 +438,9 @@ extern "C" void mm_ctx_destroy(mm_ctx *ctx) {
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
+    const int device = ctx->device;
     delete ctx;
+    dev_pool_ctx(device, -1);
 }
 
 extern "C" const char *mm_last_error(const mm_ctx *ctx) {
@@ -406,16 +512,7 @@ extern "C" mm_status mm_pointing_set_grid(mm_ctx *ctx, mm_pointing *p, int32_t w
     API_BEGIN(ctx)
     MM_CHECK(p, MM_E_INVALID, "set_grid: null pointing");
     MM_CHECK(width >= 0, MM_E_INVALID, "set_grid: negative width");
-    if (width == 0) {
-        p->seg_order.release();
-        p->grid_width = 0;
-    } else {
-        pointing_set_grid_device(ctx, p, width, 32);
-        p->grid_width = width;
-    }
-    // P's map copies first: the sliced P^T is cut by the same scan directions
-    pointing_p_slots_device(ctx, p, width);
-    pointing_slices_device(ctx, p, width);
+    pointing_layout_device(ctx, p, width);
     API_END
     return MM_OK;
 }
@@ -1373,12 +1470,12 @@ extern "C" mm_status mm_solve(mm_ctx *ctx, const mm_pointing *p, const mm_noise 
     hipStream_t s = ctx->stream;
     const int64_t n = p->n();
     const int R = nrhs;
+    Scratch tmp(ctx);
     PcgWork w;
     w.flexible = (flags & MM_SOLVE_FLEXIBLE) != 0;
-    w.alloc(n, R);
-    DBuf hist;
-    hist.alloc(sizeof(double) * (size_t)(max_iter + 1) * R);
-    w.sd.hist = hist.as<double>();
+    w.alloc(n, R, &tmp);
+    double *hist = tmp.get<double>((int64_t)(max_iter + 1) * R);
+    w.sd.hist = hist;
     w.sd.hist_len = max_iter + 1;
     pcg_init_scalars(ctx, R, w.sd, tol);
     dot_cols(ctx, n, R, b, b, w.sd.bn2);
@@ -1422,17 +1519,16 @@ extern "C" mm_status mm_solve(mm_ctx *ctx, const mm_pointing *p, const mm_noise 
     // true residual
     apply_A_impl(ctx, p, nz, R, x, w.q.as<double>());
     axpby_cols(ctx, n, R, b, w.q.as<double>(), w.r.as<double>());
-    DBuf tr;
-    tr.alloc(sizeof(double) * R);
-    dot_cols(ctx, n, R, w.r.as<double>(), w.r.as<double>(), tr.as<double>());
+    double *tr = tmp.get<double>(R);
+    dot_cols(ctx, n, R, w.r.as<double>(), w.r.as<double>(), tr);
     std::vector<double> h_tr(R), h_bn2(R), h_rn(R);
     std::vector<int> h_brk(R), h_it(R);
-    MM_HIP(hipMemcpyAsync(h_tr.data(), tr.ptr, sizeof(double) * R, hipMemcpyDeviceToHost, s));
+    MM_HIP(hipMemcpyAsync(h_tr.data(), tr, sizeof(double) * R, hipMemcpyDeviceToHost, s));
     MM_HIP(hipMemcpyAsync(h_bn2.data(), w.sd.bn2, sizeof(double) * R, hipMemcpyDeviceToHost, s));
     MM_HIP(hipMemcpyAsync(h_rn.data(), w.sd.rn2, sizeof(double) * R, hipMemcpyDeviceToHost, s));
     MM_HIP(hipMemcpyAsync(h_brk.data(), w.sd.brk, sizeof(int) * R, hipMemcpyDeviceToHost, s));
     MM_HIP(hipMemcpyAsync(h_it.data(), w.sd.iters, sizeof(int) * R, hipMemcpyDeviceToHost, s));
-    MM_HIP(hipMemcpyAsync(h_rn2.data(), hist.ptr, sizeof(double) * (size_t)(it + 1) * R,
+    MM_HIP(hipMemcpyAsync(h_rn2.data(), hist, sizeof(double) * (size_t)(it + 1) * R,
                           hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
     std::vector<double> h_pr;

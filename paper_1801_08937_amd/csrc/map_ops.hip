@@ -1241,11 +1241,10 @@ void mbd_build_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, mm_pre
     const int32_t n_obs = p->n_obs;
     M->inv.alloc(sizeof(double) * packed_sym(p->nc) * (n_obs > 0 ? n_obs : 1));
     M->blk.alloc(sizeof(double) * packed_sym(p->nc) * (n_obs > 0 ? n_obs : 1));
-    DBuf rc, bad, mn;
-    rc.alloc(sizeof(double) * (n_obs > 0 ? n_obs : 1));
-    bad.alloc(sizeof(int));
-    mn.alloc(sizeof(double));
-    MM_HIP(hipMemsetAsync(bad.ptr, 0, sizeof(int), s));
+    Scratch sc(ctx);
+    double *rc = sc.get<double>(n_obs), *mn = sc.get<double>(1);
+    int *bad = sc.get<int>(1);
+    MM_HIP(hipMemsetAsync(bad, 0, sizeof(int), s));
     if (n_obs > 0) {
         const unsigned nb = (unsigned)((n_obs + 3) / 4);
         auto nc_build = [&](auto TT, auto NN) {
@@ -1256,7 +1255,7 @@ void mbd_build_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, mm_pre
                 NC == 2 ? static_cast<const typename Vec2w<T>::type *>(p->ws.ptr) : nullptr,
                 nz->istart.as<int64_t>(), nz->n_int, nz->fid.as<int32_t>(),
                 nz->band64.as<double>(), nz->half_bw, n_obs, M->inv.as<double>(),
-                M->blk.as<double>(), rc.as<double>(), bad.as<int>());
+                M->blk.as<double>(), rc, bad);
         };
         if (p->nc == 1)
             nc_build(0.0, std::integral_constant<int, 1>());
@@ -1270,21 +1269,21 @@ void mbd_build_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, mm_pre
                                                  nz->n_int, nz->fid.as<int32_t>(),
                                                  nz->band64.as<double>(), nz->half_bw, n_obs,
                                                  M->inv.as<double>(), M->blk.as<double>(),
-                                                 rc.as<double>(), bad.as<int>());
+                                                 rc, bad);
         else
             k_mbd_build<double><<<nb, BS, 0, s>>>(p->off.as<int32_t>(), p->perm.as<int32_t>(),
                                                   p->ws.as<double2>(), nz->istart.as<int64_t>(),
                                                   nz->n_int, nz->fid.as<int32_t>(),
                                                   nz->band64.as<double>(), nz->half_bw, n_obs,
                                                   M->inv.as<double>(), M->blk.as<double>(),
-                                                  rc.as<double>(), bad.as<int>());
-        k_min_reduce<<<1, BS, 0, s>>>(rc.as<double>(), n_obs, mn.as<double>());
+                                                  rc, bad);
+        k_min_reduce<<<1, BS, 0, s>>>(rc, n_obs, mn);
         MM_HIP(hipGetLastError());
     }
     int hb = 0;
     double hm = 1.0;
-    MM_HIP(hipMemcpyAsync(&hb, bad.ptr, sizeof(int), hipMemcpyDeviceToHost, s));
-    if (n_obs > 0) MM_HIP(hipMemcpyAsync(&hm, mn.ptr, sizeof(double), hipMemcpyDeviceToHost, s));
+    MM_HIP(hipMemcpyAsync(&hb, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    if (n_obs > 0) MM_HIP(hipMemcpyAsync(&hm, mn, sizeof(double), hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
     M->rcond_min = hm;
     *n_bad_out = hb;

@@ -35,6 +35,17 @@ struct Error : std::runtime_error {
         if (!(cond)) throw ::mm::Error((code), (msg));                                 \
     } while (0)
 
+// Device memory of the library's buffers.  dev_free waits for the device, as hipFree
+// does, and keeps the block for a later dev_alloc of about its size (registering a
+// strategy of 8.4M samples and dropping it: 4.4 ms, or up to 13 ms in a process that
+// holds more memory, without this; 2.6 ms with it).
+// At most POOL_MAX_BYTES per device are kept, and given back when the device's last
+// context goes, or when a hipMalloc fails.  Any thread may call them.
+constexpr size_t POOL_MAX_BYTES = (size_t)1 << 30;
+void *dev_alloc(size_t bytes, size_t *got);  // nullptr when there is no memory
+void dev_free(void *ptr, size_t bytes);      // bytes: what dev_alloc gave
+void dev_pool_ctx(int device, int delta);    // a context was created (+1) or destroyed (-1)
+
 // Owning device buffer.
 struct DBuf {
     void *ptr = nullptr;
@@ -49,7 +60,7 @@ struct DBuf {
     }
     ~DBuf() { release(); }
     void release() {
-        if (ptr) (void)hipFree(ptr);
+        if (ptr) dev_free(ptr, bytes);
         ptr = nullptr;
         bytes = 0;
     }
@@ -57,15 +68,13 @@ struct DBuf {
     // for the device first.
     void alloc(size_t b) {
         if (b <= bytes && ptr) return;
-        if (ptr) (void)hipDeviceSynchronize();
         release();
         if (b == 0) return;
-        hipError_t e = hipMalloc(&ptr, b);
-        if (e != hipSuccess) {
-            ptr = nullptr;
+        ptr = dev_alloc(b, &bytes);
+        if (!ptr) {
+            bytes = 0;
             throw Error(MM_E_OOM, "hipMalloc of " + std::to_string(b) + " bytes failed");
         }
-        bytes = b;
     }
     template <typename T> T *as() const { return static_cast<T *>(ptr); }
 };
@@ -108,6 +117,8 @@ struct mm_ctx {
     mm::DBuf xpack;                // map repacked for P: (I, Q, U, 0) records, or I and (Q, U) split
     mm::DBuf pt_part;              // per-segment partial maps of the sliced P^T
     mm::DBuf flag;                 // device error flag of a call
+    mm::DBuf build_ws;             // scratch of the build calls (Scratch below)
+    size_t build_off = 0;          // bytes of it in use
     mm::DBuf tod_c;                // template filter: filtered TOD, ground sums and amplitudes
     // Bumped whenever one of the workspaces above is reallocated: captured
     // graphs hold their addresses and are re-captured when it changes.
@@ -125,6 +136,58 @@ inline void ws_alloc(mm_ctx *ctx, DBuf &b, size_t bytes) {
     b.alloc(bytes);
     ++ctx->ws_gen;
 }
+// Temporaries of a build call, cut from the context's build_ws: a build takes dozens
+// of them, and a hipMalloc and hipFree each cost more than the kernels (6 of 10 ms
+// at 8.4M samples, several times that in a process holding much memory).  What does
+// not fit is allocated for the call; at the end of the outermost call the workspace
+// grows to what was needed, up to MAX_KEPT.  Only work on the context's stream may
+// use the memory.  Not to be held across another context's calls.
+class Scratch {
+  public:
+    static constexpr size_t MAX_KEPT = (size_t)512 << 20;
+    explicit Scratch(mm_ctx *c) : ctx(c), off0(c->build_off) {}
+    Scratch(const Scratch &) = delete;
+    Scratch &operator=(const Scratch &) = delete;
+    ~Scratch() {
+        ctx->build_off = off0;
+        if (extra.empty()) return;
+        (void)hipStreamSynchronize(ctx->stream);
+        extra.clear();
+        if (off0 == 0 && used <= MAX_KEPT) {
+            try {
+                ctx->build_ws.alloc(used);
+            } catch (...) {  // the next call allocates its own again
+            }
+        }
+    }
+    template <typename T> T *get(int64_t n) {
+        const size_t b = (sizeof(T) * (size_t)(n > 0 ? n : 1) + 255) / 256 * 256;
+        used += b;
+        if (ctx->build_off + b <= ctx->build_ws.bytes) {
+            T *p = reinterpret_cast<T *>(static_cast<char *>(ctx->build_ws.ptr) + ctx->build_off);
+            ctx->build_off += b;
+            return p;
+        }
+        // a block as large as all taken so far (64 KiB to 256 MiB), so that a first
+        // call makes few of them
+        if (extra.empty() || extra_off + b > extra.back().bytes) {
+            size_t blk = used < ((size_t)64 << 10) ? (size_t)64 << 10 : used;
+            if (blk > ((size_t)256 << 20)) blk = (size_t)256 << 20;
+            extra.emplace_back();
+            extra.back().alloc(blk > b ? blk : b);
+            extra_off = 0;
+        }
+        T *p = reinterpret_cast<T *>(static_cast<char *>(extra.back().ptr) + extra_off);
+        extra_off += b;
+        return p;
+    }
+
+  private:
+    mm_ctx *ctx;
+    size_t off0, used = 0, extra_off = 0;
+    std::vector<DBuf> extra;
+};
+
 }  // namespace mm
 
 struct mm_pointing {
@@ -149,7 +212,6 @@ struct mm_pointing {
     mm::DBuf p_slot, p_j;
     int32_t p_copies = 0;
     mm::DBuf p_chunk_grp;  // int32 copy (scan direction) of each 4,096-sample chunk
-    int32_t max_seg = 0;
     // Order in which P^T visits the compact pixels (empty = ascending).  Each
     // pixel's own sum is independent of it; it only shapes cache locality.
     mm::DBuf seg_order;
@@ -243,12 +305,9 @@ namespace mm {
 // pointing.hip
 void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, const double *psi,
                            int32_t min_hits);
-void pointing_set_grid_device(mm_ctx *ctx, mm_pointing *p, int32_t width, int32_t tile);
-// (Re)build the sliced P^T layout; width > 0 groups 8 x 8 pixel blocks of a
-// row-major grid of that width into slices, width 0 takes ascending pixels.
-void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width);
-// (Re)build the Morton map slots of the FP64 P (width > 0), or drop them.
-void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width);
+// (Re)build everything that depends on the grid hint (width 0 = none): the visiting
+// order of the one-wave-per-pixel P^T, P's map copies and the sliced P^T layout.
+void pointing_layout_device(mm_ctx *ctx, mm_pointing *p, int32_t width);
 
 // tod_ops.hip
 // The P and P^T launchers take an optional device scratch region of at least

@@ -3,9 +3,9 @@
 // weights (cos 2psi, sin 2psi) of Eq. datamodel, all on the device.
 //
 // Integer work only apart from the weights, so every integer output is
-// bit-exact and independent of scheduling: the histogram uses integer atomics
-// (order does not change a sum of integers); the permutation comes from a
-// stable LSD radix sort of (pixel, time).
+// bit-exact and independent of scheduling: one stable LSD radix sort of (pixel,
+// time) gives the permutation, and the run boundaries of the sorted keys the hit
+// counts (an atomic histogram of 8.4M samples took 180 us, the boundaries 15).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -22,29 +22,44 @@ namespace {
 
 constexpr int BS = 256;
 
-__global__ void k_validate(const int32_t *__restrict__ pix, const double *__restrict__ psi,
-                           int64_t n, int32_t npt, int *__restrict__ flags) {
+// Sort key (pixel, flagged samples last) and time of each sample; flags[0] = 1 if a
+// pixel lies outside [-1, npt), flags[1] = 1 if an angle is not finite.
+__global__ void k_keys(const int32_t *__restrict__ pix, const double *__restrict__ psi, int64_t n,
+                       int32_t npt, uint32_t *__restrict__ keys, int32_t *__restrict__ vals,
+                       int *__restrict__ flags) {
     int bad_pix = 0, bad_psi = 0;
     for (int64_t t = blockIdx.x * (int64_t)BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-        int32_t p = pix[t];
-        bad_pix |= (p < -1 || p >= npt);
+        const int32_t p = pix[t];
+        const bool in = p >= 0 && p < npt;
+        bad_pix |= p < -1 || p >= npt;
         if (psi) bad_psi |= !isfinite(psi[t]);
+        keys[t] = in ? (uint32_t)p : (uint32_t)npt;
+        vals[t] = (int32_t)t;
     }
     if (bad_pix) atomicOr(&flags[0], 1);
     if (bad_psi) atomicOr(&flags[1], 1);
 }
 
-__global__ void k_hist(const int32_t *__restrict__ pix, int64_t n, int32_t *__restrict__ hits) {
-    for (int64_t t = blockIdx.x * (int64_t)BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-        int32_t p = pix[t];
-        if (p >= 0) atomicAdd(&hits[p], 1);
+// Runs of equal keys: run of pixel p = sorted entries [start[p], end[p]) (both zeroed
+// before, so 0 without samples).
+__global__ void k_runs(const uint32_t *__restrict__ keys, int64_t n, uint32_t npt,
+                       int32_t *__restrict__ start, int32_t *__restrict__ end) {
+    for (int64_t i = blockIdx.x * (int64_t)BS + threadIdx.x; i < n; i += (int64_t)gridDim.x * BS) {
+        const uint32_t k = keys[i];
+        if (k >= npt) continue;
+        if (i == 0 || keys[i - 1] != k) start[k] = (int32_t)i;
+        if (i == n - 1 || keys[i + 1] != k) end[k] = (int32_t)(i + 1);
     }
 }
 
-__global__ void k_obs_flag(const int32_t *__restrict__ hits, int32_t npt, int32_t min_hits,
+__global__ void k_obs_flag(const int32_t *__restrict__ start, const int32_t *__restrict__ end,
+                           int32_t npt, int32_t min_hits, int32_t *__restrict__ hits,
                            int32_t *__restrict__ flag) {
     int32_t p = blockIdx.x * BS + threadIdx.x;
-    if (p < npt) flag[p] = hits[p] >= min_hits ? 1 : 0;
+    if (p >= npt) return;
+    const int32_t h = end[p] - start[p];
+    hits[p] = h;
+    flag[p] = h >= min_hits ? 1 : 0;
 }
 
 // cidx[p] = rank among observed pixels (exclusive scan of flags), -1 if not
@@ -67,14 +82,23 @@ __global__ void k_compact(const int32_t *__restrict__ hits, const int32_t *__res
 }
 
 __global__ void k_sample_j(const int32_t *__restrict__ pix, const int32_t *__restrict__ cidx,
-                           int64_t n, uint32_t flagged_key, int32_t *__restrict__ j,
-                           uint32_t *__restrict__ keys, int32_t *__restrict__ vals) {
+                           int64_t n, int32_t npt, int32_t *__restrict__ j) {
     for (int64_t t = blockIdx.x * (int64_t)BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-        int32_t p = pix[t];
-        int32_t c = p >= 0 ? cidx[p] : -1;
-        j[t] = c;
-        keys[t] = c >= 0 ? (uint32_t)c : flagged_key;
-        vals[t] = (int32_t)t;
+        const int32_t p = pix[t];
+        j[t] = p >= 0 && p < npt ? cidx[p] : -1;
+    }
+}
+
+// perm: the sorted samples of the observed pixels only.
+__global__ void k_perm(const uint32_t *__restrict__ keys, const int32_t *__restrict__ vals,
+                       int64_t n, uint32_t npt, const int32_t *__restrict__ cidx,
+                       const int32_t *__restrict__ start, const int32_t *__restrict__ off,
+                       int32_t *__restrict__ perm) {
+    for (int64_t i = blockIdx.x * (int64_t)BS + threadIdx.x; i < n; i += (int64_t)gridDim.x * BS) {
+        const uint32_t k = keys[i];
+        if (k >= npt) continue;
+        const int32_t c = cidx[k];
+        if (c >= 0) perm[off[c] + (int32_t)(i - start[k])] = vals[i];
     }
 }
 
@@ -129,6 +153,7 @@ constexpr int DIR_CHUNK = 4096;
 constexpr int DIR_STEP = 8;
 constexpr int DIR_MAXD = 12;
 constexpr int DIR_BINS = 12;
+constexpr int MAX_COPIES = 4;  // map copies, scan directions kept
 __global__ void __launch_bounds__(BS) k_chunk_dir(const int32_t *__restrict__ j,
                                                   const int32_t *__restrict__ obs_pix, int64_t n,
                                                   int32_t width, int32_t *__restrict__ bin) {
@@ -161,29 +186,86 @@ __global__ void __launch_bounds__(BS) k_chunk_dir(const int32_t *__restrict__ j,
     }
 }
 
-// First sample of each copy's samples that hits each pixel:
-// first[g n_obs + c] = min t over samples t of copy g with pixel c.
-__global__ void k_first_touch(const int32_t *__restrict__ j, const int32_t *__restrict__ grp,
-                              int64_t n, int32_t n_obs,
-                              unsigned long long *__restrict__ first) {
-    for (int64_t t = blockIdx.x * (int64_t)BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-        const int32_t c = j[t];
-        if (c < 0) continue;
-        const int64_t g = grp[t / DIR_CHUNK];
-        atomicMin(&first[g * n_obs + c], (unsigned long long)t);
+// Of the samples of each pixel (pixel, then time order) and scan direction g < G of
+// their chunks: how many, cnt[g n_obs + c], and the first, first[g n_obs + c] (n
+// without any).  One wave per pixel, so neither needs atomics.
+__global__ void __launch_bounds__(BS) k_pixel_dirs(const int32_t *__restrict__ off,
+                                                   const int32_t *__restrict__ perm,
+                                                   const int32_t *__restrict__ grp, int32_t n_obs,
+                                                   int G, int32_t n, int32_t *__restrict__ cnt,
+                                                   int32_t *__restrict__ first) {
+    const int lane = threadIdx.x & 63;
+    const int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
+    if (c >= n_obs) return;
+    const int32_t a = off[c], b = off[c + 1];
+    int32_t num[MAX_COPIES], fst[MAX_COPIES];
+#pragma unroll
+    for (int g = 0; g < MAX_COPIES; ++g) {
+        num[g] = 0;
+        fst[g] = n;
+    }
+    for (int32_t i = a; i < b; i += 64) {
+        const bool in = i + lane < b;
+        const int32_t t = in ? perm[i + lane] : 0;
+        const int q = in ? grp[t / DIR_CHUNK] : -1;
+#pragma unroll
+        for (int g = 0; g < MAX_COPIES; ++g) {
+            const unsigned long long m = __ballot(q == g);
+            if (m != 0 && fst[g] == n) fst[g] = __shfl(t, __ffsll(m) - 1);
+            num[g] += __popcll(m);
+        }
+    }
+    if (lane != 0) return;
+#pragma unroll
+    for (int g = 0; g < MAX_COPIES; ++g)
+        if (g < G) {
+            cnt[(int64_t)g * n_obs + c] = num[g];
+            first[(int64_t)g * n_obs + c] = fst[g];
+        }
+}
+
+// The pixel-sorted samples (and weights) regrouped by (direction, pixel), time order
+// kept: virtual pixel g n_obs + c takes entries from off2[g n_obs + c] on.
+template <typename V>
+__global__ void __launch_bounds__(BS) k_dir_scatter(const int32_t *__restrict__ off,
+                                                    const int32_t *__restrict__ perm,
+                                                    const V *__restrict__ w,
+                                                    const int32_t *__restrict__ grp,
+                                                    int32_t n_obs, int G,
+                                                    const int32_t *__restrict__ off2,
+                                                    int32_t *__restrict__ perm2,
+                                                    V *__restrict__ w2) {
+    const int lane = threadIdx.x & 63;
+    const int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
+    if (c >= n_obs) return;
+    const int32_t a = off[c], b = off[c + 1];
+    int32_t at[MAX_COPIES];
+#pragma unroll
+    for (int g = 0; g < MAX_COPIES; ++g) at[g] = g < G ? off2[(int64_t)g * n_obs + c] : 0;
+    for (int32_t i = a; i < b; i += 64) {
+        const bool in = i + lane < b;
+        const int32_t t = in ? perm[i + lane] : 0;
+        const int q = in ? grp[t / DIR_CHUNK] : -1;
+#pragma unroll
+        for (int g = 0; g < MAX_COPIES; ++g) {
+            const unsigned long long m = __ballot(q == g);
+            if (q == g) {
+                const int32_t d = at[g] + __popcll(m & ((1ull << lane) - 1));
+                perm2[d] = t;
+                if (w) w2[d] = w[i + lane];
+            }
+            at[g] += __popcll(m);
+        }
     }
 }
 
-// Sort keys: copy in the top byte, then the first touch (unhit pixels last,
-// in compact id order through the stable sort); value = g n_obs + c.
-__global__ void k_touch_keys(const unsigned long long *__restrict__ first, int64_t total,
-                             int32_t n_obs, uint64_t *__restrict__ keys,
-                             int32_t *__restrict__ vals) {
+// Sort keys: copy, then the first touch (unhit pixels last, in compact id order
+// through the stable sort), below bit nb; value = g n_obs + c.
+__global__ void k_touch_keys(const int32_t *__restrict__ first, int64_t total, int32_t n_obs,
+                             int nb, uint64_t *__restrict__ keys, int32_t *__restrict__ vals) {
     for (int64_t e = blockIdx.x * (int64_t)BS + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * BS) {
-        const uint64_t g = (uint64_t)(e / n_obs);
-        const uint64_t f = first[e];
-        keys[e] = (g << 56) | (f < (1ull << 56) ? f : (1ull << 56) - 1);
+        keys[e] = ((uint64_t)(e / n_obs) << nb) | (uint64_t)first[e];
         vals[e] = (int32_t)e;
     }
 }
@@ -198,41 +280,8 @@ __global__ void k_slot_of_sample_g(const int32_t *__restrict__ j, const int32_t 
     }
 }
 
-// Sliced P^T layout.  Lane (g, l) finds, by binary search in its pixel's
-// time-sorted list perm[off[c], off[c+1]), where each time segment
-// [n s / S, n (s+1) / S) starts; cnt / start are stored per (s G + g, l).
-// Sliced P^T per scan direction.  Sort keys of the pixel-sorted samples by
-// their chunk's direction (a stable sort keeps pixel, then time, order inside
-// each direction), the sample counts of every virtual pixel d n_obs + c, and
-// the lane pixels: copy d's first-touch order of the pixels, a block of G
-// slices per direction.
-__global__ void k_perm_dir_keys(const int32_t *__restrict__ perm, int64_t n_valid,
-                                const int32_t *__restrict__ grp, uint32_t *__restrict__ keys,
-                                int32_t *__restrict__ vals) {
-    for (int64_t i = blockIdx.x * (int64_t)BS + threadIdx.x; i < n_valid;
-         i += (int64_t)gridDim.x * BS) {
-        keys[i] = (uint32_t)grp[perm[i] / DIR_CHUNK];
-        vals[i] = (int32_t)i;
-    }
-}
-__global__ void k_dir_counts(const int32_t *__restrict__ j, const int32_t *__restrict__ grp,
-                             int64_t n, int32_t n_obs, int32_t *__restrict__ cnt) {
-    for (int64_t t = blockIdx.x * (int64_t)BS + threadIdx.x; t < n; t += (int64_t)gridDim.x * BS) {
-        const int32_t c = j[t];
-        if (c >= 0) atomicAdd(&cnt[(int64_t)grp[t / DIR_CHUNK] * n_obs + c], 1);
-    }
-}
-template <typename V>
-__global__ void k_perm_gather(const int32_t *__restrict__ idx, const int32_t *__restrict__ perm,
-                              const V *__restrict__ w, int64_t n_valid,
-                              int32_t *__restrict__ perm2, V *__restrict__ w2) {
-    for (int64_t i = blockIdx.x * (int64_t)BS + threadIdx.x; i < n_valid;
-         i += (int64_t)gridDim.x * BS) {
-        const int32_t k = idx[i];
-        perm2[i] = perm[k];
-        if (w) w2[i] = w[k];
-    }
-}
+// Sliced P^T per scan direction: the lane pixels are copy d's first-touch order of
+// the virtual pixels d n_obs + c, a block of G slices per direction.
 __global__ void k_sl_pix_dir(const int32_t *__restrict__ slot, int64_t total, int32_t n_obs,
                              int32_t G, int32_t *__restrict__ sl_pix) {
     for (int64_t v = blockIdx.x * (int64_t)BS + threadIdx.x; v < total;
@@ -243,6 +292,14 @@ __global__ void k_sl_pix_dir(const int32_t *__restrict__ slot, int64_t total, in
     }
 }
 
+__global__ void k_iota(int32_t n, int32_t *__restrict__ v) {
+    const int32_t i = blockIdx.x * BS + threadIdx.x;
+    if (i < n) v[i] = i;
+}
+
+// Sliced P^T layout.  Lane (g, l) finds, by binary search in its pixel's
+// time-sorted list perm[off[c], off[c+1]), where each time segment
+// [n s / S, n (s+1) / S) starts; cnt / start are stored per (s G + g, l).
 __global__ void k_sl_bounds(const int32_t *__restrict__ sl_pix, int32_t G, int32_t S,
                             int64_t n_samp, const int32_t *__restrict__ off,
                             const int32_t *__restrict__ perm, int32_t *__restrict__ cnt,
@@ -319,19 +376,24 @@ __global__ void k_sl_fill(const int64_t *__restrict__ base, const int32_t *__res
         const int64_t len = (base[w + 1] - b0) >> 6;
         const int32_t c = cnt[w * 64 + lane];
         const int32_t st = start[w * 64 + lane];
-        for (int64_t k = 0; k < len; ++k) {
-            const int64_t idx = b0 + 64 * k + lane;
-            if (k < c) {
-                const int32_t t = perm[st + k];
-                sl_perm[idx] = t;
-                if (W) sl_w[idx] = sl_value<V>(src, st + k, t);
-            } else {
-                sl_perm[idx] = -1;
-                if (W) {
-                    V zero;
-                    sl_zero(zero);
-                    sl_w[idx] = zero;
-                }
+        // eight entries in flight per lane: their samples, then their records
+        for (int64_t k = 0; k < len; k += 8) {
+            int32_t t[8];
+            V v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t[q] = k + q < c ? perm[st + k + q] : -1;
+            if (W) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (t[q] >= 0) v[q] = sl_value<V>(src, st + k + q, t[q]);
+                    else sl_zero(v[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (k + q >= len) break;
+                const int64_t idx = b0 + 64 * (k + q) + lane;
+                sl_perm[idx] = t[q];
+                if (W) sl_w[idx] = v[q];
             }
         }
     }
@@ -343,7 +405,31 @@ int grid_for(int64_t n, int max_blocks = 8192) {
     return (int)(g < 1 ? 1 : g);
 }
 
-}  // namespace
+// bits(x): the smallest b with x < 2^b.
+unsigned bits(uint64_t x) {
+    unsigned b = 1;
+    while (b < 64 && (x >> b) != 0) ++b;
+    return b;
+}
+
+// rocPRIM with its temporary storage from the call's scratch.
+template <typename K, typename V>
+void sort_pairs(mm_ctx *ctx, Scratch &tmp, const K *k, K *ko, const V *v, V *vo, int64_t n,
+                unsigned end_bit) {
+    size_t tb = 0;
+    MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, k, ko, v, vo, (size_t)n, 0u, end_bit,
+                                     ctx->stream));
+    MM_HIP(rocprim::radix_sort_pairs(tmp.get<char>(tb + 16), tb, k, ko, v, vo, (size_t)n, 0u,
+                                     end_bit, ctx->stream));
+}
+template <typename T>
+void exclusive_sum(mm_ctx *ctx, Scratch &tmp, const T *in, T *out, int64_t n) {
+    size_t tb = 0;
+    MM_HIP(rocprim::exclusive_scan(nullptr, tb, in, out, (T)0, (size_t)n, rocprim::plus<T>(),
+                                   ctx->stream));
+    MM_HIP(rocprim::exclusive_scan(tmp.get<char>(tb + 16), tb, in, out, (T)0, (size_t)n,
+                                   rocprim::plus<T>(), ctx->stream));
+}
 
 // Map copies of the single-column P (width > 0), or none.  The lanes of
 // a wave gather the map at consecutive samples, i.e. along the scan, so the
@@ -353,26 +439,27 @@ int grid_for(int64_t n, int max_blocks = 8192) {
 // one per scan direction found (chunks of samples voting by their
 // displacement), each ordered by the first sample of its chunks that hits
 // each pixel.  The values gathered, hence P's output, do not depend on it.
-constexpr int MAX_COPIES = 4;
+}  // namespace
 
-void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
+void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch &sc,
+                             const int32_t **dir_cnt) {
     hipStream_t s = ctx->stream;
-    p->p_slot.release();
-    p->p_j.release();
-    p->p_chunk_grp.release();
-    p->p_copies = 0;
     const int32_t n_obs = p->n_obs;
-    if (width <= 0 || n_obs == 0) return;
+    p->p_copies = 0;
+    if (width <= 0 || n_obs == 0) {
+        p->p_slot.release();
+        p->p_j.release();
+        p->p_chunk_grp.release();
+        return;
+    }
     const int64_t n = p->n_samp;
     const int64_t n_chunks = (n + DIR_CHUNK - 1) / DIR_CHUNK;
-    DBuf dbin;
-    dbin.alloc(sizeof(int32_t) * n_chunks);
+    int32_t *dbin = sc.get<int32_t>(n_chunks);
     k_chunk_dir<<<(unsigned)n_chunks, BS, 0, s>>>(p->j.as<int32_t>(), p->obs_pix.as<int32_t>(), n,
-                                                  width, dbin.as<int32_t>());
+                                                  width, dbin);
     MM_HIP(hipGetLastError());
     std::vector<int32_t> bin(n_chunks);
-    MM_HIP(hipMemcpyAsync(bin.data(), dbin.ptr, sizeof(int32_t) * n_chunks,
-                          hipMemcpyDeviceToHost, s));
+    MM_HIP(hipMemcpyAsync(bin.data(), dbin, sizeof(int32_t) * n_chunks, hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
     // directions holding at least 1/16 of the directed chunks, most first; a
     // bin next to a kept one is not kept (a direction on a bin boundary
@@ -407,7 +494,12 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
         const size_t te = p->prec == MM_F32 ? sizeof(float) : sizeof(double);
         const size_t tod = te * (size_t)n;
         if (sizeof(double) * (size_t)(p->n() * G) > tod) G = 1;
-        if (sizeof(double) * (size_t)p->n() > tod) return;
+        if (sizeof(double) * (size_t)p->n() > tod) {
+            p->p_slot.release();
+            p->p_j.release();
+            p->p_chunk_grp.release();
+            return;
+        }
     }
     // each chunk to the copy of the nearest kept direction (angles mod 180),
     // undirected chunks to the most common one
@@ -426,63 +518,47 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
             }
             grp[c] = bg;
         }
-    DBuf first, keys, vals, ko, order, tmp;
     DBuf &dgrp = p->p_chunk_grp;
     dgrp.alloc(sizeof(int32_t) * n_chunks);
     MM_HIP(hipMemcpyAsync(dgrp.ptr, grp.data(), sizeof(int32_t) * n_chunks,
                           hipMemcpyHostToDevice, s));
+    MM_HIP(hipStreamSynchronize(s));  // grp goes out of scope
     const int64_t total = (int64_t)G * n_obs;
-    first.alloc(sizeof(unsigned long long) * total);
-    MM_HIP(hipMemsetAsync(first.ptr, 0xff, sizeof(unsigned long long) * total, s));
-    k_first_touch<<<grid_for(n), BS, 0, s>>>(p->j.as<int32_t>(), dgrp.as<int32_t>(), n, n_obs,
-                                             first.as<unsigned long long>());
-    keys.alloc(sizeof(uint64_t) * total);
-    vals.alloc(sizeof(int32_t) * total);
-    ko.alloc(sizeof(uint64_t) * total);
-    order.alloc(sizeof(int32_t) * total);
-    k_touch_keys<<<grid_for(total), BS, 0, s>>>(first.as<unsigned long long>(), total, n_obs,
-                                                keys.as<uint64_t>(), vals.as<int32_t>());
-    size_t tb = 0;
-    MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                     vals.as<int32_t>(), order.as<int32_t>(), (size_t)total, 0u,
-                                     64u, s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::radix_sort_pairs(tmp.ptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                     vals.as<int32_t>(), order.as<int32_t>(), (size_t)total, 0u,
-                                     64u, s));
-    // copy g's slots are [g n_obs, (g + 1) n_obs): the key's top byte is g
+    int32_t *first = sc.get<int32_t>(total), *dcnt = sc.get<int32_t>(total + 1);
+    MM_HIP(hipMemsetAsync(dcnt + total, 0, sizeof(int32_t), s));
+    k_pixel_dirs<<<(unsigned)((n_obs + 3) / 4), BS, 0, s>>>(p->off.as<int32_t>(),
+                                                           p->perm.as<int32_t>(),
+                                                           dgrp.as<int32_t>(), n_obs, G,
+                                                           (int32_t)n, dcnt, first);
+    uint64_t *keys = sc.get<uint64_t>(total), *ko = sc.get<uint64_t>(total);
+    int32_t *vals = sc.get<int32_t>(total), *order = sc.get<int32_t>(total);
+    const unsigned nb = bits((uint64_t)n);
+    k_touch_keys<<<grid_for(total), BS, 0, s>>>(first, total, n_obs, (int)nb, keys, vals);
+    // copy g's slots are [g n_obs, (g + 1) n_obs): the key's top bits are g
+    sort_pairs(ctx, sc, keys, ko, vals, order, total, nb + 2);
     p->p_slot.alloc(sizeof(int32_t) * total);
-    k_rank<<<(unsigned)((total + BS - 1) / BS), BS, 0, s>>>(order.as<int32_t>(), (int32_t)total,
+    k_rank<<<(unsigned)((total + BS - 1) / BS), BS, 0, s>>>(order, (int32_t)total,
                                                            p->p_slot.as<int32_t>());
     p->p_j.alloc(sizeof(int32_t) * n);
     k_slot_of_sample_g<<<grid_for(n), BS, 0, s>>>(p->j.as<int32_t>(), dgrp.as<int32_t>(),
                                                   p->p_slot.as<int32_t>(), n, n_obs,
                                                   p->p_j.as<int32_t>());
     MM_HIP(hipGetLastError());
-    MM_HIP(hipStreamSynchronize(s));
     p->p_copies = G;
+    *dir_cnt = dcnt;
 }
 
-void pointing_set_grid_device(mm_ctx *ctx, mm_pointing *p, int32_t width, int32_t tile) {
-    hipStream_t s = ctx->stream;
+// Visiting order of the one-wave-per-pixel P^T: square tiles of the grid.
+static void pointing_tile_order(mm_ctx *ctx, mm_pointing *p, int32_t width, int32_t tile,
+                                Scratch &sc, int32_t *order) {
     const int32_t n_obs = p->n_obs;
-    if (n_obs == 0) return;
-    DBuf keys, vals, ko, vo, tmp;
-    keys.alloc(sizeof(uint64_t) * n_obs);
-    vals.alloc(sizeof(int32_t) * n_obs);
-    ko.alloc(sizeof(uint64_t) * n_obs);
-    p->seg_order.alloc(sizeof(int32_t) * n_obs);
-    k_tile_keys<<<(n_obs + BS - 1) / BS, BS, 0, s>>>(p->obs_pix.as<int32_t>(), n_obs, width, tile,
-                                                     keys.as<uint64_t>(), vals.as<int32_t>());
-    size_t tb = 0;
-    MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                     vals.as<int32_t>(), p->seg_order.as<int32_t>(),
-                                     (size_t)n_obs, 0u, 64u, s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::radix_sort_pairs(tmp.ptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                     vals.as<int32_t>(), p->seg_order.as<int32_t>(),
-                                     (size_t)n_obs, 0u, 64u, s));
-    MM_HIP(hipStreamSynchronize(s));
+    uint64_t *keys = sc.get<uint64_t>(n_obs), *ko = sc.get<uint64_t>(n_obs);
+    int32_t *vals = sc.get<int32_t>(n_obs);
+    k_tile_keys<<<(n_obs + BS - 1) / BS, BS, 0, ctx->stream>>>(p->obs_pix.as<int32_t>(), n_obs,
+                                                              width, tile, keys, vals);
+    const int64_t tiles_x = (width + tile - 1) / tile;
+    const int64_t tiles_y = (p->n_pix_total - 1) / width / tile + 1;
+    sort_pairs(ctx, sc, keys, ko, vals, order, n_obs, 24 + bits((uint64_t)(tiles_x * tiles_y)));
 }
 
 // Time segments for the sliced P^T: enough (segment, slice) waves to fill
@@ -502,19 +578,24 @@ static int32_t slice_segments(int64_t n_samp, int64_t n_valid, int32_t n_obs, in
     return (int32_t)(S < 1 ? 1 : S);
 }
 
-void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
+// dir_cnt: samples per virtual pixel (with map copies of several directions).
+static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch &sc,
+                                   const int32_t *dir_cnt) {
     hipStream_t s = ctx->stream;
     p->sl_G = p->sl_S = 0;
     p->sl_D = 1;
-    p->sl_pix.release();
-    p->sl_base.release();
-    p->sl_perm.release();
-    p->sl_w.release();
+    // a rebuilt layout takes the old one's buffers where they are large enough
+    auto drop = [&]() {
+        p->sl_pix.release();
+        p->sl_base.release();
+        p->sl_perm.release();
+        p->sl_w.release();
+    };
     const int32_t n_obs = p->n_obs;
-    if (n_obs == 0 || p->n_valid == 0) return;
+    if (n_obs == 0 || p->n_valid == 0) return drop();
     const int32_t G0 = (n_obs + 63) / 64;
     // below ~2,048 waves the one-wave-per-pixel kernel is the faster one
-    if ((int64_t)G0 * slice_segments(p->n_samp, p->n_valid, n_obs, G0, 1) < 2048) return;
+    if ((int64_t)G0 * slice_segments(p->n_samp, p->n_valid, n_obs, G0, 1) < 2048) return drop();
     // per scan direction when the map copies of P are there
     const bool dirs = width > 0 && p->p_copies > 0 && p->p_chunk_grp.ptr;
     const int32_t D = dirs ? p->p_copies : 1;
@@ -525,59 +606,24 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     // I and QU: the partial maps too fit in a TOD vector (see the map copies)
     if (p->nc != 3 && sizeof(double) * (size_t)(p->n() * S * D) >
                           (f32 ? sizeof(float) : sizeof(double)) * (size_t)p->n_samp)
-        return;
+        return drop();
     // the pixel-sorted samples and their CSR offsets, over virtual pixels
     // d n_obs + c when cut by direction
     const int32_t *perm_u = p->perm.as<int32_t>();
     const int32_t *off_u = p->off.as<int32_t>();
     const void *ws_u = f32 ? p->ws.ptr : nullptr;
-    DBuf perm2, off2, ws2;
     if (dirs && D > 1) {
-        DBuf keys, vals, ko, idx, cnt2, tmp;
-        keys.alloc(sizeof(uint32_t) * nv);
-        vals.alloc(sizeof(int32_t) * nv);
-        ko.alloc(sizeof(uint32_t) * nv);
-        idx.alloc(sizeof(int32_t) * nv);
-        k_perm_dir_keys<<<grid_for(nv), BS, 0, s>>>(perm_u, nv, p->p_chunk_grp.as<int32_t>(),
-                                                   keys.as<uint32_t>(), vals.as<int32_t>());
-        size_t tb = 0;
-        MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, keys.as<uint32_t>(), ko.as<uint32_t>(),
-                                         vals.as<int32_t>(), idx.as<int32_t>(), (size_t)nv, 0u,
-                                         8u, s));
-        tmp.alloc(tb + 16);
-        MM_HIP(rocprim::radix_sort_pairs(tmp.ptr, tb, keys.as<uint32_t>(), ko.as<uint32_t>(),
-                                         vals.as<int32_t>(), idx.as<int32_t>(), (size_t)nv, 0u,
-                                         8u, s));
-        perm2.alloc(sizeof(int32_t) * nv);
-        if (f32 && p->nc > 1) {
-            ws2.alloc(sizeof(float2) * nv);
-            k_perm_gather<float2><<<grid_for(nv), BS, 0, s>>>(
-                idx.as<int32_t>(), perm_u, p->ws.as<float2>(), nv, perm2.as<int32_t>(),
-                ws2.as<float2>());
-        } else {
-            k_perm_gather<float2><<<grid_for(nv), BS, 0, s>>>(
-                idx.as<int32_t>(), perm_u, nullptr, nv, perm2.as<int32_t>(), nullptr);
-        }
         const int64_t nvp = (int64_t)D * n_obs;
-        cnt2.alloc(sizeof(int32_t) * (nvp + 1));
-        MM_HIP(hipMemsetAsync(cnt2.ptr, 0, sizeof(int32_t) * (nvp + 1), s));
-        k_dir_counts<<<grid_for(p->n_samp), BS, 0, s>>>(p->j.as<int32_t>(),
-                                                        p->p_chunk_grp.as<int32_t>(), p->n_samp,
-                                                        n_obs, cnt2.as<int32_t>());
-        off2.alloc(sizeof(int32_t) * (nvp + 1));
-        size_t tb2 = 0;
-        MM_HIP(rocprim::exclusive_scan(nullptr, tb2, cnt2.as<int32_t>(), off2.as<int32_t>(),
-                                       (int32_t)0, (size_t)(nvp + 1), rocprim::plus<int32_t>(),
-                                       s));
-        DBuf tmp2;
-        tmp2.alloc(tb2 + 16);
-        MM_HIP(rocprim::exclusive_scan(tmp2.ptr, tb2, cnt2.as<int32_t>(), off2.as<int32_t>(),
-                                       (int32_t)0, (size_t)(nvp + 1), rocprim::plus<int32_t>(),
-                                       s));
-        MM_HIP(hipStreamSynchronize(s));
-        perm_u = perm2.as<int32_t>();
-        off_u = off2.as<int32_t>();
-        if (f32 && p->nc > 1) ws_u = ws2.ptr;
+        int32_t *off2 = sc.get<int32_t>(nvp + 1), *perm2 = sc.get<int32_t>(nv);
+        exclusive_sum(ctx, sc, dir_cnt, off2, nvp + 1);
+        const bool w32 = f32 && p->nc > 1;
+        float2 *ws2 = w32 ? sc.get<float2>(nv) : nullptr;
+        k_dir_scatter<float2><<<(unsigned)((n_obs + 3) / 4), BS, 0, s>>>(
+            p->off.as<int32_t>(), perm_u, w32 ? p->ws.as<float2>() : nullptr,
+            p->p_chunk_grp.as<int32_t>(), n_obs, D, off2, perm2, ws2);
+        perm_u = perm2;
+        off_u = off2;
+        ws_u = ws2;
     }
 
     p->sl_pix.alloc(sizeof(int32_t) * (size_t)G * 64);
@@ -586,51 +632,20 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
         const int64_t nvp = (int64_t)D * n_obs;
         k_sl_pix_dir<<<grid_for(nvp), BS, 0, s>>>(p->p_slot.as<int32_t>(), nvp, n_obs, G0,
                                                   p->sl_pix.as<int32_t>());
-        MM_HIP(hipStreamSynchronize(s));
     } else if (width > 0) {
-        DBuf keys, vals, ko;
-        keys.alloc(sizeof(uint64_t) * n_obs);
-        vals.alloc(sizeof(int32_t) * n_obs);
-        ko.alloc(sizeof(uint64_t) * n_obs);
-        k_tile_keys<<<(n_obs + BS - 1) / BS, BS, 0, s>>>(p->obs_pix.as<int32_t>(), n_obs, width, 8,
-                                                         keys.as<uint64_t>(), vals.as<int32_t>());
-        size_t tb = 0;
-        MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                         vals.as<int32_t>(), p->sl_pix.as<int32_t>(),
-                                         (size_t)n_obs, 0u, 64u, s));
-        DBuf tmp;
-        tmp.alloc(tb + 16);
-        MM_HIP(rocprim::radix_sort_pairs(tmp.ptr, tb, keys.as<uint64_t>(), ko.as<uint64_t>(),
-                                         vals.as<int32_t>(), p->sl_pix.as<int32_t>(),
-                                         (size_t)n_obs, 0u, 64u, s));
-        MM_HIP(hipStreamSynchronize(s));
+        pointing_tile_order(ctx, p, width, 8, sc, p->sl_pix.as<int32_t>());
     } else {
-        std::vector<int32_t> id(n_obs);
-        for (int32_t c = 0; c < n_obs; ++c) id[c] = c;
-        MM_HIP(hipMemcpyAsync(p->sl_pix.ptr, id.data(), sizeof(int32_t) * n_obs,
-                              hipMemcpyHostToDevice, s));
-        MM_HIP(hipStreamSynchronize(s));
+        k_iota<<<(n_obs + BS - 1) / BS, BS, 0, s>>>(n_obs, p->sl_pix.as<int32_t>());
     }
 
     const int64_t n_waves = (int64_t)G * S;
-    DBuf cnt, start, sizes, tmp;
-    cnt.alloc(sizeof(int32_t) * n_waves * 64);
-    start.alloc(sizeof(int32_t) * n_waves * 64);
-    sizes.alloc(sizeof(int64_t) * (n_waves + 1));
+    int32_t *cnt = sc.get<int32_t>(n_waves * 64), *start = sc.get<int32_t>(n_waves * 64);
+    int64_t *sizes = sc.get<int64_t>(n_waves + 1);
     p->sl_base.alloc(sizeof(int64_t) * (n_waves + 1));
     k_sl_bounds<<<(unsigned)((G * 64 + BS - 1) / BS), BS, 0, s>>>(
-        p->sl_pix.as<int32_t>(), G, S, p->n_samp, off_u, perm_u, cnt.as<int32_t>(),
-        start.as<int32_t>());
-    k_sl_width<<<(unsigned)((n_waves + 1) * 64 / BS + 1), BS, 0, s>>>(cnt.as<int32_t>(), n_waves,
-                                                                      sizes.as<int64_t>());
-    size_t tb = 0;
-    MM_HIP(rocprim::exclusive_scan(nullptr, tb, sizes.as<int64_t>(), p->sl_base.as<int64_t>(),
-                                   (int64_t)0, (size_t)(n_waves + 1), rocprim::plus<int64_t>(),
-                                   s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::exclusive_scan(tmp.ptr, tb, sizes.as<int64_t>(), p->sl_base.as<int64_t>(),
-                                   (int64_t)0, (size_t)(n_waves + 1), rocprim::plus<int64_t>(),
-                                   s));
+        p->sl_pix.as<int32_t>(), G, S, p->n_samp, off_u, perm_u, cnt, start);
+    k_sl_width<<<(unsigned)((n_waves + 1) * 64 / BS + 1), BS, 0, s>>>(cnt, n_waves, sizes);
+    exclusive_sum(ctx, sc, sizes, p->sl_base.as<int64_t>(), n_waves + 1);
     int64_t total = 0;
     MM_HIP(hipMemcpyAsync(&total, p->sl_base.as<int64_t>() + n_waves, sizeof(int64_t),
                           hipMemcpyDeviceToHost, s));
@@ -639,24 +654,39 @@ void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
     if (p->nc > 1) p->sl_w.alloc(sizeof(double) * (size_t)total);  // psi, or two FP32 weights
     const unsigned fb = (unsigned)std::min<int64_t>((n_waves * 64 + BS - 1) / BS, 16384);
     if (p->nc == 1)
-        k_sl_fill<double, false><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt.as<int32_t>(),
-                                                   start.as<int32_t>(), perm_u, nullptr, n_waves,
+        k_sl_fill<double, false><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt,
+                                                   start, perm_u, nullptr, n_waves,
                                                    p->sl_perm.as<int32_t>(), nullptr);
     else if (f32)
-        k_sl_fill<float2><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt.as<int32_t>(),
-                                            start.as<int32_t>(), perm_u,
+        k_sl_fill<float2><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt,
+                                            start, perm_u,
                                             static_cast<const float2 *>(ws_u), n_waves,
                                             p->sl_perm.as<int32_t>(), p->sl_w.as<float2>());
     else
-        k_sl_fill<double><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt.as<int32_t>(),
-                                            start.as<int32_t>(), perm_u, p->psi.as<double>(),
+        k_sl_fill<double><<<fb, BS, 0, s>>>(p->sl_base.as<int64_t>(), cnt,
+                                            start, perm_u, p->psi.as<double>(),
                                             n_waves, p->sl_perm.as<int32_t>(),
                                             p->sl_w.as<double>());
     MM_HIP(hipGetLastError());
-    MM_HIP(hipStreamSynchronize(s));
     p->sl_G = G;
     p->sl_S = S;
     p->sl_D = D;
+}
+
+void pointing_layout_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
+    Scratch sc(ctx);
+    if (width <= 0) {
+        p->seg_order.release();
+    } else if (p->n_obs > 0) {
+        p->seg_order.alloc(sizeof(int32_t) * p->n_obs);
+        pointing_tile_order(ctx, p, width, 32, sc, p->seg_order.as<int32_t>());
+    }
+    p->grid_width = width;
+    // P's map copies first: the sliced P^T is cut by the same scan directions
+    const int32_t *dir_cnt = nullptr;
+    pointing_p_slots_device(ctx, p, width, sc, &dir_cnt);
+    pointing_slices_device(ctx, p, width, sc, dir_cnt);
+    MM_HIP(hipStreamSynchronize(ctx->stream));
 }
 
 void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, const double *psi,
@@ -665,81 +695,52 @@ void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, cons
     const int64_t n = p->n_samp;
     const int32_t npt = p->n_pix_total;
 
-    DBuf flags;
-    flags.alloc(2 * sizeof(int));
-    MM_HIP(hipMemsetAsync(flags.ptr, 0, 2 * sizeof(int), s));
-    k_validate<<<grid_for(n), BS, 0, s>>>(pix, psi, n, npt, flags.as<int>());
+    Scratch sc(ctx);
+    uint32_t *keys = sc.get<uint32_t>(n), *keys_o = sc.get<uint32_t>(n);
+    int32_t *vals = sc.get<int32_t>(n), *vals_o = sc.get<int32_t>(n);
+    int *flags = sc.get<int>(2);
+    int32_t *start = sc.get<int32_t>(npt), *end = sc.get<int32_t>(npt);
+    MM_HIP(hipMemsetAsync(flags, 0, 2 * sizeof(int), s));
+    MM_HIP(hipMemsetAsync(start, 0, sizeof(int32_t) * npt, s));
+    MM_HIP(hipMemsetAsync(end, 0, sizeof(int32_t) * npt, s));
+    k_keys<<<grid_for(n), BS, 0, s>>>(pix, psi, n, npt, keys, vals, flags);
+    sort_pairs(ctx, sc, keys, keys_o, vals, vals_o, n, bits((uint64_t)npt));
+    k_runs<<<grid_for(n), BS, 0, s>>>(keys_o, n, (uint32_t)npt, start, end);
+
+    int32_t *flag = sc.get<int32_t>(npt), *scan = sc.get<int32_t>(npt);
+    int32_t *cidx = sc.get<int32_t>(npt);
+    p->hits.alloc(sizeof(int32_t) * npt);
+    k_obs_flag<<<(npt + BS - 1) / BS, BS, 0, s>>>(start, end, npt, min_hits,
+                                                   p->hits.as<int32_t>(), flag);
+    exclusive_sum(ctx, sc, flag, scan, npt);
     int hf[2];
-    MM_HIP(hipMemcpyAsync(hf, flags.ptr, sizeof(hf), hipMemcpyDeviceToHost, s));
+    int32_t last[2];
+    MM_HIP(hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s));
+    MM_HIP(hipMemcpyAsync(&last[0], scan + npt - 1, 4, hipMemcpyDeviceToHost, s));
+    MM_HIP(hipMemcpyAsync(&last[1], flag + npt - 1, 4, hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
     MM_CHECK(!hf[0], MM_E_INVALID, "pointing: pixel index outside [-1, n_pix_total)");
     MM_CHECK(!hf[1], MM_E_NONFINITE, "pointing: non-finite angle psi");
-
-    p->hits.alloc(sizeof(int32_t) * npt);
-    MM_HIP(hipMemsetAsync(p->hits.ptr, 0, sizeof(int32_t) * npt, s));
-    k_hist<<<grid_for(n), BS, 0, s>>>(pix, n, p->hits.as<int32_t>());
-
-    DBuf flag, scan, cidx, obs_hits_tmp, tmp;
-    flag.alloc(sizeof(int32_t) * npt);
-    scan.alloc(sizeof(int32_t) * npt);
-    k_obs_flag<<<(npt + BS - 1) / BS, BS, 0, s>>>(p->hits.as<int32_t>(), npt, min_hits,
-                                                   flag.as<int32_t>());
-    size_t tb = 0;
-    MM_HIP(rocprim::exclusive_scan(nullptr, tb, flag.as<int32_t>(), scan.as<int32_t>(), 0,
-                                   (size_t)npt, rocprim::plus<int32_t>(), s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::exclusive_scan(tmp.ptr, tb, flag.as<int32_t>(), scan.as<int32_t>(), 0,
-                                   (size_t)npt, rocprim::plus<int32_t>(), s));
-    int32_t last[2];
-    MM_HIP(hipMemcpyAsync(&last[0], scan.as<int32_t>() + npt - 1, 4, hipMemcpyDeviceToHost, s));
-    MM_HIP(hipMemcpyAsync(&last[1], flag.as<int32_t>() + npt - 1, 4, hipMemcpyDeviceToHost, s));
-    MM_HIP(hipStreamSynchronize(s));
     const int32_t n_obs = last[0] + last[1];
     p->n_obs = n_obs;
 
-    cidx.alloc(sizeof(int32_t) * npt);
     p->obs_pix.alloc(sizeof(int32_t) * (n_obs > 0 ? n_obs : 1));
-    obs_hits_tmp.alloc(sizeof(int32_t) * (n_obs + 1));
-    k_compact<<<(npt + BS - 1) / BS, BS, 0, s>>>(p->hits.as<int32_t>(), flag.as<int32_t>(),
-                                                  scan.as<int32_t>(), npt, cidx.as<int32_t>(),
-                                                  p->obs_pix.as<int32_t>(),
-                                                  obs_hits_tmp.as<int32_t>());
+    int32_t *obs_hits = sc.get<int32_t>(n_obs + 1);
+    k_compact<<<(npt + BS - 1) / BS, BS, 0, s>>>(p->hits.as<int32_t>(), flag, scan, npt, cidx,
+                                                  p->obs_pix.as<int32_t>(), obs_hits);
     p->off.alloc(sizeof(int32_t) * (n_obs + 1));
-    tb = 0;
-    MM_HIP(rocprim::exclusive_scan(nullptr, tb, obs_hits_tmp.as<int32_t>(), p->off.as<int32_t>(),
-                                   0, (size_t)(n_obs + 1), rocprim::plus<int32_t>(), s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::exclusive_scan(tmp.ptr, tb, obs_hits_tmp.as<int32_t>(), p->off.as<int32_t>(),
-                                   0, (size_t)(n_obs + 1), rocprim::plus<int32_t>(), s));
+    exclusive_sum(ctx, sc, obs_hits, p->off.as<int32_t>(), n_obs + 1);
     int32_t nv;
     MM_HIP(hipMemcpyAsync(&nv, p->off.as<int32_t>() + n_obs, 4, hipMemcpyDeviceToHost, s));
-
-    // compact pixel per sample and the sort keys (flagged samples sort last)
+    // compact pixel per sample and the sorted samples of the observed pixels
     p->j.alloc(sizeof(int32_t) * n);
-    DBuf keys, vals, keys_out, vals_out;
-    keys.alloc(sizeof(uint32_t) * n);
-    vals.alloc(sizeof(int32_t) * n);
-    keys_out.alloc(sizeof(uint32_t) * n);
-    vals_out.alloc(sizeof(int32_t) * n);
-    k_sample_j<<<grid_for(n), BS, 0, s>>>(pix, cidx.as<int32_t>(), n, (uint32_t)n_obs,
-                                          p->j.as<int32_t>(), keys.as<uint32_t>(),
-                                          vals.as<int32_t>());
-    unsigned end_bit = 1;
-    while (end_bit < 32 && ((uint64_t)1 << end_bit) <= (uint64_t)n_obs) ++end_bit;
-    tb = 0;
-    MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, keys.as<uint32_t>(), keys_out.as<uint32_t>(),
-                                     vals.as<int32_t>(), vals_out.as<int32_t>(), (size_t)n, 0u,
-                                     end_bit, s));
-    tmp.alloc(tb + 16);
-    MM_HIP(rocprim::radix_sort_pairs(tmp.ptr, tb, keys.as<uint32_t>(), keys_out.as<uint32_t>(),
-                                     vals.as<int32_t>(), vals_out.as<int32_t>(), (size_t)n, 0u,
-                                     end_bit, s));
+    k_sample_j<<<grid_for(n), BS, 0, s>>>(pix, cidx, n, npt, p->j.as<int32_t>());
     MM_HIP(hipStreamSynchronize(s));
     p->n_valid = nv;
-    keys.release();
-    keys_out.release();
-    vals.release();
-    p->perm = std::move(vals_out);  // first n_valid entries are the permutation
+    p->perm.alloc(sizeof(int32_t) * (nv > 0 ? nv : 1));
+    k_perm<<<grid_for(n), BS, 0, s>>>(keys_o, vals_o, n, (uint32_t)npt, cidx, start,
+                                      p->off.as<int32_t>(), p->perm.as<int32_t>());
+    MM_HIP(hipGetLastError());
 
     // weights in time order and in pixel-sorted order; the FP64 form also
     // keeps the angles, from which its single-column P and P^T form the
@@ -747,14 +748,8 @@ void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, cons
     // intensity-only pointing has unit weights and keeps neither.
     const bool f32 = p->prec == MM_F32;
     if (p->nc == 1) {
-        std::vector<int32_t> hoff1(n_obs + 1);
-        MM_HIP(hipMemcpyAsync(hoff1.data(), p->off.ptr, sizeof(int32_t) * (n_obs + 1),
-                              hipMemcpyDeviceToHost, s));
+        pointing_slices_device(ctx, p, 0, sc, nullptr);
         MM_HIP(hipStreamSynchronize(s));
-        int32_t mx1 = 0;
-        for (int32_t c = 0; c < n_obs; ++c) mx1 = std::max(mx1, hoff1[c + 1] - hoff1[c]);
-        p->max_seg = mx1;
-        pointing_slices_device(ctx, p, 0);
         return;
     }
     if (!f32) {
@@ -777,15 +772,8 @@ void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, cons
     }
     MM_HIP(hipGetLastError());
 
-    // longest segment (used to pick the P^T launch shape)
-    std::vector<int32_t> hoff(n_obs + 1);
-    MM_HIP(hipMemcpyAsync(hoff.data(), p->off.ptr, sizeof(int32_t) * (n_obs + 1),
-                          hipMemcpyDeviceToHost, s));
+    pointing_slices_device(ctx, p, 0, sc, nullptr);
     MM_HIP(hipStreamSynchronize(s));
-    int32_t mx = 0;
-    for (int32_t c = 0; c < n_obs; ++c) mx = std::max(mx, hoff[c + 1] - hoff[c]);
-    p->max_seg = mx;
-    pointing_slices_device(ctx, p, 0);
 }
 
 }  // namespace mm

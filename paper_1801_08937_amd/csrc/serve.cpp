@@ -260,6 +260,7 @@ extern "C" mm_status mm_server_add_strategy(mm_server *srv, int32_t id, int64_t 
                          MM_NOISE_AUTO, prec, &st->nz),
           st->ctx, "server: noise");
     check(mm_mbd_build(st->ctx, st->p, st->nz, &st->mbd), st->ctx, "server: M_BD");
+    st->ctx->build_ws.release();  // not counted in the strategy's footprint
     st->n = st->p->n();
     st->b.alloc(sizeof(double) * st->n);
     if (srv->prebuild && srv->defl_k > 0) {
