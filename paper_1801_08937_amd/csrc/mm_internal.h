@@ -37,8 +37,8 @@ struct Error : std::runtime_error {
 
 // Device memory of the library's buffers.  dev_free waits for the device, as hipFree
 // does, and keeps the block for a later dev_alloc of about its size (registering a
-// strategy of 8.4M samples and dropping it: 4.4 ms, or up to 13 ms in a process that
-// holds more memory, without this; 2.6 ms with it).
+// strategy of 8.4M samples and dropping it: 4.1 ms, or up to 13 ms in a process that
+// holds more memory, without this; 2.0 ms with it).
 // At most POOL_MAX_BYTES per device are kept, and given back when the device's last
 // context goes, or when a hipMalloc fails.  Any thread may call them.
 constexpr size_t POOL_MAX_BYTES = (size_t)1 << 30;
