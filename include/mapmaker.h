@@ -251,7 +251,8 @@ mm_status mm_noise_method_used(const mm_noise *nz, mm_noise_method *method);
  * model (blocks run in waves over the compute units; a wave of the large
  * blocks takes 1.05 times as long), so it depends on the interval lengths,
  * lambda and the device's compute-unit count; mm_noise_set_fft_block and
- * mm_autotune can change it. */
+ * mm_autotune can change it.  Until they do, the blocks that run may be of
+ * another length (8,192, 16,384 or 32,768) where that is faster. */
 mm_status mm_noise_fft_block(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid);
 /* Rebuild the FFT method's tables for blocks of n_fft real samples: 16,384
  * (lambda <= 6,144) or 32,768, or 0 for the time model's pick.  Results are

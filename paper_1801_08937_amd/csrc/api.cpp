@@ -758,8 +758,8 @@ extern "C" mm_status mm_noise_method_used(const mm_noise *nz, mm_noise_method *m
 extern "C" mm_status mm_noise_fft_block(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid) {
     if (!nz || !n_fft || !n_valid) return MM_E_INVALID;
     const bool fft = nz->method == MM_NOISE_FFT;
-    *n_fft = fft ? (int32_t)nz->fft_n : 0;
-    *n_valid = fft ? (int32_t)nz->fft_valid : 0;
+    *n_fft = fft ? nz->fft_n : 0;
+    *n_valid = fft ? nz->fft_n - 2 * nz->half_bw : 0;
     return MM_OK;
 }
 

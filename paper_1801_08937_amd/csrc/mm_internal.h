@@ -237,6 +237,18 @@ struct mm_pointing {
     mm::DBuf sl_w;     // per entry: psi (FP64 form) or the weights (FP32 form); I: none
 };
 
+namespace mm {
+// Tables of the FFT N^-1 for one block length.
+struct FftTables {
+    int32_t n = 0;      // real block length
+    int32_t valid = 0;  // valid outputs per block
+    DBuf spec;          // per filter: A_k, then W^k B_k / 2, in the kernel's order
+    DBuf tw;            // twiddles of the transform's first two passes
+    DBuf blocks;        // int64 pairs (first output sample, interval index)
+    int64_t n_blocks = 0;
+};
+}  // namespace mm
+
 struct mm_noise {
     int64_t n_samp = 0;
     int32_t n_int = 0, n_filters = 0, half_bw = 0;
@@ -255,12 +267,9 @@ struct mm_noise {
     int32_t band_cl[7] = {0, 0, 0, 0, 0, 0, 0};  // tuned taps per LDS chunk per log2(nrhs); 0 = default
     bool band_small = false;  // one column in 512-sample tiles of 64 threads (short streams)
     // FFT: per-filter packed spectrum and block table
-    int32_t fft_n = 0;       // real block length
-    int32_t fft_valid = 0;   // valid outputs per block
-    mm::DBuf fft_spec;       // per filter: A_k, then W^k B_k / 2, in the kernel's order
-    mm::DBuf fft_tw;         // twiddles of the transform's first two passes
-    mm::DBuf fft_blocks;     // int64 pairs (first output sample, interval index)
-    int64_t n_fft_blocks = 0;
+    int32_t fft_n = 0;       // block length set or reported (mm_noise_fft_block)
+    bool fft_auto = false;   // picked by the library: fft.n may be another length
+    mm::FftTables fft;       // of the blocks that run
     // polynomial template filter (method MM_NOISE_POLY): subscan table, the
     // weight of each subscan's interval, G_s^-1 per subscan ((p+1)^2 FP64,
     // zeros for a subscan fitted exactly) and the flag mask as bits

@@ -59,6 +59,7 @@ __global__ void __launch_bounds__(256)
     for (int m = threadIdx.x; m < NB; m += 256) cs[m] = quarter_cs(qtab, SP_B * m, N);
     __syncthreads();
     const int f = blockIdx.z, d1 = blockIdx.y, m = blockIdx.x * 256 + threadIdx.x;
+    if (m >= NB) return;
     const double *c = band + (int64_t)f * (lam + 1);
     double sr = 0, si = 0;
     for (int d = d1, d2 = 0; d <= lam; d += SP_B, ++d2) {
@@ -96,7 +97,9 @@ bool noise_fft_big_supported(int half_bw);
 bool noise_fft_mid_supported(int half_bw);
 int noise_fft_big_nc();
 int noise_fft_mid_nc();
-void noise_fft_tables_dev(mm_ctx *ctx, mm_noise *nz, int nc, const double *H,
+int noise_fft_short_nc();
+bool noise_fft_short_supported(int half_bw);
+void noise_fft_tables_dev(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, const double *H,
                           const double *qtab);
 void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
                              const int32_t *jpix, int *bad);
@@ -106,44 +109,63 @@ bool noise_fft_supported(int half_bw, int64_t min_len) {
     return half_bw >= 1 && noise_fft_big_supported(half_bw);
 }
 
-// Measured time model of one overlap-save apply with N-sample blocks.  Blocks
-// run in waves of n_cu x (blocks per CU): in FP64 two 16,384-sample blocks
-// share a CU and a 32,768-sample block fills one; in FP32 twice as many.  A
-// wave takes 40 (16,384) or 42 (32,768) time units (29.3 and 30.6 us at 2^27
-// samples, FP64 and FP32 alike, lambda 1,024 and 4,096); the count of waves is
-// rounded up.  On less than one wave the smaller block is the faster one
-// (18.7 against 26.4 us at 2^20 samples, lambda 1,024).
-static double fft_time_model(const mm_noise *nz, int N, int n_cu) {
-    const int64_t lam = nz->half_bw, V = N - 2 * lam;
-    if (V <= 0) return 1e300;
+static int64_t fft_n_blocks(const mm_noise *nz, int N) {
+    const int64_t V = N - 2 * (int64_t)nz->half_bw;
     int64_t nb = 0;
     for (int i = 0; i < nz->n_int; ++i)
         nb += (nz->h_istart[i + 1] - nz->h_istart[i] + V - 1) / V;
-    const bool mid = N == 2 * noise_fft_mid_nc();
-    const int64_t per_wave = (int64_t)n_cu * (mid ? 2 : 1) * (nz->prec == MM_F32 ? 2 : 1);
-    const int64_t waves = (nb + per_wave - 1) / per_wave;
-    return (double)waves * (mid ? 40.0 : 42.0);
+    return nb;
 }
 
-// Tables for blocks of n_fft real samples (0 = pick by the model above).
-void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
-    hipStream_t s = ctx->stream;
-    const int lam = nz->half_bw;
-    MM_CHECK(noise_fft_supported(lam, 0), MM_E_INVALID, "FFT: bandwidth unsupported");
-    if (n_fft == 0) {
-        const int nm = 2 * noise_fft_mid_nc(), nb = 2 * noise_fft_big_nc();
-        n_fft = noise_fft_mid_supported(lam) &&
-                        fft_time_model(nz, nm, ctx->n_cu) <= fft_time_model(nz, nb, ctx->n_cu)
-                    ? nm
-                    : nb;
+// The length reported for a handle: rounds of n_cu x (blocks per CU) blocks, 40
+// (16,384) or 42 (32,768) time units each.
+static double fft_time_model(const mm_noise *nz, int N, int n_cu) {
+    if (N <= 2 * nz->half_bw) return 1e300;
+    const bool mid = N == 2 * noise_fft_mid_nc();
+    const int64_t per_wave = (int64_t)n_cu * (mid ? 2 : 1) * (nz->prec == MM_F32 ? 2 : 1);
+    return (double)((fft_n_blocks(nz, N) + per_wave - 1) / per_wave) * (mid ? 40.0 : 42.0);
+}
+
+// The length that runs: 8,192-, 16,384- and 32,768-sample blocks share a CU by four,
+// two and one (FP64; FP32 about 0.6 of these times, in the same proportions).
+// Measured, us (one column): up to one block per CU 11.5, 14 to 20 and 25 to 33; 2, 3
+// and 4 of the small ones 17, 23 and 27, two of the middle ones 29; longer streams 22.5,
+// 27 and 33 per round and a quarter of one more.  2^20 samples, lambda 1,024: 11.4,
+// 16.0, 26.6; 2^23: 38, 42, 59; 2^26: 255, 298, 391 (lambda 2,048: 361, 333, 400;
+// 4,096: -, 423, 419).  With more than three times the blocks, the small ones lose on
+// several columns what they gain on one (2^20 samples, lambda 3,072, 4 columns: 62
+// against 48 us).
+static double fft_run_model(const mm_noise *nz, int N, int n_cu) {
+    const double nb = (double)fft_n_blocks(nz, N) / n_cu;
+    if (N == 2 * noise_fft_short_nc()) {
+        if (nb <= 4) return nb <= 1 ? 11.5 : nb <= 2 ? 17 : nb <= 3 ? 23 : 27;
+        return 22.5 * (nb / 4 + 0.25);
     }
-    MM_CHECK(n_fft == 2 * noise_fft_big_nc() ||
-                 (n_fft == 2 * noise_fft_mid_nc() && noise_fft_mid_supported(lam)),
-             MM_E_INVALID, "FFT: block length must be 16,384 (lambda <= 6,144) or 32,768");
-    const int NC = n_fft / 2;
-    const int N = 2 * NC;
-    nz->fft_n = N;
-    nz->fft_valid = N - 2 * lam;
+    if (N == 2 * noise_fft_mid_nc()) {
+        if (nb <= 2) return nb <= 1 ? 14 + 6 * nb : 29;
+        return 27 * (nb / 2 + 0.25);
+    }
+    return nb <= 1 ? 25 + 8 * nb : 33 * (nb + 0.25);
+}
+
+static int fft_run_length(const mm_noise *nz, int n_cu) {
+    const int ns = 2 * noise_fft_short_nc(), nm = 2 * noise_fft_mid_nc();
+    int best = 2 * noise_fft_big_nc();
+    if (!noise_fft_mid_supported(nz->half_bw)) return best;
+    if (fft_run_model(nz, nm, n_cu) <= fft_run_model(nz, best, n_cu)) best = nm;
+    if (noise_fft_short_supported(nz->half_bw) &&
+        fft_n_blocks(nz, ns) <= 3 * fft_n_blocks(nz, nm) &&
+        fft_run_model(nz, ns, n_cu) <= fft_run_model(nz, best, n_cu))
+        best = ns;
+    return best;
+}
+
+// Spectra, twiddles and block list for blocks of N real samples.
+static void fft_tables(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, int N) {
+    hipStream_t s = ctx->stream;
+    const int lam = nz->half_bw, NC = N / 2;
+    tb.n = N;
+    tb.valid = N - 2 * lam;
     // quarter period of cos(2 pi m / N) (long double on the host, rounded once)
     std::vector<double> qtab(N / 4 + 1);
     const long double pi2 = 6.283185307179586476925286766559L;
@@ -158,25 +180,45 @@ void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
     const unsigned nf = (unsigned)nz->n_filters;
     for (unsigned f0 = 0; f0 < nf; f0 += 32768) {  // grid.z is 16 bits
         const unsigned cnt = std::min(nf - f0, 32768u);
-        k_spec_sub<<<dim3(N / SP_B / 256, SP_B, cnt), 256, 0, s>>>(
+        k_spec_sub<<<dim3((N / SP_B + 255) / 256, SP_B, cnt), 256, 0, s>>>(
             nz->band64.as<double>() + (int64_t)f0 * (lam + 1), lam, N, dq, S + (int64_t)f0 * N);
         k_spec_sum<<<dim3((NC + 1 + 255) / 256, cnt), 256, 0, s>>>(
             N, dq, S + (int64_t)f0 * N, H + (int64_t)f0 * (NC + 1));
     }
     MM_HIP(hipGetLastError());
-    noise_fft_tables_dev(ctx, nz, NC, H, dq);
+    noise_fft_tables_dev(ctx, nz, tb, H, dq);
     // block table
     std::vector<int64_t> blocks;
     for (int i = 0; i < nz->n_int; ++i)
-        for (int64_t t = nz->h_istart[i]; t < nz->h_istart[i + 1]; t += nz->fft_valid) {
+        for (int64_t t = nz->h_istart[i]; t < nz->h_istart[i + 1]; t += tb.valid) {
             blocks.push_back(t);
             blocks.push_back(i);
         }
-    nz->n_fft_blocks = (int64_t)blocks.size() / 2;
-    nz->fft_blocks.alloc(sizeof(int64_t) * blocks.size());
-    MM_HIP(hipMemcpyAsync(nz->fft_blocks.ptr, blocks.data(), sizeof(int64_t) * blocks.size(),
+    tb.n_blocks = (int64_t)blocks.size() / 2;
+    tb.blocks.alloc(sizeof(int64_t) * blocks.size());
+    MM_HIP(hipMemcpyAsync(tb.blocks.ptr, blocks.data(), sizeof(int64_t) * blocks.size(),
                           hipMemcpyHostToDevice, s));
     MM_HIP(hipStreamSynchronize(s));
+}
+
+// Tables for blocks of n_fft real samples (0 = pick by the models above).
+void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
+    const int lam = nz->half_bw;
+    MM_CHECK(noise_fft_supported(lam, 0), MM_E_INVALID, "FFT: bandwidth unsupported");
+    const int nm = 2 * noise_fft_mid_nc(), nb = 2 * noise_fft_big_nc();
+    MM_CHECK(n_fft == 0 || n_fft == nb || (n_fft == nm && noise_fft_mid_supported(lam)),
+             MM_E_INVALID, "FFT: block length must be 16,384 (lambda <= 6,144) or 32,768");
+    int run = n_fft, shown = n_fft;
+    if (n_fft == 0) {
+        run = fft_run_length(nz, ctx->n_cu);
+        shown = noise_fft_mid_supported(lam) &&
+                        fft_time_model(nz, nm, ctx->n_cu) <= fft_time_model(nz, nb, ctx->n_cu)
+                    ? nm
+                    : nb;
+    }
+    fft_tables(ctx, nz, nz->fft, run);
+    nz->fft_n = shown;
+    nz->fft_auto = n_fft == 0;
 }
 
 void noise_fft_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {

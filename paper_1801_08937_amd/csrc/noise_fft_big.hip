@@ -2,43 +2,53 @@
 // samples, packed as NC complex points (the packed-real scheme of
 // noise_fft.hip), V = N - 2 lambda valid outputs.
 //
-// A block has TH = NC / 32 threads of 32 complex values each and a transform
-// is NC = 32 x 32 x L, L = NC / 1,024:
-//   pass 1  thread j holds x[j + TH r], r < 32: DFT over r, giving k1, times
+// A block has TH = NC / X threads of X complex values each and a transform is
+// NC = X x X x L:
+//   pass 1  thread j holds x[j + TH r], r < X: DFT over r, giving k1, times
 //           W_NC^(j k1);
 //   pass 2  per k1 a TH-point transform on L lanes of one wave: lane l holds
-//           j = l + L q, q < 32; DFT over q, giving k2a, times W_TH^(l k2a);
-//   pass 3  lane l takes k2a = l + L p, p < 32 / L, for all L values of l:
-//           32 / L DFTs of L points, giving k2b.  Register p L + k2b then
-//           holds X[k1 + 32 (k2a + 32 k2b)].
+//           j = l + L q, q < X; DFT over q, giving k2a, times W_TH^(l k2a);
+//   pass 3  L-point DFTs over l, giving k2b.  L <= X: lane l takes k2a = l + L p,
+//           p < X / L, for all values of l, and register p L + k2b then holds
+//           X[k1 + X (k2a + X k2b)].  L = 2 X: two lanes share each k2a
+//           (dft_lanes); register i of lane k2a + X h holds k2b = 2 i + h.
 // and the inverse transform runs the passes backwards.  Only the exchange
 // between passes 1 and 2 crosses waves: it goes through LDS one component at
-// a time (FP64: a whole block does not fit), with three barriers.  A wave owns
-// the values k1 of a contiguous stretch of LDS rows, so the exchange between
-// passes 2 and 3 and the spectrum step stay inside the wave's own rows and
-// need no barrier: 6 barriers per block, and the waves of a block drift apart,
-// so that one wave's LDS accesses overlap another's arithmetic.
+// a time, with three barriers.  A wave owns the values k1 of a contiguous
+// stretch of LDS rows, so the exchange between passes 2 and 3 and the spectrum
+// step stay inside the wave's own rows and need no barrier: 6 barriers per
+// block, and the waves of a block drift apart, so that one wave's LDS accesses
+// overlap another's arithmetic.
 //
 // The spectrum step pairs Z_k with Z_{NC-k}.  A wave's k1 come as pairs (a,
-// 32 - a) (wave 0 has 0 and 16, each its own partner), so the partner of
-// (k1, lane l, register i) is (32 - k1, lane L-1-l, register 31-i) of the same
+// X - a) (wave 0 has 0 and X / 2, each its own partner), so the partner of
+// (k1, lane l, register i) is (X - k1, lane L-1-l, register X-1-i) of the same
 // wave; for k1 = 0 it is lane L-l, and lane 0 there pairs its own registers.
 //
-// Two geometries: L = 16 (NC = 16,384: 512 threads, one block per CU;
-// bandwidths up to 12,288) and L = 8 (NC = 8,192: 256 threads, two blocks per
-// CU; bandwidths up to 6,144).  512 threads with 32 points each leave 256
-// VGPRs for 128 of FP64 data, room for the radix-32 temporaries; 1,024 threads
-// with 16 points (radices 16 x 16 x 16 x 4) needed three exchanges per
-// direction, each across the whole block, and 25 barriers.
+// Three geometries (X, L), and the bandwidths they serve:
+//   Short (16, 16): NC =  4,096, 256 threads, FP64 four blocks per CU; 3,072;
+//   Mid   (16, 32): NC =  8,192, 512 threads, two per CU;            6,144;
+//   Big   (32, 16): NC = 16,384, 512 threads, one per CU;           12,288.
+// 16 points are 64 VGPRs of FP64 data, so that four waves share a SIMD; with 32
+// (Big) two do.
 //
-// What bounds it (FP64, 32,768-sample blocks, 2^27 samples, lambda 4,096):
-// FP64 VALU issue (13 us of a block's 31 us) and LDS traffic (8 us) inside the
-// CU, which overlap little because the waves of a block start in step; the
-// same kernel without global traffic takes 0.55 ms and its loads and stores
-// alone 0.40 ms (5.4 TB/s).  Measured against the 16 x 16 x 16 x 4 kernel:
-// FP64 0.910 -> 0.738 ms (0.751 -> 0.586 ms with 16,384-sample blocks at
-// lambda 1,024), FP32 0.611 -> 0.368 ms.  FP32 blocks need half the LDS and
-// registers, so twice as many share a CU.
+// What bounds it.  Short blocks, 2^26 samples, FP64, lambda 200: memory (238 us,
+// 4.5 TB/s of samples read and written); at lambda 2,048, and Mid ones, VALU
+// issue (70 % of the cycles at lambda 6,000; LDS 53 %).  Big blocks: one per
+// CU, whose waves start in step, so that loads, VALU (42 %) and LDS (27 %) take
+// turns; without global traffic they take 0.55 ms of 0.73 ms at 2^27 samples,
+// lambda 4,096, the loads and stores alone 0.40 ms.
+// Measured, before and after:
+//   Big against 1,024 threads of 16 points (radices 16 x 16 x 16 x 4, three
+//     exchanges across the block per direction, 25 barriers), 2^27 samples:
+//     FP64 0.910 -> 0.738 ms, FP32 0.611 -> 0.368 ms;
+//   Mid against 256 threads of 32 points (32 x 32 x 8), FP64: 2^26 samples,
+//     lambda 2,048 363 -> 338 us, 2^20 samples 18.8 -> 15.9 us;
+//   Short against that, lambda 1,024: 2^26 samples 329 -> 273 us, 2^20 samples
+//     18.8 -> 11.4 us.
+// Big blocks of 1,024 threads with 16 points (16 x 16 x 64, four lanes per
+// transform of pass 3, one row per wave and so two more barriers) took 748 us
+// where 32 points take 728 (FP32 448 against 382).
 #include <cmath>
 #include <vector>
 
@@ -50,63 +60,85 @@ namespace {
 
 using fft::dft16_at;
 using fft::dft32;
-using fft::dft4;
-using fft::dft8_at;
-using fft::out32;
+using fft::mul_w32;
 
 // Transform geometry (see the top of the file).
-template <int L_> struct Geo {
-    static constexpr int L = L_;            // lanes per sub-transform
-    static constexpr int NC = 1024 * L;     // complex points
-    static constexpr int TH = 32 * L;       // threads; points per sub-transform
-    static constexpr int P = 32 / L;        // pass-3 transforms per lane
-    static constexpr int H = 32 / L;        // pairs of sub-transforms per wave
-    // LDS row of one k1: holds TH values (exchange of passes 1 and 2), or 32
-    // groups of L values spaced Q apart (passes 2 and 3).  Odd Q and RS = L
-    // (mod 32) put the 64 lanes of every access on distinct bank pairs.
-    static constexpr int Q = L + 1;
-    static constexpr int RS = 32 * Q + L;
-    static_assert(L == 8 || L == 16, "NC must be 8,192 or 16,384");
-    static_assert(2 * H * RS >= 2048, "a wave's rows hold its half spectrum, two components");
+template <int X_, int L_> struct Geo {
+    static constexpr int X = X_;                // points per thread (radix of passes 1 and 2)
+    static constexpr int L = L_;                // lanes per sub-transform
+    static constexpr int NC = X * X * L;        // complex points
+    static constexpr int TH = X * L;            // threads; points per sub-transform
+    static constexpr bool SPLIT = L > X;        // two lanes share a transform of pass 3
+    static constexpr int W = 64 / L;            // sub-transforms (rows) per wave
+    static constexpr int LX = L < X ? L : X;
+    // LDS row of one k1: holds TH values (exchange of passes 1 and 2), or X
+    // groups of L values spaced Q apart (passes 2 and 3).  Q and RS put the lanes
+    // of every access on distinct bank pairs (RS = L mod 32); with two lanes per
+    // transform, the pairs of neighbours that 16 lanes load, 34 apart.
+    static constexpr int Q = SPLIT ? L + 2 : L + 1;
+    static constexpr int RS = X * Q + (X == 32 ? L : 0);
+    static_assert((X == 32 && L == 16) || (X == 16 && (L == 16 || L == 32)), "");
+    static_assert(W * RS >= X * 64, "a wave's rows hold its half spectrum, two components");
 };
-constexpr int BIG_MAX_LAMBDA = 12288;  // 32,768-sample blocks: V = N - 2 lambda >= 8,192
-constexpr int MID_MAX_LAMBDA = 6144;   // 16,384-sample blocks: V >= 4,096
+using Big = Geo<32, 16>;
+using Mid = Geo<16, 32>;
+using Short = Geo<16, 16>;
+constexpr int BIG_MAX_LAMBDA = 12288;   // 32,768-sample blocks: V = N - 2 lambda >= 8,192
+constexpr int MID_MAX_LAMBDA = 6144;    // 16,384-sample blocks: V >= 4,096
+constexpr int SHORT_MAX_LAMBDA = 3072;  // 8,192-sample blocks: V >= 2,048
 
-// Rows are numbered wave by wave, a wave's first H rows holding k1 = a and
-// the next H their partners 32 - a (16 for a = 0), a = H w .. H w + H - 1.
+// Slot of output k of the DFT of X points.
+template <int X> __host__ __device__ constexpr int outx(int k) {
+    return X == 32 ? fft::out32(k) : k;
+}
+template <typename T, int DIR> __device__ __forceinline__ void dftx(T (&re)[32], T (&im)[32]) {
+    dft32<T, DIR>(re, im);
+}
+template <typename T, int DIR> __device__ __forceinline__ void dftx(T (&re)[16], T (&im)[16]) {
+    dft16_at<T, DIR, 0>(re, im);
+}
+
+// Rows are numbered wave by wave, a wave's first W / 2 rows holding k1 = a and
+// the next their partners X - a (X / 2 for a = 0).
 template <typename G> __host__ __device__ constexpr int row_k1(int row) {
-    const int w = row / (2 * G::H), s = row % (2 * G::H);
-    const int a = G::H * w + s % G::H;
-    return s < G::H ? a : (a == 0 ? 16 : 32 - a);
+    constexpr int H = G::W / 2;
+    const int w = row / G::W, s = row % G::W, a = H * w + s % H;
+    return s < H ? a : (a == 0 ? G::X / 2 : G::X - a);
 }
 template <typename G> __host__ __device__ constexpr int k1_row(int k1) {
-    const int a = k1 == 16 ? 0 : (k1 > 16 ? 32 - k1 : k1);
-    return (a / G::H) * 2 * G::H + a % G::H + (k1 >= 16 ? G::H : 0);
+    constexpr int H = G::W / 2;
+    const int a = k1 == G::X / 2 ? 0 : (k1 > G::X / 2 ? G::X - k1 : k1);
+    return (a / H) * G::W + a % H + (k1 >= G::X / 2 ? H : 0);
 }
-// Partner, among its own 32 registers, of register e of the lane that pairs
-// itself (k1 = 0, lane 0: k = 32 L p + 1024 k2b).
+// Partner, among its own registers, of register e of the lane that pairs itself
+// (k1 = 0, lane 0).
 template <typename G> __host__ __device__ constexpr int self_partner(int e) {
+    if (G::L >= G::X) return (G::X - e) % G::X;
     const int p = e / G::L, k = e % G::L;
-    return p == 0 ? (G::L - k) % G::L : (G::P - p) * G::L + G::L - 1 - k;
+    return p == 0 ? (G::L - k) % G::L : (G::X / G::L - p) * G::L + G::L - 1 - k;
 }
 // That lane's table entries are numbered in order of the pairs' lower
-// register; the last register paired with itself, L / 2 (k = NC / 2), is entry 16.
+// register; the last register paired with itself (k = NC / 2) is entry X / 2.
 template <typename G> __host__ __device__ constexpr int self_entry(int e) {
     int n = 0;
-    for (int f = 0; f < e; ++f) n += f != G::L / 2 && self_partner<G>(f) >= f;
-    return e == G::L / 2 ? 16 : n;
+    for (int f = 0; f < e; ++f) n += f != G::LX / 2 && self_partner<G>(f) >= f;
+    return e == G::LX / 2 ? G::X / 2 : n;
 }
-// Frequency of table entry (i, tid) of a filter's spectrum table, i < 16 (the
-// owner's register), and of the one entry past them (i = 16, tid = 0).
+// Frequency held by register i of lane l of sub-transform k1.
+template <typename G> __host__ __device__ constexpr int reg_k(int k1, int l, int i) {
+    return k1 + G::X * l + (G::L >= G::X ? G::X * G::L * i
+                                         : G::X * G::L * (i / G::L) + G::X * G::X * (i % G::L));
+}
+// Frequency of table entry (i, tid) of a filter's spectrum table, i < X / 2 (the
+// owner's register), and of the one entry past them (i = X / 2, tid = 0).
 template <typename G> __device__ int spec_k(int i, int tid) {
     if (tid == 0) {
-        for (int e = 0; e < 32; ++e)
-            if ((e == G::L / 2 || self_partner<G>(e) >= e) && self_entry<G>(e) == i)
-                return 32 * G::L * (e / G::L) + 1024 * (e % G::L);
+        for (int e = 0; e < G::X; ++e)
+            if ((e == G::LX / 2 || self_partner<G>(e) >= e) && self_entry<G>(e) == i)
+                return reg_k<G>(0, 0, e);
         return 0;
     }
-    const int k1 = row_k1<G>(tid / G::L), l = tid % G::L;
-    return k1 + 32 * l + 32 * G::L * (i / G::L) + 1024 * (i % G::L);
+    return reg_k<G>(row_k1<G>(tid / G::L), tid % G::L, i);
 }
 
 // Raw buffer accesses (resource word of the gfx9 family, stride 0): a load
@@ -161,20 +193,21 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Twiddles w^k, 1 <= k < 32, from w, w^2, w^4, w^8 and w^16 (each a rounded
+// Twiddles w^k, 1 <= k < X, from w, w^2, w^4, w^8 (and w^16) (each a rounded
 // table value, S apart at t): w^k is a product of at most five of them, so its
 // error does not grow with k as it does for powers of one rounded w.
 // f(k, w^k) is called for every k.
+constexpr int n_powers(int X) { return X == 32 ? 5 : 4; }
 template <typename T> struct Cx { T r, i; };
 template <typename T> __device__ __forceinline__ Cx<T> cmul(Cx<T> a, Cx<T> b) {
     return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r};
 }
-template <int DIR, int S, typename T2, typename F>
-__device__ __forceinline__ void powers32(const T2 *__restrict__ t, const F &f) {
+template <int X, int DIR, int S, typename T2, typename F>
+__device__ __forceinline__ void powers(const T2 *__restrict__ t, const F &f) {
     using T = decltype(T2::x);
-    Cx<T> w[5];
+    Cx<T> w[n_powers(X)];
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
+    for (int c = 0; c < n_powers(X); ++c) {
         const auto v = t[c * S];
         w[c] = {v.x, DIR < 0 ? v.y : -v.y};
     }
@@ -191,75 +224,130 @@ __device__ __forceinline__ void powers32(const T2 *__restrict__ t, const F &f) {
     four(4, w[2]);
     four(8, w[3]);
     four(12, cmul(w[3], w[2]));
-    four(16, w[4]);
-    four(20, cmul(w[4], w[2]));
-    const Cx<T> w24 = cmul(w[4], w[3]);
-    four(24, w24);
-    four(28, cmul(w24, w[2]));
-}
-
-// The L-point DFTs of pass 3.
-template <typename G, typename T, int DIR>
-__device__ __forceinline__ void dft_lanes(T (&re)[32], T (&im)[32]) {
-    if constexpr (G::L == 16) {
-        dft16_at<T, DIR, 0>(re, im);
-        dft16_at<T, DIR, 16>(re, im);
-    } else {
-        dft8_at<T, DIR, 0>(re, im);
-        dft8_at<T, DIR, 8>(re, im);
-        dft8_at<T, DIR, 16>(re, im);
-        dft8_at<T, DIR, 24>(re, im);
+    if constexpr (X == 32) {
+        four(16, w[4]);
+        four(20, cmul(w[4], w[2]));
+        const Cx<T> w24 = cmul(w[4], w[3]);
+        four(24, w24);
+        four(28, cmul(w24, w[2]));
     }
 }
 
-// Forward exchange of passes 1 and 2, one component: thread j stores its 32
-// outputs (X[k1] in slot out32(k1)) in column j of the rows k1, then loads its
-// own row's elements l + L q.
-template <typename G, typename T>
-__device__ __forceinline__ void put_cols(T *__restrict__ sh, const T (&v)[32], int tid) {
+// Swap between lanes 16 apart: a of the upper lane <-> b of the lower.
+__device__ __forceinline__ void lane_swap(unsigned &a, unsigned &b) {
+    const auto v = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = v[0];
+    b = v[1];
+}
+__device__ __forceinline__ void lane_swap(float &a, float &b) {
+    unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    lane_swap(x, y);
+    a = __builtin_bit_cast(float, x);
+    b = __builtin_bit_cast(float, y);
+}
+__device__ __forceinline__ void lane_swap(double &a, double &b) {
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    lane_swap(x.x, y.x);
+    lane_swap(x.y, y.y);
+    a = __builtin_bit_cast(double, x);
+    b = __builtin_bit_cast(double, y);
+}
+
+// The L-point DFTs of pass 3.  SPLIT (L = 32 on 16 registers): lanes h = 0 and 1,
+// 16 apart, share a transform.  Forward: registers i and i + 8 hold elements
+// 8 h + i and 8 h + i + 16; radix 2 and its twiddle W32^(8 h + i) in the lane, then
+// lane 0 takes the sums and lane 1 the differences, in order, and register i of
+// lane h ends with output 2 i + h.
+template <typename G, typename T, int DIR>
+__device__ __forceinline__ void dft_lanes(T (&re)[G::X], T (&im)[G::X], int l) {
+    auto radix2 = [&](int i) {
+        const T r = re[i] - re[i + 8], m = im[i] - im[i + 8];
+        re[i] += re[i + 8];
+        im[i] += im[i + 8];
+        re[i + 8] = r;
+        im[i + 8] = m;
+    };
+    auto twiddle = [&](int i) {
+        mul_w32<T, DIR>(re[i + 8], im[i + 8], i);
+        const T r = re[i + 8], m = im[i + 8];
+        re[i + 8] = l >= 16 ? -DIR * m : r;
+        im[i + 8] = l >= 16 ? DIR * r : m;
+    };
+    if constexpr (G::SPLIT && DIR < 0) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) sh[k1_row<G>(k) * G::RS + tid] = v[out32(k)];
+        for (int i = 0; i < 8; ++i) {
+            radix2(i);
+            twiddle(i);
+            lane_swap(re[i], re[i + 8]);
+            lane_swap(im[i], im[i + 8]);
+        }
+    }
+    dft16_at<T, DIR, 0>(re, im);
+    if constexpr (G::X == 32) dft16_at<T, DIR, 16>(re, im);
+    if constexpr (G::SPLIT && DIR > 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            lane_swap(re[i], re[i + 8]);
+            lane_swap(im[i], im[i + 8]);
+            twiddle(i);
+            radix2(i);
+        }
+    }
+}
+
+// Forward exchange of passes 1 and 2, one component: thread j stores its X
+// outputs (k1 in slot outx(k1)) in column j of the rows k1, then loads its own
+// row's elements l + L q.
+template <typename G, typename T>
+__device__ __forceinline__ void put_cols(T *__restrict__ sh, const T (&v)[G::X], int tid) {
+#pragma unroll
+    for (int k = 0; k < G::X; ++k) sh[k1_row<G>(k) * G::RS + tid] = v[outx<G::X>(k)];
 }
 template <typename G, typename T>
-__device__ __forceinline__ void get_row(const T *__restrict__ row, T (&v)[32], int l) {
+__device__ __forceinline__ void get_row(const T *__restrict__ row, T (&v)[G::X], int l) {
 #pragma unroll
-    for (int q = 0; q < 32; ++q) v[q] = row[l + G::L * q];
+    for (int q = 0; q < G::X; ++q) v[q] = row[l + G::L * q];
 }
-// Inverse: a lane stores y[l + L q] (slot out32(q)) in its row, then thread j
+// Inverse: a lane stores y[l + L q] (slot outx(q)) in its row, then thread j
 // loads column j of all rows.
 template <typename G, typename T>
-__device__ __forceinline__ void put_row(T *__restrict__ row, const T (&v)[32], int l) {
+__device__ __forceinline__ void put_row(T *__restrict__ row, const T (&v)[G::X], int l) {
 #pragma unroll
-    for (int q = 0; q < 32; ++q) row[l + G::L * q] = v[out32(q)];
+    for (int q = 0; q < G::X; ++q) row[l + G::L * q] = v[outx<G::X>(q)];
 }
 template <typename G, typename T>
-__device__ __forceinline__ void get_cols(const T *__restrict__ sh, T (&v)[32], int tid) {
+__device__ __forceinline__ void get_cols(const T *__restrict__ sh, T (&v)[G::X], int tid) {
 #pragma unroll
-    for (int k = 0; k < 32; ++k) v[k] = sh[k1_row<G>(k) * G::RS + tid];
+    for (int k = 0; k < G::X; ++k) v[k] = sh[k1_row<G>(k) * G::RS + tid];
 }
 // Exchange of passes 2 and 3 within a row: [k2a][l] groups, Q apart.  Forward:
-// store k2a (slot out32(k2a)) for the own l, load k2a = l + L p for all l.
-template <typename G, typename T>
-__device__ __forceinline__ void row_fwd(T *__restrict__ row, T (&v)[32], int l) {
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 32; ++k) row[k * G::Q + l] = v[out32(k)];
-    wave_sync();
-#pragma unroll
-    for (int p = 0; p < G::P; ++p)
-#pragma unroll
-        for (int s = 0; s < G::L; ++s) v[p * G::L + s] = row[(l + G::L * p) * G::Q + s];
+// store k2a (slot outx(k2a)) for the own l, load k2a = l + L p for all l.  SPLIT:
+// lane k2a + 16 h loads elements 8 h + i and 8 h + i + 16, i < 8, which are kept
+// side by side, at 16 h.
+template <typename G> __device__ __forceinline__ int row_pos(int l) {
+    return G::SPLIT ? (l & 7) | ((l & 16) >> 1) | ((l & 8) << 1) : l;
+}
+template <typename G> __device__ __forceinline__ int row_at(int l, int i) {
+    return G::SPLIT ? (l & 15) * G::Q + (l & 16) + i
+                    : (l + G::L * (i / G::LX)) * G::Q + i % G::LX;
 }
 template <typename G, typename T>
-__device__ __forceinline__ void row_inv(T *__restrict__ row, T (&v)[32], int l) {
+__device__ __forceinline__ void row_fwd(T *__restrict__ row, T (&v)[G::X], int l) {
     wave_sync();
 #pragma unroll
-    for (int p = 0; p < G::P; ++p)
-#pragma unroll
-        for (int s = 0; s < G::L; ++s) row[(l + G::L * p) * G::Q + s] = v[p * G::L + s];
+    for (int k = 0; k < G::X; ++k) row[k * G::Q + row_pos<G>(l)] = v[outx<G::X>(k)];
     wave_sync();
 #pragma unroll
-    for (int k = 0; k < 32; ++k) v[k] = row[k * G::Q + l];
+    for (int i = 0; i < G::X; ++i) v[i] = row[row_at<G>(l, i)];
+}
+template <typename G, typename T>
+__device__ __forceinline__ void row_inv(T *__restrict__ row, T (&v)[G::X], int l) {
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < G::X; ++i) row[row_at<G>(l, i)] = v[i];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < G::X; ++k) v[k] = row[k * G::Q + row_pos<G>(l)];
 }
 
 // Z'_k and Z'_{NC-k} of a pair in place.  With E = z1 + conj z2 and O = (z1 -
@@ -280,45 +368,47 @@ __device__ __forceinline__ void spectrum_pair(T &z1r, T &z1i, T &z2r, T &z2i, T 
 }
 
 // Entries of a filter's spectrum table: A_k and W^k B_k / 2, each rounded once,
-// at k = spec_k(i, tid), entry i TH + tid for i < 16 and one entry past them:
+// at k = spec_k(i, tid), entry i TH + tid for i < X / 2 and one entry past them:
 // the A of all filters' entries first, then the W^k B_k / 2.
-template <typename G> __host__ __device__ constexpr int spec_len() { return 16 * G::TH + 16; }
+template <typename G> __host__ __device__ constexpr int spec_len() {
+    return G::X / 2 * G::TH + 16;
+}
 
-// Spectrum step.  A lane owns the pairs of its registers i < 16; the partners
-// (registers 31 - i of the partner lane) go through the wave's own LDS rows
+// Spectrum step.  A lane owns the pairs of its registers i < X / 2; the partners
+// (registers X - 1 - i of the partner lane) go through the wave's own LDS rows
 // and back.
 template <typename G, typename T>
-__device__ __forceinline__ void spectrum_step(T *__restrict__ wsh, T (&re)[32], T (&im)[32],
+__device__ __forceinline__ void spectrum_step(T *__restrict__ wsh, T (&re)[G::X], T (&im)[G::X],
                                               const T *__restrict__ sa,
                                               const typename Vec2T<T>::type *__restrict__ sw,
                                               int tid) {
+    constexpr int HX = G::X / 2;
     const int lane = tid & 63, l = tid % G::L;
     const int k1 = row_k1<G>(tid / G::L);
     wave_sync();
 #pragma unroll
-    for (int i = 16; i < 32; ++i) {
-        wsh[((i - 16) * 2) * 64 + lane] = re[i];
-        wsh[((i - 16) * 2 + 1) * 64 + lane] = im[i];
+    for (int i = HX; i < G::X; ++i) {
+        wsh[((i - HX) * 2) * 64 + lane] = re[i];
+        wsh[((i - HX) * 2 + 1) * 64 + lane] = im[i];
     }
     wave_sync();
     if (tid != 0) {
-        // partner lane: rows k1 and 32 - k1 are H rows apart
+        // partner lane: rows k1 and X - k1 are W / 2 rows apart
         const int s = lane / G::L;
         const int pl = k1 == 0 ? G::L - l
-                               : ((k1 == 16 ? s : (s < G::H ? s + G::H : s - G::H)) * G::L +
-                                  G::L - 1 - l);
+                               : ((k1 == HX ? s : s ^ (G::W / 2)) * G::L + G::L - 1 - l);
         T *ps = wsh + pl;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < HX; ++i) {
             const auto w = sw[i * G::TH + tid];
-            T z2r = ps[(15 - i) * 128], z2i = ps[(15 - i) * 128 + 64];
+            T z2r = ps[(HX - 1 - i) * 128], z2i = ps[(HX - 1 - i) * 128 + 64];
             spectrum_pair<T>(re[i], im[i], z2r, z2i, sa[i * G::TH + tid], {w.x, w.y});
-            ps[(15 - i) * 128] = z2r;
-            ps[(15 - i) * 128 + 64] = z2i;
+            ps[(HX - 1 - i) * 128] = z2r;
+            ps[(HX - 1 - i) * 128 + 64] = z2i;
         }
     } else {
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
+        for (int e = 0; e < G::X; ++e) {
             const int f = self_partner<G>(e);
             if (f < e) continue;
             const auto w = sw[self_entry<G>(e) * G::TH];
@@ -332,16 +422,16 @@ __device__ __forceinline__ void spectrum_step(T *__restrict__ wsh, T (&re)[32], 
         }
         // its upper half comes back from LDS with the others'
 #pragma unroll
-        for (int i = 16; i < 32; ++i) {
-            wsh[((i - 16) * 2) * 64] = re[i];
-            wsh[((i - 16) * 2 + 1) * 64] = im[i];
+        for (int i = HX; i < G::X; ++i) {
+            wsh[((i - HX) * 2) * 64] = re[i];
+            wsh[((i - HX) * 2 + 1) * 64] = im[i];
         }
     }
     wave_sync();
 #pragma unroll
-    for (int i = 16; i < 32; ++i) {
-        re[i] = wsh[((i - 16) * 2) * 64 + lane];
-        im[i] = wsh[((i - 16) * 2 + 1) * 64 + lane];
+    for (int i = HX; i < G::X; ++i) {
+        re[i] = wsh[((i - HX) * 2) * 64 + lane];
+        im[i] = wsh[((i - HX) * 2 + 1) * 64 + lane];
     }
 }
 
@@ -355,8 +445,8 @@ __global__ void k_fft_spec(const double *__restrict__ H, int n_filters,
     if (e >= (int64_t)n_filters * NE) return;
     const int64_t f = e / NE;
     const int s = (int)(e % NE);
-    // the entries after the 16 TH + 1 used ones only pad the table
-    const int k = s <= 16 * G::TH ? spec_k<G>(s / G::TH, s % G::TH) : 0;
+    // the entries after the X / 2 TH + 1 used ones only pad the table
+    const int k = s <= G::X / 2 * G::TH ? spec_k<G>(s / G::TH, s % G::TH) : 0;
     const double hk = H[f * (G::NC + 1) + k];
     const double hc = H[f * (G::NC + 1) + (G::NC - k)];  // H_{k+NC} = H_{NC-k}
     // W^k = e^(-2 pi i k / N), 0 <= k <= NC = N / 2
@@ -377,14 +467,14 @@ __global__ void k_fft_spec(const double *__restrict__ H, int n_filters,
 // copy of d (2^26 samples, FP64: a pass of 231 us less; with several columns
 // the reads are contiguous too).
 template <typename G, typename T, int RC, bool MASK>
-__global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+__global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 || G::X == 16 ? 4 : 2)))
     k_noise_fft_reg(const int64_t *__restrict__ blocks, const int64_t *__restrict__ istart,
                     const int32_t *__restrict__ fid,
                     const T *__restrict__ sa, const typename Vec2T<T>::type *__restrict__ sw,
                     const typename Vec2T<T>::type *__restrict__ tw, int lam, int V, int R_,
                     int64_t n_blk, const T *__restrict__ y, T *__restrict__ z,
                     const int32_t *__restrict__ jpix, int64_t n, int *__restrict__ bad) {
-    __shared__ T sh[32 * G::RS];
+    __shared__ T sh[G::X * G::RS];
     const int R = RC > 0 ? RC : R_;
     const int tid = threadIdx.x;
     // One flat grid of (block, column) pairs, padded to a multiple of 8 and
@@ -405,7 +495,7 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     const int64_t iv = blocks[2 * bx + 1];
     const int64_t a = istart[iv], e = istart[iv + 1];
     const int64_t base = t0 - lam;
-    T re[32], im[32];
+    T re[G::X], im[G::X];
     // pass 1 reads global memory: z_m = y_{base+2m} + i y_{base+2m+1}, m = tid + TH r.
     // The resource spans the window [base, base + 2 NC) clipped to the
     // interval [a, e): samples outside it read as 0.
@@ -434,11 +524,11 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     };
     if (pairs) {
 #pragma unroll
-        for (int r = 0; r < 32; ++r)
+        for (int r = 0; r < G::X; ++r)
             buf_ld2(ry, off0 + 2 * (tid + G::TH * r) * (int)sizeof(T), re[r], im[r]);
         if constexpr (MASK) {
 #pragma unroll
-            for (int r = 0; r < 32; ++r) {
+            for (int r = 0; r < G::X; ++r) {
                 const u32x2 j = __builtin_bit_cast(
                     u32x2, __builtin_amdgcn_raw_buffer_load_b64(
                                rj, offj + 8 * (tid + G::TH * r), 0, 0));
@@ -448,7 +538,7 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) {
+        for (int r = 0; r < G::X; ++r) {
             const int off = off0 + 2 * (tid + G::TH * r) * RI * (int)sizeof(T);
             int off1 = off + RI * (int)sizeof(T);
             asm volatile("" : "+v"(off1));
@@ -457,7 +547,7 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
         }
         if constexpr (MASK) {
 #pragma unroll
-            for (int r = 0; r < 32; ++r) {
+            for (int r = 0; r < G::X; ++r) {
                 const int off = offj + 8 * (tid + G::TH * r);
                 int off1 = off + 4;
                 asm volatile("" : "+v"(off1));
@@ -467,16 +557,17 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
         }
     }
     if (MASK && nf) atomicOr(bad, 1);
+    constexpr int NW = n_powers(G::X);
     const int l = tid % G::L;
     T *const row = sh + (tid / G::L) * G::RS;                      // the lane's k1
-    T *const wsh = sh + (tid >> 6) * 2 * G::H * G::RS;             // the wave's rows
+    T *const wsh = sh + (tid >> 6) * G::W * G::RS;                 // the wave's rows
     // pass 1
-    dft32<T, -1>(re, im);
+    dftx<T, -1>(re, im);
     {
-        powers32<-1, G::TH>(tw + tid, [&](int k, Cx<T> v) {
-            const Cx<T> x = cmul(Cx<T>{re[out32(k)], im[out32(k)]}, v);
-            re[out32(k)] = x.r;
-            im[out32(k)] = x.i;
+        powers<G::X, -1, G::TH>(tw + tid, [&](int k, Cx<T> v) {
+            const Cx<T> x = cmul(Cx<T>{re[outx<G::X>(k)], im[outx<G::X>(k)]}, v);
+            re[outx<G::X>(k)] = x.r;
+            im[outx<G::X>(k)] = x.i;
         });
     }
     put_cols<G>(sh, re, tid);
@@ -487,31 +578,31 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     __syncthreads();
     get_row<G>(row, im, l);
     // pass 2
-    dft32<T, -1>(re, im);
+    dftx<T, -1>(re, im);
     {
-        powers32<-1, G::L>(tw + 5 * G::TH + l, [&](int k, Cx<T> v) {
-            const Cx<T> x = cmul(Cx<T>{re[out32(k)], im[out32(k)]}, v);
-            re[out32(k)] = x.r;
-            im[out32(k)] = x.i;
+        powers<G::X, -1, G::L>(tw + NW * G::TH + l, [&](int k, Cx<T> v) {
+            const Cx<T> x = cmul(Cx<T>{re[outx<G::X>(k)], im[outx<G::X>(k)]}, v);
+            re[outx<G::X>(k)] = x.r;
+            im[outx<G::X>(k)] = x.i;
         });
     }
     row_fwd<G>(row, re, l);
     row_fwd<G>(row, im, l);
     // pass 3, the spectrum, and back
-    dft_lanes<G, T, -1>(re, im);
+    dft_lanes<G, T, -1>(re, im, l);
     spectrum_step<G, T>(wsh, re, im, sa + (int64_t)fid[iv] * spec_len<G>(),
                         sw + (int64_t)fid[iv] * spec_len<G>(), tid);
-    dft_lanes<G, T, 1>(re, im);
+    dft_lanes<G, T, 1>(re, im, l);
     row_inv<G>(row, re, l);
     row_inv<G>(row, im, l);
     {
-        powers32<1, G::L>(tw + 5 * G::TH + l, [&](int k, Cx<T> v) {
+        powers<G::X, 1, G::L>(tw + NW * G::TH + l, [&](int k, Cx<T> v) {
             const Cx<T> x = cmul(Cx<T>{re[k], im[k]}, v);
             re[k] = x.r;
             im[k] = x.i;
         });
     }
-    dft32<T, 1>(re, im);
+    dftx<T, 1>(re, im);
     // the wave's rows are its own until the first barrier
     wave_sync();
     put_row<G>(row, re, l);
@@ -522,14 +613,14 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     __syncthreads();
     get_cols<G>(sh, im, tid);
     {
-        powers32<1, G::TH>(tw + tid, [&](int k, Cx<T> v) {
+        powers<G::X, 1, G::TH>(tw + tid, [&](int k, Cx<T> v) {
             const Cx<T> x = cmul(Cx<T>{re[k], im[k]}, v);
             re[k] = x.r;
             im[k] = x.i;
         });
     }
-    dft32<T, 1>(re, im);
-    // slot out32(r) holds z'_m, m = tid + TH r: outputs 2m and 2m + 1 of the
+    dftx<T, 1>(re, im);
+    // slot outx(r) holds z'_m, m = tid + TH r: outputs 2m and 2m + 1 of the
     // block.  Output 2m - lam is valid in [0, nvalid): the resource spans
     // exactly those outputs, the stores of the others are dropped.
     const int64_t nvalid = e - t0 < V ? e - t0 : V;
@@ -538,17 +629,17 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     // each pair's even offset 2m, so pairs are whole when lam and nvalid are even
     if (RC == 1 && ((lam | (int)nvalid) & 1) == 0) {
 #pragma unroll
-        for (int r = 0; r < 32; ++r)
-            buf_st2(rz, (2 * (tid + G::TH * r) - lam) * (int)sizeof(T), re[out32(r)],
-                    im[out32(r)]);
+        for (int r = 0; r < G::X; ++r)
+            buf_st2(rz, (2 * (tid + G::TH * r) - lam) * (int)sizeof(T), re[outx<G::X>(r)],
+                    im[outx<G::X>(r)]);
     } else {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) {
+        for (int r = 0; r < G::X; ++r) {
             const int off = ((2 * (tid + G::TH * r) - lam) * R + rr) * (int)sizeof(T);
             int off1 = off + R * (int)sizeof(T);
             asm volatile("" : "+v"(off1));
-            buf_st(rz, off, re[out32(r)]);
-            buf_st(rz, off1, im[out32(r)]);
+            buf_st(rz, off, re[outx<G::X>(r)]);
+            buf_st(rz, off1, im[outx<G::X>(r)]);
         }
     }
 }
@@ -557,39 +648,51 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
 
 bool noise_fft_big_supported(int half_bw) { return half_bw >= 1 && half_bw <= BIG_MAX_LAMBDA; }
 bool noise_fft_mid_supported(int half_bw) { return half_bw >= 1 && half_bw <= MID_MAX_LAMBDA; }
-int noise_fft_big_nc() { return Geo<16>::NC; }
-int noise_fft_mid_nc() { return Geo<8>::NC; }
+int noise_fft_big_nc() { return Big::NC; }
+int noise_fft_mid_nc() { return Mid::NC; }
+int noise_fft_short_nc() { return Short::NC; }
+bool noise_fft_short_supported(int half_bw) {
+    return half_bw >= 1 && half_bw <= SHORT_MAX_LAMBDA;
+}
 
-// Spectrum and twiddle tables for blocks of 2 nc real samples, from H_k,
+// The block lengths.
+template <typename F> static void pick_geo(int n, const F &f) {
+    if (n == 2 * Big::NC) f(Big());
+    else if (n == 2 * Mid::NC) f(Mid());
+    else f(Short());
+}
+
+// Spectrum and twiddle tables for blocks of tb.n = 2 nc real samples, from H_k,
 // k <= nc, per filter and cos(2 pi m / 2nc), m <= nc / 2.
-void noise_fft_tables_dev(mm_ctx *ctx, mm_noise *nz, int nc, const double *H,
+void noise_fft_tables_dev(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, const double *H,
                           const double *qtab) {
     auto go = [&](auto GG, auto TT) {
         using G = decltype(GG);
         using T = decltype(TT);
         using T2 = typename Vec2T<T>::type;
         const int64_t tot = (int64_t)nz->n_filters * spec_len<G>();
-        nz->fft_spec.alloc(sizeof(T) * 3 * (size_t)tot);
-        T *sa = nz->fft_spec.as<T>();
+        tb.spec.alloc(sizeof(T) * 3 * (size_t)tot);
+        T *sa = tb.spec.as<T>();
         k_fft_spec<G, T><<<(unsigned)((tot + 255) / 256), 256, 0, ctx->stream>>>(
             H, nz->n_filters, qtab, sa, reinterpret_cast<T2 *>(sa + tot));
         MM_HIP(hipGetLastError());
-        // W_NC^(j 2^c), j < TH, then W_TH^(l 2^c), l < L, c < 5 (long double
+        // W_NC^(j 2^c), j < TH, then W_TH^(l 2^c), l < L, c < NW (long double
         // on the host, rounded once)
-        std::vector<T2> tw(5 * G::TH + 5 * G::L);
+        constexpr int NW = n_powers(G::X);
+        std::vector<T2> tw(NW * G::TH + NW * G::L);
         const long double pi2 = 6.283185307179586476925286766559L;
         auto set = [&](T2 &v, int64_t m, int n) {
             const long double x = pi2 * (m % n) / n;
             v.x = (T)cosl(x);
             v.y = (T)-sinl(x);
         };
-        for (int c = 0; c < 5; ++c) {
+        for (int c = 0; c < NW; ++c) {
             for (int j = 0; j < G::TH; ++j) set(tw[c * G::TH + j], (int64_t)j << c, G::NC);
             for (int l = 0; l < G::L; ++l)
-                set(tw[5 * G::TH + c * G::L + l], (int64_t)l << c, G::TH);
+                set(tw[NW * G::TH + c * G::L + l], (int64_t)l << c, G::TH);
         }
-        nz->fft_tw.alloc(sizeof(T2) * tw.size());
-        MM_HIP(hipMemcpyAsync(nz->fft_tw.ptr, tw.data(), sizeof(T2) * tw.size(),
+        tb.tw.alloc(sizeof(T2) * tw.size());
+        MM_HIP(hipMemcpyAsync(tb.tw.ptr, tw.data(), sizeof(T2) * tw.size(),
                               hipMemcpyHostToDevice, ctx->stream));
         MM_HIP(hipStreamSynchronize(ctx->stream));
     };
@@ -597,41 +700,40 @@ void noise_fft_tables_dev(mm_ctx *ctx, mm_noise *nz, int nc, const double *H,
         if (nz->prec == MM_F32) go(GG, 0.f);
         else go(GG, 0.0);
     };
-    if (nc == Geo<16>::NC) pick(Geo<16>());
-    else pick(Geo<8>());
+    pick_geo(tb.n, pick);
 }
 
-// Register-resident overlap-save apply with the block size the handle was
-// prepared for (nz->fft_n = 32,768 or 16,384).
+// Register-resident overlap-save apply with the block length the handle was
+// prepared for.
 // jpix (with bad): y is unmasked data [nrhs][n_samp], masked as it is read.
 void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
                              const int32_t *jpix, int *bad) {
     Scope sc(ctx->prof, ctx->stream, "Ninv_fft");
+    const FftTables &tb = nz->fft;
     // (block, column) pairs on a flat grid padded to a multiple of 8 (see
     // the kernel)
-    const int64_t nb = nz->n_fft_blocks;
+    const int64_t nb = tb.n_blocks;
     const dim3 grid((unsigned)((nb * nrhs + 7) / 8 * 8));
     auto go = [&](auto GG, auto TT) {
         using G = decltype(GG);
         using T = decltype(TT);
         using T2 = typename Vec2T<T>::type;
-        const T *sa = nz->fft_spec.as<T>();
+        const T *sa = tb.spec.as<T>();
         auto k = jpix ? (nrhs == 1 ? k_noise_fft_reg<G, T, 1, true>
                                    : k_noise_fft_reg<G, T, 0, true>)
                       : (nrhs == 1 ? k_noise_fft_reg<G, T, 1, false>
                                    : k_noise_fft_reg<G, T, 0, false>);
         k<<<grid, G::TH, 0, ctx->stream>>>(
-            nz->fft_blocks.as<int64_t>(), nz->istart.as<int64_t>(), nz->fid.as<int32_t>(), sa,
+            tb.blocks.as<int64_t>(), nz->istart.as<int64_t>(), nz->fid.as<int32_t>(), sa,
             reinterpret_cast<const T2 *>(sa + (int64_t)nz->n_filters * spec_len<G>()),
-            nz->fft_tw.as<T2>(), nz->half_bw, nz->fft_valid, nrhs, nb,
+            tb.tw.as<T2>(), nz->half_bw, tb.valid, nrhs, nb,
             static_cast<const T *>(y), static_cast<T *>(z), jpix, nz->n_samp, bad);
     };
     auto pick = [&](auto GG) {
         if (nz->prec == MM_F32) go(GG, 0.f);
         else go(GG, 0.0);
     };
-    if (nz->fft_n == 2 * Geo<16>::NC) pick(Geo<16>());
-    else pick(Geo<8>());
+    pick_geo(tb.n, pick);
     MM_HIP(hipGetLastError());
 }
 

@@ -1166,20 +1166,21 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
         // stage 3: FFT block length (results move at the rounding level)
         if ((flags & MM_TUNE_FFT_BLOCK) && nz->method == MM_NOISE_FFT) {
             const int keep = nz->fft_n;
+            const bool was_auto = nz->fft_auto;  // the length picked at build: as it ran then
+            auto prep = [&](int n) {
+                MM_HIP(hipStreamSynchronize(ctx->stream));
+                noise_fft_prepare(ctx, nz, was_auto && n == keep ? 0 : n);
+            };
             double best = 1e30;
             int best_n = keep;
             for (int n_fft : {16384, 32768}) {
                 if (n_fft == 16384 && nz->half_bw > 6144) continue;
-                MM_HIP(hipStreamSynchronize(ctx->stream));
-                noise_fft_prepare(ctx, nz, n_fft);
+                prep(n_fft);
                 const double ms = time_it([&]() { noise_apply_dev(ctx, nz, nrhs, y.ptr, z.ptr); });
                 note(3, n_fft, ms);
                 if (ms < best) { best = ms; best_n = n_fft; }
             }
-            if (best_n != nz->fft_n) {
-                MM_HIP(hipStreamSynchronize(ctx->stream));
-                noise_fft_prepare(ctx, nz, best_n);
-            }
+            if (best_n != nz->fft_n) prep(best_n);
         }
     } catch (...) {
         ctx->prof.on = prof;

@@ -46,6 +46,32 @@ def test_fft_block_edges(ctx, n_fft, lam, prec, R):
         assert maxrel(z[:, r], ref) <= tol, (r, maxrel(z[:, r], ref))
 
 
+@pytest.mark.parametrize("lam", [1, 31, 32, 1000, 2047, 3072])
+@pytest.mark.parametrize("prec,R", [(0, 1), (0, 2), (1, 1), (1, 4)])
+def test_fft_short_stream(ctx, lam, prec, R):
+    """A short stream on its own choice of blocks (8,192 samples, or 16,384 where those
+    would be too many): intervals about one and two of their valid stretches."""
+    import torch
+    rng = np.random.default_rng(77 * lam + 10 * prec + R)
+    V = 8192 - 2 * lam
+    lens = [max(v, 2 * lam + 1) for v in (0, V - 1, V, V + 1, 2 * V, 2 * lam + 2)]
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    fid = np.array([0, 1, 0, 1, 1, 0], dtype=np.int32)
+    band = rng.standard_normal((2, lam + 1)) / np.sqrt(2 * lam + 1)
+    nz = ctx.noise(istart, fid, band, lam, method=2, prec=prec)
+    assert nz.fft_n == 16384 and nz.fft_valid == 16384 - 2 * lam
+    y = rng.standard_normal((istart[-1], R)) + 1.0
+    t = dev(y, torch.float32 if prec else torch.float64)
+    z = host(ctx.noise_apply(nz, t.reshape(-1), nrhs=R)).reshape(-1, R)
+    on = O.noise_build(istart, fid, band, lam)
+    tol = 2e-5 if prec else 1e-12
+    for r in range(R):
+        ref = O.noise_apply_fft(on, host(t)[:, r].astype(np.float64))
+        assert maxrel(z[:, r], ref) <= tol, (r, maxrel(z[:, r], ref))
+        one = host(ctx.noise_apply(nz, t[:, r].contiguous()))
+        np.testing.assert_array_equal(one, z[:, r])
+
+
 @pytest.mark.parametrize("n_fft", [16384, 32768])
 @pytest.mark.parametrize("lam", [33, 1000])
 @pytest.mark.parametrize("prec,R", [(0, 1), (0, 4), (1, 1), (1, 2)])
