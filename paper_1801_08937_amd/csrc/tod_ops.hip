@@ -28,44 +28,63 @@ __global__ void __launch_bounds__(BS) k_zero(int64_t n, T *__restrict__ y) {
         y[e] = (T)0;
 }
 
-template <typename T, int R>
-__device__ __forceinline__ T p_gather(int32_t j, typename Vec2<T>::type ww,
-                                      const double *__restrict__ x, int r) {
-    // branch-free: an unobserved sample (j < 0) reads pixel 0 and yields 0,
-    // so the gathers of several samples are in flight together (the map is
-    // never empty here)
-    const double *xp = x + (int64_t)3 * (j < 0 ? 0 : j) * R + r;
-    const T v = (T)xp[0] + ww.x * (T)xp[R] + ww.y * (T)xp[2 * R];
-    return j < 0 ? (T)0 : v;
-}
+template <typename E> struct Pair {  // two neighbours at any alignment
+    typedef E type __attribute__((ext_vector_type(2), aligned(sizeof(E))));
+};
 
-// y = P x.  Each wave step covers G = 64/R consecutive samples x R columns;
-// four steps are issued together so each lane has four pixel-index loads and
-// twelve map gathers in flight.
-template <typename T, int R>
+// y = P x for R > 1 columns of IQU (NC = 3: weights 1, cos, sin), QU or I maps
+// x[(NC j + a) R + r].  A lane holds two columns of a sample, and a wave takes `per`
+// consecutive samples, PR_U x 128 / R at a time: PR_U pixel indices and weights, then
+// the PR_U x NC map gathers, are in flight together.  Bound by HBM at 20 + 8 R bytes
+// per sample (IQU, FP64).  One column per lane, samples a grid's stride apart, took
+// (us, before and after): 8.4M samples x 4 columns 175 -> 62 (7.0 TB/s, part of it
+// from the Infinity Cache); 1M x 16 44 -> 24, x 64 230 -> 97; 65,536 x 64 14 -> 9;
+// I, 1M x 64 179 -> 92.  PR_U = 4 takes 70 us where 2 takes 62.
+constexpr int PR_U = 2;
+template <typename T, int R, int NC>
 __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix,
                                                 const typename Vec2<T>::type *__restrict__ w,
-                                                int64_t n, const double *__restrict__ x,
+                                                int64_t n, int64_t per,
+                                                const double *__restrict__ x,
                                                 T *__restrict__ y) {
-    constexpr int G = 64 / R;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane / R, r = lane % R;
-    const int64_t wave = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * BS) >> 6;
-    const int64_t step = nwave * G;
-    int64_t t = wave * G + sub;
-    for (; t + 3 * step < n; t += 4 * step) {
-        int32_t j[4];
-        typename Vec2<T>::type ww[4];
+    typedef typename Pair<double>::type d2;
+    typedef typename Pair<T>::type t2;
+    constexpr int LPS = R / 2, SPW = 64 / LPS;
+    const int lane = threadIdx.x & 63, sub = lane / LPS, r = 2 * (lane % LPS);
+    const int64_t t0 = (((int64_t)blockIdx.x * BS + threadIdx.x) >> 6) * per;
+    const int64_t t1 = t0 + per < n ? t0 + per : n;
+    for (int64_t t = t0 + sub; t - sub < t1; t += PR_U * SPW) {
+        int32_t j[PR_U];
+        typename Vec2<T>::type ww[PR_U];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            j[q] = jpix[t + q * step];
-            ww[q] = w[t + q * step];
+        for (int q = 0; q < PR_U; ++q) {
+            const int64_t tq = t + q * SPW < t1 ? t + q * SPW : t1 - 1;
+            j[q] = jpix[tq];
+            if constexpr (NC > 1) ww[q] = w[tq];
         }
+        d2 m[PR_U][NC];
+        // branch-free: an unobserved sample (j < 0) reads pixel 0 and yields 0
+        // (the map is never empty here)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) y[(t + q * step) * R + r] = p_gather<T, R>(j[q], ww[q], x, r);
+        for (int q = 0; q < PR_U; ++q)
+#pragma unroll
+            for (int a = 0; a < NC; ++a)
+                m[q][a] = *reinterpret_cast<const d2 *>(
+                    x + ((int64_t)NC * (j[q] < 0 ? 0 : j[q]) + a) * R + r);
+#pragma unroll
+        for (int q = 0; q < PR_U; ++q) {
+            auto at = [&](auto v) {
+                if constexpr (NC == 1) return (T)v(0);
+                else if constexpr (NC == 2) return ww[q].x * (T)v(0) + ww[q].y * (T)v(1);
+                else return (T)v(0) + ww[q].x * (T)v(1) + ww[q].y * (T)v(2);
+            };
+            t2 o = {at([&](int a) { return m[q][a].x; }), at([&](int a) { return m[q][a].y; })};
+            if (j[q] < 0) o = (T)0;
+            if (t + q * SPW < t1)
+                __builtin_nontemporal_store(
+                    o, reinterpret_cast<t2 *>(y + (t + q * SPW) * R + r));
+        }
     }
-    for (; t < n; t += step) y[t * R + r] = p_gather<T, R>(jpix[t], w[t], x, r);
 }
 
 // Single column: the map is first packed as 32-byte records (I, Q, U, 0) so
@@ -139,7 +158,7 @@ __global__ void __launch_bounds__(BS) k_apply_P1(S src, int64_t n, T *__restrict
 // tiles of the map, and each XCD takes a contiguous range of that order: the
 // pixels one XCD reduces together are neighbours, hit by the same stretches of
 // the scan, so their gathers of z share cache lines in that XCD's L2.
-template <typename T, int R>
+template <typename T, int R, int NC>
 __global__ void __launch_bounds__(BS) k_apply_PT(const int32_t *__restrict__ off,
                                                  const int32_t *__restrict__ perm,
                                                  const typename Vec2<T>::type *__restrict__ ws,
@@ -154,7 +173,14 @@ __global__ void __launch_bounds__(BS) k_apply_PT(const int32_t *__restrict__ off
     if (s >= n_obs) return;
     const int64_t j = order ? order[s] : s;
     const int32_t a = off[j], b = off[j + 1];
-    T s0 = 0, s1 = 0, s2 = 0;
+    T acc[NC] = {};
+    auto add = [&](T zq, typename Vec2<T>::type wq) {
+        if constexpr (NC != 2) acc[0] += zq;
+        if constexpr (NC > 1) {
+            acc[NC - 2] += wq.x * zq;
+            acc[NC - 1] += wq.y * zq;
+        }
+    };
     int32_t i = a + sub;
     // four entries in flight per lane, accumulated in segment order
     for (; i + 3 * G < b; i += 4 * G) {
@@ -166,35 +192,23 @@ __global__ void __launch_bounds__(BS) k_apply_PT(const int32_t *__restrict__ off
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             zz[q] = z[(int64_t)tt[q] * R + r];
-            ww[q] = ws[i + q * G];
+            if constexpr (NC > 1) ww[q] = ws[i + q * G];
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            s0 += zz[q];
-            s1 += ww[q].x * zz[q];
-            s2 += ww[q].y * zz[q];
-        }
+        for (int q = 0; q < 4; ++q) add(zz[q], ww[q]);
     }
     for (; i < b; i += G) {
-        const int32_t tq = perm[i];
-        const T zq = z[(int64_t)tq * R + r];
-        const auto wq = ws[i];
-        s0 += zq;
-        s1 += wq.x * zq;
-        s2 += wq.y * zq;
+        typename Vec2<T>::type wq{};
+        if constexpr (NC > 1) wq = ws[i];
+        add(z[(int64_t)perm[i] * R + r], wq);
     }
 #pragma unroll
-    for (int m = 32; m >= R; m >>= 1) {
-        s0 += __shfl_xor(s0, m);
-        s1 += __shfl_xor(s1, m);
-        s2 += __shfl_xor(s2, m);
-    }
-    if (sub == 0) {
-        double *xp = x + (int64_t)3 * j * R + r;
-        xp[0] = (double)s0;
-        xp[R] = (double)s1;
-        xp[2 * R] = (double)s2;
-    }
+    for (int m = 32; m >= R; m >>= 1)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] += __shfl_xor(acc[c], m);
+    if (sub == 0)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[((int64_t)NC * j + c) * R + r] = (double)acc[c];
 }
 
 // Sliced single-column P^T.  Wave w = s G + g (remapped so that each XCD takes
@@ -293,36 +307,6 @@ __global__ void __launch_bounds__(BS) k_pt_sum_parts(const double *__restrict__ 
     }
 }
 
-// Pointings of the pair-sum (I, NC = 1: weight 1) and pair-difference (QU,
-// NC = 2: weights cos 2psi, sin 2psi) streams (Eqs. d+ and d-).  Same
-// structure as k_apply_P / k_apply_PT; map x[(NC j + a) R + r].
-template <typename T, int R, int NC>
-__device__ __forceinline__ T p_gather_nc(int32_t j, typename Vec2<T>::type ww,
-                                         const double *__restrict__ x, int r) {
-    if (j < 0) return (T)0;
-    const double *xp = x + (int64_t)NC * j * R + r;
-    if constexpr (NC == 1) return (T)xp[0];
-    else return ww.x * (T)xp[0] + ww.y * (T)xp[R];
-}
-
-template <typename T, int R, int NC>
-__global__ void __launch_bounds__(BS) k_apply_P_nc(const int32_t *__restrict__ jpix,
-                                                   const typename Vec2<T>::type *__restrict__ w,
-                                                   int64_t n, const double *__restrict__ x,
-                                                   T *__restrict__ y) {
-    constexpr int G = 64 / R;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane / R, r = lane % R;
-    const int64_t wave = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * BS) >> 6;
-    const int64_t step = nwave * G;
-    for (int64_t t = wave * G + sub; t < n; t += step) {
-        typename Vec2<T>::type ww{};
-        if constexpr (NC == 2) ww = w[t];
-        y[t * R + r] = p_gather_nc<T, R, NC>(jpix[t], ww, x, r);
-    }
-}
-
 // The copies of an I or QU map, NC values per slot.
 template <int NC>
 __global__ void __launch_bounds__(BS) k_pack_map_nc(const double *__restrict__ x, int32_t n_obs,
@@ -342,43 +326,87 @@ __global__ void __launch_bounds__(BS) k_pack_map_nc(const double *__restrict__ x
     }
 }
 
-template <typename T, int R, int NC>
-__global__ void __launch_bounds__(BS) k_apply_PT_nc(const int32_t *__restrict__ off,
-                                                    const int32_t *__restrict__ perm,
-                                                    const typename Vec2<T>::type *__restrict__ ws,
-                                                    int32_t n_obs,
-                                                    const int32_t *__restrict__ order,
-                                                    const T *__restrict__ z,
-                                                    double *__restrict__ x) {
-    constexpr int G = 64 / R;
-    const int lane = threadIdx.x & 63;
-    const int sub = lane / R, r = lane % R;
+// P^T of several columns: a lane holds two columns of an entry, 128 / R entries per
+// wave side by side and PT_U of those steps in flight.  A pixel is a wave's (S = 1),
+// or a block's (S = 4, each wave a quarter of its entries, added in order) where a wave
+// per pixel leaves most of the chip idle.  Against one column per lane (k_apply_PT),
+// us: 65,536 samples on 1,024 pixels x 64 columns 11.1 -> 7.0; 1M on 4,096 x 32
+// 55 -> 44, I x 64 229 -> 95; 8.4M on 16,384 x 8 151 -> 135.  With four columns that
+// form is the faster one (96 against 104 us).  Bound by HBM and the gathers of z.
+constexpr int PT_U = 4;
+constexpr int PT_SPLIT_WAVES = 16;  // per CU
+constexpr int PT_MIN_COLS = 8;
+template <typename T, int R, int NC, int S>
+__global__ void __launch_bounds__(BS) k_apply_PT_cols(
+    const int32_t *__restrict__ off, const int32_t *__restrict__ perm,
+    const typename Vec2<T>::type *__restrict__ ws, int32_t n_obs,
+    const int32_t *__restrict__ order, const T *__restrict__ z, double *__restrict__ x) {
+    typedef typename Pair<double>::type d2;
+    typedef typename Pair<T>::type t2;
+    constexpr int LPS = R / 2, G = 64 / LPS;
+    const int lane = threadIdx.x & 63, sub = lane / LPS, r = 2 * (lane % LPS);
+    const int wv = threadIdx.x >> 6;
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t s = blk * (BS / 64) + (threadIdx.x >> 6);
+    const int64_t s = S == 1 ? blk * (BS / 64) + wv : blk;
     if (s >= n_obs) return;
     const int64_t j = order ? order[s] : s;
-    const int32_t a = off[j], b = off[j + 1];
-    T s0 = 0, s1 = 0;
-    for (int32_t i = a + sub; i < b; i += G) {
-        const T zq = z[(int64_t)perm[i] * R + r];
-        if constexpr (NC == 1) {
-            s0 += zq;
-        } else {
-            const auto wq = ws[i];
-            s0 += wq.x * zq;
-            s1 += wq.y * zq;
+    int32_t a = off[j], b = off[j + 1];
+    if constexpr (S > 1) {
+        const int32_t len = b - a, q = len / S, e = len % S;
+        a += wv * q + (wv < e ? wv : e);
+        b = a + q + (wv < e ? 1 : 0);
+    }
+    t2 acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = (T)0;
+    for (int32_t i = a + sub; i < b; i += PT_U * G) {
+        int32_t tt[PT_U];
+        t2 zz[PT_U];
+        typename Vec2<T>::type ww[PT_U];
+#pragma unroll
+        for (int q = 0; q < PT_U; ++q) {
+            const int32_t iq = i + q * G < b ? i + q * G : b - 1;
+            tt[q] = perm[iq];
+            if constexpr (NC > 1) ww[q] = ws[iq];
+        }
+#pragma unroll
+        for (int q = 0; q < PT_U; ++q) {
+            zz[q] = *reinterpret_cast<const t2 *>(z + (int64_t)tt[q] * R + r);
+            if (i + q * G >= b) zz[q] = (T)0;  // past the end: the last entry, as 0
+        }
+#pragma unroll
+        for (int q = 0; q < PT_U; ++q) {
+            if constexpr (NC != 2) acc[0] += zz[q];
+            if constexpr (NC > 1) {
+                acc[NC - 2] += ww[q].x * zz[q];
+                acc[NC - 1] += ww[q].y * zz[q];
+            }
         }
     }
 #pragma unroll
-    for (int m = 32; m >= R; m >>= 1) {
-        s0 += __shfl_xor(s0, m);
-        if constexpr (NC == 2) s1 += __shfl_xor(s1, m);
+    for (int m = 32; m >= LPS; m >>= 1)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            acc[c].x += __shfl_xor(acc[c].x, m);
+            acc[c].y += __shfl_xor(acc[c].y, m);
+        }
+    if constexpr (S > 1) {
+        __shared__ t2 part[S][NC][LPS];
+        if (sub == 0)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) part[wv][c][lane] = acc[c];
+        __syncthreads();
+        if (wv != 0) return;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 1; k < S; ++k) acc[c] += part[k][c][lane % LPS];
     }
-    if (sub == 0) {
-        double *xp = x + (int64_t)NC * j * R + r;
-        xp[0] = (double)s0;
-        if constexpr (NC == 2) xp[R] = (double)s1;
-    }
+    if (sub == 0)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            *reinterpret_cast<d2 *>(x + ((int64_t)NC * j + c) * R + r) =
+                d2{(double)acc[c].x, (double)acc[c].y};
 }
 
 // plus = (a + b) / 2, minus = (a - b) / 2 (either output may be null; an
@@ -668,13 +696,13 @@ template <typename F> void dispatch_r(int nrhs, F &&f) {
 
 // f(time-domain type, component count 1 or 2) of an I or QU pointing.
 template <typename F> void dispatch_t_nc(const mm_pointing *p, F &&f) {
-    if (p->prec == MM_F32) {
-        if (p->nc == 1) f(0.f, std::integral_constant<int, 1>());
-        else f(0.f, std::integral_constant<int, 2>());
-    } else {
-        if (p->nc == 1) f(0.0, std::integral_constant<int, 1>());
-        else f(0.0, std::integral_constant<int, 2>());
-    }
+    auto nc = [&](auto TT) {
+        if (p->nc == 1) f(TT, std::integral_constant<int, 1>());
+        else if (p->nc == 2) f(TT, std::integral_constant<int, 2>());
+        else f(TT, std::integral_constant<int, 3>());
+    };
+    if (p->prec == MM_F32) nc(0.f);
+    else nc(0.0);
 }
 
 }  // namespace
@@ -757,35 +785,24 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
         MM_HIP(hipGetLastError());
         return;
     }
-    if (p->nc != 3) {
-        dispatch_r(nrhs, [&](auto RR) {
-            constexpr int R = decltype(RR)::value;
-            const int grid = grid_for(n * R, 8 * ctx->n_cu * 4);
+    dispatch_r(nrhs, [&](auto RR) {
+        constexpr int R = decltype(RR)::value;
+        if constexpr (R > 1) {
+            constexpr int step = PR_U * 128 / R;  // samples of a wave at a time
+            const int tuned = p->p_blocks[log2i(R)];
+            int64_t per = tuned > 0 ? (n + 4 * tuned - 1) / (4 * (int64_t)tuned) : step;
+            per = (per + step - 1) / step * step;
+            const unsigned grid = (unsigned)((n + 4 * per - 1) / (4 * per));
             auto go = [&](auto TT, auto NN) {
                 using T = decltype(TT);
                 constexpr int NC = decltype(NN)::value;
-                k_apply_P_nc<T, R, NC><<<grid, BS, 0, ctx->stream>>>(
+                k_apply_P<T, R, NC><<<grid, BS, 0, ctx->stream>>>(
                     p->j.as<int32_t>(),
-                    NC == 2 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, n,
-                    x, static_cast<T *>(y));
+                    NC > 1 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, n,
+                    per, x, static_cast<T *>(y));
             };
             dispatch_t_nc(p, go);
-        });
-        MM_HIP(hipGetLastError());
-        return;
-    }
-    dispatch_r(nrhs, [&](auto RR) {
-        constexpr int R = decltype(RR)::value;
-        const int tuned = p->p_blocks[log2i(R)];
-        const int grid = tuned > 0 ? tuned : grid_for(n * R, 8 * ctx->n_cu * 4);
-        if (p->prec == MM_F32)
-            k_apply_P<float, R><<<grid, BS, 0, ctx->stream>>>(p->j.as<int32_t>(),
-                                                              p->w.as<float2>(), n, x,
-                                                              static_cast<float *>(y));
-        else
-            k_apply_P<double, R><<<grid, BS, 0, ctx->stream>>>(p->j.as<int32_t>(),
-                                                               p->w.as<double2>(), n, x,
-                                                               static_cast<double *>(y));
+        }
     });
     MM_HIP(hipGetLastError());
 }
@@ -834,47 +851,36 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
                 p->sl_w.as<typename SlRec<T>::type>(), p->sl_pix.as<int32_t>(), G, S, nv,
                 static_cast<const T *>(z), out);
         };
-        if (p->nc != 3) dispatch_t_nc(p, go);
-        else if (p->prec == MM_F32) go(0.f, std::integral_constant<int, 3>());
-        else go(0.0, std::integral_constant<int, 3>());
+        dispatch_t_nc(p, go);
         if (parts > 1)
             k_pt_sum_parts<<<grid_for(n3, 2048), BS, 0, ctx->stream>>>(out, parts, n3, x);
         MM_HIP(hipGetLastError());
         return;
     }
-    if (p->nc != 3) {
-        int64_t nb = (p->n_obs + 3) / 4;
-        if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
-        const int32_t *order = p->seg_order.ptr ? p->seg_order.as<int32_t>() : nullptr;
-        dispatch_r(nrhs, [&](auto RR) {
-            constexpr int R = decltype(RR)::value;
-            auto go = [&](auto TT, auto NN) {
-                using T = decltype(TT);
-                constexpr int NC = decltype(NN)::value;
-                k_apply_PT_nc<T, R, NC><<<(unsigned)nb, BS, 0, ctx->stream>>>(
-                    p->off.as<int32_t>(), p->perm.as<int32_t>(),
-                    NC == 2 ? static_cast<const typename Vec2<T>::type *>(p->ws.ptr) : nullptr,
-                    p->n_obs, order, static_cast<const T *>(z), x);
-            };
-            dispatch_t_nc(p, go);
-        });
-        MM_HIP(hipGetLastError());
-        return;
-    }
-    int64_t nb = (p->n_obs + 3) / 4;
-    if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
     const int po = p->pt_order[log2i(nrhs)];
-    const int32_t *order = (p->seg_order.ptr && po != 0) ? p->seg_order.as<int32_t>() : nullptr;
+    const bool tiled = p->seg_order.ptr && (nrhs == 1 || p->nc != 3 || po != 0);
+    const int32_t *order = tiled ? p->seg_order.as<int32_t>() : nullptr;
+    // a block per pixel where a wave per pixel leaves most of the chip idle
+    const bool cols = nrhs >= PT_MIN_COLS, split = p->n_obs < PT_SPLIT_WAVES * (int64_t)ctx->n_cu;
+    int64_t nb = cols && split ? p->n_obs : (p->n_obs + 3) / 4;
+    if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
     dispatch_r(nrhs, [&](auto RR) {
         constexpr int R = decltype(RR)::value;
-        if (p->prec == MM_F32)
-            k_apply_PT<float, R><<<(unsigned)nb, BS, 0, ctx->stream>>>(
-                p->off.as<int32_t>(), p->perm.as<int32_t>(), p->ws.as<float2>(), p->n_obs, order,
-                static_cast<const float *>(z), x);
-        else
-            k_apply_PT<double, R><<<(unsigned)nb, BS, 0, ctx->stream>>>(
-                p->off.as<int32_t>(), p->perm.as<int32_t>(), p->ws.as<double2>(), p->n_obs,
-                order, static_cast<const double *>(z), x);
+        auto go = [&](auto TT, auto NN) {
+            using T = decltype(TT);
+            constexpr int NC = decltype(NN)::value;
+            const auto *ws =
+                NC > 1 ? static_cast<const typename Vec2<T>::type *>(p->ws.ptr) : nullptr;
+            auto run = [&](auto k) {
+                k<<<(unsigned)nb, BS, 0, ctx->stream>>>(p->off.as<int32_t>(),
+                                                        p->perm.as<int32_t>(), ws, p->n_obs,
+                                                        order, static_cast<const T *>(z), x);
+            };
+            if constexpr (R < PT_MIN_COLS) run(k_apply_PT<T, R, NC>);
+            else if (split) run(k_apply_PT_cols<T, R, NC, 4>);
+            else run(k_apply_PT_cols<T, R, NC, 1>);
+        };
+        dispatch_t_nc(p, go);
     });
     MM_HIP(hipGetLastError());
 }

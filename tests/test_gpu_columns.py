@@ -1,0 +1,58 @@
+"""P and P^T of several columns at the edges of their launches: a wave's run of samples
+(256 / R) and one more or less, one sample, pixels with no, one and many samples, few
+and many pixels (a block or a wave per pixel), all three Stokes layouts.  FP64: sums
+of at most some thousand products of order one, 1e-12 of the largest; FP32: 1e-5."""
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_util import dev, host, maxrel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1801_08937_amd import mapmaker as mm
+    return mm.Context(0)
+
+
+@pytest.mark.parametrize("stokes", ["IQU", "QU", "I"])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("R", [2, 4, 8, 16, 32, 64])
+def test_columns(ctx, R, prec, stokes):
+    import torch
+    run = 256 // R
+    for n, side in [(1, 1), (run - 1, 2), (run, 3), (run + 1, 3), (4 * run + 1, 4), (3001, 9),
+                    (20000, 72)]:
+        if n < 1:
+            continue
+        rng = np.random.default_rng(100 * R + n)
+        pix = np.sort(rng.integers(0, side * side, n)).astype(np.int32)
+        pix[rng.random(n) < 0.3] = 0  # one pixel with many samples
+        if n > 2:
+            pix[rng.random(n) < 0.1] = -1
+        if not (pix >= 0).any():
+            pix[0] = 0
+        psi = None if stokes == "I" else rng.uniform(0.0, np.pi, n)
+        lp = ctx.pointing(dev(pix), None if psi is None else dev(psi), side * side, 1, prec,
+                          stokes=stokes)
+        op = O.pointing_build(pix, psi, side * side, 1, stokes)
+        x, z = rng.standard_normal((op.n, R)), rng.standard_normal((n, R))
+        tt = torch.float32 if prec else torch.float64
+        # x and the outputs start 8 (FP32: 4) bytes off a 16-byte boundary
+        bx = torch.zeros(op.n * R + 1, dtype=torch.float64, device="cuda")
+        bx[1:] = dev(x).reshape(-1)
+        by = torch.full((n * R + 2,), 7.0, dtype=tt, device="cuda")
+        ctx.apply_P(lp, bx[1:], by[1:n * R + 1], nrhs=R)
+        tol = 1e-5 if prec else 1e-12
+        y = host(by[1:n * R + 1]).reshape(n, R)
+        assert float(by[0]) == 7.0 and float(by[n * R + 1]) == 7.0
+        zt = dev(z, tt).reshape(-1)
+        bz = torch.full((op.n * R + 2,), 7.0, dtype=torch.float64, device="cuda")
+        ctx.apply_PT(lp, zt, bz[1:op.n * R + 1], nrhs=R)
+        assert float(bz[0]) == 7.0 and float(bz[op.n * R + 1]) == 7.0
+        m = host(bz[1:op.n * R + 1]).reshape(op.n, R)
+        for r in {0, 1, R // 2, R - 1}:
+            assert maxrel(y[:, r], O.apply_P(op, x[:, r].copy())) <= tol
+            assert maxrel(m[:, r], O.apply_PT(op, z[:, r].copy())) <= tol
