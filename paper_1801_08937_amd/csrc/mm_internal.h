@@ -326,7 +326,7 @@ size_t apply_P_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t apply_PT_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t noise_scratch_bytes(const mm_noise *nz, int nrhs);
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
-                 char *scratch = nullptr);
+                 char *scratch = nullptr, bool planar = false);
 void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, double *x,
                   char *scratch = nullptr);
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);

@@ -102,7 +102,7 @@ bool noise_fft_short_supported(int half_bw);
 void noise_fft_tables_dev(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, const double *H,
                           const double *qtab);
 void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                             const int32_t *jpix, int *bad);
+                             bool planar, const int32_t *jpix, int *bad);
 
 bool noise_fft_supported(int half_bw, int64_t min_len) {
     (void)min_len;
@@ -222,12 +222,17 @@ void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
 }
 
 void noise_fft_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {
-    noise_fft_reg_apply_dev(ctx, nz, nrhs, y, z, nullptr, nullptr);
+    noise_fft_reg_apply_dev(ctx, nz, nrhs, y, z, false, nullptr, nullptr);
+}
+
+// y column after column, [R][n]; z interleaved.
+void noise_fft_planar_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {
+    noise_fft_reg_apply_dev(ctx, nz, nrhs, y, z, true, nullptr, nullptr);
 }
 
 void noise_fft_masked_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
                           const void *tod, void *z, int *bad) {
-    noise_fft_reg_apply_dev(ctx, nz, nrhs, tod, z, p->j.as<int32_t>(), bad);
+    noise_fft_reg_apply_dev(ctx, nz, nrhs, tod, z, true, p->j.as<int32_t>(), bad);
 }
 
 

@@ -461,12 +461,13 @@ __global__ void k_fft_spec(const double *__restrict__ H, int n_filters,
 }
 
 // RC = the column count when it is known at compile time (1), else 0 and the
-// column count is R.  MASK: y is the data as given, column after column
-// ([R][n]); flagged samples (jpix < 0) are read as 0 and a non-finite value on
-// any other sample sets *bad, so that b = P^T N^-1 (mask . d) needs no masked
-// copy of d (2^26 samples, FP64: a pass of 231 us less; with several columns
-// the reads are contiguous too).
-template <typename G, typename T, int RC, bool MASK>
+// column count is R.  IN_PLANAR: y holds column after column ([R][n], contiguous
+// reads; 8.4M samples x 4 columns, FP64, 16,384-sample blocks: 295 -> 273 us).  IN_MASKED: the data
+// as given, [R][n]; flagged samples (jpix < 0) are read as 0 and a non-finite
+// value on any other sample sets *bad, so that b = P^T N^-1 (mask . d) needs no
+// masked copy of d (2^26 samples, FP64: a pass of 231 us less).
+enum { IN_INTERLEAVED, IN_PLANAR, IN_MASKED };
+template <typename G, typename T, int RC, int IN>
 __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 || G::X == 16 ? 4 : 2)))
     k_noise_fft_reg(const int64_t *__restrict__ blocks, const int64_t *__restrict__ istart,
                     const int32_t *__restrict__ fid,
@@ -501,11 +502,12 @@ __global__ void __launch_bounds__(G::TH) __attribute__((amdgpu_waves_per_eu(size
     // interval [a, e): samples outside it read as 0.
     const int64_t w0 = base > a ? base : a;
     const int64_t w1 = base + 2 * G::NC < e ? base + 2 * G::NC : e;
-    const int RI = MASK ? 1 : R;  // distance of a column's samples in the input
-    const auto ry = raw_rsrc(MASK ? y + rr * n + w0 : y + w0 * R,
+    constexpr bool MASK = IN == IN_MASKED, PLANAR = IN != IN_INTERLEAVED;
+    const int RI = PLANAR ? 1 : R;  // distance of a column's samples in the input
+    const auto ry = raw_rsrc(PLANAR ? y + rr * n + w0 : y + w0 * R,
                              (w1 - w0) * RI * (int64_t)sizeof(T));
-    const int off0 = ((int)(base - w0) * RI + (MASK ? 0 : rr)) * (int)sizeof(T);
-    const bool pairs = (RC == 1 || MASK) && (((w0 - base) | (w1 - base)) & 1) == 0;
+    const int off0 = ((int)(base - w0) * RI + (PLANAR ? 0 : rr)) * (int)sizeof(T);
+    const bool pairs = (RC == 1 || PLANAR) && (((w0 - base) | (w1 - base)) & 1) == 0;
     // One column: each thread's pair (y_{2m}, y_{2m+1}) is one access when
     // the window's ends fall on even offsets from base, so that no pair
     // straddles them (block-uniform; false only for odd lambda or an odd
@@ -705,9 +707,9 @@ void noise_fft_tables_dev(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, const 
 
 // Register-resident overlap-save apply with the block length the handle was
 // prepared for.
-// jpix (with bad): y is unmasked data [nrhs][n_samp], masked as it is read.
+// planar: y is [nrhs][n_samp]; jpix (with bad): and unmasked data, masked as it is read.
 void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z,
-                             const int32_t *jpix, int *bad) {
+                             bool planar, const int32_t *jpix, int *bad) {
     Scope sc(ctx->prof, ctx->stream, "Ninv_fft");
     const FftTables &tb = nz->fft;
     // (block, column) pairs on a flat grid padded to a multiple of 8 (see
@@ -719,10 +721,11 @@ void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const vo
         using T = decltype(TT);
         using T2 = typename Vec2T<T>::type;
         const T *sa = tb.spec.as<T>();
-        auto k = jpix ? (nrhs == 1 ? k_noise_fft_reg<G, T, 1, true>
-                                   : k_noise_fft_reg<G, T, 0, true>)
-                      : (nrhs == 1 ? k_noise_fft_reg<G, T, 1, false>
-                                   : k_noise_fft_reg<G, T, 0, false>);
+        auto k = nrhs == 1 ? (jpix ? k_noise_fft_reg<G, T, 1, IN_MASKED>
+                                   : k_noise_fft_reg<G, T, 1, IN_INTERLEAVED>)
+                           : (jpix     ? k_noise_fft_reg<G, T, 0, IN_MASKED>
+                              : planar ? k_noise_fft_reg<G, T, 0, IN_PLANAR>
+                                       : k_noise_fft_reg<G, T, 0, IN_INTERLEAVED>);
         k<<<grid, G::TH, 0, ctx->stream>>>(
             tb.blocks.as<int64_t>(), nz->istart.as<int64_t>(), nz->fid.as<int32_t>(), sa,
             reinterpret_cast<const T2 *>(sa + (int64_t)nz->n_filters * spec_len<G>()),

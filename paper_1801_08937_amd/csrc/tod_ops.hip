@@ -35,16 +35,18 @@ template <typename E> struct Pair {  // two neighbours at any alignment
 // y = P x for R > 1 columns of IQU (NC = 3: weights 1, cos, sin), QU or I maps
 // x[(NC j + a) R + r].  A lane holds two columns of a sample, and a wave takes `per`
 // consecutive samples, PR_U x 128 / R at a time: PR_U pixel indices and weights, then
-// the PR_U x NC map gathers, are in flight together.  Bound by HBM at 20 + 8 R bytes
+// the PR_U x NC map gathers, are in flight together.  The output is interleaved, or
+// planar with the columns `plane` apart (plane > 0).  Bound by HBM at 20 + 8 R bytes
 // per sample (IQU, FP64).  One column per lane, samples a grid's stride apart, took
 // (us, before and after): 8.4M samples x 4 columns 175 -> 62 (7.0 TB/s, part of it
 // from the Infinity Cache); 1M x 16 44 -> 24, x 64 230 -> 97; 65,536 x 64 14 -> 9;
 // I, 1M x 64 179 -> 92.  PR_U = 4 takes 70 us where 2 takes 62.
 constexpr int PR_U = 2;
+constexpr int P_PLANAR_COLS = 16;  // most columns of a planar output
 template <typename T, int R, int NC>
 __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix,
                                                 const typename Vec2<T>::type *__restrict__ w,
-                                                int64_t n, int64_t per,
+                                                int64_t n, int64_t per, int64_t plane,
                                                 const double *__restrict__ x,
                                                 T *__restrict__ y) {
     typedef typename Pair<double>::type d2;
@@ -80,9 +82,15 @@ __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix
             };
             t2 o = {at([&](int a) { return m[q][a].x; }), at([&](int a) { return m[q][a].y; })};
             if (j[q] < 0) o = (T)0;
-            if (t + q * SPW < t1)
-                __builtin_nontemporal_store(
-                    o, reinterpret_cast<t2 *>(y + (t + q * SPW) * R + r));
+            const int64_t tq = t + q * SPW;
+            if (tq < t1) {
+                if (R > P_PLANAR_COLS || plane == 0) {
+                    __builtin_nontemporal_store(o, reinterpret_cast<t2 *>(y + tq * R + r));
+                } else {
+                    __builtin_nontemporal_store((T)o.x, y + r * plane + tq);
+                    __builtin_nontemporal_store((T)o.y, y + (r + 1) * plane + tq);
+                }
+            }
         }
     }
 }
@@ -756,8 +764,9 @@ PMap p_map_dev(mm_ctx *ctx, const mm_pointing *p, const double *x, char *scratch
     return m;
 }
 
+// planar: several columns one after the other, [R][n], instead of interleaved.
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
-                 char *scratch) {
+                 char *scratch, bool planar) {
     Scope sc(ctx->prof, ctx->stream, "P");
     const int64_t n = p->n_samp;
     if (p->n_obs == 0) {  // no observed pixel: y = 0 (the gathers assume a pixel 0)
@@ -799,7 +808,7 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
                 k_apply_P<T, R, NC><<<grid, BS, 0, ctx->stream>>>(
                     p->j.as<int32_t>(),
                     NC > 1 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, n,
-                    per, x, static_cast<T *>(y));
+                    per, planar ? n : 0, x, static_cast<T *>(y));
             };
             dispatch_t_nc(p, go);
         }
@@ -886,6 +895,7 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
 }
 
 void noise_fft_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
+void noise_fft_planar_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
 
 // Whether R columns take the register kernel without LDS: from 8 columns on,
 // where a row load of a wave falls in at most 8 runs of cache lines, and from
@@ -1005,8 +1015,14 @@ void apply_A_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs
         z = polyfilter_apply_P_dev(ctx, p, nz, nrhs, x, ta, tb, scratch,
                                    in_tod ? static_cast<char *>(ta) : scratch);
     } else {
-        apply_P_dev(ctx, p, nrhs, x, ta, in_tod ? static_cast<char *>(tb) : scratch);
-        noise_apply_dev(ctx, nz, nrhs, ta, tb);
+        // up to 16 columns, A's own TOD between P and the FFT is planar: the FFT then
+        // reads runs of 16 bytes per lane, which saves more than P's shorter runs cost.
+        // Interleaved and planar, us (FP64): 8.4M samples x 4 columns 491 and 477, x 8
+        // 974 and 848; 1M x 8 118 and 107, x 16 248 and 218, x 32 469 and 657
+        const bool planar = nrhs > 1 && nrhs <= P_PLANAR_COLS && nz->method == MM_NOISE_FFT;
+        apply_P_dev(ctx, p, nrhs, x, ta, in_tod ? static_cast<char *>(tb) : scratch, planar);
+        if (planar) noise_fft_planar_dev(ctx, nz, nrhs, ta, tb);
+        else noise_apply_dev(ctx, nz, nrhs, ta, tb);
     }
     apply_PT_dev(ctx, p, nrhs, z, y,
                  in_tod ? static_cast<char *>(z == tb ? ta : tb) : scratch);

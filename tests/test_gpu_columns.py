@@ -56,3 +56,24 @@ def test_columns(ctx, R, prec, stokes):
         for r in {0, 1, R // 2, R - 1}:
             assert maxrel(y[:, r], O.apply_P(op, x[:, r].copy())) <= tol
             assert maxrel(m[:, r], O.apply_PT(op, z[:, r].copy())) <= tol
+
+
+@pytest.mark.parametrize("stokes", ["IQU", "I"])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("R", [2, 4, 8, 16, 32])
+def test_A_keeps_the_columns(ctx, R, prec, stokes):
+    """A's own TOD may hold its columns one after the other; the values are those of P,
+    N^-1 and P^T one by one, bit for bit."""
+    import torch
+    rng = np.random.default_rng(R)
+    lens = [9001, 70, 8191, 12000]
+    n, lam, side = sum(lens), 33, 11
+    pix = rng.integers(-1, side * side, n).astype(np.int32)
+    psi = None if stokes == "I" else dev(rng.uniform(0.0, np.pi, n))
+    lp = ctx.pointing(dev(pix), psi, side * side, 1, prec, stokes=stokes)
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    band = rng.standard_normal((2, lam + 1))
+    nz = ctx.noise(istart, np.array([0, 1, 1, 0], dtype=np.int32), band, lam, method=2, prec=prec)
+    x = dev(rng.standard_normal(lp.n * R))
+    parts = ctx.apply_PT(lp, ctx.noise_apply(nz, ctx.apply_P(lp, x, nrhs=R), nrhs=R), nrhs=R)
+    assert torch.equal(ctx.apply_A(lp, nz, x, nrhs=R), parts)
