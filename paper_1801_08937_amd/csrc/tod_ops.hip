@@ -32,8 +32,37 @@ template <typename E> struct Pair {  // two neighbours at any alignment
     typedef E type __attribute__((ext_vector_type(2), aligned(sizeof(E))));
 };
 
-// y = P x for R > 1 columns of IQU (NC = 3: weights 1, cos, sin), QU or I maps
-// x[(NC j + a) R + r].  A lane holds two columns of a sample, and a wave takes `per`
+// Columns r and r + 1 of P x at U samples (pixels j, weights ww), maps
+// x[(NC j + a) R + r], NC = 3: weights 1, cos, sin; 2: cos, sin; 1: 1.  Branch-free,
+// so that the U x NC gathers are in flight together: an unobserved sample (j < 0)
+// reads pixel 0 and yields 0 (the map is never empty here).
+template <typename T, int R, int NC, int U>
+__device__ __forceinline__ void p_rows(const int32_t (&j)[U],
+                                       const typename Vec2<T>::type (&ww)[U],
+                                       const double *__restrict__ x, int r,
+                                       typename Pair<T>::type (&o)[U]) {
+    typedef typename Pair<double>::type d2;
+    d2 m[U][NC];
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+#pragma unroll
+        for (int a = 0; a < NC; ++a)
+            m[q][a] = *reinterpret_cast<const d2 *>(
+                x + ((int64_t)NC * (j[q] < 0 ? 0 : j[q]) + a) * R + r);
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        auto at = [&](auto v) {
+            if constexpr (NC == 1) return (T)v(0);
+            else if constexpr (NC == 2) return ww[q].x * (T)v(0) + ww[q].y * (T)v(1);
+            else return (T)v(0) + ww[q].x * (T)v(1) + ww[q].y * (T)v(2);
+        };
+        o[q].x = at([&](int a) { return m[q][a].x; });
+        o[q].y = at([&](int a) { return m[q][a].y; });
+        if (j[q] < 0) o[q] = (T)0;
+    }
+}
+
+// y = P x for R > 1 columns of IQU, QU or I maps.  A lane holds two columns of a sample, and a wave takes `per`
 // consecutive samples, PR_U x 128 / R at a time: PR_U pixel indices and weights, then
 // the PR_U x NC map gathers, are in flight together.  The output is interleaved, or
 // planar with the columns `plane` apart (plane > 0).  Bound by HBM at 20 + 8 R bytes
@@ -49,7 +78,6 @@ __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix
                                                 int64_t n, int64_t per, int64_t plane,
                                                 const double *__restrict__ x,
                                                 T *__restrict__ y) {
-    typedef typename Pair<double>::type d2;
     typedef typename Pair<T>::type t2;
     constexpr int LPS = R / 2, SPW = 64 / LPS;
     const int lane = threadIdx.x & 63, sub = lane / LPS, r = 2 * (lane % LPS);
@@ -64,31 +92,17 @@ __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix
             j[q] = jpix[tq];
             if constexpr (NC > 1) ww[q] = w[tq];
         }
-        d2 m[PR_U][NC];
-        // branch-free: an unobserved sample (j < 0) reads pixel 0 and yields 0
-        // (the map is never empty here)
-#pragma unroll
-        for (int q = 0; q < PR_U; ++q)
-#pragma unroll
-            for (int a = 0; a < NC; ++a)
-                m[q][a] = *reinterpret_cast<const d2 *>(
-                    x + ((int64_t)NC * (j[q] < 0 ? 0 : j[q]) + a) * R + r);
+        t2 o[PR_U];
+        p_rows<T, R, NC, PR_U>(j, ww, x, r, o);
 #pragma unroll
         for (int q = 0; q < PR_U; ++q) {
-            auto at = [&](auto v) {
-                if constexpr (NC == 1) return (T)v(0);
-                else if constexpr (NC == 2) return ww[q].x * (T)v(0) + ww[q].y * (T)v(1);
-                else return (T)v(0) + ww[q].x * (T)v(1) + ww[q].y * (T)v(2);
-            };
-            t2 o = {at([&](int a) { return m[q][a].x; }), at([&](int a) { return m[q][a].y; })};
-            if (j[q] < 0) o = (T)0;
             const int64_t tq = t + q * SPW;
             if (tq < t1) {
                 if (R > P_PLANAR_COLS || plane == 0) {
-                    __builtin_nontemporal_store(o, reinterpret_cast<t2 *>(y + tq * R + r));
+                    __builtin_nontemporal_store(o[q], reinterpret_cast<t2 *>(y + tq * R + r));
                 } else {
-                    __builtin_nontemporal_store((T)o.x, y + r * plane + tq);
-                    __builtin_nontemporal_store((T)o.y, y + (r + 1) * plane + tq);
+                    __builtin_nontemporal_store((T)o[q].x, y + r * plane + tq);
+                    __builtin_nontemporal_store((T)o[q].y, y + (r + 1) * plane + tq);
                 }
             }
         }
@@ -567,19 +581,11 @@ constexpr int BC_OPT = 16;
 constexpr int BC_MIN_R = 8;       // fewer columns: a wave's row loads fall in 16 or more lines
 constexpr int BC_MIN_LAMBDA = 8;  // 2 lambda + 1 >= BC_OPT
 
-template <typename T, int R, bool EDGE>
-__device__ __forceinline__ void band_rows(const T *__restrict__ f, int lam, int64_t t0,
-                                          int64_t a, int64_t b, int r, const T *__restrict__ y,
-                                          T *__restrict__ z) {
+// row(u) is input row t0 - lam + u of the column; EDGE: outputs from b on are not written.
+template <typename T, int R, bool EDGE, typename F>
+__device__ __forceinline__ void band_rows(const T *__restrict__ f, int lam, int64_t t0, int64_t b,
+                                          int r, const F &row, T *__restrict__ z) {
     constexpr int O = BC_OPT;
-    const T *yr = y + r;
-    auto row = [&](int u) {  // input row t0 - lam + u, 0 outside the interval
-        const int64_t t = t0 - lam + u;
-        if (!EDGE) return yr[t * R];
-        const bool in = t >= a && t < b;
-        const T v = yr[(in ? t : a) * R];
-        return in ? v : (T)0;
-    };
     T acc[O];
 #pragma unroll
     for (int m = 0; m < O; ++m) acc[m] = 0;
@@ -655,11 +661,101 @@ __global__ void __launch_bounds__(BS) k_band_cols(const int64_t *__restrict__ pr
     const int64_t tw = a + (bt - pref[lo]) * TL + wave * GW * BC_OPT;  // the wave's first output
     if (tw >= b) return;
     const int64_t t0 = tw + lane / R * BC_OPT;
+    const int r = lane % R;
+    const T *yr = y + r;
     // rows read ahead past the last needed one by at most 8
     if (tw - lam >= a && tw + GW * BC_OPT + lam + 8 <= b)
-        band_rows<T, R, false>(f, lam, t0, a, b, lane % R, y, z);
+        band_rows<T, R, false>(f, lam, t0, b, r, [&](int u) { return yr[(t0 - lam + u) * R]; }, z);
     else
-        band_rows<T, R, true>(f, lam, t0, a, b, lane % R, y, z);
+        band_rows<T, R, true>(
+            f, lam, t0, b, r,
+            [&](int u) {  // 0 outside the interval
+                const int64_t t = t0 - lam + u;
+                const bool in = t >= a && t < b;
+                const T v = yr[(in ? t : a) * R];
+                return in ? v : (T)0;
+            },
+            z);
+}
+
+// z = N^-1 P x of many columns in one pass: a block gathers the rows of P x that its
+// outputs, CB columns of a tile, need into LDS (as k_apply_P does), and walks them from
+// there as k_band_cols does.  The tile's halo, 2 lambda rows, is gathered by its
+// neighbours too, but P x is neither written nor read back.  The same bits as the two
+// launches.  Bound by the gathers, from the L2, and the FMAs of the band.  A of 64
+// columns, FP64, P and band apart or in one pass, us: 131,072 samples, lambda 32
+// 73 -> 48, lambda 80 103 -> 81; 524,288 299 -> 174; 8 columns of 2^20 samples, lambda
+// 32, 80 -> 53.  64-column blocks, whose halo is twice the share, took 56 us where
+// 32 take 48.  From halos of 2.5 tiles on the gathers outweigh (FP32, 32 columns of
+// 2^20, lambda 120 338 -> 305, 200 494 -> 513).
+constexpr int BP_MIN_R = 8;
+constexpr int BP_LDS = 80 * 1024;  // two blocks per CU
+template <int R> constexpr int bp_cols() { return R < 32 ? R : 32; }
+// Row stride in LDS: the rows of two neighbouring threads of a column, BC_OPT apart,
+// on different banks.
+template <int R> constexpr int bp_stride() { return bp_cols<R>() < 32 ? bp_cols<R>() + 1 : 32; }
+template <typename T, int R> size_t bp_lds(int lam) {
+    return sizeof(T) * bp_stride<R>() *
+           (size_t)((BS / bp_cols<R>()) * BC_OPT + 2 * lam + 8);  // 8 are read ahead
+}
+
+template <typename T, int R, int NC>
+__global__ void __launch_bounds__(BS) k_band_P(const int64_t *__restrict__ pref, int n_int,
+                                               const int64_t *__restrict__ istart,
+                                               const int32_t *__restrict__ fid,
+                                               const T *__restrict__ full, int lam,
+                                               int64_t n_tiles, const int32_t *__restrict__ jpix,
+                                               const typename Vec2<T>::type *__restrict__ w,
+                                               const double *__restrict__ x, T *__restrict__ z) {
+    extern __shared__ char smem[];
+    T *const sy = reinterpret_cast<T *>(smem);
+    constexpr int CB = bp_cols<R>(), SR = bp_stride<R>(), K = R / CB, TL = (BS / CB) * BC_OPT;
+    // the K column groups of a tile are neighbours; pref counts tiles of CB columns
+    const int64_t blk = xcd_block(blockIdx.x, gridDim.x), bt = blk / K;
+    if (bt >= n_tiles) return;
+    const int c0 = (int)(blk % K) * CB;
+    int lo = 0, hi = n_int;  // pref[lo] <= bt < pref[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pref[mid] <= bt) lo = mid; else hi = mid;
+    }
+    const int64_t a = istart[lo], b = istart[lo + 1];
+    const int64_t ta = a + (bt - pref[lo]) * TL;  // the tile's first output
+    const T *f = full + (int64_t)fid[lo] * (2 * lam + 1);
+    {
+        // two columns per lane, BP_U steps of the block's rows in flight
+        constexpr int LPS = CB / 2, RPB = BS / LPS, BP_U = 4;
+        const int sub = threadIdx.x / LPS, r = 2 * (threadIdx.x % LPS);
+        const int rows = TL + 2 * lam;
+        for (int i = sub; i < rows; i += BP_U * RPB) {
+            int32_t j[BP_U];
+            typename Vec2<T>::type ww[BP_U];
+            bool in[BP_U];
+#pragma unroll
+            for (int q = 0; q < BP_U; ++q) {
+                const int64_t t = ta - lam + i + q * RPB;
+                in[q] = t >= a && t < b;
+                const int64_t tq = in[q] ? t : a;
+                j[q] = jpix[tq];
+                if constexpr (NC > 1) ww[q] = w[tq];
+            }
+            typename Pair<T>::type v[BP_U];
+            p_rows<T, R, NC, BP_U>(j, ww, x, c0 + r, v);
+#pragma unroll
+            for (int q = 0; q < BP_U; ++q) {
+                const int row = i + q * RPB;
+                if (row >= rows) break;
+                if (!in[q]) v[q] = (T)0;
+                sy[row * SR + r] = v[q].x;
+                sy[row * SR + r + 1] = v[q].y;
+            }
+        }
+    }
+    __syncthreads();
+    const int m0 = threadIdx.x / CB * BC_OPT, r = threadIdx.x % CB;
+    if (ta + m0 >= b) return;
+    const T *const yr = sy + m0 * SR + r;
+    band_rows<T, R, true>(f, lam, ta + m0, b, c0 + r, [&](int u) { return yr[u * SR]; }, z);
 }
 
 // y[t R + r] = mask_t * tod[r * n + t]; flags non-finite data on kept samples.
@@ -929,6 +1025,43 @@ size_t noise_scratch_bytes(const mm_noise *nz, int nrhs) {
     return nz->method == MM_NOISE_POLY ? polyfilter_scratch_bytes(nz, nrhs) : 0;
 }
 
+// z = N^-1 P x in one launch, where the direct band runs by rows, two blocks' rows fit in
+// a CU's LDS and the halo is at most 2.5 tiles; false where it does not apply.
+static bool band_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
+                       const double *x, void *z) {
+    const int lam = nz->half_bw;
+    if (nz->method != MM_NOISE_DIRECT || p->n_obs == 0) return false;
+    bool done = false;
+    dispatch_r(nrhs, [&](auto RR) {
+        constexpr int R = decltype(RR)::value;
+        if constexpr (R >= BP_MIN_R) {
+            auto go = [&](auto TT, auto NN) {
+                using T = decltype(TT);
+                constexpr int NC = decltype(NN)::value, K = R / bp_cols<R>();
+                constexpr int CB = bp_cols<R>();
+                const size_t lds = bp_lds<T, R>(lam);
+                if (lds > BP_LDS || 4 * lam > 5 * (BS / CB) * BC_OPT ||
+                    !band_by_rows(CB, lam, nz->n_samp))
+                    return;
+                Scope sc(ctx->prof, ctx->stream, "Ninv_band");
+                const size_t li = (size_t)log2i(CB) * (nz->n_int + 1);
+                const int64_t n_tiles = nz->h_tile_pref[li + nz->n_int];
+                k_band_P<T, R, NC><<<(unsigned)((n_tiles * K + 7) / 8 * 8), BS, lds,
+                                     ctx->stream>>>(
+                    nz->tile_pref.as<int64_t>() + li, nz->n_int, nz->istart.as<int64_t>(),
+                    nz->fid.as<int32_t>(), nz->band_full.as<T>(), lam, n_tiles,
+                    p->j.as<int32_t>(),
+                    NC > 1 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, x,
+                    static_cast<T *>(z));
+                done = true;
+            };
+            dispatch_t_nc(p, go);
+        }
+    });
+    MM_HIP(hipGetLastError());
+    return done;
+}
+
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z) {
     if (nz->method == MM_NOISE_FFT) {
         noise_fft_apply_dev(ctx, nz, nrhs, y, z);
@@ -1014,7 +1147,7 @@ void apply_A_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs
         // the filter's first pass reads the copies while it writes tb
         z = polyfilter_apply_P_dev(ctx, p, nz, nrhs, x, ta, tb, scratch,
                                    in_tod ? static_cast<char *>(ta) : scratch);
-    } else {
+    } else if (!band_P_dev(ctx, p, nz, nrhs, x, tb)) {
         // up to 16 columns, A's own TOD between P and the FFT is planar: the FFT then
         // reads runs of 16 bytes per lane, which saves more than P's shorter runs cost.
         // Interleaved and planar, us (FP64): 8.4M samples x 4 columns 491 and 477, x 8

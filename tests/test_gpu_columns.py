@@ -77,3 +77,25 @@ def test_A_keeps_the_columns(ctx, R, prec, stokes):
     x = dev(rng.standard_normal(lp.n * R))
     parts = ctx.apply_PT(lp, ctx.noise_apply(nz, ctx.apply_P(lp, x, nrhs=R), nrhs=R), nrhs=R)
     assert torch.equal(ctx.apply_A(lp, nz, x, nrhs=R), parts)
+
+
+@pytest.mark.parametrize("stokes", ["IQU", "QU", "I"])
+@pytest.mark.parametrize("prec,R,lam", [(0, 64, 8), (0, 64, 32), (0, 64, 92), (0, 64, 93),
+                                        (0, 32, 33), (0, 16, 60), (0, 8, 12), (0, 8, 150),
+                                        (1, 64, 32), (1, 32, 100), (1, 16, 9), (1, 8, 40)])
+def test_A_band_in_one_pass(ctx, prec, R, lam, stokes):
+    """Direct band of many columns: A gathers P x inside N^-1 (FP64, 64 columns: up to
+    lambda 92), with the bits of P, N^-1 and P^T one by one."""
+    import torch
+    rng = np.random.default_rng(R + lam)
+    lens = [2 * lam + 1, 2 * lam + 2, 1000, 64 * 40, 64 * 40 + 1, 127 * 16, (1 << 21) // min(R, 32)]
+    n, side = sum(lens), 13
+    pix = rng.integers(-1, side * side, n).astype(np.int32)
+    psi = None if stokes == "I" else dev(rng.uniform(0.0, np.pi, n))
+    lp = ctx.pointing(dev(pix), psi, side * side, 1, prec, stokes=stokes)
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    fid = rng.integers(0, 3, len(lens)).astype(np.int32)
+    nz = ctx.noise(istart, fid, rng.standard_normal((3, lam + 1)), lam, method=1, prec=prec)
+    x = dev(rng.standard_normal(lp.n * R))
+    parts = ctx.apply_PT(lp, ctx.noise_apply(nz, ctx.apply_P(lp, x, nrhs=R), nrhs=R), nrhs=R)
+    assert torch.equal(ctx.apply_A(lp, nz, x, nrhs=R), parts)
