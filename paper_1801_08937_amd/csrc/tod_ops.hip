@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(BS) k_sum_diff(int64_t n, const T *a, const T 
 // Direct band, register-tiled.  A block owns TL = (BS / R) * BT_OPT
 // consecutive outputs of one interval for all R columns; thread (g, r) =
 // (threadIdx / R, threadIdx mod R) keeps outputs g*BT_OPT .. g*BT_OPT + 7 of
-// column r in registers.  The filter is taken as the full symmetric one,
+// column r in registers (O = BT_OPT).  The filter is taken as the full symmetric one,
 // f[d] = c_|d - lambda|, d = 0 .. 2 lambda, and walked in chunks of at most
 // CL taps; for each chunk the taps and the input window [t0 - lambda + d0,
 // t0 + TL - lambda + d0 + CL - 1) (zero outside the interval, R values per
@@ -459,19 +459,76 @@ __global__ void __launch_bounds__(BS) k_sum_diff(int64_t n, const T *a, const T 
 // exactly +0.
 constexpr int BT_OPT = 8;
 constexpr int BT_LDS = 65536;  // bytes of LDS per block
-// One column on a short stream (nz->band_small): blocks of 64 threads, tiles
-// of 512 outputs, so that the few tiles of such a stream still spread over
-// the CUs (config 1's 131,072 samples: 256 blocks instead of 64).
-constexpr int BAND_SMALL_NT = 64;
+// One column on a short stream (nz->band_small): tiles of 512 outputs, so that the few
+// tiles of such a stream still spread over the CUs (131,072 samples: 256 blocks
+// instead of 64), in blocks of 128 threads with 4 outputs each: 64 threads of 8 took,
+// for A of 2^17 samples at lambda 32, 12.2 us where these take 11.3 (lambda 300: 26.8
+// and 19.6); 256 of 2 gain on at most 2^17 samples and lose beyond.
+constexpr int BAND_SMALL_NT = 128, BAND_SMALL_OPT = 4;
 
-template <typename T, int R, int NT = BS>
+// Stages rows w0 .. w0 + rows - 1 of the R columns (0 outside [a, b)) in sy.
+template <typename T> struct TodRows {
+    const T *__restrict__ y;
+    template <int R, int NT>
+    __device__ __forceinline__ void stage(T *__restrict__ sy, int64_t w0, int rows, int64_t a,
+                                          int64_t b) const {
+        int e = threadIdx.x;
+        for (; e + 7 * NT < rows * R; e += 8 * NT) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int eu = e + u * NT;
+                const int64_t t = w0 + eu / R;
+                const bool in = t >= a && t < b;
+                v[u] = y[(in ? t : a) * R + eu % R];
+                v[u] = in ? v[u] : (T)0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sy[e + u * NT] = v[u];
+        }
+        for (; e < rows * R; e += NT) {
+            const int64_t t = w0 + e / R;
+            sy[e] = (t >= a && t < b) ? y[t * R + e % R] : (T)0;
+        }
+    }
+};
+// One column of P x, gathered here (A = P^T N^-1 P): the window is staged once, for
+// all taps, and its 2 lambda halo rows are gathered by the neighbouring tiles too.  A
+// in all, P and band apart or in one launch, FP64, lambda 32, us: 2^17 samples
+// 11.3 -> 9.0, 2^20 28.3 -> 24.2, 2^25 459 -> 402.  On short streams latency bounds it.
+template <typename T, typename S> struct PRows {
+    S src;
+    template <int R, int NT>
+    __device__ __forceinline__ void stage(T *__restrict__ sy, int64_t w0, int rows, int64_t a,
+                                          int64_t b) const {
+        static_assert(R == 1, "");
+        constexpr int U = 5;
+        for (int e = threadIdx.x; e < rows; e += U * NT) {
+            int64_t t[U];
+            T v[U];
+            bool in[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                t[u] = w0 + e + u * NT;
+                in[u] = t[u] >= a && t[u] < b;
+                t[u] = in[u] ? t[u] : a;
+            }
+            src.get(t, v);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (e + u * NT < rows) sy[e + u * NT] = in[u] ? v[u] : (T)0;
+        }
+    }
+};
+
+template <typename T, int R, int NT, int O, typename Rows>
 __global__ void __launch_bounds__(NT) k_band_tiled(const int64_t *__restrict__ pref, int n_int,
                                                    const int64_t *__restrict__ istart,
                                                    const int32_t *__restrict__ fid,
                                                    const T *__restrict__ band, int lam, int CL,
-                                                   const T *__restrict__ y, T *__restrict__ z) {
+                                                   Rows src, T *__restrict__ z) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    constexpr int TL = (NT / R) * BT_OPT;
+    constexpr int TL = (NT / R) * O;
     const int nf = 2 * lam + 1;
     const int nf_pad = (nf + BT_OPT - 1) / BT_OPT * BT_OPT;
     // CL is a multiple of BT_OPT; rounding it here lets the compiler see
@@ -491,10 +548,10 @@ __global__ void __launch_bounds__(NT) k_band_tiled(const int64_t *__restrict__ p
     const int64_t t0 = a + (bt - pref[iv]) * TL;
     const T *c = band + (int64_t)fid[iv] * (lam + 1);
     const int r = threadIdx.x % R;
-    const int m0 = (threadIdx.x / R) * BT_OPT;
-    T acc[BT_OPT];
+    const int m0 = (threadIdx.x / R) * O;
+    T acc[O];
 #pragma unroll
-    for (int m = 0; m < BT_OPT; ++m) acc[m] = 0;
+    for (int m = 0; m < O; ++m) acc[m] = 0;
     for (int d0 = 0; d0 < nf_pad; d0 += CLa) {
         const int cl = nf_pad - d0 < CLa ? nf_pad - d0 : CLa;
         __syncthreads();  // the previous chunk's reads are done
@@ -521,41 +578,23 @@ __global__ void __launch_bounds__(NT) k_band_tiled(const int64_t *__restrict__ p
             sf[k] = d0 + k < nf ? c[d < 0 ? -d : d] : (T)0;
         }
         const int rows = TL + cl - 1;
-        const int64_t w0 = t0 - lam + d0;
-        int e = threadIdx.x;
-        for (; e + 7 * NT < rows * R; e += 8 * NT) {
-            T v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int eu = e + u * NT;
-                const int64_t t = w0 + eu / R;
-                const bool in = t >= a && t < b;
-                v[u] = y[(in ? t : a) * R + eu % R];
-                v[u] = in ? v[u] : (T)0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sy[e + u * NT] = v[u];
-        }
-        for (; e < rows * R; e += NT) {
-            const int64_t t = w0 + e / R;
-            sy[e] = (t >= a && t < b) ? y[t * R + e % R] : (T)0;
-        }
+        src.template stage<R, NT>(sy, t0 - lam + d0, rows, a, b);
         __syncthreads();
-        for (int db = 0; db < cl; db += BT_OPT) {
-            T w[2 * BT_OPT - 1], cf[BT_OPT];
+        for (int db = 0; db < cl; db += O) {
+            T w[2 * O - 1], cf[O];
 #pragma unroll
-            for (int q = 0; q < 2 * BT_OPT - 1; ++q) w[q] = sy[(m0 + db + q) * R + r];
+            for (int q = 0; q < 2 * O - 1; ++q) w[q] = sy[(m0 + db + q) * R + r];
 #pragma unroll
-            for (int q = 0; q < BT_OPT; ++q) cf[q] = sf[db + q];
+            for (int q = 0; q < O; ++q) cf[q] = sf[db + q];
 #pragma unroll
-            for (int q = 0; q < BT_OPT; ++q)
+            for (int q = 0; q < O; ++q)
 #pragma unroll
-                for (int m = 0; m < BT_OPT; ++m) acc[m] += cf[q] * w[m + q];
+                for (int m = 0; m < O; ++m) acc[m] += cf[q] * w[m + q];
         }
     }
     const int64_t t1 = t0 + TL < b ? t0 + TL : b;
 #pragma unroll
-    for (int m = 0; m < BT_OPT; ++m) {
+    for (int m = 0; m < O; ++m) {
         const int64_t t = t0 + m0 + m;
         if (t < t1) z[t * R + r] = acc[m];
     }
@@ -1007,7 +1046,7 @@ static bool band_by_rows(int nrhs, int lam, int64_t n_samp) {
 // Tile length of the direct band for R columns.
 int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp) {
     if (band_by_rows(nrhs, lam, n_samp)) return (BS / nrhs) * BC_OPT;
-    return nrhs == 1 && small ? BAND_SMALL_NT * BT_OPT : (BS / nrhs) * BT_OPT;
+    return nrhs == 1 && small ? BAND_SMALL_NT * BAND_SMALL_OPT : (BS / nrhs) * BT_OPT;
 }
 
 // Taps per LDS chunk of the direct band: taps + window rows of R values fit
@@ -1025,12 +1064,61 @@ size_t noise_scratch_bytes(const mm_noise *nz, int nrhs) {
     return nz->method == MM_NOISE_POLY ? polyfilter_scratch_bytes(nz, nrhs) : 0;
 }
 
-// z = N^-1 P x in one launch, where the direct band runs by rows, two blocks' rows fit in
-// a CU's LDS and the halo is at most 2.5 tiles; false where it does not apply.
+// Tile counts for every column count are built with the noise handle, so an apply
+// never modifies it (handles may be shared across contexts).
+static const int64_t *band_tiles(const mm_noise *nz, int nrhs, int64_t *n_tiles) {
+    const size_t li = (size_t)log2i(nrhs) * (nz->n_int + 1);
+    *n_tiles = nz->h_tile_pref[li + nz->n_int];
+    return nz->tile_pref.as<int64_t>() + li;
+}
+
+static int band_chunk_used(const mm_noise *nz, int nrhs) {
+    const int tuned = nz->band_cl[log2i(nrhs)];
+    return tuned > 0 ? tuned
+                     : band_chunk(nz->half_bw, nrhs, nz->prec, nz->band_small, nz->n_samp);
+}
+
+template <typename T, int R, typename Rows>
+static void band_tiled_launch(mm_ctx *ctx, const mm_noise *nz, const Rows &rows, T *z) {
+    const int lam = nz->half_bw, cl = band_chunk_used(nz, R);
+    const int tl = band_tile_len(R, nz->band_small, lam, nz->n_samp);
+    int64_t n_tiles;
+    const int64_t *pref = band_tiles(nz, R, &n_tiles);
+    const size_t sm = sizeof(T) * ((size_t)cl + (size_t)(tl + cl - 1) * R);
+    auto run = [&](auto k, int nt) {
+        k<<<(unsigned)n_tiles, nt, sm, ctx->stream>>>(pref, nz->n_int, nz->istart.as<int64_t>(),
+                                                      nz->fid.as<int32_t>(), nz->band.as<T>(),
+                                                      lam, cl, rows, z);
+    };
+    if constexpr (R == 1)
+        if (nz->band_small)  // short single streams: 64-thread blocks
+            return run(k_band_tiled<T, R, BAND_SMALL_NT, BAND_SMALL_OPT, Rows>, BAND_SMALL_NT);
+    run(k_band_tiled<T, R, BS, BT_OPT, Rows>, BS);
+}
+
+// z = N^-1 P x in one launch; false where that does not apply.  One column: all taps in
+// one LDS chunk.  More: the direct band runs by rows, two blocks' rows fit in a CU's LDS
+// and the halo is at most 2.5 tiles.
 static bool band_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs,
-                       const double *x, void *z) {
+                       const double *x, void *z, char *scratch) {
     const int lam = nz->half_bw;
     if (nz->method != MM_NOISE_DIRECT || p->n_obs == 0) return false;
+    if (nrhs == 1) {
+        if (band_chunk_used(nz, 1) < 2 * lam + 1) return false;  // several windows per tile
+        Scope sc(ctx->prof, ctx->stream, "Ninv_band");
+        const PMap m = p_map_dev(ctx, p, x, scratch);
+        auto go = [&](auto TT) {
+            using T = decltype(TT);
+            dispatch_src<T>(m, [&](auto src) {
+                band_tiled_launch<T, 1>(ctx, nz, PRows<T, decltype(src)>{src},
+                                        static_cast<T *>(z));
+            });
+        };
+        if (nz->prec == MM_F32) go(0.f);
+        else go(0.0);
+        MM_HIP(hipGetLastError());
+        return true;
+    }
     bool done = false;
     dispatch_r(nrhs, [&](auto RR) {
         constexpr int R = decltype(RR)::value;
@@ -1044,11 +1132,11 @@ static bool band_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, in
                     !band_by_rows(CB, lam, nz->n_samp))
                     return;
                 Scope sc(ctx->prof, ctx->stream, "Ninv_band");
-                const size_t li = (size_t)log2i(CB) * (nz->n_int + 1);
-                const int64_t n_tiles = nz->h_tile_pref[li + nz->n_int];
+                int64_t n_tiles;
+                const int64_t *pref = band_tiles(nz, CB, &n_tiles);
                 k_band_P<T, R, NC><<<(unsigned)((n_tiles * K + 7) / 8 * 8), BS, lds,
                                      ctx->stream>>>(
-                    nz->tile_pref.as<int64_t>() + li, nz->n_int, nz->istart.as<int64_t>(),
+                    pref, nz->n_int, nz->istart.as<int64_t>(),
                     nz->fid.as<int32_t>(), nz->band_full.as<T>(), lam, n_tiles,
                     p->j.as<int32_t>(),
                     NC > 1 ? static_cast<const typename Vec2<T>::type *>(p->w.ptr) : nullptr, x,
@@ -1073,35 +1161,13 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
     }
     Scope sc(ctx->prof, ctx->stream, "Ninv_band");
     const int lam = nz->half_bw;
-    const int tl = band_tile_len(nrhs, nz->band_small, lam, nz->n_samp);
-    // tile counts for every column count are built with the noise handle, so
-    // an apply never modifies it (handles may be shared across contexts)
-    const int li = log2i(nrhs);
-    const int64_t *pref = nz->tile_pref.as<int64_t>() + (int64_t)li * (nz->n_int + 1);
-    const unsigned n_tiles = (unsigned)nz->h_tile_pref[(size_t)li * (nz->n_int + 1) + nz->n_int];
-    const int cl =
-        nz->band_cl[li] > 0 ? nz->band_cl[li] : band_chunk(lam, nrhs, nz->prec, nz->band_small, nz->n_samp);
-    const size_t te = nz->prec == MM_F32 ? sizeof(float) : sizeof(double);
-    const size_t sm = te * ((size_t)cl + (size_t)(tl + cl - 1) * nrhs);
-    if (nrhs == 1 && nz->band_small) {  // short single streams: 64-thread blocks
-        if (nz->prec == MM_F32)
-            k_band_tiled<float, 1, BAND_SMALL_NT><<<n_tiles, BAND_SMALL_NT, sm, ctx->stream>>>(
-                pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(),
-                nz->band.as<float>(), lam, cl, static_cast<const float *>(y),
-                static_cast<float *>(z));
-        else
-            k_band_tiled<double, 1, BAND_SMALL_NT><<<n_tiles, BAND_SMALL_NT, sm, ctx->stream>>>(
-                pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(),
-                nz->band.as<double>(), lam, cl, static_cast<const double *>(y),
-                static_cast<double *>(z));
-        MM_HIP(hipGetLastError());
-        return;
-    }
     if (band_by_rows(nrhs, lam, nz->n_samp)) {
         dispatch_r(nrhs, [&](auto RR) {
             constexpr int R = decltype(RR)::value;
             if constexpr (R >= BC_MIN_R) {
-                const unsigned grid = (n_tiles + 7) / 8 * 8;
+                int64_t n_tiles;
+                const int64_t *pref = band_tiles(nz, R, &n_tiles);
+                const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
                 auto go = [&](auto TT) {
                     using T = decltype(TT);
                     k_band_cols<T, R><<<grid, BS, 0, ctx->stream>>>(
@@ -1118,14 +1184,13 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
     }
     dispatch_r(nrhs, [&](auto RR) {
         constexpr int R = decltype(RR)::value;
-        if (nz->prec == MM_F32)
-            k_band_tiled<float, R><<<n_tiles, BS, sm, ctx->stream>>>(
-                pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(), nz->band.as<float>(), lam,
-                cl, static_cast<const float *>(y), static_cast<float *>(z));
-        else
-            k_band_tiled<double, R><<<n_tiles, BS, sm, ctx->stream>>>(
-                pref, nz->n_int, nz->istart.as<int64_t>(), nz->fid.as<int32_t>(), nz->band.as<double>(),
-                lam, cl, static_cast<const double *>(y), static_cast<double *>(z));
+        auto go = [&](auto TT) {
+            using T = decltype(TT);
+            band_tiled_launch<T, R>(ctx, nz, TodRows<T>{static_cast<const T *>(y)},
+                                    static_cast<T *>(z));
+        };
+        if (nz->prec == MM_F32) go(0.f);
+        else go(0.0);
     });
     MM_HIP(hipGetLastError());
 }
@@ -1147,7 +1212,8 @@ void apply_A_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, int nrhs
         // the filter's first pass reads the copies while it writes tb
         z = polyfilter_apply_P_dev(ctx, p, nz, nrhs, x, ta, tb, scratch,
                                    in_tod ? static_cast<char *>(ta) : scratch);
-    } else if (!band_P_dev(ctx, p, nz, nrhs, x, tb)) {
+    } else if (!band_P_dev(ctx, p, nz, nrhs, x, tb,
+                           in_tod ? static_cast<char *>(ta) : scratch)) {
         // up to 16 columns, A's own TOD between P and the FFT is planar: the FFT then
         // reads runs of 16 bytes per lane, which saves more than P's shorter runs cost.
         // Interleaved and planar, us (FP64): 8.4M samples x 4 columns 491 and 477, x 8

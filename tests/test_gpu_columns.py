@@ -99,3 +99,31 @@ def test_A_band_in_one_pass(ctx, prec, R, lam, stokes):
     x = dev(rng.standard_normal(lp.n * R))
     parts = ctx.apply_PT(lp, ctx.noise_apply(nz, ctx.apply_P(lp, x, nrhs=R), nrhs=R), nrhs=R)
     assert torch.equal(ctx.apply_A(lp, nz, x, nrhs=R), parts)
+
+
+@pytest.mark.parametrize("stokes", ["IQU", "QU", "I"])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("big,lam", [(False, 0), (False, 1), (False, 32), (False, 300),
+                                     (True, 7), (True, 64), (True, 1700)])
+def test_A_band_one_column(ctx, big, lam, prec, stokes):
+    """One column: P x gathered as the band's window is staged, on short streams (tiles of
+    512) and long ones (2,048; and from map copies); the bits of the three launches."""
+    import torch
+    rng = np.random.default_rng(lam)
+    lens = [2 * lam + 1, 2 * lam + 2, 511 + 2 * lam, 512 + 2 * lam, 513 + 2 * lam, 5000]
+    if big:
+        lens += [2047 + 2 * lam, 2049 + 2 * lam, (1 << 22) + 3]
+    n, side = sum(lens), 13
+    u, v = np.arange(n) % side, np.arange(n) // side % side  # back and forth
+    pix = (v * side + np.where(np.arange(n) // side % 2 == 0, u, side - 1 - u)).astype(np.int32)
+    pix[rng.random(n) < 0.05] = -1
+    psi = None if stokes == "I" else dev(rng.uniform(0.0, np.pi, n))
+    lp = ctx.pointing(dev(pix), psi, side * side, 1, prec, stokes=stokes)
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    fid = rng.integers(0, 3, len(lens)).astype(np.int32)
+    nz = ctx.noise(istart, fid, rng.standard_normal((3, lam + 1)), lam, method=1, prec=prec)
+    x = dev(rng.standard_normal(lp.n))
+    for width in (0, side):
+        lp.set_grid(width)
+        parts = ctx.apply_PT(lp, ctx.noise_apply(nz, ctx.apply_P(lp, x)))
+        assert torch.equal(ctx.apply_A(lp, nz, x), parts)
