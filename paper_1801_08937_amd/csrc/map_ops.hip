@@ -845,19 +845,148 @@ __global__ void __launch_bounds__(64) k_coarse_apply(int k, int R, const double 
     c[i * R + r] = acc;
 }
 
+// out = M_BD (v - AZ c) + Z c of one column (Eq. m2l), with optional partial sums of
+// v . out, where each block forms c = E^-1 Z^T v itself from the partial sums of Z^T v
+// (g_part[b k + a], b < g_parts), which saves two launches.  A block takes M1_P pixels
+// at a time, its threads M1_Q groups of the k columns for each, so that a short map
+// spreads over the chip and few loads wait for each other; the groups are then added
+// in order.  Bound by latency: 12,288 unknowns, k = 32, 14.0 -> 8.8 us against one
+// thread per pixel on 48 blocks.
+constexpr int M1_P = 32, M1_Q = BS / M1_P;
+template <int NC>
+__global__ void __launch_bounds__(BS) k_m2l_one(const double *__restrict__ inv, int32_t n_obs,
+                                                int k, int64_t n, const double *__restrict__ Z,
+                                                const double *__restrict__ AZ,
+                                                const double *__restrict__ g_part, int g_parts,
+                                                const double *__restrict__ Einv,
+                                                const double *__restrict__ v,
+                                                double *__restrict__ out,
+                                                double *__restrict__ partial,
+                                                int64_t pix_per_block) {
+    __shared__ double gs[64], cs[4][64], sc[64], sm[M1_Q][2 * NC][M1_P];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // wave wv sums columns wv + 4t, eight at a time with their loads in flight together
+    for (int a0 = wv; a0 < k; a0 += 4 * 8) {
+        double s8[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s8[t] = 0;
+        for (int b = lane; b < g_parts; b += 64) {
+            double x8[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int a = a0 + 4 * t;
+                x8[t] = g_part[(int64_t)b * k + (a < k ? a : k - 1)];
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t) s8[t] += x8[t];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            double s = s8[t];
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+            const int a = a0 + 4 * t;
+            if (lane == 0 && a < k) gs[a] = s;
+        }
+    }
+    __syncthreads();
+    {  // c_i = sum_j (E^-1)_{ij} g_j, a quarter of the j per wave
+        const int i = lane < k ? lane : 0;
+        double acc = 0, e[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int j = wv * 16 + q;
+            e[q] = Einv[(int64_t)(j < k ? j : 0) * k + i];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (wv * 16 + q < k) acc = __builtin_fma(e[q], gs[wv * 16 + q], acc);
+        cs[wv][lane] = acc;
+    }
+    __syncthreads();
+    if (threadIdx.x < k)
+        sc[lane] = ((cs[0][lane] + cs[1][lane]) + cs[2][lane]) + cs[3][lane];
+    __syncthreads();
+    const int pl = threadIdx.x % M1_P, qg = threadIdx.x / M1_P;
+    const int64_t p0 = (int64_t)blockIdx.x * pix_per_block;
+    const int64_t p1 = p0 + pix_per_block < n_obs ? p0 + pix_per_block : n_obs;
+    double dot = 0;
+    for (int64_t pb = p0; pb < p1; pb += M1_P) {
+        const int64_t j = pb + pl < p1 ? pb + pl : p1 - 1;
+        double sz[NC] = {}, sa[NC] = {};
+        for (int q0 = qg; q0 < k; q0 += 4 * M1_Q) {
+            double z[4][NC], az[4][NC];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int q = q0 + t * M1_Q < k ? q0 + t * M1_Q : k - 1;
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    z[t][a] = Z[(int64_t)q * n + NC * j + a];
+                    az[t][a] = AZ[(int64_t)q * n + NC * j + a];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int q = q0 + t * M1_Q;
+                if (q >= k) break;
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    sz[a] += z[t][a] * sc[q];
+                    sa[a] += az[t][a] * sc[q];
+                }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            sm[qg][a][pl] = sz[a];
+            sm[qg][NC + a][pl] = sa[a];
+        }
+        __syncthreads();
+        if (qg == 0 && pb + pl < p1) {
+            double u[NC], vv[NC], o[NC];
+#pragma unroll
+            for (int a = 0; a < NC; ++a) {
+                double s0 = 0, s1 = 0;
+#pragma unroll
+                for (int g = 0; g < M1_Q; ++g) {
+                    s0 += sm[g][a][pl];
+                    s1 += sm[g][NC + a][pl];
+                }
+                sz[a] = s0;
+                vv[a] = v[NC * j + a];
+                u[a] = vv[a] - s1;
+            }
+            const double *m = inv + (NC * (NC + 1) / 2) * j;
+            if constexpr (NC == 3) {
+                o[0] = m[0] * u[0] + m[1] * u[1] + m[2] * u[2];
+                o[1] = m[1] * u[0] + m[3] * u[1] + m[4] * u[2];
+                o[2] = m[2] * u[0] + m[4] * u[1] + m[5] * u[2];
+            } else {
+                sym_mul<NC>(m, u, o);
+            }
+#pragma unroll
+            for (int a = 0; a < NC; ++a) {
+                const double oe = o[a] + sz[a];
+                out[NC * j + a] = oe;
+                dot += vv[a] * oe;
+            }
+        }
+        __syncthreads();
+    }
+    if (partial && threadIdx.x < 64) {  // M1_P threads hold a share
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) dot += __shfl_xor(dot, m);
+        if (threadIdx.x == 0) partial[blockIdx.x] = dot;
+    }
+}
+
 // out = M_BD (v - AZ c) + Z c per pixel and column (Eq. m2l), with optional
 // partial sums of dot_with . out.  Z, AZ are column-major n x k, c is k x R.
-// One column with g_part given: each block first forms c = E^-1 Z^T v itself
-// from the partial sums of Z^T v (g_part[b k + a], b < g_parts), summing each
-// column and then forming E^-1 g exactly as k_dot_final and k_coarse_apply
-// do, so every block holds the same c, bitwise that of those two launches.
 template <int R, int NC>
 __global__ void __launch_bounds__(BS) k_m2l_final(const double *__restrict__ inv, int32_t n_obs,
                                                   int k, int64_t n, const double *__restrict__ Z,
                                                   const double *__restrict__ AZ,
                                                   const double *__restrict__ cc,
-                                                  const double *__restrict__ g_part, int g_parts,
-                                                  const double *__restrict__ Einv,
                                                   const double *__restrict__ v,
                                                   double *__restrict__ out,
                                                   const double *__restrict__ dot_with,
@@ -865,52 +994,7 @@ __global__ void __launch_bounds__(BS) k_m2l_final(const double *__restrict__ inv
                                                   int64_t pix_per_block) {
     constexpr int NG = BS / R;
     __shared__ double sc[64 * 64];
-    if (R == 1 && g_part) {
-        __shared__ double gs[64];
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        // wave wv sums columns wv + 4t, eight at a time with their loads in
-        // flight together; each column in the order of wave_sum_parts
-        for (int a0 = wv; a0 < k; a0 += 4 * 8) {
-            double s8[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) s8[t] = 0;
-            for (int b = lane; b < g_parts; b += 64) {
-                double x8[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int a = a0 + 4 * t;
-                    x8[t] = g_part[(int64_t)b * k + (a < k ? a : k - 1)];
-                }
-#pragma unroll
-                for (int t = 0; t < 8; ++t) s8[t] += x8[t];
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                double sm = s8[t];
-#pragma unroll
-                for (int m = 32; m >= 1; m >>= 1) sm += __shfl_xor(sm, m);
-                const int a = a0 + 4 * t;
-                if (lane == 0 && a < k) gs[a] = sm;
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < k) {  // c_i = sum_j (E^-1)_{ij} g_j, in the order of j
-            const int i = threadIdx.x;
-            double acc = 0.0;
-            int j = 0;
-            for (; j + 16 <= k; j += 16) {
-                double e[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) e[q] = Einv[(int64_t)(j + q) * k + i];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) acc = __builtin_fma(e[q], gs[j + q], acc);
-            }
-            for (; j < k; ++j) acc = __builtin_fma(Einv[(int64_t)j * k + i], gs[j], acc);
-            sc[i] = acc;
-        }
-    } else {
-        for (int e = threadIdx.x; e < k * R; e += BS) sc[e] = cc[e];
-    }
+    for (int e = threadIdx.x; e < k * R; e += BS) sc[e] = cc[e];
     __syncthreads();
     const int r = threadIdx.x % R, rg = threadIdx.x / R;
     const int64_t p0 = (int64_t)blockIdx.x * pix_per_block;
@@ -1225,10 +1309,10 @@ int grid_for(int64_t n, int max_blocks = 4096) {
 
 int reduction_parts(int64_t n_rows, int nrhs) {
     const int64_t m = n_rows * nrhs;
-    // up to 65,536 elements a block per 256 (one per thread), so that these
-    // latency-bound launches spread over more CUs; beyond, a block per 1,024,
-    // at most 512 blocks
-    int64_t p = m <= 65536 ? (m + 255) / 256 : (m + 1023) / 1024;
+    // up to 49,152 elements a block per 96 (32 IQU pixels), so that these
+    // latency-bound launches spread over more CUs; beyond, a block per 1,024, at
+    // most 512 blocks
+    int64_t p = m <= 49152 ? (m + 95) / 96 : (m + 1023) / 1024;
     if (p > 512) p = 512;
     return (int)(p < 1 ? 1 : p);
 }
@@ -1547,31 +1631,36 @@ void m2l_apply_dev(mm_ctx *ctx, const mm_precond *M, int nrhs, const double *v, 
     const int k = M->k;
     ws_alloc(ctx, ctx->scal, sizeof(double) * 64 * 64 + 4096);
     double *c = ctx->scal.as<double>();
-    // one column: the Z^T v partial sums go straight to the final kernel,
-    // whose blocks each form c = E^-1 Z^T v (two launches fewer)
-    const double *g_part = nullptr;
-    int g_parts = 0;
-    if (nrhs == 1) {
-        Scope sg(ctx->prof, ctx->stream, "gemv");
-        g_parts = gemv_t_parts(ctx, n, k, M->Z.as<double>(), v);
-        g_part = ctx->red.as<double>();
-    } else {
-        m2l_coef_dev(ctx, M, nrhs, v, c);
-    }
     const int parts = partial ? n_part : reduction_parts(n, nrhs);
     const int64_t ppb = rows_per(M->n_obs, parts);
-    dispatch_r(nrhs, [&](auto RR) {
-        constexpr int R = decltype(RR)::value;
-        auto go = [&](auto NN) {
-            constexpr int NC = decltype(NN)::value;
-            k_m2l_final<R, NC><<<parts, BS, 0, ctx->stream>>>(
-                M->inv.as<double>(), M->n_obs, k, n, M->Z.as<double>(), M->AZ.as<double>(), c,
-                g_part, g_parts, M->Einv.as<double>(), v, out, partial ? v : nullptr, partial,
-                ppb);
-        };
+    auto dispatch_nc = [&](auto go) {
         if (M->nc == 1) go(std::integral_constant<int, 1>());
         else if (M->nc == 2) go(std::integral_constant<int, 2>());
         else go(std::integral_constant<int, 3>());
+    };
+    if (nrhs == 1) {
+        int g_parts;
+        {
+            Scope sg(ctx->prof, ctx->stream, "gemv");
+            g_parts = gemv_t_parts(ctx, n, k, M->Z.as<double>(), v);
+        }
+        dispatch_nc([&](auto NN) {
+            k_m2l_one<decltype(NN)::value><<<parts, BS, 0, ctx->stream>>>(
+                M->inv.as<double>(), M->n_obs, k, n, M->Z.as<double>(), M->AZ.as<double>(),
+                ctx->red.as<double>(), g_parts, M->Einv.as<double>(), v, out, partial, ppb);
+        });
+        MM_HIP(hipGetLastError());
+        return;
+    }
+    m2l_coef_dev(ctx, M, nrhs, v, c);
+    dispatch_r(nrhs, [&](auto RR) {
+        constexpr int R = decltype(RR)::value;
+        if constexpr (R > 1)
+            dispatch_nc([&](auto NN) {
+                k_m2l_final<R, decltype(NN)::value><<<parts, BS, 0, ctx->stream>>>(
+                    M->inv.as<double>(), M->n_obs, k, n, M->Z.as<double>(), M->AZ.as<double>(),
+                    c, v, out, partial ? v : nullptr, partial, ppb);
+            });
     });
     MM_HIP(hipGetLastError());
 }
