@@ -282,7 +282,8 @@ struct PcgWork {
         }
         template <typename T> T *as() const { return static_cast<T *>(ptr); }
     };
-    Vec r, z, pv, q, part, part2, sc;  // part2: the ||r||^2 partials of an iteration
+    // part2: the ||r||^2 partials of an iteration; part3: the r.z ones next to them
+    Vec r, z, pv, q, part, part2, part3, sc;
     PcgDev sd{};
     bool flexible = false;  // Polak-Ribiere beta (sd.rzo holds r'.z_old)
     void alloc(int64_t n_, int R_, Scratch *tmp = nullptr) {
@@ -296,6 +297,7 @@ struct PcgWork {
         q.alloc(vb, tmp);
         part.alloc(sizeof(double) * n_part * R, tmp);
         part2.alloc(sizeof(double) * n_part * R, tmp);
+        part3.alloc(sizeof(double) * n_part * R, tmp);
         sc.alloc(sizeof(double) * 8 * 64 + sizeof(int) * 3 * 64, tmp);
         double *sb = sc.as<double>();
         sd.rho = sb; sd.pq = sb + 64; sd.alpha = sb + 128; sd.beta = sb + 192;
@@ -351,6 +353,14 @@ void pcg_iteration(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, const 
     apply_A_impl(ctx, p, nz, R, w.pv.as<double>(), w.q.as<double>());
     dot_partial_cols(ctx, w.n, R, w.pv.as<double>(), w.q.as<double>(), w.part.as<double>(),
                      w.n_part);
+    if (M && M->kind == 0 && !w.flexible) {
+        pcg_update_xrz(ctx, M, R, w.sd, w.part.as<double>(), w.pv.as<double>(), w.q.as<double>(),
+                       x, w.r.as<double>(), w.z.as<double>(), w.part2.as<double>(),
+                       w.part3.as<double>(), w.n_part);
+        pcg_after_rnrz(ctx, R, w.sd, w.part2.as<double>(), w.part3.as<double>(), w.n_part);
+        pcg_update_p(ctx, w.n, R, w.sd, w.z.as<double>(), w.pv.as<double>());
+        return;
+    }
     pcg_update_xr(ctx, w.n, R, w.sd, w.part.as<double>(), w.pv.as<double>(), w.q.as<double>(), x,
                   w.r.as<double>(), w.part2.as<double>(), w.n_part);
     if (w.flexible) {  // r'.z_old before z is overwritten

@@ -409,6 +409,10 @@ void axpby_cols(mm_ctx *ctx, int64_t n, int nrhs, const double *b, const double 
 void pcg_update_xr(mm_ctx *ctx, int64_t n, int nrhs, PcgDev s, const double *pq_part,
                    const double *p, const double *q, double *x, double *r, double *partial,
                    int n_part);
+// The same with z = M r of an M_BD and its r.z partials (into a buffer other than pq_part).
+void pcg_update_xrz(mm_ctx *ctx, const mm_precond *M, int nrhs, PcgDev s, const double *pq_part,
+                    const double *p, const double *q, double *x, double *r, double *z,
+                    double *part_rn, double *part_rz, int n_part);
 // breakdown flag, iteration count and convergence from ||r||^2, then rho', beta
 void pcg_after_rnrz(mm_ctx *ctx, int nrhs, PcgDev s, const double *part_rn,
                     const double *part_rz, int n_part);
