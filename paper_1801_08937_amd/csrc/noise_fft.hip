@@ -176,14 +176,15 @@ static void fft_tables(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, int N) {
     double *H = sc.get<double>((int64_t)nz->n_filters * (NC + 1));
     MM_HIP(hipMemcpyAsync(dq, qtab.data(), sizeof(double) * qtab.size(), hipMemcpyHostToDevice,
                           s));
-    double2 *S = sc.get<double2>((int64_t)nz->n_filters * N);
-    const unsigned nf = (unsigned)nz->n_filters;
-    for (unsigned f0 = 0; f0 < nf; f0 += 32768) {  // grid.z is 16 bits
-        const unsigned cnt = std::min(nf - f0, 32768u);
+    // 256 filters at a time: their S is 32 to 128 MiB, which the next ones use again
+    const unsigned nf = (unsigned)nz->n_filters, step = std::min(nf, 256u);
+    double2 *S = sc.get<double2>((int64_t)step * N);
+    for (unsigned f0 = 0; f0 < nf; f0 += step) {
+        const unsigned cnt = std::min(nf - f0, step);
         k_spec_sub<<<dim3((N / SP_B + 255) / 256, SP_B, cnt), 256, 0, s>>>(
-            nz->band64.as<double>() + (int64_t)f0 * (lam + 1), lam, N, dq, S + (int64_t)f0 * N);
+            nz->band64.as<double>() + (int64_t)f0 * (lam + 1), lam, N, dq, S);
         k_spec_sum<<<dim3((NC + 1 + 255) / 256, cnt), 256, 0, s>>>(
-            N, dq, S + (int64_t)f0 * N, H + (int64_t)f0 * (NC + 1));
+            N, dq, S, H + (int64_t)f0 * (NC + 1));
     }
     MM_HIP(hipGetLastError());
     noise_fft_tables_dev(ctx, nz, tb, H, dq);

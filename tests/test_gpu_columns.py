@@ -104,7 +104,8 @@ def test_A_band_in_one_pass(ctx, prec, R, lam, stokes):
 @pytest.mark.parametrize("stokes", ["IQU", "QU", "I"])
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("big,lam", [(False, 0), (False, 1), (False, 32), (False, 300),
-                                     (True, 7), (True, 64), (True, 1700)])
+                                     (False, 1023), (False, 1024), (True, 7), (True, 64),
+                                     (True, 1700)])
 def test_A_band_one_column(ctx, big, lam, prec, stokes):
     """One column: P x gathered as the band's window is staged, on short streams (tiles of
     512) and long ones (2,048; and from map copies); the bits of the three launches."""

@@ -112,3 +112,17 @@ def test_fft_masked_rhs(ctx, n_fft, lam, prec, R):
         with pytest.raises(mm.MapmakerError, match="NONFINITE"):
             ctx.rhs(lp, nz, dev(dn2).reshape(-1), out, nrhs=R)
         assert bool((out == 7.0).all())
+
+
+def test_fft_many_filters(ctx):
+    """More filters than the 256 whose spectra are formed at a time, one per interval."""
+    rng = np.random.default_rng(4)
+    lam, ni = 40, 521
+    lens = rng.integers(2 * lam + 1, 200, ni)
+    istart = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    band = rng.standard_normal((ni, lam + 1)) / np.sqrt(2 * lam + 1)
+    fid = rng.permutation(ni).astype(np.int32)
+    nz = ctx.noise(istart, fid, band, lam, method=2, prec=0)
+    y = rng.standard_normal(istart[-1])
+    ref = O.noise_apply_direct(O.noise_build(istart, fid, band, lam), y)
+    assert maxrel(host(ctx.noise_apply(nz, dev(y))), ref) <= 1e-12
