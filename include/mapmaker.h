@@ -166,7 +166,8 @@ mm_status mm_pair_sum_diff(mm_ctx *ctx, int64_t n, mm_precision prec, const void
  * several, P^T sums each pixel's samples in another fixed order: bitwise
  * repeatable, equal to the unhinted result to rounding.  width = 0
  * restores ascending order and one map copy.
- * Errors: MM_E_INVALID (negative width). */
+ * Errors: MM_E_INVALID (negative width); MM_E_OOM, which leaves the pointing
+ * usable, without a grid and with P^T one wave per pixel. */
 mm_status mm_pointing_set_grid(mm_ctx *ctx, mm_pointing *p, int32_t width);
 /* Map copies the single-column P gathers from: 0 without a grid (one copy
  * in compact id order), else 1 to 4.  [host] output. */

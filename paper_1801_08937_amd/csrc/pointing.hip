@@ -445,10 +445,11 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch
                              const int32_t **dir_cnt) {
     hipStream_t s = ctx->stream;
     const int32_t n_obs = p->n_obs;
+    // the old slots go with the count: P gathers from copies where p_j is there
     p->p_copies = 0;
+    p->p_j.release();
     if (width <= 0 || n_obs == 0) {
         p->p_slot.release();
-        p->p_j.release();
         p->p_chunk_grp.release();
         return;
     }
@@ -496,7 +497,6 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch
         if (sizeof(double) * (size_t)(p->n() * G) > tod) G = 1;
         if (sizeof(double) * (size_t)p->n() > tod) {
             p->p_slot.release();
-            p->p_j.release();
             p->p_chunk_grp.release();
             return;
         }
@@ -673,20 +673,31 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
     p->sl_D = D;
 }
 
+// A failure leaves the pointing without the layouts (as with no grid and too few waves
+// for the sliced P^T), so that no apply reads a half-written one.
 void pointing_layout_device(mm_ctx *ctx, mm_pointing *p, int32_t width) {
-    Scratch sc(ctx);
-    if (width <= 0) {
-        p->seg_order.release();
-    } else if (p->n_obs > 0) {
-        p->seg_order.alloc(sizeof(int32_t) * p->n_obs);
-        pointing_tile_order(ctx, p, width, 32, sc, p->seg_order.as<int32_t>());
+    try {
+        Scratch sc(ctx);
+        if (width <= 0) {
+            p->seg_order.release();
+        } else if (p->n_obs > 0) {
+            p->seg_order.alloc(sizeof(int32_t) * p->n_obs);
+            pointing_tile_order(ctx, p, width, 32, sc, p->seg_order.as<int32_t>());
+        }
+        p->grid_width = width;
+        // P's map copies first: the sliced P^T is cut by the same scan directions
+        const int32_t *dir_cnt = nullptr;
+        pointing_p_slots_device(ctx, p, width, sc, &dir_cnt);
+        pointing_slices_device(ctx, p, width, sc, dir_cnt);
+        MM_HIP(hipStreamSynchronize(ctx->stream));
+    } catch (...) {
+        p->grid_width = p->p_copies = p->sl_G = p->sl_S = 0;
+        p->sl_D = 1;
+        for (DBuf *b : {&p->seg_order, &p->p_slot, &p->p_j, &p->p_chunk_grp, &p->sl_pix,
+                        &p->sl_base, &p->sl_perm, &p->sl_w})
+            b->release();
+        throw;
     }
-    p->grid_width = width;
-    // P's map copies first: the sliced P^T is cut by the same scan directions
-    const int32_t *dir_cnt = nullptr;
-    pointing_p_slots_device(ctx, p, width, sc, &dir_cnt);
-    pointing_slices_device(ctx, p, width, sc, dir_cnt);
-    MM_HIP(hipStreamSynchronize(ctx->stream));
 }
 
 void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, const double *psi,

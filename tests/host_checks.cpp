@@ -1,0 +1,106 @@
+// Checks of the library's host code on a machine without a GPU, where every device
+// allocation fails: one per argument, exit status 0 = passed.  Linked against
+// libmapmaker.so by test_host_checks.py.
+#include <cstdio>
+#include <cstring>
+#include <unistd.h>
+
+#include "mm_internal.h"
+
+namespace mm {
+void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch &sc,
+                             const int32_t **dir_cnt);
+}
+
+namespace {
+
+int failures = 0;
+#define EXPECT(c)                                                 \
+    do {                                                          \
+        if (!(c)) {                                               \
+            std::printf("line %d: %s\n", __LINE__, #c);           \
+            ++failures;                                           \
+        }                                                         \
+    } while (0)
+
+// A buffer that a working device would have given (never dereferenced here).
+void pretend(mm::DBuf &b, size_t bytes) {
+    b.ptr = reinterpret_cast<void *>((uintptr_t)1 << 20);
+    b.bytes = bytes;
+}
+
+// A pointing with a grid of three map copies, a tile order and a sliced P^T.
+void gridded(mm_pointing &p) {
+    p.n_samp = (int64_t)1 << 23;
+    p.n_pix_total = p.n_obs = 16384;
+    p.n_valid = p.n_samp;
+    p.nc = 3;
+    p.grid_width = 128;
+    p.p_copies = 3;
+    pretend(p.j, 4 * p.n_samp);
+    pretend(p.p_j, 4 * p.n_samp);
+    pretend(p.p_slot, 4 * 3 * p.n_obs);
+    pretend(p.p_chunk_grp, 4 * (p.n_samp >> 12));
+    pretend(p.seg_order, 4 * p.n_obs);
+    p.sl_G = 256 * 3;
+    p.sl_S = 5;
+    p.sl_D = 3;
+    pretend(p.sl_pix, 4 * 64 * p.sl_G);
+}
+
+// Set-up of a new grid fails at its first allocation, or at the first one inside the
+// map copies: what the applies look at afterwards is whole or absent, never a new
+// count with old slots or an order that was not written.
+void regrid() {
+    {
+        mm_ctx ctx;
+        mm_pointing p;
+        gridded(p);
+        bool threw = false;
+        try {
+            mm::pointing_layout_device(&ctx, &p, 64);
+        } catch (const mm::Error &e) {
+            threw = e.code == MM_E_OOM;
+        }
+        EXPECT(threw);
+        EXPECT(p.p_j.ptr == nullptr && p.p_copies == 0);
+        EXPECT(p.seg_order.ptr == nullptr && p.grid_width == 0);
+        EXPECT(p.sl_G == 0 && p.sl_S == 0 && p.sl_D == 1);
+        EXPECT(mm::apply_PT_scratch_bytes(&p, 1) == 0);
+    }
+    {
+        mm_ctx ctx;
+        mm_pointing p;
+        gridded(p);
+        bool threw = false;
+        try {
+            mm::Scratch sc(&ctx);
+            const int32_t *cnt = nullptr;
+            mm::pointing_p_slots_device(&ctx, &p, 64, sc, &cnt);
+        } catch (const mm::Error &e) {
+            threw = e.code == MM_E_OOM;
+        }
+        EXPECT(threw);
+        EXPECT(p.p_copies == 0 && p.p_j.ptr == nullptr);
+        // one copy at the compact ids
+        EXPECT(mm::apply_P_scratch_bytes(&p, 1) == 32 * (size_t)p.n_obs);
+    }
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    int n = 0;
+    if (hipGetDeviceCount(&n) == hipSuccess && n > 0) {
+        std::printf("a GPU is here\n");
+        return 77;
+    }
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!std::strcmp(what, "regrid")) regrid();
+    else {
+        std::printf("no check named '%s'\n", what);
+        return 2;
+    }
+    std::fflush(stdout);
+    _exit(failures ? 1 : 0);
+}
