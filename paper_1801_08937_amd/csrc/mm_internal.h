@@ -327,6 +327,17 @@ size_t apply_PT_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t noise_scratch_bytes(const mm_noise *nz, int nrhs);
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
                  char *scratch = nullptr, bool planar = false);
+// Consecutive samples of a wave of the P of several columns, a multiple of step (what
+// it takes at a time): step, or what `blocks` blocks of four waves make (blocks > 0);
+// more where the launch would pass 2^22 blocks, as one of 2^32 threads is refused.
+inline int64_t p_wave_samples(int64_t n, int step, int64_t blocks) {
+    if (blocks <= 0 || blocks > (1 << 22)) {
+        if ((n + 4 * step - 1) / (4 * step) <= (1 << 22)) return step;
+        blocks = 1 << 22;
+    }
+    const int64_t per = (n + 4 * blocks - 1) / (4 * blocks);
+    return (per + step - 1) / step * step;
+}
 void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, double *x,
                   char *scratch = nullptr);
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);

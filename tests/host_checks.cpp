@@ -87,6 +87,23 @@ void regrid() {
     }
 }
 
+// The P of 2 to 64 columns: every sample has a wave and the launch stays below 2^32
+// threads, up to the most samples a pointing takes.
+void p_launch() {
+    for (int R = 2; R <= 64; R *= 2)
+        for (int64_t n : {(int64_t)1, (int64_t)1000, (int64_t)1 << 28, ((int64_t)1 << 28) + 1,
+                          ((int64_t)1 << 31) - 1})
+            for (int64_t blocks : {0, 512, 8192}) {
+                const int step = 256 / R;
+                const int64_t per = mm::p_wave_samples(n, step, blocks);
+                const int64_t grid = (n + 4 * per - 1) / (4 * per);
+                EXPECT(per >= step && per % step == 0);
+                EXPECT(grid * 4 * per >= n && grid * 256 < (int64_t)1 << 32);
+                if (blocks > 0) EXPECT(grid <= blocks);
+                else if (n * R < (int64_t)1 << 32) EXPECT(per == step);
+            }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -97,6 +114,7 @@ int main(int argc, char **argv) {
     }
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "regrid")) regrid();
+    else if (!std::strcmp(what, "p_launch")) p_launch();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;
