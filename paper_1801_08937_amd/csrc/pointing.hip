@@ -195,33 +195,34 @@ __global__ void __launch_bounds__(BS) k_pixel_dirs(const int32_t *__restrict__ o
                                                    int G, int32_t n, int32_t *__restrict__ cnt,
                                                    int32_t *__restrict__ first) {
     const int lane = threadIdx.x & 63;
-    const int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
-    if (c >= n_obs) return;
-    const int32_t a = off[c], b = off[c + 1];
-    int32_t num[MAX_COPIES], fst[MAX_COPIES];
-#pragma unroll
-    for (int g = 0; g < MAX_COPIES; ++g) {
-        num[g] = 0;
-        fst[g] = n;
-    }
-    for (int32_t i = a; i < b; i += 64) {
-        const bool in = i + lane < b;
-        const int32_t t = in ? perm[i + lane] : 0;
-        const int q = in ? grp[t / DIR_CHUNK] : -1;
+    const int64_t nw = ((int64_t)gridDim.x * BS) >> 6;
+    for (int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6; c < n_obs; c += nw) {
+        const int64_t a = off[c], b = off[c + 1];
+        int32_t num[MAX_COPIES], fst[MAX_COPIES];
 #pragma unroll
         for (int g = 0; g < MAX_COPIES; ++g) {
-            const unsigned long long m = __ballot(q == g);
-            if (m != 0 && fst[g] == n) fst[g] = __shfl(t, __ffsll(m) - 1);
-            num[g] += __popcll(m);
+            num[g] = 0;
+            fst[g] = n;
         }
-    }
-    if (lane != 0) return;
+        for (int64_t i = a; i < b; i += 64) {
+            const bool in = i + lane < b;
+            const int32_t t = in ? perm[i + lane] : 0;
+            const int q = in ? grp[t / DIR_CHUNK] : -1;
 #pragma unroll
-    for (int g = 0; g < MAX_COPIES; ++g)
-        if (g < G) {
-            cnt[(int64_t)g * n_obs + c] = num[g];
-            first[(int64_t)g * n_obs + c] = fst[g];
+            for (int g = 0; g < MAX_COPIES; ++g) {
+                const unsigned long long m = __ballot(q == g);
+                if (m != 0 && fst[g] == n) fst[g] = __shfl(t, __ffsll(m) - 1);
+                num[g] += __popcll(m);
+            }
         }
+        if (lane != 0) continue;
+#pragma unroll
+        for (int g = 0; g < MAX_COPIES; ++g)
+            if (g < G) {
+                cnt[(int64_t)g * n_obs + c] = num[g];
+                first[(int64_t)g * n_obs + c] = fst[g];
+            }
+    }
 }
 
 // The pixel-sorted samples (and weights) regrouped by (direction, pixel), time order
@@ -236,25 +237,26 @@ __global__ void __launch_bounds__(BS) k_dir_scatter(const int32_t *__restrict__ 
                                                     int32_t *__restrict__ perm2,
                                                     V *__restrict__ w2) {
     const int lane = threadIdx.x & 63;
-    const int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6;
-    if (c >= n_obs) return;
-    const int32_t a = off[c], b = off[c + 1];
-    int32_t at[MAX_COPIES];
+    const int64_t nw = ((int64_t)gridDim.x * BS) >> 6;
+    for (int64_t c = ((int64_t)blockIdx.x * BS + threadIdx.x) >> 6; c < n_obs; c += nw) {
+        const int64_t a = off[c], b = off[c + 1];
+        int32_t at[MAX_COPIES];
 #pragma unroll
-    for (int g = 0; g < MAX_COPIES; ++g) at[g] = g < G ? off2[(int64_t)g * n_obs + c] : 0;
-    for (int32_t i = a; i < b; i += 64) {
-        const bool in = i + lane < b;
-        const int32_t t = in ? perm[i + lane] : 0;
-        const int q = in ? grp[t / DIR_CHUNK] : -1;
+        for (int g = 0; g < MAX_COPIES; ++g) at[g] = g < G ? off2[(int64_t)g * n_obs + c] : 0;
+        for (int64_t i = a; i < b; i += 64) {
+            const bool in = i + lane < b;
+            const int32_t t = in ? perm[i + lane] : 0;
+            const int q = in ? grp[t / DIR_CHUNK] : -1;
 #pragma unroll
-        for (int g = 0; g < MAX_COPIES; ++g) {
-            const unsigned long long m = __ballot(q == g);
-            if (q == g) {
-                const int32_t d = at[g] + __popcll(m & ((1ull << lane) - 1));
-                perm2[d] = t;
-                if (w) w2[d] = w[i + lane];
+            for (int g = 0; g < MAX_COPIES; ++g) {
+                const unsigned long long m = __ballot(q == g);
+                if (q == g) {
+                    const int32_t d = at[g] + __popcll(m & ((1ull << lane) - 1));
+                    perm2[d] = t;
+                    if (w) w2[d] = w[i + lane];
+                }
+                at[g] += __popcll(m);
             }
-            at[g] += __popcll(m);
         }
     }
 }
@@ -405,6 +407,12 @@ int grid_for(int64_t n, int max_blocks = 8192) {
     return (int)(g < 1 ? 1 : g);
 }
 
+// Blocks for a wave per pixel; the kernels go round where a launch of that many threads
+// (2^26 pixels) would be refused.
+unsigned pixel_waves_grid(int32_t n_obs) {
+    return (unsigned)std::min<int64_t>(((int64_t)n_obs + 3) / 4, (int64_t)1 << 22);
+}
+
 // bits(x): the smallest b with x < 2^b.
 unsigned bits(uint64_t x) {
     unsigned b = 1;
@@ -416,6 +424,7 @@ unsigned bits(uint64_t x) {
 template <typename K, typename V>
 void sort_pairs(mm_ctx *ctx, Scratch &tmp, const K *k, K *ko, const V *v, V *vo, int64_t n,
                 unsigned end_bit) {
+    MM_HIP(hipGetLastError());  // of the launches before: rocPRIM would clear it
     size_t tb = 0;
     MM_HIP(rocprim::radix_sort_pairs(nullptr, tb, k, ko, v, vo, (size_t)n, 0u, end_bit,
                                      ctx->stream));
@@ -424,6 +433,7 @@ void sort_pairs(mm_ctx *ctx, Scratch &tmp, const K *k, K *ko, const V *v, V *vo,
 }
 template <typename T>
 void exclusive_sum(mm_ctx *ctx, Scratch &tmp, const T *in, T *out, int64_t n) {
+    MM_HIP(hipGetLastError());
     size_t tb = 0;
     MM_HIP(rocprim::exclusive_scan(nullptr, tb, in, out, (T)0, (size_t)n, rocprim::plus<T>(),
                                    ctx->stream));
@@ -526,7 +536,7 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch
     const int64_t total = (int64_t)G * n_obs;
     int32_t *first = sc.get<int32_t>(total), *dcnt = sc.get<int32_t>(total + 1);
     MM_HIP(hipMemsetAsync(dcnt + total, 0, sizeof(int32_t), s));
-    k_pixel_dirs<<<(unsigned)((n_obs + 3) / 4), BS, 0, s>>>(p->off.as<int32_t>(),
+    k_pixel_dirs<<<pixel_waves_grid(n_obs), BS, 0, s>>>(p->off.as<int32_t>(),
                                                            p->perm.as<int32_t>(),
                                                            dgrp.as<int32_t>(), n_obs, G,
                                                            (int32_t)n, dcnt, first);
@@ -618,9 +628,10 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
         exclusive_sum(ctx, sc, dir_cnt, off2, nvp + 1);
         const bool w32 = f32 && p->nc > 1;
         float2 *ws2 = w32 ? sc.get<float2>(nv) : nullptr;
-        k_dir_scatter<float2><<<(unsigned)((n_obs + 3) / 4), BS, 0, s>>>(
+        k_dir_scatter<float2><<<pixel_waves_grid(n_obs), BS, 0, s>>>(
             p->off.as<int32_t>(), perm_u, w32 ? p->ws.as<float2>() : nullptr,
             p->p_chunk_grp.as<int32_t>(), n_obs, D, off2, perm2, ws2);
+        MM_HIP(hipGetLastError());
         perm_u = perm2;
         off_u = off2;
         ws_u = ws2;
