@@ -314,6 +314,19 @@ namespace mm {
 // pointing.hip
 void pointing_build_device(mm_ctx *ctx, mm_pointing *p, const int32_t *pix, const double *psi,
                            int32_t min_hits);
+// bits(x): the smallest b with x < 2^b.
+inline unsigned bits(uint64_t x) {
+    unsigned b = 1;
+    while (b < 64 && (x >> b) != 0) ++b;
+    return b;
+}
+// Bits of the tile keys (tile number << 24, then the place in the tile) of a row-major
+// grid of n_pix pixels.
+inline unsigned tile_key_bits(int32_t n_pix, int32_t width, int32_t tile) {
+    const int64_t tiles_x = ((int64_t)width + tile - 1) / tile;
+    const int64_t tiles_y = (n_pix - 1) / width / tile + 1;
+    return 24 + bits((uint64_t)(tiles_x * tiles_y));
+}
 // (Re)build everything that depends on the grid hint (width 0 = none): the visiting
 // order of the one-wave-per-pixel P^T, P's map copies and the sliced P^T layout.
 void pointing_layout_device(mm_ctx *ctx, mm_pointing *p, int32_t width);

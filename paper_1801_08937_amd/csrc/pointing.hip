@@ -131,7 +131,7 @@ __global__ void k_tile_keys(const int32_t *__restrict__ obs_pix, int32_t n_obs, 
     if (c >= n_obs) return;
     const int64_t g = obs_pix[c];
     const int64_t y = g / width, x = g % width;
-    const int64_t tiles_x = (width + tile - 1) / tile;
+    const int64_t tiles_x = ((int64_t)width + tile - 1) / tile;
     const uint64_t k = ((uint64_t)((y / tile) * tiles_x + x / tile) << 24) |
                        (uint64_t)((y % tile) * tile + (x % tile));
     keys[c] = k;
@@ -413,13 +413,6 @@ unsigned pixel_waves_grid(int32_t n_obs) {
     return (unsigned)std::min<int64_t>(((int64_t)n_obs + 3) / 4, (int64_t)1 << 22);
 }
 
-// bits(x): the smallest b with x < 2^b.
-unsigned bits(uint64_t x) {
-    unsigned b = 1;
-    while (b < 64 && (x >> b) != 0) ++b;
-    return b;
-}
-
 // rocPRIM with its temporary storage from the call's scratch.
 template <typename K, typename V>
 void sort_pairs(mm_ctx *ctx, Scratch &tmp, const K *k, K *ko, const V *v, V *vo, int64_t n,
@@ -566,9 +559,7 @@ static void pointing_tile_order(mm_ctx *ctx, mm_pointing *p, int32_t width, int3
     int32_t *vals = sc.get<int32_t>(n_obs);
     k_tile_keys<<<(n_obs + BS - 1) / BS, BS, 0, ctx->stream>>>(p->obs_pix.as<int32_t>(), n_obs,
                                                               width, tile, keys, vals);
-    const int64_t tiles_x = (width + tile - 1) / tile;
-    const int64_t tiles_y = (p->n_pix_total - 1) / width / tile + 1;
-    sort_pairs(ctx, sc, keys, ko, vals, order, n_obs, 24 + bits((uint64_t)(tiles_x * tiles_y)));
+    sort_pairs(ctx, sc, keys, ko, vals, order, n_obs, tile_key_bits(p->n_pix_total, width, tile));
 }
 
 // Time segments for the sliced P^T: enough (segment, slice) waves to fill

@@ -104,6 +104,22 @@ void p_launch() {
             }
 }
 
+// The tile keys of every pixel fit in the bits that are sorted, at most 64.
+void tile_keys() {
+    for (int32_t tile : {8, 32})
+        for (int32_t n_pix : {1, 1000, 1 << 20, 2147483647})
+            for (int32_t width : {1, 7, 32, 33, 46341, 2147483616, 2147483617, 2147483647}) {
+                const unsigned b = mm::tile_key_bits(n_pix, width, tile);
+                EXPECT(b <= 64);
+                const int64_t tiles_x = ((int64_t)width + tile - 1) / tile;
+                for (int64_t g : {(int64_t)n_pix - 1, (int64_t)n_pix / 2, (int64_t)width - 1}) {
+                    if (g >= n_pix) continue;
+                    const uint64_t t = (uint64_t)(g / width / tile * tiles_x + g % width / tile);
+                    EXPECT(((t << 24 | 0xffffff) >> (b - 1)) <= 1);
+                }
+            }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -115,6 +131,7 @@ int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
+    else if (!std::strcmp(what, "tile_keys")) tile_keys();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;
