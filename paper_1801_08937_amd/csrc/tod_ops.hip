@@ -241,6 +241,9 @@ __global__ void __launch_bounds__(BS) k_apply_PT(const int32_t *__restrict__ off
 // similar pace and the lines of z it gathers are shared in L2 and the
 // Infinity Cache instead of re-read from HBM.  Partial maps per segment go to
 // part[s][3 c + a] (or straight to x when S = 1).
+// FP32 I and QU sums are kept in FP64: a lane's chain of hits / (S directions) samples
+// is longer than the 64-way split of the one-wave-per-pixel form (512 samples in 8
+// segments: rounding 3.5e-6 of a sample against 2.0e-6).
 template <typename T, int NC>
 __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ base,
                                                     const int32_t *__restrict__ sl_perm,
@@ -249,6 +252,7 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
                                                     int32_t S, int32_t n_obs,
                                                     const T *__restrict__ z,
                                                     double *__restrict__ out) {
+    using A = std::conditional_t<NC == 3, T, double>;
     const int lane = threadIdx.x & 63;
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int64_t w = blk * (BS / 64) + (threadIdx.x >> 6);
@@ -258,7 +262,7 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
     const int64_t W = (base[w + 1] - b0) >> 6;
     const int32_t *pp = sl_perm + b0 + lane;
     const auto *wp = NC > 1 ? sl_w + b0 + lane : nullptr;
-    T s0 = 0, s1 = 0, s2 = 0;
+    A s0 = 0, s1 = 0, s2 = 0;
     int64_t k = 0;
     // eight entries in flight per lane, accumulated in entry order
     for (; k + 7 < W; k += 8) {
@@ -279,24 +283,24 @@ __global__ void __launch_bounds__(BS) k_apply_PT_sl(const int64_t *__restrict__ 
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            if constexpr (NC != 2) s0 += zz[q];
+            if constexpr (NC != 2) s0 += (A)zz[q];
             if constexpr (NC > 1) {
                 T c, sn;
                 SlRec<T>::weights(ww[q], c, sn);
-                s1 += c * zz[q];
-                s2 += sn * zz[q];
+                s1 += (A)c * (A)zz[q];
+                s2 += (A)sn * (A)zz[q];
             }
         }
     }
     for (; k < W; ++k) {
         const int32_t tq = pp[64 * k];
         const T zq = tq >= 0 ? z[tq] : (T)0;
-        if constexpr (NC != 2) s0 += zq;
+        if constexpr (NC != 2) s0 += (A)zq;
         if constexpr (NC > 1) {
             T c, sn;
             SlRec<T>::weights(wp[64 * k], c, sn);
-            s1 += c * zq;
-            s2 += sn * zq;
+            s1 += (A)c * (A)zq;
+            s2 += (A)sn * (A)zq;
         }
     }
     const int32_t c = sl_pix[(int64_t)g * 64 + lane];
