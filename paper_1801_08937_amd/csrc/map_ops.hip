@@ -1391,12 +1391,19 @@ int grid_for(int64_t n, int max_blocks = 4096) {
 
 // ----------------------------------------------------------------- launchers
 
+// A block per 96 elements (32 IQU pixels) up to 256 blocks, so that these latency-bound
+// launches spread over the CUs; those 256 up to 262,144 elements; beyond, a block per
+// 1,024, at most 512.  More blocks make the second stages longer, which sum the
+// partial sums of all.  Map-domain kernels of an iteration, one column, us, with 256,
+// 192 and 512 blocks at most for the middle part, and with a block per 256 elements up
+// to 65,536 and per 1,024 beyond: M_BD, 49,152 unknowns 20.9, 20.9, 21.6 and 25.7;
+// 98,283 23.1, 24.0, 23.7 and 29.9; M_2l (k = 32), 49,152 56, 59, 77 and 57; 64,827 63, 66,
+// 85 and 61; 98,283 71, 76, 87 and 65.
 int reduction_parts(int64_t n_rows, int nrhs) {
     const int64_t m = n_rows * nrhs;
-    // up to 49,152 elements a block per 96 (32 IQU pixels), so that these
-    // latency-bound launches spread over more CUs; beyond, a block per 1,024, at
-    // most 512 blocks
-    int64_t p = m <= 49152 ? (m + 95) / 96 : (m + 1023) / 1024;
+    const int64_t spread = (m + 95) / 96, full = (m + 1023) / 1024;
+    int64_t p = spread < 256 ? spread : 256;
+    if (full > p) p = full;
     if (p > 512) p = 512;
     return (int)(p < 1 ? 1 : p);
 }

@@ -120,6 +120,21 @@ void tile_keys() {
             }
 }
 
+// Blocks of the map-domain reductions: never fewer for a larger map, at most 512, and
+// no block without a row.
+void reduction_blocks() {
+    for (int R = 1; R <= 64; R *= 2) {
+        int last = 1;
+        for (int64_t n = 1; n * R <= 1000000; n += 1 + n / 97) {
+            const int p = mm::reduction_parts(n, R);
+            EXPECT(p >= last && p <= 512);
+            if (R == 1) EXPECT(p <= n);
+            last = p;
+        }
+    }
+    EXPECT(mm::reduction_parts(49153, 1) >= 192 && mm::reduction_parts(65536, 1) >= 192);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -132,6 +147,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "reduction_blocks")) reduction_blocks();
     else {
         std::printf("no check named '%s'\n", what);
         return 2;
