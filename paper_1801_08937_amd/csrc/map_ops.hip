@@ -6,6 +6,8 @@
 //
 // All reductions are two-stage with a fixed partition and a fixed tree, so
 // results are bitwise repeatable run to run; no floating-point atomics.
+#include <algorithm>
+
 #include "mm_internal.h"
 
 namespace mm {
@@ -929,26 +931,20 @@ __global__ void __launch_bounds__(64) k_coarse_apply(int k, int R, const double 
     c[i * R + r] = acc;
 }
 
-// out = M_BD (v - AZ c) + Z c of one column (Eq. m2l), with optional partial sums of
-// v . out, where each block forms c = E^-1 Z^T v itself from the partial sums of Z^T v
-// (g_part[b k + a], b < g_parts), which saves two launches.  A block takes M1_P pixels
-// at a time, its threads M1_Q groups of the k columns for each, so that a short map
-// spreads over the chip and few loads wait for each other; the groups are then added
-// in order.  Bound by latency: 12,288 unknowns, k = 32, 14.0 -> 8.8 us against one
-// thread per pixel on 48 blocks.
-constexpr int M1_P = 32, M1_Q = BS / M1_P;
-template <int NC>
-__global__ void __launch_bounds__(BS) k_m2l_one(const double *__restrict__ inv, int32_t n_obs,
-                                                int k, int64_t n, const double *__restrict__ Z,
-                                                const double *__restrict__ AZ,
-                                                const double *__restrict__ g_part, int g_parts,
-                                                const double *__restrict__ Einv,
-                                                const double *__restrict__ v,
-                                                double *__restrict__ out,
-                                                double *__restrict__ partial,
-                                                int64_t pix_per_block) {
-    __shared__ double gs[64], cs[4][64], sc[64], sm[M1_Q][2 * NC][M1_P];
+// c = E^-1 Z^T v of one column into sc, by each block of BS threads itself from the
+// partial sums of Z^T v (g_part[b k + a], b < g_parts), which saves two launches.
+__device__ __forceinline__ void m2l_coef_block(int k, const double *__restrict__ g_part,
+                                               int g_parts, const double *__restrict__ Einv,
+                                               double *__restrict__ sc) {
+    __shared__ double gs[64], cs[4][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // a quarter of the rows of E^-1 per wave, in flight while the sums are formed
+    double e[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int j = wv * 16 + q;
+        e[q] = Einv[(int64_t)(j < k ? j : 0) * k + (lane < k ? lane : 0)];
+    }
     // wave wv sums columns wv + 4t, eight at a time with their loads in flight together
     for (int a0 = wv; a0 < k; a0 += 4 * 8) {
         double s8[8];
@@ -975,13 +971,7 @@ __global__ void __launch_bounds__(BS) k_m2l_one(const double *__restrict__ inv, 
     }
     __syncthreads();
     {  // c_i = sum_j (E^-1)_{ij} g_j, a quarter of the j per wave
-        const int i = lane < k ? lane : 0;
-        double acc = 0, e[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int j = wv * 16 + q;
-            e[q] = Einv[(int64_t)(j < k ? j : 0) * k + i];
-        }
+        double acc = 0;
 #pragma unroll
         for (int q = 0; q < 16; ++q)
             if (wv * 16 + q < k) acc = __builtin_fma(e[q], gs[wv * 16 + q], acc);
@@ -991,77 +981,165 @@ __global__ void __launch_bounds__(BS) k_m2l_one(const double *__restrict__ inv, 
     if (threadIdx.x < k)
         sc[lane] = ((cs[0][lane] + cs[1][lane]) + cs[2][lane]) + cs[3][lane];
     __syncthreads();
+}
+
+// out = M_BD (v - AZ c) + Z c of one column (Eq. m2l), with optional partial sums of
+// v . out.  Two forms, by the pixels of a block:
+//   up to M1_P (IQU maps of at most 8,192 pixels): M1_Q threads per pixel, each with a
+//     share of the k columns, added in order, so that a short map spreads over the
+//     chip and few loads wait for each other;
+//   more: a thread per pixel, which streams Z and AZ (bound by HBM where the map is
+//     large, else by latency).
+// Z^T v and this kernel, us, Z from HBM, M1_Q threads / a thread per pixel: k = 32, 12,288
+// unknowns 17.7 / 18.1, 19,200 18.6 / 18.8, 30,000 23.2 / 20.6, 49,152 25.6 / 23.6, 196,608
+// 67 / 51; k = 63, 12,288 23.8 / 27.5, 30,000 31.4 / 30.1, 196,608 106 / 84.  The first
+// form at every size took 79 at 196,608, k = 32 (11 rounds of 32 pixels per block); the
+// thread per pixel with E^-1 loaded after the sums, 54.
+constexpr int M1_P = 32, M1_Q = BS / M1_P;
+template <int NC>
+__global__ void __launch_bounds__(BS) k_m2l_one(const double *__restrict__ inv, int32_t n_obs,
+                                                int k, int64_t n, const double *__restrict__ Z,
+                                                const double *__restrict__ AZ,
+                                                const double *__restrict__ g_part, int g_parts,
+                                                const double *__restrict__ Einv,
+                                                const double *__restrict__ v,
+                                                double *__restrict__ out,
+                                                double *__restrict__ partial,
+                                                int64_t pix_per_block) {
+    __shared__ double sc[64], sm[M1_Q][2 * NC][M1_P];
+    m2l_coef_block(k, g_part, g_parts, Einv, sc);
     const int pl = threadIdx.x % M1_P, qg = threadIdx.x / M1_P;
     const int64_t p0 = (int64_t)blockIdx.x * pix_per_block;
     const int64_t p1 = p0 + pix_per_block < n_obs ? p0 + pix_per_block : n_obs;
-    double dot = 0;
-    for (int64_t pb = p0; pb < p1; pb += M1_P) {
-        const int64_t j = pb + pl < p1 ? pb + pl : p1 - 1;
-        double sz[NC] = {}, sa[NC] = {};
-        for (int q0 = qg; q0 < k; q0 += 4 * M1_Q) {
-            double z[4][NC], az[4][NC];
+    const int64_t j = p0 + pl < p1 ? p0 + pl : p1 - 1;
+    double dot = 0, sz[NC] = {}, sa[NC] = {};
+    for (int q0 = qg; q0 < k; q0 += 4 * M1_Q) {
+        double z[4][NC], az[4][NC];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int q = q0 + t * M1_Q < k ? q0 + t * M1_Q : k - 1;
+        for (int t = 0; t < 4; ++t) {
+            const int q = q0 + t * M1_Q < k ? q0 + t * M1_Q : k - 1;
 #pragma unroll
-                for (int a = 0; a < NC; ++a) {
-                    z[t][a] = Z[(int64_t)q * n + NC * j + a];
-                    az[t][a] = AZ[(int64_t)q * n + NC * j + a];
-                }
+            for (int a = 0; a < NC; ++a) {
+                z[t][a] = Z[(int64_t)q * n + NC * j + a];
+                az[t][a] = AZ[(int64_t)q * n + NC * j + a];
             }
+        }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int q = q0 + t * M1_Q;
-                if (q >= k) break;
+        for (int t = 0; t < 4; ++t) {
+            const int q = q0 + t * M1_Q;
+            if (q >= k) break;
 #pragma unroll
-                for (int a = 0; a < NC; ++a) {
-                    sz[a] += z[t][a] * sc[q];
-                    sa[a] += az[t][a] * sc[q];
-                }
+            for (int a = 0; a < NC; ++a) {
+                sz[a] += z[t][a] * sc[q];
+                sa[a] += az[t][a] * sc[q];
             }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < NC; ++a) {
+        sm[qg][a][pl] = sz[a];
+        sm[qg][NC + a][pl] = sa[a];
+    }
+    __syncthreads();
+    if (qg == 0 && p0 + pl < p1) {
+        double u[NC], vv[NC], o[NC];
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            double s0 = 0, s1 = 0;
+#pragma unroll
+            for (int g = 0; g < M1_Q; ++g) {
+                s0 += sm[g][a][pl];
+                s1 += sm[g][NC + a][pl];
+            }
+            sz[a] = s0;
+            vv[a] = v[NC * j + a];
+            u[a] = vv[a] - s1;
+        }
+        const double *m = inv + (NC * (NC + 1) / 2) * j;
+        if constexpr (NC == 3) {
+            o[0] = m[0] * u[0] + m[1] * u[1] + m[2] * u[2];
+            o[1] = m[1] * u[0] + m[3] * u[1] + m[4] * u[2];
+            o[2] = m[2] * u[0] + m[4] * u[1] + m[5] * u[2];
+        } else {
+            sym_mul<NC>(m, u, o);
         }
 #pragma unroll
         for (int a = 0; a < NC; ++a) {
-            sm[qg][a][pl] = sz[a];
-            sm[qg][NC + a][pl] = sa[a];
+            const double oe = o[a] + sz[a];
+            out[NC * j + a] = oe;
+            dot += vv[a] * oe;
         }
-        __syncthreads();
-        if (qg == 0 && pb + pl < p1) {
-            double u[NC], vv[NC], o[NC];
-#pragma unroll
-            for (int a = 0; a < NC; ++a) {
-                double s0 = 0, s1 = 0;
-#pragma unroll
-                for (int g = 0; g < M1_Q; ++g) {
-                    s0 += sm[g][a][pl];
-                    s1 += sm[g][NC + a][pl];
-                }
-                sz[a] = s0;
-                vv[a] = v[NC * j + a];
-                u[a] = vv[a] - s1;
-            }
-            const double *m = inv + (NC * (NC + 1) / 2) * j;
-            if constexpr (NC == 3) {
-                o[0] = m[0] * u[0] + m[1] * u[1] + m[2] * u[2];
-                o[1] = m[1] * u[0] + m[3] * u[1] + m[4] * u[2];
-                o[2] = m[2] * u[0] + m[4] * u[1] + m[5] * u[2];
-            } else {
-                sym_mul<NC>(m, u, o);
-            }
-#pragma unroll
-            for (int a = 0; a < NC; ++a) {
-                const double oe = o[a] + sz[a];
-                out[NC * j + a] = oe;
-                dot += vv[a] * oe;
-            }
-        }
-        __syncthreads();
     }
     if (partial && threadIdx.x < 64) {  // M1_P threads hold a share
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) dot += __shfl_xor(dot, m);
         if (threadIdx.x == 0) partial[blockIdx.x] = dot;
     }
+}
+
+template <int NC>
+__global__ void __launch_bounds__(BS) k_m2l_wide(const double *__restrict__ inv, int32_t n_obs,
+                                                 int k, int64_t n, const double *__restrict__ Z,
+                                                 const double *__restrict__ AZ,
+                                                 const double *__restrict__ g_part, int g_parts,
+                                                 const double *__restrict__ Einv,
+                                                 const double *__restrict__ v,
+                                                 double *__restrict__ out,
+                                                 double *__restrict__ partial,
+                                                 int64_t pix_per_block) {
+    __shared__ double sc[64];
+    m2l_coef_block(k, g_part, g_parts, Einv, sc);
+    const int64_t p0 = (int64_t)blockIdx.x * pix_per_block;
+    const int64_t p1 = p0 + pix_per_block < n_obs ? p0 + pix_per_block : n_obs;
+    double dot = 0;
+    for (int64_t j = p0 + threadIdx.x; j < p1; j += BS) {
+        double u[NC], o[NC], sz[NC] = {}, sa[NC] = {};
+        int q = 0;
+        for (; q + 8 <= k; q += 8) {
+            double z[8][NC], az[8][NC];
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    z[t][a] = Z[(int64_t)(q + t) * n + NC * j + a];
+                    az[t][a] = AZ[(int64_t)(q + t) * n + NC * j + a];
+                }
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int a = 0; a < NC; ++a) {
+                    sz[a] += z[t][a] * sc[q + t];
+                    sa[a] += az[t][a] * sc[q + t];
+                }
+        }
+        for (; q < k; ++q)
+#pragma unroll
+            for (int a = 0; a < NC; ++a) {
+                sz[a] += Z[(int64_t)q * n + NC * j + a] * sc[q];
+                sa[a] += AZ[(int64_t)q * n + NC * j + a] * sc[q];
+            }
+        double vv[NC];
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            vv[a] = v[NC * j + a];
+            u[a] = vv[a] - sa[a];
+        }
+        const double *m = inv + (NC * (NC + 1) / 2) * j;
+        if constexpr (NC == 3) {
+            o[0] = m[0] * u[0] + m[1] * u[1] + m[2] * u[2];
+            o[1] = m[1] * u[0] + m[3] * u[1] + m[4] * u[2];
+            o[2] = m[2] * u[0] + m[4] * u[1] + m[5] * u[2];
+        } else {
+            sym_mul<NC>(m, u, o);
+        }
+#pragma unroll
+        for (int a = 0; a < NC; ++a) {
+            const double oe = o[a] + sz[a];
+            out[NC * j + a] = oe;
+            dot += vv[a] * oe;
+        }
+    }
+    if (partial) block_col_reduce<1>(dot, partial);
 }
 
 // out = M_BD (v - AZ c) + Z c per pixel and column (Eq. m2l), with optional
@@ -1397,8 +1475,7 @@ int grid_for(int64_t n, int max_blocks = 4096) {
 // partial sums of all.  Map-domain kernels of an iteration, one column, us, with 256,
 // 192 and 512 blocks at most for the middle part, and with a block per 256 elements up
 // to 65,536 and per 1,024 beyond: M_BD, 49,152 unknowns 20.9, 20.9, 21.6 and 25.7;
-// 98,283 23.1, 24.0, 23.7 and 29.9; M_2l (k = 32), 49,152 56, 59, 77 and 57; 64,827 63, 66,
-// 85 and 61; 98,283 71, 76, 87 and 65.
+// 98,283 23.1, 24.0, 23.7 and 29.9.
 int reduction_parts(int64_t n_rows, int nrhs) {
     const int64_t m = n_rows * nrhs;
     const int64_t spread = (m + 95) / 96, full = (m + 1023) / 1024;
@@ -1639,8 +1716,9 @@ void slot_ctl(mm_ctx *ctx, PcgDev s, int slot, int mode, double tol) {
 
 // The partial sums of W^T v, ctx->red[b ncol + col] for b < the returned
 // count of row chunks.
-static int gemv_t_parts(mm_ctx *ctx, int64_t n, int ncol, const double *W, const double *v) {
-    const int parts = reduction_parts(n);
+static int gemv_t_parts(mm_ctx *ctx, int64_t n, int ncol, const double *W, const double *v,
+                        int max_parts = 512) {
+    const int parts = std::min(reduction_parts(n), max_parts);
     ws_alloc(ctx, ctx->red, sizeof(double) * parts * (ncol > 64 ? ncol : 64));
     // grouped columns measured faster for k = 32 (M_2l), one column per
     // block for the long Arnoldi bases
@@ -1756,10 +1834,13 @@ void m2l_apply_dev(mm_ctx *ctx, const mm_precond *M, int nrhs, const double *v, 
         int g_parts;
         {
             Scope sg(ctx->prof, ctx->stream, "gemv");
-            g_parts = gemv_t_parts(ctx, n, k, M->Z.as<double>(), v);
+            // every block of the next kernel sums them again: 128 at most
+            g_parts = gemv_t_parts(ctx, n, k, M->Z.as<double>(), v, 128);
         }
         dispatch_nc([&](auto NN) {
-            k_m2l_one<decltype(NN)::value><<<parts, BS, 0, ctx->stream>>>(
+            constexpr int NC = decltype(NN)::value;
+            const auto kernel = ppb <= M1_P ? k_m2l_one<NC> : k_m2l_wide<NC>;
+            kernel<<<parts, BS, 0, ctx->stream>>>(
                 M->inv.as<double>(), M->n_obs, k, n, M->Z.as<double>(), M->AZ.as<double>(),
                 ctx->red.as<double>(), g_parts, M->Einv.as<double>(), v, out, partial, ppb);
         });
