@@ -577,7 +577,7 @@ def main():
     a_ms = ev0.elapsed_time(ev1) / n_apply
     alg_bytes = dict(ALG_BYTES)
     if ln.method == 2:
-        alg_bytes["Ninv_fft"] = fft_bytes_per_sample(p.interval_start, p.half_bw, ln.fft_valid)
+        alg_bytes["Ninv_fft"] = fft_bytes_per_sample(p.interval_start, p.half_bw, ln.fft_run_valid)
     ninv = alg_bytes["Ninv_fft"] if ln.method == 2 else alg_bytes["Ninv_band"]
     a_apply = {"ms": a_ms, "samples_per_s": p.n_samp / (a_ms * 1e-3),
                "design_bytes_per_sample": alg_bytes["P"] + alg_bytes["PT"] + ninv,
@@ -1196,10 +1196,10 @@ def _n1_size(mm, ctx, lams, n_samp, L, dev, ev):
                 tf = n_samp * 2.0 * (2 * lam + 1) / (ms * 1e-3) / 1e12
                 row[name] = {"ms": ms, "TFLOPs": tf, "frac_fp64_peak": tf / FP64_PEAK_TF}
             else:
-                bps = fft_bytes_per_sample(istart, lam, ln.fft_valid)
+                bps = fft_bytes_per_sample(istart, lam, ln.fft_run_valid)
                 gbs = n_samp * bps / (ms * 1e-3) / 1e9
                 row[name] = {"ms": ms, "GBps": gbs, "frac_hbm_peak": gbs / HBM_PEAK_GBS,
-                             "fft_n": ln.fft_n}
+                             "fft_n": ln.fft_run_n}
             ln.close()
         picked = ctx.noise(istart, fid, band, lam, 0)
         row["auto_picks"] = {1: "direct", 2: "fft"}[picked.method]

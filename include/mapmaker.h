@@ -253,10 +253,15 @@ mm_status mm_noise_method_used(const mm_noise *nz, mm_noise_method *method);
  * blocks takes 1.05 times as long), so it depends on the interval lengths,
  * lambda and the device's compute-unit count; mm_noise_set_fft_block and
  * mm_autotune can change it.  Until they do, the blocks that run may be of
- * another length (8,192, 16,384 or 32,768) where that is faster. */
+ * another length (8,192, 16,384 or 32,768) where that is faster:
+ * mm_noise_fft_run gives the length that runs. */
 mm_status mm_noise_fft_block(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid);
-/* Rebuild the FFT method's tables for blocks of n_fft real samples: 16,384
- * (lambda <= 6,144) or 32,768, or 0 for the time model's pick.  Results are
+/* The same of the blocks that an apply runs now; its bytes and its rounding
+ * follow from these.  mm_noise_set_fft_block(*n_fft) keeps the results. */
+mm_status mm_noise_fft_run(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid);
+/* Rebuild the FFT method's tables for blocks of n_fft real samples: 8,192
+ * (lambda <= 3,072), 16,384 (lambda <= 6,144) or 32,768, or 0 for the
+ * library's pick.  Results are
  * the same to rounding (<= 1e-11 relative in FP64), not bitwise.  The handle
  * is modified: no other call may use it meanwhile.  Errors: MM_E_INVALID for
  * a non-FFT handle or an unsupported size. */
@@ -631,7 +636,8 @@ void mm_server_destroy(mm_server *srv);
  *            blocks per compute unit);
  *   stage 2, P^T with several columns: tiled or ascending pixel order;
  *   stage 3, FFT N^-1, only with MM_TUNE_FFT_BLOCK in flags: the overlap-save
- *            block length (16,384 or 32,768; see mm_noise_set_fft_block).
+ *            block length (16,384 or 32,768; see mm_noise_set_fft_block), kept
+ *            only where it is faster than the blocks that run already.
  * Stages 0-2 change speed only: every output sums its terms in an order no
  * candidate changes, so results stay bitwise the same.  Stage 3 changes
  * results at the rounding level (<= 1e-11 relative in FP64).

@@ -773,6 +773,14 @@ extern "C" mm_status mm_noise_fft_block(const mm_noise *nz, int32_t *n_fft, int3
     return MM_OK;
 }
 
+extern "C" mm_status mm_noise_fft_run(const mm_noise *nz, int32_t *n_fft, int32_t *n_valid) {
+    if (!nz || !n_fft || !n_valid) return MM_E_INVALID;
+    const bool fft = nz->method == MM_NOISE_FFT;
+    *n_fft = fft ? nz->fft.n : 0;
+    *n_valid = fft ? nz->fft.valid : 0;
+    return MM_OK;
+}
+
 extern "C" mm_status mm_noise_set_fft_block(mm_ctx *ctx, mm_noise *nz, int32_t n_fft) {
     if (!ctx) return MM_E_INVALID;
     API_BEGIN(ctx)

@@ -117,7 +117,8 @@ static int64_t fft_n_blocks(const mm_noise *nz, int N) {
     return nb;
 }
 
-// The length reported for a handle: rounds of n_cu x (blocks per CU) blocks, 40
+// The length that mm_noise_fft_block reports where the library picks (the pick of the
+// two larger lengths; fft_run_model picks what runs): rounds of n_cu x (blocks per CU) blocks, 40
 // (16,384) or 42 (32,768) time units each.
 static double fft_time_model(const mm_noise *nz, int N, int n_cu) {
     if (N <= 2 * nz->half_bw) return 1e300;
@@ -206,9 +207,13 @@ static void fft_tables(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, int N) {
 void noise_fft_prepare(mm_ctx *ctx, mm_noise *nz, int n_fft) {
     const int lam = nz->half_bw;
     MM_CHECK(noise_fft_supported(lam, 0), MM_E_INVALID, "FFT: bandwidth unsupported");
-    const int nm = 2 * noise_fft_mid_nc(), nb = 2 * noise_fft_big_nc();
-    MM_CHECK(n_fft == 0 || n_fft == nb || (n_fft == nm && noise_fft_mid_supported(lam)),
-             MM_E_INVALID, "FFT: block length must be 16,384 (lambda <= 6,144) or 32,768");
+    const int ns = 2 * noise_fft_short_nc(), nm = 2 * noise_fft_mid_nc();
+    const int nb = 2 * noise_fft_big_nc();
+    MM_CHECK(n_fft == 0 || n_fft == nb || (n_fft == nm && noise_fft_mid_supported(lam)) ||
+                 (n_fft == ns && noise_fft_short_supported(lam)),
+             MM_E_INVALID,
+             "FFT: block length must be 8,192 (lambda <= 3,072), 16,384 (lambda <= 6,144) or "
+             "32,768");
     int run = n_fft, shown = n_fft;
     if (n_fft == 0) {
         run = fft_run_length(nz, ctx->n_cu);

@@ -1388,22 +1388,31 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
         }
         // stage 3: FFT block length (results move at the rounding level)
         if ((flags & MM_TUNE_FFT_BLOCK) && nz->method == MM_NOISE_FFT) {
-            const int keep = nz->fft_n;
-            const bool was_auto = nz->fft_auto;  // the length picked at build: as it ran then
+            // the state as it is first, then the lengths that it does not run already;
+            // the state stays, a pick at build as such, unless one of them is faster
+            const int run = nz->fft.n, keep = nz->fft_auto ? 0 : nz->fft_n;
             auto prep = [&](int n) {
                 MM_HIP(hipStreamSynchronize(ctx->stream));
-                noise_fft_prepare(ctx, nz, was_auto && n == keep ? 0 : n);
+                noise_fft_prepare(ctx, nz, n);
             };
-            double best = 1e30;
-            int best_n = keep;
+            auto time_apply = [&]() {
+                return time_it([&]() { noise_apply_dev(ctx, nz, nrhs, y.ptr, z.ptr); });
+            };
+            const double now = time_apply();
+            double best = now;
+            int best_n = keep, is = keep;
             for (int n_fft : {16384, 32768}) {
                 if (n_fft == 16384 && nz->half_bw > 6144) continue;
-                prep(n_fft);
-                const double ms = time_it([&]() { noise_apply_dev(ctx, nz, nrhs, y.ptr, z.ptr); });
+                double ms = now;
+                if (n_fft != run) {
+                    prep(n_fft);
+                    is = n_fft;
+                    ms = time_apply();
+                }
                 note(3, n_fft, ms);
                 if (ms < best) { best = ms; best_n = n_fft; }
             }
-            if (best_n != nz->fft_n) prep(best_n);
+            if (is != best_n) prep(best_n);
         }
     } catch (...) {
         ctx->prof.on = prof;

@@ -91,6 +91,7 @@ def lib() -> C.CDLL:
             "mm_noise_method_used": (C.c_int, [P, C.POINTER(C.c_int)]),
             "mm_polyfilter_build": (C.c_int, [P, P, I32, P, P, I64, P, I32, P, I32, PP]),
             "mm_noise_fft_block": (C.c_int, [P, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
+            "mm_noise_fft_run": (C.c_int, [P, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
             "mm_noise_apply": (C.c_int, [P, P, I32, P, P]),
             "mm_noise_destroy": (None, [P]),
             "mm_apply_P": (C.c_int, [P, P, I32, P, P]),
@@ -636,9 +637,13 @@ class Noise(_Handle):
         nf, nv = C.c_int32(0), C.c_int32(0)
         lib().mm_noise_fft_block(self.h, C.byref(nf), C.byref(nv))
         self.fft_n, self.fft_valid = nf.value, nv.value
+        # of the blocks that run: another length where the library picks a faster one
+        lib().mm_noise_fft_run(self.h, C.byref(nf), C.byref(nv))
+        self.fft_run_n, self.fft_run_valid = nf.value, nv.value
 
     def set_fft_block(self, n_fft: int):
-        """Overlap-save block length of the FFT method (16384, 32768, 0 = model)."""
+        """Overlap-save block length of the FFT method (8192, 16384, 32768, 0 = the
+        library's pick)."""
         self.ctx._check(lib().mm_noise_set_fft_block(self.ctx.h, self.h, n_fft),
                         "mm_noise_set_fft_block")
         self._read_block()
