@@ -165,6 +165,7 @@ static int fft_run_length(const mm_noise *nz, int n_cu) {
 static void fft_tables(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, int N) {
     hipStream_t s = ctx->stream;
     const int lam = nz->half_bw, NC = N / 2;
+    tb.n_blocks = 0;  // until the tables are whole: a failure on the way leaves none
     tb.n = N;
     tb.valid = N - 2 * lam;
     // quarter period of cos(2 pi m / N) (long double on the host, rounded once)
@@ -196,11 +197,11 @@ static void fft_tables(mm_ctx *ctx, const mm_noise *nz, FftTables &tb, int N) {
             blocks.push_back(t);
             blocks.push_back(i);
         }
-    tb.n_blocks = (int64_t)blocks.size() / 2;
     tb.blocks.alloc(sizeof(int64_t) * blocks.size());
     MM_HIP(hipMemcpyAsync(tb.blocks.ptr, blocks.data(), sizeof(int64_t) * blocks.size(),
                           hipMemcpyHostToDevice, s));
     MM_HIP(hipStreamSynchronize(s));
+    tb.n_blocks = (int64_t)blocks.size() / 2;
 }
 
 // Tables for blocks of n_fft real samples (0 = pick by the models above).

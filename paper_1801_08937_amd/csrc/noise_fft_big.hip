@@ -715,6 +715,7 @@ void noise_fft_reg_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const vo
     // (block, column) pairs on a flat grid padded to a multiple of 8 (see
     // the kernel)
     const int64_t nb = tb.n_blocks;
+    MM_CHECK(nb > 0, MM_E_OOM, "FFT: no tables (setting the block length ran out of memory)");
     const dim3 grid((unsigned)((nb * nrhs + 7) / 8 * 8));
     auto go = [&](auto GG, auto TT) {
         using G = decltype(GG);

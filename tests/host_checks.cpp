@@ -135,6 +135,34 @@ void reduction_blocks() {
     EXPECT(mm::reduction_parts(49153, 1) >= 192 && mm::reduction_parts(65536, 1) >= 192);
 }
 
+// Another FFT block length fails half way: no apply may run its kernels with what is
+// left of the tables of the old length.
+void fft_block() {
+    mm_ctx ctx;
+    mm_noise nz;
+    nz.method = MM_NOISE_FFT;
+    nz.half_bw = 100;
+    nz.n_samp = 100000;
+    nz.n_int = 1;
+    nz.n_filters = 1;
+    nz.h_istart = {0, nz.n_samp};
+    nz.fft_n = nz.fft.n = 16384;
+    nz.fft.valid = 16384 - 200;
+    nz.fft.n_blocks = 7;
+    for (mm::DBuf *b : {&nz.fft.spec, &nz.fft.tw, &nz.fft.blocks}) pretend(*b, 1 << 20);
+    auto code = [](auto f) {
+        try {
+            f();
+        } catch (const mm::Error &e) {
+            return (int)e.code;
+        }
+        return 0;
+    };
+    EXPECT(code([&] { mm::noise_fft_prepare(&ctx, &nz, 32768); }) == MM_E_OOM);
+    EXPECT(nz.fft.n_blocks == 0 || nz.fft.n == 16384);
+    EXPECT(code([&] { mm::noise_apply_dev(&ctx, &nz, 1, nullptr, nullptr); }) == MM_E_OOM);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -147,6 +175,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "fft_block")) fft_block();
     else if (!std::strcmp(what, "reduction_blocks")) reduction_blocks();
     else {
         std::printf("no check named '%s'\n", what);
