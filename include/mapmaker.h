@@ -631,13 +631,15 @@ void mm_server_destroy(mm_server *srv);
 /* Per-stage autotuner: for nrhs columns, time candidates with HIP events and
  * keep the fastest, stored in the handles for later calls with that nrhs
  * (the handles are modified: no other call may use them meanwhile).
- *   stage 0, P: the grid size;
+ *   stage 0, P of several columns: the grid size (0 = the default);
  *   stage 1, direct band N^-1: taps per LDS chunk (less LDS per block, more
- *            blocks per compute unit);
+ *            blocks per compute unit); an A that forms P inside the band takes
+ *            all taps at once whatever is kept here;
  *   stage 2, P^T with several columns: tiled or ascending pixel order;
  *   stage 3, FFT N^-1, only with MM_TUNE_FFT_BLOCK in flags: the overlap-save
  *            block length (16,384 or 32,768; see mm_noise_set_fft_block), kept
  *            only where it is faster than the blocks that run already.
+ * A kernel without the parameter is timed once.
  * Stages 0-2 change speed only: every output sums its terms in an order no
  * candidate changes, so results stay bitwise the same.  Stage 3 changes
  * results at the rounding level (<= 1e-11 relative in FP64).

@@ -1081,8 +1081,8 @@ static int band_chunk_used(const mm_noise *nz, int nrhs) {
 }
 
 template <typename T, int R, typename Rows>
-static void band_tiled_launch(mm_ctx *ctx, const mm_noise *nz, const Rows &rows, T *z) {
-    const int lam = nz->half_bw, cl = band_chunk_used(nz, R);
+static void band_tiled_launch(mm_ctx *ctx, const mm_noise *nz, const Rows &rows, T *z, int cl) {
+    const int lam = nz->half_bw;
     const int tl = band_tile_len(R, nz->band_small, lam, nz->n_samp);
     int64_t n_tiles;
     const int64_t *pref = band_tiles(nz, R, &n_tiles);
@@ -1106,14 +1106,16 @@ static bool band_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, in
     const int lam = nz->half_bw;
     if (nz->method != MM_NOISE_DIRECT || p->n_obs == 0) return false;
     if (nrhs == 1) {
-        if (band_chunk_used(nz, 1) < 2 * lam + 1) return false;  // several windows per tile
+        // the window is gathered once, for all taps: whatever chunk N^-1 alone is tuned to
+        const int cl = band_chunk(lam, 1, nz->prec, nz->band_small, nz->n_samp);
+        if (cl < 2 * lam + 1) return false;  // several windows per tile
         Scope sc(ctx->prof, ctx->stream, "Ninv_band");
         const PMap m = p_map_dev(ctx, p, x, scratch);
         auto go = [&](auto TT) {
             using T = decltype(TT);
             dispatch_src<T>(m, [&](auto src) {
                 band_tiled_launch<T, 1>(ctx, nz, PRows<T, decltype(src)>{src},
-                                        static_cast<T *>(z));
+                                        static_cast<T *>(z), cl);
             });
         };
         if (nz->prec == MM_F32) go(0.f);
@@ -1189,7 +1191,7 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
         auto go = [&](auto TT) {
             using T = decltype(TT);
             band_tiled_launch<T, R>(ctx, nz, TodRows<T>{static_cast<const T *>(y)},
-                                    static_cast<T *>(z));
+                                    static_cast<T *>(z), band_chunk_used(nz, R));
         };
         if (nz->prec == MM_F32) go(0.f);
         else go(0.0);
@@ -1301,9 +1303,11 @@ void build_band_tiles(mm_ctx *ctx, mm_noise *nz) {
 }
 
 // Measure candidates for each stage with HIP events and keep the fastest:
-//   stage 0, P: the grid size (grid-stride kernels);
+//   stage 0, P of several columns: the grid size, i.e. the samples per wave (the P of
+//     one column has no such choice: it is timed once);
 //   stage 1, direct band: the taps per LDS chunk (smaller chunks need less
-//     LDS per block, so more blocks share a CU);
+//     LDS per block, so more blocks share a CU); the kernel by rows has none and is
+//     timed once, and so is untouched an A that forms P inside the band;
 //   stage 2, P^T with several columns: visiting the pixels in the tiled
 //     order or ascending;
 //   stage 3 (flag MM_TUNE_FFT_BLOCK only), FFT: the overlap-save block length.
@@ -1349,7 +1353,8 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
         {
             double best = 1e30;
             int best_g = 0;
-            for (int mult : {2, 4, 8, 16, 32}) {
+            for (int mult : {0, 2, 4, 8, 16, 32}) {  // 0: the default
+                if (nrhs == 1 && mult > 0) break;
                 const int g = ctx->n_cu * mult;
                 p->p_blocks[li] = g;
                 const double ms =
@@ -1364,9 +1369,10 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
             const int def = band_chunk(nz->half_bw, nrhs, nz->prec, nz->band_small, nz->n_samp);
             double best = 1e30;
             int best_c = 0;
+            const bool rows = band_by_rows(nrhs, nz->half_bw, nz->n_samp);
             for (int div : {1, 2, 4, 8}) {
                 const int c = def / div / BT_OPT * BT_OPT;
-                if (c < BT_OPT || (div > 1 && c == def)) continue;
+                if (c < BT_OPT || (div > 1 && (c == def || rows))) continue;
                 nz->band_cl[li] = c;
                 const double ms = time_it([&]() { noise_apply_dev(ctx, nz, nrhs, y.ptr, z.ptr); });
                 note(1, c, ms);
