@@ -1,0 +1,33 @@
+"""The serving engine's byte budget against what it allocates."""
+import pytest
+
+import synth
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(32, (4, 2), 1 << 15, 128), (64, (4, 4), 1 << 17, 256)]
+
+
+def _server(ids, slots=4, budget=8 << 30):
+    from paper_1801_08937_amd import mapmaker as mm
+    srv = mm.Server(0, hbm_budget_bytes=budget, slots=slots, defl_k=0, iters_per_step=3)
+    ps = [synth.serve_strategy(s, 0, shapes=SHAPES[s], L=1 << 13) for s in ids]
+    for s, p in zip(ids, ps):
+        srv.add_strategy(s, dev(p.pix), dev(p.psi), p.n_pix_total, p.interval_start, p.filter_id,
+                         p.band, p.half_bw, grid_width=p.n_side)
+    return srv, ps
+
+
+@pytest.mark.parametrize("slots", [1, 8])
+def test_session_charge(slots):
+    """A session is charged its vectors (x, r, z, p, q and one column), three sets of
+    512 partial sums per column (p.q, ||r||^2, r.z), the TOD workspaces, and 64 partial
+    maps of P^T."""
+    from paper_1801_08937_amd import mapmaker as mm
+    srv, (p,) = _server([0], slots)
+    ctx = mm.Context(0)
+    n = ctx.pointing(dev(p.pix), dev(p.psi), p.n_pix_total, 3, 0).n
+    assert srv.memory(0)["session"] == (8 * n * (5 * slots + 1) + 3 * 8 * 512 * slots
+                                        + 2 * 8 * p.pix.size * slots + 8 * n * 64)
+    srv.close()
