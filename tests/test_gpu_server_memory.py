@@ -10,7 +10,9 @@ SHAPES = [(32, (4, 2), 1 << 15, 128), (64, (4, 4), 1 << 17, 256)]
 
 
 def _server(ids, slots=4, budget=8 << 30):
+    import torch
     from paper_1801_08937_amd import mapmaker as mm
+    assert torch.cuda.is_available()
     srv = mm.Server(0, hbm_budget_bytes=budget, slots=slots, defl_k=0, iters_per_step=3)
     ps = [synth.serve_strategy(s, 0, shapes=SHAPES[s], L=1 << 13) for s in ids]
     for s, p in zip(ids, ps):
