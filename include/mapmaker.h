@@ -28,8 +28,13 @@
  *    The caller owns every array it passes; the library never frees them and
  *    keeps no reference to them after the call returns.
  *  - Handles (mm_ctx, mm_pointing, mm_noise, mm_precond) own all memory the
- *    library allocates; mm_*_destroy releases it.  A handle must be destroyed
- *    before the context that created it.
+ *    library allocates; mm_*_destroy releases it.  The library keeps up to
+ *    1 GiB of released device memory per device for its next allocations, and
+ *    a context up to 512 MiB of its calls' temporaries; both go back to the
+ *    device with the device's last context, what is kept also when one of the
+ *    library's own allocations fails.  Other allocators of the process see it
+ *    as in use.  A server gives back what its builds and evictions release.
+ *    A handle must be destroyed before the context that created it.
  *  - Work is enqueued on the HIP stream given at context creation.  Calls that
  *    return host-visible results (counts, status, solve info) synchronise that
  *    stream; others are asynchronous with respect to the host.

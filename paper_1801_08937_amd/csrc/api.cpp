@@ -95,6 +95,16 @@ void dev_free(void *ptr, size_t bytes) {
     (void)hipFree(ptr);
 }
 
+void dev_pool_trim(int device) {
+    Pool &P = pool();
+    std::vector<void *> v;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        v = take_all(P, device);
+    }
+    for (void *q : v) (void)hipFree(q);
+}
+
 void dev_pool_ctx(int device, int delta) {
     Pool &P = pool();
     std::vector<void *> v;

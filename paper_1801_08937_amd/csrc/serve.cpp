@@ -23,7 +23,7 @@
 // is charged when the lane first admits a request, and stays (cached) while
 // memory allows; a request whose lane has no session and whose session does
 // not fit waits for memory, and idle sessions of other lanes are evicted (their
-// memory freed) to make room.  A request joining a session with a free slot
+// memory given back to the device, not kept by the library) to make room.  A request joining a session with a free slot
 // needs no new memory; one whose session is full waits for a slot.
 #include <atomic>
 #include <chrono>
@@ -250,6 +250,11 @@ extern "C" mm_status mm_server_add_strategy(mm_server *srv, int32_t id, int64_t 
         throw Error(MM_E_BUSY, "server: strategy footprint " + std::to_string(bytes) + " B + " +
                                    std::to_string(sess) +
                                    " B for a session exceeds the remaining budget");
+    // what the builds free, also those that fail, is outside the budget: given back
+    struct Trim {
+        int device;
+        ~Trim() { dev_pool_trim(device); }
+    } trim{srv->device};
     auto st = std::make_unique<Strategy>();
     st->id = id;
     check(mm_ctx_create(srv->device, nullptr, &st->ctx), nullptr, "server: context");
@@ -326,10 +331,12 @@ static void poll_build(Strategy &st) {
     const int b = st.build.load();
     if (b == BUILD_READY && !st.m2l) {
         st.join_builder();
+        dev_pool_trim(st.ctx->device);
         st.m2l = st.m2l_new;
         st.m2l_new = nullptr;
     } else if (b == BUILD_FAILED && st.builder.joinable()) {
         st.join_builder();
+        dev_pool_trim(st.ctx->device);
     }
 }
 
@@ -368,6 +375,7 @@ static void evict(mm_server *srv, Strategy &st, Lane &ln) {
             d->release();
         ++st.ctx->ws_gen;
     }
+    dev_pool_trim(srv->device);
 }
 
 // Make room for `need` bytes by evicting idle sessions other than `keep`;
@@ -527,4 +535,9 @@ extern "C" mm_status mm_server_memory(mm_server *srv, int32_t strategy, int64_t 
     return MM_OK;
 }
 
-extern "C" void mm_server_destroy(mm_server *srv) { delete srv; }
+extern "C" void mm_server_destroy(mm_server *srv) {
+    if (!srv) return;
+    const int device = srv->device;
+    delete srv;
+    dev_pool_trim(device);
+}

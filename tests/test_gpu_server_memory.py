@@ -33,3 +33,29 @@ def test_session_charge(slots):
     assert srv.memory(0)["session"] == (8 * n * (5 * slots + 1) + 3 * 8 * 512 * slots
                                         + 2 * 8 * p.pix.size * slots + 8 * n * 64)
     srv.close()
+
+
+def test_registration_leaves_no_more_than_charged():
+    """Registering a strategy while another context lives: the memory that its builds
+    release goes back to the device, so what is taken is what is charged (64 MiB for
+    the runtime's own and for rounding to blocks)."""
+    import torch
+    from paper_1801_08937_amd import mapmaker as mm
+    other = mm.Context(0)
+    torch.cuda.synchronize()
+    warm, _ = _server([0])  # kernels and libraries are loaded
+    warm.close()
+    p = synth.serve_strategy(1, 0, shapes=SHAPES[1], L=1 << 13)
+    pix, psi = dev(p.pix), dev(p.psi)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    srv = mm.Server(0, hbm_budget_bytes=8 << 30, slots=4, defl_k=0, iters_per_step=3)
+    srv.add_strategy(0, pix, psi, p.n_pix_total, p.interval_start, p.filter_id, p.band,
+                     p.half_bw, grid_width=p.n_side)
+    taken = free - torch.cuda.mem_get_info()[0]
+    print("taken", taken, "charged", srv.memory()["used"])
+    assert taken <= srv.memory()["used"] + (64 << 20)
+    srv.close()
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] <= 64 << 20
+    other.close()
