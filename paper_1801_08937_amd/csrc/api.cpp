@@ -17,9 +17,10 @@ namespace mm {
 // ------------------------------------------------------- device memory
 
 namespace {
+typedef std::multimap<size_t, void *> Blocks;  // by size
 struct Pool {
     std::mutex mu;
-    std::map<int, std::multimap<size_t, void *>> free;  // per device, by size
+    std::map<int, Blocks> free;  // per device
     std::map<int, size_t> kept;
     std::map<int, int> contexts;
 };
@@ -27,12 +28,19 @@ Pool &pool() {
     static Pool *p = new Pool();  // never destroyed: the runtime may go first at exit
     return *p;
 }
-std::vector<void *> take_all(Pool &P, int dev) {
-    std::vector<void *> v;
-    for (auto &e : P.free[dev]) v.push_back(e.second);
-    P.free[dev].clear();
-    P.kept[dev] = 0;
-    return v;
+// Gives back all blocks of a device; takes no host memory, as buffers are released
+// where host memory ran out too.  Returns whether there were any.
+bool give_back(Pool &P, int dev) noexcept {
+    Blocks v;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        const auto f = P.free.find(dev);
+        if (f == P.free.end()) return false;
+        v.swap(f->second);
+        P.kept.find(dev)->second = 0;
+    }
+    for (const auto &e : v) (void)hipFree(e.second);
+    return !v.empty();
 }
 }  // namespace
 
@@ -43,27 +51,23 @@ void *dev_alloc(size_t bytes, size_t *got) {
     Pool &P = pool();
     {
         std::lock_guard<std::mutex> lk(P.mu);
-        auto &f = P.free[dev];
-        auto it = f.lower_bound(bytes);
-        if (it != f.end() && it->first <= bytes + bytes / 8 + 4096) {
-            void *p = it->second;
-            *got = it->first;
-            P.kept[dev] -= it->first;
-            f.erase(it);
-            return p;
+        const auto f = P.free.find(dev);
+        if (f != P.free.end()) {
+            const auto it = f->second.lower_bound(bytes);
+            if (it != f->second.end() && it->first <= bytes + bytes / 8 + 4096) {
+                void *p = it->second;
+                *got = it->first;
+                P.kept.find(dev)->second -= it->first;
+                f->second.erase(it);
+                return p;
+            }
         }
     }
     void *p = nullptr;
     if (hipMalloc(&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        std::vector<void *> v;
-        {
-            std::lock_guard<std::mutex> lk(P.mu);
-            v = take_all(P, dev);
-        }
-        for (void *q : v) (void)hipFree(q);
         p = nullptr;
-        if (v.empty() || hipMalloc(&p, bytes) != hipSuccess) {
+        if (!give_back(P, dev) || hipMalloc(&p, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
@@ -72,7 +76,7 @@ void *dev_alloc(size_t bytes, size_t *got) {
     return p;
 }
 
-void dev_free(void *ptr, size_t bytes) {
+void dev_free(void *ptr, size_t bytes) noexcept {
     int cur = 0, dev = 0;
     (void)hipGetDevice(&cur);
     hipPointerAttribute_t at;
@@ -83,36 +87,43 @@ void dev_free(void *ptr, size_t bytes) {
     // no kernel may still use the block when it is handed out again
     if (dev != cur) (void)hipSetDevice(dev);
     const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();  // of this call: the next launch's check is not for it
     if (dev != cur) (void)hipSetDevice(cur);
     if (known && idle) {
         std::lock_guard<std::mutex> lk(P.mu);
-        if (P.contexts[dev] > 0 && P.kept[dev] + bytes <= POOL_MAX_BYTES) {
-            P.free[dev].emplace(bytes, ptr);
-            P.kept[dev] += bytes;
-            return;
+        const auto c = P.contexts.find(dev);
+        if (c != P.contexts.end() && c->second > 0) {
+            size_t &kept = P.kept.find(dev)->second;
+            if (kept + bytes <= POOL_MAX_BYTES) {
+                try {
+                    P.free.find(dev)->second.emplace(bytes, ptr);
+                    kept += bytes;
+                    return;
+                } catch (...) {  // no host memory for the entry
+                }
+            }
         }
     }
     (void)hipFree(ptr);
 }
 
-void dev_pool_trim(int device) {
-    Pool &P = pool();
-    std::vector<void *> v;
-    {
-        std::lock_guard<std::mutex> lk(P.mu);
-        v = take_all(P, device);
-    }
-    for (void *q : v) (void)hipFree(q);
-}
+void dev_pool_trim(int device) noexcept { (void)give_back(pool(), device); }
 
 void dev_pool_ctx(int device, int delta) {
     Pool &P = pool();
-    std::vector<void *> v;
+    bool last = false;
     {
         std::lock_guard<std::mutex> lk(P.mu);
-        if ((P.contexts[device] += delta) <= 0) v = take_all(P, device);
+        if (delta > 0) {  // all of a device's entries, so that nothing later needs host memory
+            P.kept[device];  // first: where a device has an entry in free, it has one here
+            P.free[device];
+            P.contexts[device] += delta;
+        } else {
+            const auto c = P.contexts.find(device);
+            last = c != P.contexts.end() && (c->second += delta) <= 0;
+        }
     }
-    for (void *q : v) (void)hipFree(q);
+    if (last) (void)give_back(P, device);
 }
 
 // ------------------------------------------------------------ profiler

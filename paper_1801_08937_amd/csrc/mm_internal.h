@@ -43,9 +43,9 @@ struct Error : std::runtime_error {
 // context goes, or when a hipMalloc fails.  Any thread may call them.
 constexpr size_t POOL_MAX_BYTES = (size_t)1 << 30;
 void *dev_alloc(size_t bytes, size_t *got);  // nullptr when there is no memory
-void dev_free(void *ptr, size_t bytes);      // bytes: what dev_alloc gave
+void dev_free(void *ptr, size_t bytes) noexcept;  // bytes: what dev_alloc gave
 void dev_pool_ctx(int device, int delta);    // a context was created (+1) or destroyed (-1)
-void dev_pool_trim(int device);              // gives back what is kept for the device
+void dev_pool_trim(int device) noexcept;     // gives back what is kept for the device
 
 // Owning device buffer.
 struct DBuf {

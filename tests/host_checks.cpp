@@ -2,7 +2,9 @@
 // allocation fails: one per argument, exit status 0 = passed.  Linked against
 // libmapmaker.so by test_host_checks.py.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <unistd.h>
 
 #include "mm_internal.h"
@@ -11,6 +13,17 @@ namespace mm {
 void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch &sc,
                              const int32_t **dir_cnt);
 }
+
+namespace {
+bool no_host_memory = false;
+}
+void *operator new(std::size_t n) {
+    void *p = no_host_memory ? nullptr : std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -163,6 +176,25 @@ void fft_block() {
     EXPECT(code([&] { mm::noise_apply_dev(&ctx, &nz, 1, nullptr, nullptr); }) == MM_E_OOM);
 }
 
+// Buffers and contexts are released in destructors and behind a C interface, where no
+// exception may leave: nothing there takes host memory.
+void release_without_host_memory() {
+    mm::dev_pool_ctx(0, 1);
+    mm::DBuf *b = new mm::DBuf();
+    pretend(*b, 4096);
+    bool threw = false;
+    no_host_memory = true;
+    try {
+        b->release();
+        mm::dev_pool_ctx(0, -1);
+    } catch (...) {
+        threw = true;
+    }
+    no_host_memory = false;
+    EXPECT(!threw);
+    EXPECT(noexcept(mm::dev_free(nullptr, 0)) && noexcept(mm::dev_pool_trim(0)));
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -175,6 +207,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "release")) release_without_host_memory();
     else if (!std::strcmp(what, "fft_block")) fft_block();
     else if (!std::strcmp(what, "reduction_blocks")) reduction_blocks();
     else {
