@@ -1513,6 +1513,7 @@ extern "C" mm_status mm_solve(mm_ctx *ctx, const mm_pointing *p, const mm_noise 
     PcgWork w;
     w.flexible = (flags & MM_SOLVE_FLEXIBLE) != 0;
     w.alloc(n, R, &tmp);
+    MM_CHECK(max_iter < INT32_MAX, MM_E_OOM, "solve: no memory for a history of 2^31 iterations");
     double *hist = tmp.get<double>((int64_t)(max_iter + 1) * R);
     w.sd.hist = hist;
     w.sd.hist_len = max_iter + 1;

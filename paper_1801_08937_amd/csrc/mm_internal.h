@@ -162,6 +162,8 @@ class Scratch {
         }
     }
     template <typename T> T *get(int64_t n) {
+        if (n < 0 || n > (int64_t)1 << 50)  // a size that overflowed on the way here
+            throw Error(MM_E_OOM, "scratch of " + std::to_string(n) + " elements");
         const size_t b = (sizeof(T) * (size_t)(n > 0 ? n : 1) + 255) / 256 * 256;
         used += b;
         if (ctx->build_off + b <= ctx->build_ws.bytes) {

@@ -195,6 +195,23 @@ void release_without_host_memory() {
     EXPECT(noexcept(mm::dev_free(nullptr, 0)) && noexcept(mm::dev_pool_trim(0)));
 }
 
+// A count of elements that overflowed is refused, not taken as one element.
+void scratch_sizes() {
+    for (int64_t n : {(int64_t)-1, (int64_t)-64, -((int64_t)1 << 37), (int64_t)1 << 61}) {
+        mm_ctx ctx;
+        pretend(ctx.build_ws, 1 << 20);
+        bool threw = false;
+        try {
+            mm::Scratch sc(&ctx);
+            (void)sc.get<double>(n);
+        } catch (const mm::Error &e) {
+            threw = e.code == MM_E_OOM;
+        }
+        EXPECT(threw);
+        EXPECT(ctx.build_off == 0);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -207,6 +224,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "scratch_sizes")) scratch_sizes();
     else if (!std::strcmp(what, "release")) release_without_host_memory();
     else if (!std::strcmp(what, "fft_block")) fft_block();
     else if (!std::strcmp(what, "reduction_blocks")) reduction_blocks();
