@@ -174,8 +174,10 @@ mm_status mm_pair_sum_diff(mm_ctx *ctx, int64_t n, mm_precision prec, const void
  * Errors: MM_E_INVALID (negative width); MM_E_OOM, which leaves the pointing
  * usable, without a grid and with P^T one wave per pixel. */
 mm_status mm_pointing_set_grid(mm_ctx *ctx, mm_pointing *p, int32_t width);
-/* Map copies the single-column P gathers from: 0 without a grid (one copy
- * in compact id order), else 1 to 4.  [host] output. */
+/* Map copies laid out for the single-column P: 0 without a grid, else 1 to 4
+ * (0 for an I or QU pointing with too few samples for them).  P gathers from
+ * them where that repays packing them, from 2^22 samples and 256 per pixel on,
+ * else from x itself.  [host] output. */
 mm_status mm_pointing_p_layout(const mm_pointing *p, int32_t *copies);
 /* n_obs (observed pixels) and n_valid (unflagged samples).  [host] outputs. */
 mm_status mm_pointing_counts(const mm_pointing *p, int32_t *n_obs, int64_t *n_valid);
@@ -657,8 +659,11 @@ mm_status mm_autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int32_t nrhs, i
 /* ---------------------------------------------------------- profiling aid */
 
 /* When on, each kernel of mm_apply_A / mm_solve is bracketed by HIP events on
- * the context's stream and its time accumulated per stage (P, N^-1, P^T,
- * precond, vector ops).  Stage names and totals via mm_profile_read. */
+ * the context's stream and its time accumulated per stage: "P", "Ninv_fft",
+ * "Ninv_band" or "Ninv_poly", "PT", "precond", "gemv", "vec".  Where A forms P
+ * inside the next kernel there is no "P": its time is in "Ninv_band" (direct
+ * band), or in "P_Ninv_poly", P and the first pass of a template filter.  Stage
+ * names and totals via mm_profile_read. */
 mm_status mm_profile_enable(mm_ctx *ctx, int on);
 /* names [host] receives up to max entries of "name" (each <= 31 chars + NUL,
  * 32 bytes per entry), ms [host] total milliseconds, calls [host] launches.

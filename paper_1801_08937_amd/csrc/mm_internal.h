@@ -268,7 +268,7 @@ struct mm_noise {
     mm::DBuf tile_pref;
     std::vector<int64_t> h_tile_pref;
     int32_t band_cl[7] = {0, 0, 0, 0, 0, 0, 0};  // tuned taps per LDS chunk per log2(nrhs); 0 = default
-    bool band_small = false;  // one column in 512-sample tiles of 64 threads (short streams)
+    bool band_small = false;  // one column in 512-sample tiles of 128 threads (short streams)
     // FFT: per-filter packed spectrum and block table
     int32_t fft_n = 0;       // block length set or reported (mm_noise_fft_block)
     bool fft_auto = false;   // picked by the library: fft.n may be another length

@@ -4,10 +4,11 @@
 // noise_fft.hip.
 //
 // Layouts: map x[(3 j + a) R + r] (FP64); TOD y[t R + r] (T = float or double).
-// A wavefront's 64 lanes are split into G = 64 / R sample groups of R columns,
-// so one wave step touches G consecutive samples x R columns: contiguous TOD
-// rows.  Each column is computed with the same arithmetic and order whatever
-// the other columns hold.
+// With several columns a lane holds two of them (P, P^T from 8 columns) or one (P^T of
+// 2 and 4, the direct band), and a wave's lanes are split into sample groups of R
+// columns, so one wave step touches consecutive samples x R columns: contiguous TOD
+// rows.  Each column is computed with the same arithmetic and order whatever the other
+// columns hold.
 #include <algorithm>
 #include <functional>
 #include <type_traits>
@@ -109,11 +110,9 @@ __global__ void __launch_bounds__(BS) k_apply_P(const int32_t *__restrict__ jpix
     }
 }
 
-// Single column: the map is first packed as 32-byte records (I, Q, U, 0) so
-// each sample's gather is two aligned 16-byte loads instead of three 8-byte
-// ones.
-// 32-byte records (I, Q, U, 0) at each of the n_copies slots of every pixel
-// (slot = NULL: one copy at the compact id).
+// The copies of an IQU map for the FP32 P of one column: 32-byte records (I, Q, U, 0)
+// at each of the n_copies slots of every pixel, so that a sample's gather is two aligned
+// 16-byte loads instead of three 8-byte ones.
 __global__ void __launch_bounds__(BS) k_pack_map(const double *__restrict__ x, int32_t n_obs,
                                                  int n_copies, const int32_t *__restrict__ slot,
                                                  double2 *__restrict__ x4) {
@@ -122,15 +121,15 @@ __global__ void __launch_bounds__(BS) k_pack_map(const double *__restrict__ x, i
         const double2 iq = make_double2(x[3 * j], x[3 * j + 1]);
         const double2 u0 = make_double2(x[3 * j + 2], 0.0);
         for (int g = 0; g < n_copies; ++g) {
-            const int64_t s = slot ? slot[(int64_t)g * n_obs + j] : j;
+            const int64_t s = slot[(int64_t)g * n_obs + j];
             x4[2 * s] = iq;
             x4[2 * s + 1] = u0;
         }
     }
 }
 
-// Split map for P: I in xi, (Q, U) in xqu, at each of the n_copies slots of
-// every pixel (slot = NULL: one copy at the compact id).
+// The copies for the FP64 P: I in xi, (Q, U) in xqu, at each of the n_copies slots of
+// every pixel.
 __global__ void __launch_bounds__(BS) k_pack_map_split(const double *__restrict__ x,
                                                        int32_t n_obs, int n_copies,
                                                        const int32_t *__restrict__ slot,
@@ -141,7 +140,7 @@ __global__ void __launch_bounds__(BS) k_pack_map_split(const double *__restrict_
         const double vi = x[3 * c];
         const double2 vqu = make_double2(x[3 * c + 1], x[3 * c + 2]);
         for (int g = 0; g < n_copies; ++g) {
-            const int64_t s = slot ? slot[(int64_t)g * n_obs + c] : c;
+            const int64_t s = slot[(int64_t)g * n_obs + c];
             xi[s] = vi;
             xqu[s] = vqu;
         }
@@ -1093,7 +1092,7 @@ static void band_tiled_launch(mm_ctx *ctx, const mm_noise *nz, const Rows &rows,
                                                       lam, cl, rows, z);
     };
     if constexpr (R == 1)
-        if (nz->band_small)  // short single streams: 64-thread blocks
+        if (nz->band_small)  // short single streams
             return run(k_band_tiled<T, R, BAND_SMALL_NT, BAND_SMALL_OPT, Rows>, BAND_SMALL_NT);
     run(k_band_tiled<T, R, BS, BT_OPT, Rows>, BS);
 }
