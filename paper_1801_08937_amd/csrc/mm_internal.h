@@ -356,6 +356,15 @@ inline int64_t p_wave_samples(int64_t n, int step, int64_t blocks) {
 }
 void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, double *x,
                   char *scratch = nullptr);
+// The P^T of a wave or block per pixel: one column per lane, two columns per lane, or
+// the latter with four waves per pixel (measured beside k_apply_PT_cols).
+enum class PtForm { LANES, COLUMNS, BLOCK };
+inline PtForm pt_form(int32_t n_obs, int64_t n_valid, int nrhs, int n_cu) {
+    const int64_t work = n_valid * nrhs;  // n_obs h R
+    if (nrhs < 8 || work < 256 * (int64_t)n_obs) return PtForm::LANES;
+    return n_obs < 8 * (int64_t)n_cu && work >= 4096 * (int64_t)n_obs ? PtForm::BLOCK
+                                                                      : PtForm::COLUMNS;
+}
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
 int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp);
 void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod_rm, void *y,

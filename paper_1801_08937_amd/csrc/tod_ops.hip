@@ -354,12 +354,18 @@ __global__ void __launch_bounds__(BS) k_pack_map_nc(const double *__restrict__ x
 // P^T of several columns: a lane holds two columns of an entry, 128 / R entries per
 // wave side by side and PT_U of those steps in flight.  A pixel is a wave's (S = 1),
 // or a block's (S = 4, each wave a quarter of its entries, added in order) where a wave
-// per pixel leaves most of the chip idle.  Against one column per lane (k_apply_PT),
-// us: 65,536 samples on 1,024 pixels x 64 columns 11.1 -> 7.0; 1M on 4,096 x 32
-// 55 -> 44, I x 64 229 -> 95; 8.4M on 16,384 x 8 151 -> 135.  With four columns that
-// form is the faster one (96 against 104 us).  Bound by HBM and the gathers of z.
+// per pixel leaves most of the chip idle.  Bound by HBM and the gathers of z.  Which
+// kernel, by the pixels and by hits per pixel times R, h R (pt_form), us, IQU FP64, one
+// column per lane (k_apply_PT) / S = 1 / S = 4:
+//   h R = 128: 65,536 samples on 4,096 pixels x 8 3.9 / 4.9 / 12.6; 1M on 65,536 x 8
+//     28 / 38 / 158; 256: 65,536 on 4,096 x 16 4.5 / 4.5 / 10.7, 262,144 on 16,384 x 16
+//     12.1 / 10.5 / 34;
+//   2,048: 65,536 on 1,024 x 32 5.8 / 5.1 / 4.8, 262,144 on 1,024 x 8 7.2 / 5.6 / 6.0;
+//     4,096: 65,536 on 1,024 x 64 14 / 10.6 / 6.8, 262,144 on 1,024 x 16 15 / 9.3 / 6.8;
+//   4,096 pixels: 1M x 64 123 / 95 / 99, 262,144 x 64 24 / 21 / 21; 256 pixels: 1M x 64
+//     903 / 596 / 169.
+// With four columns one column per lane is the faster form (96 against 104 us).
 constexpr int PT_U = 4;
-constexpr int PT_SPLIT_WAVES = 16;  // per CU
 constexpr int PT_MIN_COLS = 8;
 template <typename T, int R, int NC, int S>
 __global__ void __launch_bounds__(BS) k_apply_PT_cols(
@@ -1005,9 +1011,8 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
     const int po = p->pt_order[log2i(nrhs)];
     const bool tiled = p->seg_order.ptr && (nrhs == 1 || p->nc != 3 || po != 0);
     const int32_t *order = tiled ? p->seg_order.as<int32_t>() : nullptr;
-    // a block per pixel where a wave per pixel leaves most of the chip idle
-    const bool cols = nrhs >= PT_MIN_COLS, split = p->n_obs < PT_SPLIT_WAVES * (int64_t)ctx->n_cu;
-    int64_t nb = cols && split ? p->n_obs : (p->n_obs + 3) / 4;
+    const PtForm form = pt_form(p->n_obs, p->n_valid, nrhs, ctx->n_cu);
+    int64_t nb = form == PtForm::BLOCK ? p->n_obs : (p->n_obs + 3) / 4;
     if (nb >= 64) nb = (nb + 7) & ~(int64_t)7;
     dispatch_r(nrhs, [&](auto RR) {
         constexpr int R = decltype(RR)::value;
@@ -1021,9 +1026,11 @@ void apply_PT_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *z, do
                                                         p->perm.as<int32_t>(), ws, p->n_obs,
                                                         order, static_cast<const T *>(z), x);
             };
-            if constexpr (R < PT_MIN_COLS) run(k_apply_PT<T, R, NC>);
-            else if (split) run(k_apply_PT_cols<T, R, NC, 4>);
-            else run(k_apply_PT_cols<T, R, NC, 1>);
+            if constexpr (R >= PT_MIN_COLS) {
+                if (form == PtForm::BLOCK) return run(k_apply_PT_cols<T, R, NC, 4>);
+                if (form == PtForm::COLUMNS) return run(k_apply_PT_cols<T, R, NC, 1>);
+            }
+            run(k_apply_PT<T, R, NC>);
         };
         dispatch_t_nc(p, go);
     });

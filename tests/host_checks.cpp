@@ -212,6 +212,31 @@ void scratch_sizes() {
     }
 }
 
+// The P^T kernel of several columns: few hits per pixel do not fill the steps of the
+// two-column kernel (65,536 samples on 4,096 pixels x 8 columns took 3.2 times as long
+// there), nor a quarter of them those of a block per pixel.
+void pt_forms() {
+    using mm::PtForm;
+    const auto f = [](int32_t n_obs, int64_t hits, int R) {
+        return mm::pt_form(n_obs, hits * n_obs, R, 256);
+    };
+    EXPECT(f(4096, 16, 8) == PtForm::LANES && f(1024, 16, 8) == PtForm::LANES);
+    EXPECT(f(65536, 16, 8) == PtForm::LANES && f(4096, 4, 32) == PtForm::LANES);
+    EXPECT(f(1024, 10000, 4) == PtForm::LANES);
+    EXPECT(f(4096, 16, 16) == PtForm::COLUMNS && f(1024, 64, 16) == PtForm::COLUMNS);
+    EXPECT(f(4096, 256, 64) == PtForm::COLUMNS && f(65536, 2048, 64) == PtForm::COLUMNS);
+    EXPECT(f(1024, 64, 64) == PtForm::BLOCK && f(1, 512, 8) == PtForm::BLOCK);
+    for (int R = 1; R <= 64; R *= 2)  // more hits never go back to fewer waves
+        for (int32_t n_obs : {1, 300, 2047, 2048, 100000}) {
+            int last = 0;
+            for (int64_t h = 1; h < 100000; h += 1 + h / 9) {
+                const int v = (int)f(n_obs, h, R);
+                EXPECT(v >= last);
+                last = v;
+            }
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -224,6 +249,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "pt_forms")) pt_forms();
     else if (!std::strcmp(what, "scratch_sizes")) scratch_sizes();
     else if (!std::strcmp(what, "release")) release_without_host_memory();
     else if (!std::strcmp(what, "fft_block")) fft_block();
