@@ -188,7 +188,8 @@ mm_status mm_pointing_counts(const mm_pointing *p, int32_t *n_obs, int64_t *n_va
  * the one-wave-per-pixel form.  Each pixel sums its samples in time order
  * within a segment (and scan direction), then those partial sums in order;
  * the layout is a function of the pointing (n_obs, n_valid, the directions
- * found), never of the device.  [host] outputs. */
+ * found), never of the device.  An I or QU pointing whose pixels of a slice are
+ * hit too unequally takes a wave per pixel all the same.  [host] outputs. */
 mm_status mm_pointing_pt_layout(const mm_pointing *p, int32_t *slices, int32_t *segments);
 /* Hit counts per global pixel and the observed pixels' global ids.
  *   hits [device] int32[n_pix_total]; obs_pix [device] int32[n_obs] (either may be NULL) */

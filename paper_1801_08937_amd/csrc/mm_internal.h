@@ -330,6 +330,18 @@ inline unsigned tile_key_bits(int32_t n_pix, int32_t width, int32_t tile) {
     const int64_t tiles_y = (n_pix - 1) / width / tile + 1;
     return 24 + bits((uint64_t)(tiles_x * tiles_y));
 }
+// Whether the sliced P^T (entries with padding: the longest lane of each wave) is taken
+// for a pointing of nc components that has waves enough for it: IQU always.  I and QU,
+// whose sums read less per sample, only where the lanes of a wave have about equally
+// many samples: one wave per pixel and sliced, us, QU FP64, with entries / n_valid:
+// 2^23 samples on 128 x 128 pixels, 1.02: 43 and 37, 1.6: 70 and 69 (I 41 and 50), 4.7:
+// 104 and 182; on 256 x 256, 1.3: 51 and 57, 4.4: 74 and 242; from 2^24 on z no longer
+// stays in the cache: 2^24 on 128 x 128, 1.6: 180 and 114, 4.7: 284 and 301; 2^25 on
+// 256 x 256, 1.3: 400 and 216, 4.5: 515 and 783.
+inline bool slices_pay(int nc, int64_t n_samp, int64_t n_valid, int64_t entries) {
+    if (nc == 3) return true;
+    return 5 * entries <= (n_samp >= (int64_t)1 << 24 ? 10 : 6) * n_valid;
+}
 // (Re)build everything that depends on the grid hint (width 0 = none): the visiting
 // order of the one-wave-per-pixel P^T, P's map copies and the sliced P^T layout.
 void pointing_layout_device(mm_ctx *ctx, mm_pointing *p, int32_t width);

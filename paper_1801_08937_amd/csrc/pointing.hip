@@ -585,7 +585,8 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
     hipStream_t s = ctx->stream;
     p->sl_G = p->sl_S = 0;
     p->sl_D = 1;
-    // a rebuilt layout takes the old one's buffers where they are large enough
+    // a rebuilt layout takes the old one's buffers where they are large enough; without
+    // sl_perm, P^T takes a wave per pixel
     auto drop = [&]() {
         p->sl_pix.release();
         p->sl_base.release();
@@ -652,6 +653,10 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
     MM_HIP(hipMemcpyAsync(&total, p->sl_base.as<int64_t>() + n_waves, sizeof(int64_t),
                           hipMemcpyDeviceToHost, s));
     MM_HIP(hipStreamSynchronize(s));
+    p->sl_G = G;
+    p->sl_S = S;
+    p->sl_D = D;
+    if (!slices_pay(p->nc, p->n_samp, nv, total)) return drop();
     p->sl_perm.alloc(sizeof(int32_t) * (size_t)total);
     if (p->nc > 1) p->sl_w.alloc(sizeof(double) * (size_t)total);  // psi, or two FP32 weights
     const unsigned fb = (unsigned)std::min<int64_t>((n_waves * 64 + BS - 1) / BS, 16384);
@@ -670,9 +675,6 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
                                             n_waves, p->sl_perm.as<int32_t>(),
                                             p->sl_w.as<double>());
     MM_HIP(hipGetLastError());
-    p->sl_G = G;
-    p->sl_S = S;
-    p->sl_D = D;
 }
 
 // A failure leaves the pointing without the layouts (as with no grid and too few waves

@@ -58,7 +58,7 @@ void gridded(mm_pointing &p) {
     p.sl_G = 256 * 3;
     p.sl_S = 5;
     p.sl_D = 3;
-    pretend(p.sl_pix, 4 * 64 * p.sl_G);
+    for (mm::DBuf *b : {&p.sl_pix, &p.sl_base, &p.sl_perm, &p.sl_w}) pretend(*b, 1 << 20);
 }
 
 // Set-up of a new grid fails at its first allocation, or at the first one inside the
@@ -237,6 +237,18 @@ void pt_forms() {
         }
 }
 
+// The sliced P^T of I and QU only with little padding (seven times slower at 4.4 times
+// the entries, and of no bound in memory); IQU always.
+void slices() {
+    const int64_t n = (int64_t)1 << 23, m = (int64_t)1 << 25;
+    for (int nc : {1, 2}) {
+        EXPECT(mm::slices_pay(nc, n, n / 2, n / 2) && mm::slices_pay(nc, n, 1000, 1200));
+        EXPECT(!mm::slices_pay(nc, n, 1000, 1201) && !mm::slices_pay(nc, n, n / 2, 3 * n));
+        EXPECT(mm::slices_pay(nc, m, 1000, 2000) && !mm::slices_pay(nc, m, 1000, 2001));
+    }
+    EXPECT(mm::slices_pay(3, n, n, 64 * n));
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -249,6 +261,7 @@ int main(int argc, char **argv) {
     if (!std::strcmp(what, "regrid")) regrid();
     else if (!std::strcmp(what, "p_launch")) p_launch();
     else if (!std::strcmp(what, "tile_keys")) tile_keys();
+    else if (!std::strcmp(what, "slices")) slices();
     else if (!std::strcmp(what, "pt_forms")) pt_forms();
     else if (!std::strcmp(what, "scratch_sizes")) scratch_sizes();
     else if (!std::strcmp(what, "release")) release_without_host_memory();

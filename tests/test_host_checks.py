@@ -26,7 +26,7 @@ def host_checks(tmp_path_factory):
 
 @pytest.mark.parametrize("check", ["regrid", "p_launch", "tile_keys", "reduction_blocks",
                                    "fft_block", "release", "scratch_sizes",
-                                   "pt_forms"])
+                                   "pt_forms", "slices"])
 def test_host_check(host_checks, check):
     r = subprocess.run([host_checks, check], capture_output=True, text=True, timeout=60)
     if r.returncode == 77:
