@@ -550,7 +550,7 @@ extern "C" mm_status mm_pointing_set_grid(mm_ctx *ctx, mm_pointing *p, int32_t w
 
 extern "C" mm_status mm_pointing_p_layout(const mm_pointing *p, int32_t *copies) {
     if (!p || !copies) return MM_E_INVALID;
-    *copies = p->p_j.ptr ? p->p_copies : 0;
+    *copies = p->p_copies;
     return MM_OK;
 }
 

@@ -208,7 +208,8 @@ struct mm_pointing {
     mm::DBuf psi;  // f64[n_samp] angles (FP64 form only)
     // Map copies of the single-column P (with a grid): p_copies copies,
     // one per scan direction found, each ordered by first touch along its
-    // samples.  p_slot[g n_obs + c] is pixel c's slot in copy g (counted over
+    // samples; p_slot and p_chunk_grp only where P or the sliced P^T takes them,
+    // p_j where P does.  p_slot[g n_obs + c] is pixel c's slot in copy g (counted over
     // all copies) and p_j[t] the slot of sample t's pixel in its chunk's copy
     // (-1 flagged), so the pixels a wave gathers along the scan share cache
     // lines.  Without a grid the slot is the compact id and there is one copy.
@@ -329,6 +330,14 @@ inline unsigned tile_key_bits(int32_t n_pix, int32_t width, int32_t tile) {
     const int64_t tiles_x = ((int64_t)width + tile - 1) / tile;
     const int64_t tiles_y = (n_pix - 1) / width / tile + 1;
     return 24 + bits((uint64_t)(tiles_x * tiles_y));
+}
+// Whether the one-column P gathers from map copies: that saves cache lines per sample,
+// packing them costs a launch and a pass over copies x n_obs.  It pays from 2^22 samples and 256
+// per pixel on (us, copies / x itself, IQU FP64, three directions: 64 x 64 pixels, 2^20
+// samples 8.3 / 6.2; 128 x 128, 2^21 14.0 / 12.4, 2^23 38.8 / 43.6; 256 x 256, 2^23 44.7 /
+// 42.5, 2^25 138 / 160, 2^27 520 / 632).
+inline bool gathers_copies(int64_t n_samp, int32_t n_obs) {
+    return n_samp >= (int64_t)1 << 22 && n_samp >= 256 * (int64_t)n_obs;
 }
 // Whether the sliced P^T (entries with padding: the longest lane of each wave) is taken
 // for a pointing of nc components that has waves enough for it: IQU always.  I and QU,

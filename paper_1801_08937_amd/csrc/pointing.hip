@@ -444,6 +444,31 @@ void exclusive_sum(mm_ctx *ctx, Scratch &tmp, const T *in, T *out, int64_t n) {
 // each pixel.  The values gathered, hence P's output, do not depend on it.
 }  // namespace
 
+// Time segments for the sliced P^T: enough (segment, slice) waves to fill
+// the device (8,192 = 32 per CU on 256 CUs), and at least one segment per 2^22
+// samples of time, so that the stretch of the TOD the resident waves gather from at
+// any moment stays small enough for the L2 (at 1.34e8 samples: 32 segments,
+// measured best among 8..128); at most 64, and at least 32 entries per lane,
+// segment and scan direction on average.  A function of the problem size only, so the
+// summation order (and the bits of the result) does not depend on the device.
+static int32_t slice_segments(int64_t n_samp, int64_t n_valid, int32_t n_obs, int32_t G,
+                              int32_t D) {
+    int64_t S = 8192 / G;
+    if (S < (n_samp >> 22)) S = n_samp >> 22;
+    if (S > 64) S = 64;
+    const int64_t cap = n_obs > 0 ? n_valid / n_obs / 32 / D : 0;
+    if (S > cap) S = cap;
+    return (int32_t)(S < 1 ? 1 : S);
+}
+
+// Whether the sliced P^T has waves enough: below about 2,048 the one-wave-per-pixel
+// kernel is the faster one.
+static bool slice_waves(const mm_pointing *p) {
+    const int32_t G0 = (p->n_obs + 63) / 64;
+    return p->n_valid > 0 &&
+           (int64_t)G0 * slice_segments(p->n_samp, p->n_valid, p->n_obs, G0, 1) >= 2048;
+}
+
 void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch &sc,
                              const int32_t **dir_cnt) {
     hipStream_t s = ctx->stream;
@@ -504,6 +529,15 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch
             return;
         }
     }
+    // the slots and the chunks' directions only where P gathers from the copies or P^T
+    // is cut by them
+    const bool gathers = gathers_copies(n, n_obs);
+    if (!gathers && !slice_waves(p)) {
+        p->p_slot.release();
+        p->p_chunk_grp.release();
+        p->p_copies = G;
+        return;
+    }
     // each chunk to the copy of the nearest kept direction (angles mod 180),
     // undirected chunks to the most common one
     std::vector<int32_t> grp(n_chunks, 0);
@@ -542,10 +576,12 @@ void pointing_p_slots_device(mm_ctx *ctx, mm_pointing *p, int32_t width, Scratch
     p->p_slot.alloc(sizeof(int32_t) * total);
     k_rank<<<(unsigned)((total + BS - 1) / BS), BS, 0, s>>>(order, (int32_t)total,
                                                            p->p_slot.as<int32_t>());
-    p->p_j.alloc(sizeof(int32_t) * n);
-    k_slot_of_sample_g<<<grid_for(n), BS, 0, s>>>(p->j.as<int32_t>(), dgrp.as<int32_t>(),
-                                                  p->p_slot.as<int32_t>(), n, n_obs,
-                                                  p->p_j.as<int32_t>());
+    if (gathers) {
+        p->p_j.alloc(sizeof(int32_t) * n);
+        k_slot_of_sample_g<<<grid_for(n), BS, 0, s>>>(p->j.as<int32_t>(), dgrp.as<int32_t>(),
+                                                      p->p_slot.as<int32_t>(), n, n_obs,
+                                                      p->p_j.as<int32_t>());
+    }
     MM_HIP(hipGetLastError());
     p->p_copies = G;
     *dir_cnt = dcnt;
@@ -560,23 +596,6 @@ static void pointing_tile_order(mm_ctx *ctx, mm_pointing *p, int32_t width, int3
     k_tile_keys<<<(n_obs + BS - 1) / BS, BS, 0, ctx->stream>>>(p->obs_pix.as<int32_t>(), n_obs,
                                                               width, tile, keys, vals);
     sort_pairs(ctx, sc, keys, ko, vals, order, n_obs, tile_key_bits(p->n_pix_total, width, tile));
-}
-
-// Time segments for the sliced P^T: enough (segment, slice) waves to fill
-// the device (8,192 = 32 per CU on 256 CUs), and at least one segment per 2^22
-// samples of time, so that the stretch of the TOD the resident waves gather from at
-// any moment stays small enough for the L2 (at 1.34e8 samples: 32 segments,
-// measured best among 8..128); at most 64, and at least 32 entries per lane,
-// segment and scan direction on average.  A function of the problem size only, so the
-// summation order (and the bits of the result) does not depend on the device.
-static int32_t slice_segments(int64_t n_samp, int64_t n_valid, int32_t n_obs, int32_t G,
-                              int32_t D) {
-    int64_t S = 8192 / G;
-    if (S < (n_samp >> 22)) S = n_samp >> 22;
-    if (S > 64) S = 64;
-    const int64_t cap = n_obs > 0 ? n_valid / n_obs / 32 / D : 0;
-    if (S > cap) S = cap;
-    return (int32_t)(S < 1 ? 1 : S);
 }
 
 // dir_cnt: samples per virtual pixel (with map copies of several directions).
@@ -595,9 +614,8 @@ static void pointing_slices_device(mm_ctx *ctx, mm_pointing *p, int32_t width, S
     };
     const int32_t n_obs = p->n_obs;
     if (n_obs == 0 || p->n_valid == 0) return drop();
+    if (!slice_waves(p)) return drop();
     const int32_t G0 = (n_obs + 63) / 64;
-    // below ~2,048 waves the one-wave-per-pixel kernel is the faster one
-    if ((int64_t)G0 * slice_segments(p->n_samp, p->n_valid, n_obs, G0, 1) < 2048) return drop();
     // per scan direction when the map copies of P are there
     const bool dirs = width > 0 && p->p_copies > 0 && p->p_chunk_grp.ptr;
     const int32_t D = dirs ? p->p_copies : 1;

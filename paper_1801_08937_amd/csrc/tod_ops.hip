@@ -865,13 +865,7 @@ PMap p_map_dev(mm_ctx *ctx, const mm_pointing *p, const double *x, char *scratch
     const bool f32 = p->prec == MM_F32;
     PMap m{};
     m.w = p->nc == 1 ? nullptr : (f32 ? p->w.ptr : p->psi.ptr);
-    // Gathering from copies saves cache lines per sample, packing them costs a
-    // launch and a pass over copies x n_obs: it pays from 2^22 samples and 256
-    // per pixel on (us, copies / x itself, IQU FP64, three directions: 64 x 64
-    // pixels, 2^20 samples 8.3 / 6.2; 128 x 128, 2^21 14.0 / 12.4, 2^23 38.8 / 43.6;
-    // 256 x 256, 2^23 44.7 / 42.5, 2^25 138 / 160, 2^27 520 / 632).
-    if (p->p_j.ptr == nullptr || p->n_samp < ((int64_t)1 << 22) ||
-        p->n_samp < 256 * (int64_t)p->n_obs) {
+    if (p->p_j.ptr == nullptr) {
         m.kind = p->nc;
         m.slot = p->j.as<int32_t>();
         m.xm = x;
@@ -965,7 +959,7 @@ size_t apply_P_scratch_bytes(const mm_pointing *p, int nrhs) {
     // I and QU gather from x itself without a grid, else from NC-value copies
     if (p->nc != 3)
         return p->p_j.ptr ? sizeof(double) * (size_t)(p->nc * (int64_t)p->n_obs * p->p_copies) : 0;
-    const int copies = p->p_j.ptr != nullptr ? p->p_copies : 1;
+    const int copies = p->p_copies > 0 ? p->p_copies : 1;
     return sizeof(double2) * 2 * (size_t)(p->n_obs > 0 ? p->n_obs : 1) * copies;
 }
 
