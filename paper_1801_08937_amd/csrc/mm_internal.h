@@ -364,12 +364,18 @@ size_t apply_PT_scratch_bytes(const mm_pointing *p, int nrhs);
 size_t noise_scratch_bytes(const mm_noise *nz, int nrhs);
 void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, void *y,
                  char *scratch = nullptr, bool planar = false);
-// Consecutive samples of a wave of the P of several columns, a multiple of step (what
-// it takes at a time): step, or what `blocks` blocks of four waves make (blocks > 0);
-// more where the launch would pass 2^22 blocks, as one of 2^32 threads is refused.
-inline int64_t p_wave_samples(int64_t n, int step, int64_t blocks) {
+// Consecutive samples of a wave of the P of several columns, a multiple of step = 256 / R
+// (what it takes at a time): step, or what `blocks` blocks of four waves make (blocks >
+// 0); more where the launch would pass 2^22 blocks, as one of 2^32 threads is refused.
+// From 32 columns on, with a map beyond the L2s (x over 20 MB), runs of 16 steps: a
+// wave's gathers then stay among neighbouring pixels, us, step / 16 steps: 1M samples x
+// 64, FP32, 128 x 128 pixels (25 MB) 196 / 110, 96 x 96 (14 MB, FP64) 168 / 176, 256 x 256
+// (101 MB), sweeps along rows 261 / 152; x 32, (50 MB) 130 / 68; x 16 (25 MB) 51 / 56.
+inline int64_t p_wave_samples(int64_t n, int step, int64_t blocks, int64_t map_bytes = 0) {
     if (blocks <= 0 || blocks > (1 << 22)) {
-        if ((n + 4 * step - 1) / (4 * step) <= (1 << 22)) return step;
+        const bool far = step <= 8 && map_bytes > 20000000 && n >= (int64_t)step << 17;
+        const int64_t per = far ? 16 * step : step;
+        if ((n + 4 * per - 1) / (4 * per) <= (1 << 22)) return per;
         blocks = 1 << 22;
     }
     const int64_t per = (n + 4 * blocks - 1) / (4 * blocks);

@@ -938,7 +938,8 @@ void apply_P_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const double *x, v
         constexpr int R = decltype(RR)::value;
         if constexpr (R > 1) {
             constexpr int step = PR_U * 128 / R;  // samples of a wave at a time
-            const int64_t per = p_wave_samples(n, step, p->p_blocks[log2i(R)]);
+            const int64_t per =
+                p_wave_samples(n, step, p->p_blocks[log2i(R)], (int64_t)sizeof(double) * p->n() * R);
             const unsigned grid = (unsigned)((n + 4 * per - 1) / (4 * per));
             auto go = [&](auto TT, auto NN) {
                 using T = decltype(TT);

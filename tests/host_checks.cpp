@@ -114,6 +114,11 @@ void p_launch() {
                 EXPECT(grid * 4 * per >= n && grid * 256 < (int64_t)1 << 32);
                 if (blocks > 0) EXPECT(grid <= blocks);
                 else if (n * R < (int64_t)1 << 32) EXPECT(per == step);
+                // a map beyond the L2s: longer runs, from 32 columns and 2^25 values on
+                const int64_t far = mm::p_wave_samples(n, step, blocks, 25 << 20);
+                EXPECT((n + 4 * far - 1) / (4 * far) * 256 < (int64_t)1 << 32);
+                if (R == 64 && blocks == 0 && n == (int64_t)1 << 28) EXPECT(far >= 16 * step);
+                if (R < 32 || blocks > 0 || n < 1 << 19) EXPECT(far == per);
             }
 }
 
