@@ -1272,20 +1272,22 @@ namespace mm {
 
 // Tile counts of the direct band for every column count R = 2^li (tile
 // length band_tile_len(R)): pref[li][i] = tiles in the intervals before i; and
-// the full symmetric filters f[d] = c_|d - lambda| of the register kernel.
+// the full symmetric filters f[d] = c_|d - lambda| of the register kernel where 64
+// columns would take it.
 void build_band_tiles(mm_ctx *ctx, mm_noise *nz) {
-    if (nz->half_bw >= BC_MIN_LAMBDA) {
-        const size_t lam = (size_t)nz->half_bw, nf = 2 * lam + 1;
+    std::vector<char> full;  // in use until the copies are done
+    if (band_by_rows(64, nz->half_bw, nz->n_samp)) {
+        const size_t lam = (size_t)nz->half_bw, nf = 2 * lam + 1, n = nf * nz->n_filters;
         auto fill = [&](auto TT) {
             using T = decltype(TT);
-            std::vector<T> full(nf * nz->n_filters);
+            full.resize(sizeof(T) * n);
+            T *out = reinterpret_cast<T *>(full.data());
             for (size_t f = 0; f < (size_t)nz->n_filters; ++f)
                 for (size_t d = 0; d < nf; ++d)
-                    full[f * nf + d] = (T)nz->h_band[f * (lam + 1) + (d < lam ? lam - d : d - lam)];
-            nz->band_full.alloc(sizeof(T) * full.size());
-            MM_HIP(hipMemcpyAsync(nz->band_full.ptr, full.data(), sizeof(T) * full.size(),
-                                  hipMemcpyHostToDevice, ctx->stream));
-            MM_HIP(hipStreamSynchronize(ctx->stream));
+                    out[f * nf + d] = (T)nz->h_band[f * (lam + 1) + (d < lam ? lam - d : d - lam)];
+            nz->band_full.alloc(sizeof(T) * n);
+            MM_HIP(hipMemcpyAsync(nz->band_full.ptr, out, sizeof(T) * n, hipMemcpyHostToDevice,
+                                  ctx->stream));
         };
         if (nz->prec == MM_F32) fill(0.f);
         else fill(0.0);
