@@ -264,7 +264,8 @@ struct mm_noise {
     mm::DBuf istart, fid, band, band64;
     mm::DBuf band_full;  // direct band: the symmetric filters [n_filters][2 half_bw + 1]
     // direct band: per column count R = 2^li (li = 0..6), the number of
-    // tiles in the intervals before each interval, int64[7][n_int + 1]
+    // tiles in the intervals before each interval, int64[14][n_int + 1]: of N^-1
+    // alone, and of A with P inside the band by rows
     // (device copy and host copy); built with the handle, read-only after
     mm::DBuf tile_pref;
     std::vector<int64_t> h_tile_pref;
@@ -393,7 +394,6 @@ inline PtForm pt_form(int32_t n_obs, int64_t n_valid, int nrhs, int n_cu) {
                                                                       : PtForm::COLUMNS;
 }
 void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, void *z);
-int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp);
 void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod_rm, void *y,
                   int *nonfinite_flag);
 // z = N^-1 (mask . tod) by the FFT method, tod [nrhs][n_samp] masked as it is

@@ -1048,9 +1048,23 @@ static bool band_by_rows(int nrhs, int lam, int64_t n_samp) {
     return nrhs >= BC_MIN_R && lam >= BC_MIN_LAMBDA && n_samp * nrhs >= ((int64_t)1 << 21);
 }
 
-// Tile length of the direct band for R columns.
-int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp) {
-    if (band_by_rows(nrhs, lam, n_samp)) return (BS / nrhs) * BC_OPT;
+// The same for N^-1 alone.  8 columns in FP64 with short filters on long streams are
+// bound by the rows' traffic, which the tiled kernel's LDS saves (us, register / tiled,
+// 2^25 values: lambda 8 114 / 106, 16 135 / 130, 24 156 / 148, 32 175 / 177; 24M values,
+// lambda 16 103 / 91; 2^23, lambda 16 34 / 37).  16 and 32 columns in FP32 with longer
+// filters fill the chip sooner in the tiled kernel (2^21 values x 32 columns, lambda 24 9.0 / 8.6, 48
+// 13.0 / 10.9, 80 18.3 / 14.9; 2^23 values 34 / 36, 51 / 48 at 48 and 80).  With P inside, the
+// rows win there too.
+static bool band_rows_alone(int nrhs, int lam, int64_t n_samp, mm_precision prec) {
+    if (!band_by_rows(nrhs, lam, n_samp)) return false;
+    if (prec == MM_F64) return !(nrhs == 8 && lam < 32 && n_samp >= ((int64_t)1 << 21));
+    return !((nrhs == 16 || nrhs == 32) && lam >= 32 && n_samp * nrhs < ((int64_t)1 << 22));
+}
+
+// Tile length of N^-1 by the direct band for R columns.
+static int band_rows_tile(int nrhs) { return (BS / nrhs) * BC_OPT; }
+static int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp, mm_precision prec) {
+    if (band_rows_alone(nrhs, lam, n_samp, prec)) return band_rows_tile(nrhs);
     return nrhs == 1 && small ? BAND_SMALL_NT * BAND_SMALL_OPT : (BS / nrhs) * BT_OPT;
 }
 
@@ -1058,7 +1072,7 @@ int band_tile_len(int nrhs, bool small, int lam, int64_t n_samp) {
 // in BT_LDS bytes; a multiple of BT_OPT, at most the padded filter length.
 static int band_chunk(int lam, int R, mm_precision prec, bool small, int64_t n_samp) {
     const size_t te = prec == MM_F32 ? sizeof(float) : sizeof(double);
-    const int tl = band_tile_len(R, small, lam, n_samp);
+    const int tl = band_tile_len(R, small, lam, n_samp, prec);
     const int nf_pad = (2 * lam + 1 + BT_OPT - 1) / BT_OPT * BT_OPT;
     int cl = (int)(((int64_t)(BT_LDS / te) - (int64_t)(tl - 1) * R) / (R + 1));
     cl = cl / BT_OPT * BT_OPT;
@@ -1070,9 +1084,12 @@ size_t noise_scratch_bytes(const mm_noise *nz, int nrhs) {
 }
 
 // Tile counts for every column count are built with the noise handle, so an apply
-// never modifies it (handles may be shared across contexts).
-static const int64_t *band_tiles(const mm_noise *nz, int nrhs, int64_t *n_tiles) {
-    const size_t li = (size_t)log2i(nrhs) * (nz->n_int + 1);
+// never modifies it (handles may be shared across contexts): of N^-1 alone, then of the
+// rows with P inside.
+constexpr int BAND_TABLES = 14;
+static const int64_t *band_tiles(const mm_noise *nz, int nrhs, int64_t *n_tiles,
+                                 bool with_P = false) {
+    const size_t li = (size_t)(log2i(nrhs) + (with_P ? 7 : 0)) * (nz->n_int + 1);
     *n_tiles = nz->h_tile_pref[li + nz->n_int];
     return nz->tile_pref.as<int64_t>() + li;
 }
@@ -1086,7 +1103,7 @@ static int band_chunk_used(const mm_noise *nz, int nrhs) {
 template <typename T, int R, typename Rows>
 static void band_tiled_launch(mm_ctx *ctx, const mm_noise *nz, const Rows &rows, T *z, int cl) {
     const int lam = nz->half_bw;
-    const int tl = band_tile_len(R, nz->band_small, lam, nz->n_samp);
+    const int tl = band_tile_len(R, nz->band_small, lam, nz->n_samp, nz->prec);
     int64_t n_tiles;
     const int64_t *pref = band_tiles(nz, R, &n_tiles);
     const size_t sm = sizeof(T) * ((size_t)cl + (size_t)(tl + cl - 1) * R);
@@ -1140,7 +1157,7 @@ static bool band_P_dev(mm_ctx *ctx, const mm_pointing *p, const mm_noise *nz, in
                     return;
                 Scope sc(ctx->prof, ctx->stream, "Ninv_band");
                 int64_t n_tiles;
-                const int64_t *pref = band_tiles(nz, CB, &n_tiles);
+                const int64_t *pref = band_tiles(nz, CB, &n_tiles, true);
                 k_band_P<T, R, NC><<<(unsigned)((n_tiles * K + 7) / 8 * 8), BS, lds,
                                      ctx->stream>>>(
                     pref, nz->n_int, nz->istart.as<int64_t>(),
@@ -1168,7 +1185,7 @@ void noise_apply_dev(mm_ctx *ctx, const mm_noise *nz, int nrhs, const void *y, v
     }
     Scope sc(ctx->prof, ctx->stream, "Ninv_band");
     const int lam = nz->half_bw;
-    if (band_by_rows(nrhs, lam, nz->n_samp)) {
+    if (band_rows_alone(nrhs, lam, nz->n_samp, nz->prec)) {
         dispatch_r(nrhs, [&](auto RR) {
             constexpr int R = decltype(RR)::value;
             if constexpr (R >= BC_MIN_R) {
@@ -1270,9 +1287,9 @@ void mask_tod_dev(mm_ctx *ctx, const mm_pointing *p, int nrhs, const void *tod, 
 
 namespace mm {
 
-// Tile counts of the direct band for every column count R = 2^li (tile
-// length band_tile_len(R)): pref[li][i] = tiles in the intervals before i; and
-// the full symmetric filters f[d] = c_|d - lambda| of the register kernel where 64
+// Tile counts of the direct band for every column count R = 2^li (tile lengths above, of
+// N^-1 alone and with P inside): pref[li][i] = tiles in the intervals before i; and the
+// full symmetric filters f[d] = c_|d - lambda| of the register kernel where 64
 // columns would take it.
 void build_band_tiles(mm_ctx *ctx, mm_noise *nz) {
     std::vector<char> full;  // in use until the copies are done
@@ -1293,9 +1310,11 @@ void build_band_tiles(mm_ctx *ctx, mm_noise *nz) {
         else fill(0.0);
     }
     const size_t np = (size_t)nz->n_int + 1;
-    nz->h_tile_pref.assign(7 * np, 0);
-    for (int li = 0; li < 7; ++li) {
-        const int64_t tl = band_tile_len(1 << li, nz->band_small, nz->half_bw, nz->n_samp);
+    nz->h_tile_pref.assign(BAND_TABLES * np, 0);
+    for (int li = 0; li < BAND_TABLES; ++li) {
+        const int64_t tl = li < 7 ? band_tile_len(1 << li, nz->band_small, nz->half_bw,
+                                                  nz->n_samp, nz->prec)
+                                  : band_rows_tile(1 << (li - 7));
         int64_t *pr = nz->h_tile_pref.data() + li * np;
         for (int i = 0; i < nz->n_int; ++i)
             pr[i + 1] = pr[i] + (nz->h_istart[i + 1] - nz->h_istart[i] + tl - 1) / tl;
@@ -1374,7 +1393,7 @@ void autotune(mm_ctx *ctx, mm_pointing *p, mm_noise *nz, int nrhs, int flags, do
             const int def = band_chunk(nz->half_bw, nrhs, nz->prec, nz->band_small, nz->n_samp);
             double best = 1e30;
             int best_c = 0;
-            const bool rows = band_by_rows(nrhs, nz->half_bw, nz->n_samp);
+            const bool rows = band_rows_alone(nrhs, nz->half_bw, nz->n_samp, nz->prec);
             for (int div : {1, 2, 4, 8}) {
                 const int c = def / div / BT_OPT * BT_OPT;
                 if (c < BT_OPT || (div > 1 && (c == def || rows))) continue;
